@@ -136,7 +136,7 @@ size_t griffin_prefill_workspace_bytes(const griffin_layer *L, int64_t total_tok
 {
     if (check_layer(L) != GRIFFIN_OK || total_tokens < 0 || n_seqs < 1 || n_seqs > GRIFFIN_MAX_SEQS)
         return 0;
-    return plan_prefill(*L, total_tokens, n_seqs, have_z_out != 0).total;
+    return plan_prefill(*L, total_tokens, n_seqs, have_z_out != 0).total + align256(ff1_slab_bytes(*L, total_tokens));
 }
 
 int griffin_prefill_select(const griffin_layer *L, const void *X, int64_t ldx,
@@ -172,7 +172,9 @@ int griffin_prefill_select(const griffin_layer *L, const void *X, int64_t ldx,
     float *s = (float *)(ws + pl.off_s);
 
     int32_t nt = 0;
-    if ((rc = launch_ff1(*L, X, ldx, total, Z, zld, rowpart, &nt, st)) != GRIFFIN_OK)
+    // the slabs of a short prompt lie behind the rest; a workspace without room for them takes the product in one range
+    float *slabs = workspace_bytes >= pl.total + ff1_slab_bytes(*L, total) ? (float *)(ws + pl.total) : nullptr;
+    if ((rc = launch_ff1(*L, X, ldx, total, Z, zld, rowpart, &nt, st, nullptr, 0, slabs)) != GRIFFIN_OK)
         return rc;
     if ((rc = launch_stat(Z, zld, rowpart, nt, total, L->n, seqs, s2part, s, s_out, st)) != GRIFFIN_OK)
         return rc;
@@ -293,7 +295,8 @@ size_t griffin_prompt_phase_workspace_bytes(const griffin_layer *L, int64_t tota
         n_seqs > GRIFFIN_MAX_SEQS)
         return 0;
     const size_t first = plan_prefill(*L, total_tokens, n_seqs, false).total;
-    return first + align256(total_tokens > 0 ? ff2_workspace_bytes(total_tokens, L->n, L->d) : 0);
+    return first + align256(total_tokens > 0 ? ff2_workspace_bytes(total_tokens, L->n, L->d) : 0) +
+           align256(ff1_slab_bytes(*L, total_tokens));
 }
 
 int griffin_prompt_phase(const griffin_layer *L, const void *W2p, int64_t ldw, const void *X, int64_t ldx,
@@ -336,7 +339,9 @@ int griffin_prompt_phase(const griffin_layer *L, const void *W2p, int64_t ldw, c
     const bool fuse = total > 0 && ff2_takes_zb(Z, L->n, total, L->n, L->d, bf16, W2p, ldw) &&
                       ff1_can_write_zb(*L, ldx, Z, L->n);
     int32_t nt = 0;
-    if ((rc = launch_ff1(*L, X, ldx, total, Z, L->n, rowpart, &nt, st, fuse ? (uint16_t *)ws2 : nullptr, L->n)) != GRIFFIN_OK)
+    const size_t before = pl.total + align256(second);
+    float *slabs = workspace_bytes >= before + ff1_slab_bytes(*L, total) ? (float *)(ws + before) : nullptr;
+    if ((rc = launch_ff1(*L, X, ldx, total, Z, L->n, rowpart, &nt, st, fuse ? (uint16_t *)ws2 : nullptr, L->n, slabs)) != GRIFFIN_OK)
         return rc;
     if ((rc = launch_stat(Z, L->n, rowpart, nt, total, L->n, seqs, s2part, s, s_out, st)) != GRIFFIN_OK)
         return rc;

@@ -110,9 +110,12 @@ int set_hip_error(hipError_t e, const char *what);   // records text, returns GR
 int check_launch(const char *what);                  // hipGetLastError -> status
 
 // launchers (one per source file); all return a griffin_status
-// Zb (optional): a bf16 copy of Z [M][ldzb] written by the same epilogue when ff1_can_write_zb() says so
+// slabs (optional): room of ff1_slab_bytes() for the raw products of ranges of d.  Zb (optional): a bf16 copy of Z [M][ldzb] written by the same epilogue when ff1_can_write_zb() says so
 int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz,
-               float *rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb = nullptr, int64_t ldzb = 0);
+               float *rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb = nullptr, int64_t ldzb = 0,
+               float *slabs = nullptr);
+// bytes of the slabs that a short prompt's product wants (0: none); without them it runs in one range
+size_t ff1_slab_bytes(const griffin_layer &L, int64_t M);
 bool ff1_can_write_zb(const griffin_layer &L, int64_t ldx, const float *Z, int64_t ldz);
 int ff1_ntiles(const griffin_layer &L);
 int launch_stat(const float *Z, int64_t ldz, const float *rowpart, int nt, int64_t M, int32_t F,
@@ -130,7 +133,7 @@ int launch_compact(const griffin_layer &L, const int32_t *idx, int32_t k, const 
 bool gemm_nt_partials_ok(int64_t M, int32_t N, int32_t K, int64_t lda, int64_t ldb);
 void gemm_nt_split_plan(int64_t M, int32_t N, int32_t K, int *splits, int *kt_per_split);
 int launch_gemm_nt_partials(const void *A, int64_t lda, const void *B, int64_t ldb, int64_t M, int32_t N, int32_t K,
-                            int splits, int kt_per_split, float *C, hipStream_t st);
+                            int splits, int kt_per_split, float *C, int64_t ldc, hipStream_t st);
 // zb_ready: the bf16 copy of Z already sits at the head of ws (written by the first GEMM's epilogue)
 int launch_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, bool bf16, const void *W2p,
                int64_t ldw, const void *b2, void *Y, int64_t ldy, float *ws, size_t ws_bytes, hipStream_t st,

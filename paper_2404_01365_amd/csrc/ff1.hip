@@ -114,18 +114,21 @@ __device__ __forceinline__ float ff1_acc_read(float a)
 
 // EXTRA: the instantiation that also knows biases and the bf16 copy of Z; the lean one (most models: no FF
 // biases, selection alone) is 2 % faster for not carrying those branches and registers through the epilogue.
-template <int ACT, bool GATED, int MI, bool PLAIN, bool EQ2W = false, bool EXTRA = true>
+template <int ACT, bool GATED, int MI, bool PLAIN, bool EQ2W = false, bool EXTRA = true, bool DUAL = false>
 __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x16 (&accU)[MI][2], f32x16 (&accG)[MI][2],
                                                     float (*rs)[64 * MI], uint32_t rs_lds, uint32_t patch_lds, int m0, int n0,
                                                     int tile_n)
 {
     constexpr int BM = 64 * MI;
     // one B matrix (the plain product, or an Eq. 2 block) over a 256-column tile: accG = columns n0 + 128 ..
-    constexpr bool WIDE = (PLAIN && GATED) || EQ2W;
+    constexpr bool WIDE = (PLAIN && GATED) || EQ2W;         // two column halves to store
     constexpr bool GLU = GATED && !PLAIN && !EQ2W;          // accG is the gate (Eq. 3)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, l31 = lane & 31, lh = lane >> 5;
-    const bool vec = ((p.F | (int32_t)p.ldz) & 3) == 0 && ((uintptr_t)p.Z & 15) == 0;
+    // slabs of raw products (PLAIN) are whole rows of ldz columns, a multiple of 4: the columns past F hold repeats of
+    // the last one and are never read
+    const int FS = PLAIN ? (int)p.ldz : p.F;
+    const bool vec = ((FS | (int32_t)p.ldz) & 3) == 0 && ((uintptr_t)p.Z & 15) == 0;
     const bool hb = EXTRA && !PLAIN && (p.b1 != nullptr || (GLU && p.bg != nullptr));
     const uint16_t *b1p = (const uint16_t *)p.b1, *bgp = (const uint16_t *)p.bg;
     const bool bias8 = (((uintptr_t)p.b1 | (uintptr_t)p.bg) & 7) == 0;       // four biases per 8-byte load
@@ -166,7 +169,8 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x16 (
             float sq = 0.0f;
 #pragma unroll
         for (int half = 0; half < (WIDE ? 2 : 1); ++half) {
-        const int nh = n0 + half * G_BN;
+        const int nh = n0 + (DUAL ? 0 : half * G_BN);
+        float *const Zh = p.Z + (DUAL && half == 1 ? (int64_t)p.M * p.ldz : (int64_t)0);   // the gate's slab follows the up product's
         const int ncol = nh + wn * 64 + rch * 4;
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni) {
@@ -186,7 +190,7 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x16 (
                         }
                         v[e] = PLAIN ? u : (GLU ? act_apply_t<ACT>(gt) * u : act_apply_t<ACT>(u));
                     }
-                    if (nh + wn * 64 + ni * 32 + g * 8 + lh * 4 >= p.F)
+                    if (nh + wn * 64 + ni * 32 + g * 8 + lh * 4 >= FS)
                         v = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
                     sq = fmaf(v[0], v[0], sq); sq = fmaf(v[1], v[1], sq);
                     sq = fmaf(v[2], v[2], sq); sq = fmaf(v[3], v[3], sq);
@@ -216,11 +220,11 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x16 (
             {                                                                                        \
                 asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(pv[j_]) : "n"(7 - (j_)) : "memory");     \
                 const int tok = tok0 + 4 * (j_);                                                     \
-                if (tok < p.M && ncol < p.F) {                                                       \
+                if (tok < p.M && ncol < FS) {                                                        \
                     if (p.z_stream)      /* a buffer store: the two flavours must stay two instructions */ \
                         FF1_Z_STREAM_STORE(pv[j_], (tok - m0) * (int)p.ldz + ncol);                  \
                     else                                                                             \
-                        *(f32x4_t *)(p.Z + (int64_t)tok * p.ldz + ncol) = pv[j_];                    \
+                        *(f32x4_t *)(Zh + (int64_t)tok * p.ldz + ncol) = pv[j_];                     \
                     if (EXTRA && !PLAIN && p.Zb) {                                                   \
                         uint2 h_;                                                                    \
                         h_.x = f32_to_bf16_bits(pv[j_][0]) | (f32_to_bf16_bits(pv[j_][1]) << 16);    \
@@ -290,7 +294,8 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x16 (
                 }
             }
         }
-        rs[wn * 2 + lh][lrow] = sq;
+        if (!PLAIN)
+            rs[wn * 2 + lh][lrow] = sq;
     }
     if (PLAIN)
         return false;
@@ -322,7 +327,7 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // slot swizzle of row r (rows of every stage section start at a multiple of 16)
 #define FF1_SWZ(r) (((r) >> 1) & 7)
 
-template <int ACT, bool GATED, int MI, bool PLAIN, bool EQ2W = false, bool EXTRA = true>
+template <int ACT, bool GATED, int MI, bool PLAIN, bool EQ2W = false, bool EXTRA = true, bool DUAL = false>
 __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass has no buffer-descriptor builtins; it only needs the launch stub
@@ -335,11 +340,14 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     // The plain product has one B matrix: its tile is 256 columns wide and the "gate" half of the
     // machinery (LDS section, fragments, accumulators) takes columns n0 + 128 .. n0 + 255, which
     // halves the X traffic per flop exactly as the dual product does.
-    constexpr bool WIDE = (PLAIN && GATED) || EQ2W;        // EQ2W: an Eq. 2 block (no gate) through the same machinery
+    // DUAL: the plain kernel over both matrices of a gated block (raw products of one range of d, two slabs per range);
+    // the gate's section holds Wg again and the tile is 128 columns of both.
+    constexpr bool WIDE = (PLAIN && GATED && !DUAL) || EQ2W;        // EQ2W: an Eq. 2 block (no gate) through the same machinery
+    static_assert(!DUAL || (PLAIN && GATED), "DUAL is a form of the plain product");
     static_assert(!EQ2W || (GATED && !PLAIN), "the Eq. 2 wide tile uses both LDS sections and both accumulator sets");
     constexpr int TILE_N = WIDE ? 2 * G_BN : G_BN;
     __shared__ u32x4 lds[2 * STAGE];
-    __shared__ float rs[4][BM];
+    __shared__ float rs[PLAIN ? 1 : 4][PLAIN ? 1 : BM];     // (the plain product of 64-token tiles fits twice into a CU without it)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -385,7 +393,7 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
             m0 = ((in_full_ ? (tile_ / (PANEL_M * p.nt)) * PANEL_M : full_m) + w_ % pm_) * BM;           \
         }                                                                                                \
         n0 = tile_n * TILE_N;                                                                            \
-        Zt = PLAIN ? p.Z + (int64_t)split_ * p.M * p.ldz : p.Z;                                          \
+        Zt = PLAIN ? p.Z + (int64_t)split_ * (DUAL ? 2 : 1) * p.M * p.ldz : p.Z;                         \
         _Pragma("unroll") for (int q = 0; q < XQ; ++q)                                                   \
             xvo[q] = (uint32_t)min((wave * XQ + q) * 8 + lrow, p.M - 1 - m0) * (uint32_t)(p.ldx * 2) +   \
                      (uint32_t)(((lane & 7) ^ FF1_SWZ((wave * XQ + q) * 8 + lrow)) * 16);                \
@@ -401,7 +409,7 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
                                                RSRC_RECORDS, RSRC_FLAGS);                                \
         rW1 = __builtin_amdgcn_make_buffer_rsrc((void *)((const uint16_t *)p.W1 + (int64_t)n0 * p.ldw), 0, \
                                                 RSRC_RECORDS, RSRC_FLAGS);                               \
-        rWg = __builtin_amdgcn_make_buffer_rsrc((void *)((const uint16_t *)((GATED && !PLAIN && !EQ2W) ? p.Wg : p.W1) + (int64_t)n0 * p.ldw), 0, \
+        rWg = __builtin_amdgcn_make_buffer_rsrc((void *)((const uint16_t *)((GATED && (!PLAIN || DUAL) && !EQ2W) ? p.Wg : p.W1) + (int64_t)n0 * p.ldw), 0, \
                                                 RSRC_RECORDS, RSRC_FLAGS);                               \
         kt0 = split_ * p.kt_per_split;                                                                   \
         KT = min(p.kt_per_split, p.d / BK - kt0);      /* k-tiles of this range (>= 1 by construction) */ \
@@ -455,6 +463,7 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     constexpr int NREADS = MI + (GATED ? 4 : 2);
     constexpr int NMFMA = MI * 2;                  // MFMA pairs (up, gate) or singles per k-step
     constexpr int NSLOTS = NMFMA > NREADS ? NMFMA : NREADS;   // interleaving slots per k-step
+    static_assert(MI > 1 || GATED, "the epilogue's patches need the room of two weight sections");
     static_assert(H1 <= NSLOTS && NLOADS - H1 <= NSLOTS, "the loads of a k-tile must fit two k-steps");
 
 // read number r (0 .. NREADS-1) of fragment set F_ from stage addresses sa_/sb_ (32 rows = 4096 B apart)
@@ -480,8 +489,11 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
         if (MI == 4)                                                                           \
             asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fa[F_][0]), "+v"(fa[F_][1]), "+v"(fa[F_][MI - 2]), "+v"(fa[F_][MI - 1]), \
                          "+v"(f1[F_][0]), "+v"(f1[F_][1]), "+v"(fg[F_][0]), "+v"(fg[F_][1]));  \
+        else if (MI == 1)                                                                      \
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fa[F_][0]),                             \
+                         "+v"(f1[F_][0]), "+v"(f1[F_][1]), "+v"(fg[F_][0]), "+v"(fg[F_][1]));  \
         else                                                                                   \
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fa[F_][0]), "+v"(fa[F_][1]),            \
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fa[F_][0]), "+v"(fa[F_][MI > 1 ? 1 : 0]), \
                          "+v"(f1[F_][0]), "+v"(f1[F_][1]), "+v"(fg[F_][0]), "+v"(fg[F_][1]));  \
     }
 // one k-step: MFMAs on fragment set FM_, the reads of set FR_ (k-step KR_ of the stage at sr_)
@@ -514,7 +526,7 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     // wholly inside the matrix (8 per 32-token block, plus the row sums when all four waves write them).
     // The wait for k-tile 0 of the next tile may leave that many operations outstanding, no more: a
     // wave that issued fewer stores than the wait allows would sail through before its loads landed.
-    constexpr int EPI_STORES = MI * 8 * (WIDE ? 2 : 1) + ((!PLAIN && MI == 4) ? 1 : 0);
+    constexpr int EPI_STORES = MI * 8 * (WIDE || DUAL ? 2 : 1) + ((!PLAIN && MI == 4) ? 1 : 0);
     const uint32_t rs_lds = (uint32_t)(uintptr_t)(lds_void_t *)rs;
     const uint32_t patch_lds = lds0 + (uint32_t)(STAGE * 16) + (GATED ? (uint32_t)(BM * 128) : 0u);
 #define FF1_FIRST_LOADS()                                                                      \
@@ -585,7 +597,7 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
             FF1_TILE_ADDR(logical_n)
             FF1_FIRST_LOADS()
         }
-        const bool usual = ff1_mfma_epilogue_t<ACT, GATED, MI, PLAIN, EQ2W, EXTRA>(pt, accU, accG, rs, rs_lds, patch_lds, m0c, n0c, tile_nc);
+        const bool usual = ff1_mfma_epilogue_t<ACT, GATED, MI, PLAIN, EQ2W, EXTRA, DUAL>(pt, accU, accG, (float(*)[BM])rs, rs_lds, patch_lds, m0c, n0c, tile_nc);
         if (!more)
             break;
         FF1_BARRIER()              // every wave is done with its patch and the row sums
@@ -836,6 +848,139 @@ __global__ __launch_bounds__(256) void ff1_f32_kernel(Ff1Params p, int act)
     }
 }
 
+// ------------------------------------------------------------------------------------ short prompts: d in ranges
+// A short prompt has few token tiles, and few neuron tiles times few token tiles leave most of the chip without work
+// while the call has to read all the weights (40 tokens of a 4096 x 11008 block: 86 tiles for 256 CUs).  The contraction is
+// then cut into ranges of d that each write their raw products (fp32 slabs, [range][up, gate][M][ldu]); this kernel adds
+// the ranges in ascending order and applies what the epilogue of the whole product applies: biases, sigma, the gating
+// product, Z (and its bf16 copy), the row sums of squares.  A workgroup takes 1024 columns of one token.
+struct Ff1ActParams {
+    const float *U;
+    const void *bg, *b1;
+    float *Z, *rowpart;
+    uint16_t *Zb;
+    int64_t ldu, ldz, ldzb;
+    int32_t M, F, act, splits;
+};
+constexpr int ACT_COLS = 1024;
+
+template <bool GATED>
+__global__ __launch_bounds__(256) void ff1_act_kernel(Ff1ActParams p)
+{
+    __shared__ float part[4];
+    const int row = blockIdx.y, j = blockIdx.x * ACT_COLS + threadIdx.x * 4;
+    const int64_t slab = (int64_t)p.M * p.ldu;
+    float sq = 0.0f;
+    if (j < p.F) {
+        const float *up = p.U + (int64_t)row * p.ldu + j;
+        f32x4_t u = *(const f32x4_t *)up, g = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (GATED)
+            g = *(const f32x4_t *)(up + slab);
+#pragma unroll 4
+        for (int s = 1; s < p.splits; ++s) {
+            u += *(const f32x4_t *)(up + (int64_t)s * (GATED ? 2 : 1) * slab);
+            if (GATED)
+                g += *(const f32x4_t *)(up + (int64_t)(2 * s + 1) * slab);
+        }
+        float z[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int je = min(j + e, p.F - 1);
+            const float uu = u[e] + (p.b1 ? bf16_bits_to_f32(((const uint16_t *)p.b1)[je]) : 0.0f);
+            if (GATED)
+                z[e] = act_apply(p.act, g[e] + (p.bg ? bf16_bits_to_f32(((const uint16_t *)p.bg)[je]) : 0.0f)) * uu;
+            else
+                z[e] = act_apply(p.act, uu);
+            if (j + e < p.F)
+                sq = fmaf(z[e], z[e], sq);
+        }
+        float *zo = p.Z + (int64_t)row * p.ldz + j;
+        if (((p.F | (int32_t)p.ldz) & 3) == 0 && ((uintptr_t)p.Z & 15) == 0) {
+            *(f32x4_t *)zo = (f32x4_t){z[0], z[1], z[2], z[3]};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (j + e < p.F)
+                    zo[e] = z[e];
+        }
+        if (p.Zb) {                      // only with F, ldzb multiples of 4 (ff1_can_write_zb)
+            uint2 h;
+            h.x = f32_to_bf16_bits(z[0]) | (f32_to_bf16_bits(z[1]) << 16);
+            h.y = f32_to_bf16_bits(z[2]) | (f32_to_bf16_bits(z[3]) << 16);
+            *(uint2 *)(p.Zb + (int64_t)row * p.ldzb + j) = h;
+        }
+    }
+    sq = wave_sum(sq);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x >> 6] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        p.rowpart[(int64_t)row * gridDim.x + blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
+}
+
+struct Ff1Plan {
+    int splits, per;         // ranges of d, k-tiles per range; 1 range: the epilogue of the product does it all
+    int64_t ldu;             // columns of a slab's row
+};
+
+// How many ranges: the cheapest by a cost in microseconds, from (measured) the time of a k-tile on a CU with its item's
+// fixed part in k-tiles, the weights at the rate the loop draws them from HBM, the slabs written and read again, and the
+// second kernel:
+//   * the whole product: a k-tile 1.15 us (256 tokens; 1.05 with up to 128; an Eq. 2 block's 128-column tiles 0.95 / 0.8), 8 (3)
+//     k-tiles of prologue and epilogue;
+//   * in ranges: the same without sigma in the epilogue (5, 3); up to 64 tokens 1.0 us, 1.25 us where two workgroups share a CU.
+// Whole selections of a 4096 x 11008 block, in one range / in 2, 3, 4, 5, 8 ranges (us): 40 tokens 96 / 70, 69, 64, 65, 70;
+// 128 tokens 97 / 75, 97, 87, 84, 102; 256 tokens 111 / 88, 120, 114, 112, 138; 512 tokens 115 / 152, 178, ...; of a 2048 x 8192
+// block: 40 tokens 58 / 45, 42, 41, 44, 46; 256 tokens 70 / 60, 58, 59, 83, 89; of a 8192 x 8192 Eq. 2 block: 40 tokens
+// 127 / 92, 73, 64, 58, 52; 512 tokens 151 / 120, 101, 107, 134, 125.
+static Ff1Plan ff1_plan(const griffin_layer &L, int64_t M)
+{
+    const int KT = L.d / 64;
+    Ff1Plan pl = {1, KT, ((int64_t)L.n + 3) & ~(int64_t)3};
+    if (L.dtype != GRIFFIN_BF16 || L.d % 64 != 0 || L.ld > (1 << 21) || M < 1 || M > 2048)
+        return pl;
+    const bool gated = L.Wg != nullptr;
+    const int64_t mt = M > 128 ? (M + 255) / 256 : 1;
+    const int64_t n128 = mt * ((L.n + G_BN - 1) / G_BN), n256 = mt * ((L.n + 2 * G_BN - 1) / (2 * G_BN));
+    const int fix_whole = M > 128 ? 8 : 3, fix_raw = M > 128 ? 5 : 3;
+    const double kt_us = M > 128 ? 1.15 : 1.05, kt_narrow_us = M > 128 ? 0.95 : 0.8;
+    double best = (double)((n128 + 255) / 256) * (KT + fix_whole) * (gated ? kt_us : kt_narrow_us);
+    if (!gated) {
+        const double wide = (double)((n256 + 255) / 256) * (KT + fix_whole) * kt_us;
+        best = wide < best ? wide : best;
+    }
+    const int64_t ntile = gated ? n128 : n256;
+    const double hbm_us = (double)(gated ? 2 : 1) * L.n * L.d * 2 / 6.9e6;
+    for (int s = 2; s <= 16; ++s) {
+        const int per = (KT + s - 1) / s;
+        if (per < 4)
+            break;
+        const int used = (KT + per - 1) / per;
+        const double slab = (double)used * (gated ? 2 : 1) * M * pl.ldu * 4;       // bytes
+        if (slab > (double)(128 << 20))
+            break;
+        const int64_t items = ntile * used;
+        double t;
+        if (M <= 64)
+            t = (double)((items + 511) / 512) * (per + fix_raw) * (items > 256 ? 1.25 : 1.0);
+        else
+            t = (double)((items + 255) / 256) * (per + fix_raw) * kt_us;
+        t = (t > hbm_us ? t : hbm_us) + slab * 2 / 7e6 + 5.0;
+        if (t < best) {
+            best = t;
+            pl.splits = used;
+            pl.per = per;
+        }
+    }
+    return pl;
+}
+
+size_t ff1_slab_bytes(const griffin_layer &L, int64_t M)
+{
+    const Ff1Plan pl = ff1_plan(L, M);
+    return pl.splits > 1 ? (size_t)pl.splits * (L.Wg ? 2 : 1) * M * pl.ldu * sizeof(float) : 0;
+}
+
 int ff1_ntiles(const griffin_layer &L)
 {
     const int bn = L.dtype == GRIFFIN_BF16 ? G_BN : F_BN;
@@ -844,7 +989,7 @@ int ff1_ntiles(const griffin_layer &L)
 
 // one workgroup per CU (a multiple of 8, so that every XCD gets the same number), fewer if there are fewer tiles.
 // The CU count is asked of the current device at every launch's first use on that device and kept per device.
-static int ff1_grid(int nblk)
+static int ff1_grid(int nblk, int per_cu = 1)
 {
     constexpr int MAX_DEV = 64;
     static std::atomic<int> cus_of[MAX_DEV];
@@ -861,7 +1006,7 @@ static int ff1_grid(int nblk)
             cus_of[dev].store(cus, std::memory_order_relaxed);
     }
     const int want = ((nblk + 7) / 8) * 8;
-    return want < cus ? want : cus;
+    return want < cus * per_cu ? want : cus * per_cu;
 }
 
 template <int ACT, int MI>
@@ -904,7 +1049,7 @@ bool ff1_can_write_zb(const griffin_layer &L, int64_t ldx, const float *Z, int64
 }
 
 int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz,
-               float *rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb)
+               float *rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb, float *slabs)
 {
     Ff1Params p;
     p.X = X; p.Wg = L.Wg; p.W1 = L.W1; p.bg = L.bg; p.b1 = L.b1;
@@ -932,6 +1077,39 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
         if (wide)
             p.nt = (L.n + 2 * G_BN - 1) / (2 * G_BN);
     }
+    const Ff1Plan pl = ff1_plan(L, M);
+    if (slabs && pl.splits > 1 && ldx <= (1 << 21)) {
+        const int nb = (L.n + ACT_COLS - 1) / ACT_COLS;
+        *nt_out = nb;
+        if (gated) {
+            p.Z = slabs; p.ldz = pl.ldu; p.Zb = nullptr; p.z_stream = 0;
+            p.splits = pl.splits; p.kt_per_split = pl.per;
+            p.mt = (int32_t)(M > 128 ? (M + 255) / 256 : 1);
+            const dim3 grid(ff1_grid(p.mt * p.nt * pl.splits, M <= 64 ? 2 : 1)), block(G_THREADS);
+            if (M <= 64)
+                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 1, true, false, true, true>), grid, block, 0, st, p);
+            else if (M > 128)
+                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 4, true, false, true, true>), grid, block, 0, st, p);
+            else
+                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 2, true, false, true, true>), grid, block, 0, st, p);
+        } else {
+            launch_gemm_nt_partials(X, ldx, L.W1, L.ld, M, L.n, L.d, pl.splits, pl.per, slabs, pl.ldu, st);
+        }
+        int rc = check_launch("ff1_bf16_mfma_kernel");
+        if (rc != GRIFFIN_OK)
+            return rc;
+        Ff1ActParams a;
+        a.U = slabs; a.bg = L.bg; a.b1 = L.b1; a.Z = Z; a.rowpart = rowpart;
+        a.Zb = (Zb && ff1_can_write_zb(L, ldx, Z, ldz)) ? Zb : nullptr;
+        a.ldu = pl.ldu; a.ldz = ldz; a.ldzb = ldzb;
+        a.M = (int32_t)M; a.F = L.n; a.act = L.act; a.splits = pl.splits;
+        const dim3 agrid(nb, (unsigned)M);
+        if (gated)
+            hipLaunchKernelGGL(ff1_act_kernel<true>, agrid, dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL(ff1_act_kernel<false>, agrid, dim3(256), 0, st, a);
+        return check_launch("ff1_act_kernel");
+    }
     *nt_out = p.nt;
     if (M == 0)
         return GRIFFIN_OK;
@@ -956,7 +1134,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
 }
 
 // C[s] = A B^T over the s-th range of the contraction, fp32, for s = 0 .. splits-1, on the
-// direct-to-LDS kernel: A [M][K] and B [N][K] bf16 with K a multiple of 64, C [splits][M][N].
+// direct-to-LDS kernel: A [M][K] and B [N][K] bf16 with K a multiple of 64, C [splits][M][ldc], ldc a multiple of 4.
 // Used by the prompt-output GEMM (Section 5.1) on a bf16 copy of Z.
 bool gemm_nt_partials_ok(int64_t M, int32_t N, int32_t K, int64_t lda, int64_t ldb)
 {
@@ -992,13 +1170,13 @@ void gemm_nt_split_plan(int64_t M, int32_t N, int32_t K, int *splits, int *kt_pe
 }
 
 int launch_gemm_nt_partials(const void *A, int64_t lda, const void *B, int64_t ldb, int64_t M, int32_t N, int32_t K,
-                            int splits, int kt_per_split, float *C, hipStream_t st)
+                            int splits, int kt_per_split, float *C, int64_t ldc, hipStream_t st)
 {
     Ff1Params p;
     p.X = A; p.Wg = nullptr; p.W1 = B; p.bg = nullptr; p.b1 = nullptr;
     p.Z = C; p.rowpart = nullptr;
     p.Zb = nullptr; p.ldzb = 0;
-    p.ldx = lda; p.ldw = ldb; p.ldz = N;
+    p.ldx = lda; p.ldw = ldb; p.ldz = ldc;
     p.M = (int32_t)M; p.F = N; p.d = K;
     p.splits = splits; p.kt_per_split = kt_per_split;
     p.z_stream = 0;
@@ -1007,6 +1185,9 @@ int launch_gemm_nt_partials(const void *A, int64_t lda, const void *B, int64_t l
         p.mt = (int32_t)((M + 255) / 256);
         const int nblk = p.mt * p.nt * splits;
         hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 4, true>), dim3(ff1_grid(nblk)), dim3(G_THREADS), 0, st, p);
+    } else if (M <= 64) {
+        p.mt = 1;
+        hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 1, true>), dim3(ff1_grid(p.nt * splits, 2)), dim3(G_THREADS), 0, st, p);
     } else {
         p.mt = (int32_t)((M + 127) / 128);
         const int nblk = p.mt * p.nt * splits;

@@ -325,7 +325,7 @@ int launch_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, boo
             if ((rc = check_launch("ff2_z_to_bf16_kernel")) != GRIFFIN_OK)
                 return rc;
         }
-        if ((rc = launch_gemm_nt_partials(Zb, F, W2p, ldw, M, d, F, p.splits, per, p.part, st)) != GRIFFIN_OK)
+        if ((rc = launch_gemm_nt_partials(Zb, F, W2p, ldw, M, d, F, p.splits, per, p.part, d, st)) != GRIFFIN_OK)
             return rc;
         const int64_t quads = (int64_t)M * d / 4;
         hipLaunchKernelGGL(ff2_split_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p);

@@ -381,6 +381,62 @@ def test_prefill_select_when_workgroups_walk_tiles(dtype, d, F, lens, k, act, ga
     test_prefill_select_matches_oracle(dtype, d, F, lens, k, act, gated, bias)
 
 
+# ------------------------------------------------------------------ prefill: short prompts, d cut into ranges
+# Few token tiles times few neuron tiles: the product runs over ranges of d that leave raw slabs, and a second kernel adds
+# them and applies sigma (64-, 128- and 256-token tiles; slabs' rows padded to four columns; the last range shorter).
+RANGE_CASES = [
+    # dtype, d, F, lens, k, act, gated, bias
+    (synth.DT_BF16, 1024, 1001, [1], 500, synth.ACT_SILU, True, True),             # one token, F odd (scalar stores of Z)
+    (synth.DT_BF16, 1088, 700, [40, 0, 23], 350, synth.ACT_GELU_TANH, True, False),  # 17 k-tiles, 63 tokens in three prompts
+    (synth.DT_BF16, 2048, 130, [64], 65, synth.ACT_SILU, True, False),             # 64-token tile full, last neuron tile of 2
+    (synth.DT_BF16, 2048, 515, [65], 200, synth.ACT_SILU, True, True),             # 128-token tile, one row more than 64
+    (synth.DT_BF16, 1024, 2000, [128], 999, synth.ACT_RELU, True, False),
+    (synth.DT_BF16, 2048, 1500, [129], 700, synth.ACT_SILU, True, False),          # 256-token tile
+    (synth.DT_BF16, 4096, 900, [300, 13], 450, synth.ACT_GELU_TANH, True, True),   # two token tiles, ragged
+    (synth.DT_BF16, 2048, 1030, [33], 500, synth.ACT_RELU, False, True),           # Eq. 2: 256-column tiles, last one 6 wide
+    (synth.DT_BF16, 2048, 1029, [100], 500, synth.ACT_GELU_TANH, False, False),    # Eq. 2, F odd
+    (synth.DT_BF16, 2048, 2100, [260], 500, synth.ACT_RELU, False, True),          # Eq. 2, two token tiles
+    (synth.DT_BF16, 4096, 19197, [70], 9000, synth.ACT_SILU, True, False),         # 450 items: workgroups walk two of them
+]
+
+
+@pytest.mark.parametrize("dtype,d,F,lens,k,act,gated,bias", RANGE_CASES)
+def test_prefill_select_of_short_prompts_in_ranges(dtype, d, F, lens, k, act, gated, bias):
+    test_prefill_select_matches_oracle(dtype, d, F, lens, k, act, gated, bias)
+
+
+def test_prefill_takes_a_workspace_without_room_for_the_slabs():
+    """The slabs are a convenience: the least workspace that is accepted gives the same answer in one range."""
+    dtype, d, F, S, k = synth.DT_BF16, 1024, 1000, 40, 500
+    c = synth.small_case(5, d, F, S, dtype)
+    W1 = c["W1"].copy()
+    _, s_ref = open_margin([c["X"]], c["Wg"], W1, synth.ACT_SILU, dtype, [k])
+    L, _ = dev_layer(c["Wg"], W1, c["W2"], synth.ACT_SILU, dtype)
+    X = to_dev(c["X"], dtype)
+    idx = torch.full((1, k), -1, dtype=torch.int32, device="cuda")
+    s = torch.full((1, F), -1.0, dtype=torch.float32, device="cuda")
+
+    def accepted(nbytes):
+        try:
+            G.griffin_prefill_select(L, X, [0, S], k, idx, s_out=s, workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+        except G.GriffinError:
+            return False
+        return True
+
+    full = G.griffin_prefill_workspace_bytes(L, S, 1, False)
+    lo, hi = 0, full // 256                     # in units of 256 bytes: lo is refused, hi is accepted
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if accepted(max(mid, 1) * 256) else (mid, hi)
+    assert hi * 256 < full - 2 * S * F * 4      # the slabs of two ranges at the least were in the difference
+    idx.fill_(-1)
+    s.fill_(-1.0)
+    assert accepted(hi * 256)
+    sync()
+    assert max_rel(s.cpu().numpy()[0], s_ref[0]) <= TOL_S
+    np.testing.assert_array_equal(idx.cpu().numpy()[0], oracle.topk(s_ref[0], k))
+
+
 @pytest.mark.parametrize("d,F,lens,k,gated,bias", [
     (192, 11000, [1700], 5000, True, False),     # the first product leaves the bf16 copy of Z while it walks 602 tiles
     (128, 11000, [1000, 700], 5000, True, True), # the same with biases
