@@ -118,6 +118,11 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
 size_t ff1_slab_bytes(const griffin_layer &L, int64_t M);
 bool ff1_can_write_zb(const griffin_layer &L, int64_t ldx, const float *Z, int64_t ldz);
 int ff1_ntiles(const griffin_layer &L);
+int f32_ntiles(int32_t n);
+int launch_f32_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz, float *rowpart,
+                   hipStream_t st);
+int launch_f32_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, bool bf16, const void *W2p, int64_t ldw,
+                   const void *b2, void *Y, int64_t ldy, hipStream_t st);
 int launch_stat(const float *Z, int64_t ldz, const float *rowpart, int nt, int64_t M, int32_t F,
                 const SeqTable &seqs, float *s2part, float *s, float *s_out, hipStream_t st);
 int64_t stat_max_chunks(int64_t total_tokens, int32_t n_seqs, int32_t F);

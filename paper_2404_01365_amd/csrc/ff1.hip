@@ -13,7 +13,7 @@
 // reuses W tiles in its own L2.  The main kernel loads tiles straight into LDS; a register-staged
 // variant takes the shapes it cannot (d not a multiple of 64).
 //
-// fp32: a plain LDS-tiled FMA kernel (64x64 tile); exists for exactness tests and small cases.
+// fp32 blocks: f32.hip.
 #include "common.h"
 
 #include <atomic>
@@ -26,7 +26,6 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // one 16-byte chu
 
 constexpr int G_BN = 128, G_BK = 64;
 constexpr int G_THREADS = 256;
-constexpr int F_BM = 64, F_BN = 64, F_BK = 16;
 // s_waitcnt immediate that waits for vmcnt <= n only (expcnt / lgkmcnt fields left at "no wait")
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
@@ -766,88 +765,6 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_staged_kernel(Ff1Para
     ff1_mfma_epilogue<ACT, GATED, MI>(p, accU, accG, rs, m0, n0, tile_n);
 }
 
-// ------------------------------------------------------------------------------------ fp32 / FMA
-template <bool GATED>
-__global__ __launch_bounds__(256) void ff1_f32_kernel(Ff1Params p, int act)
-{
-    __shared__ float Xs[F_BK][F_BM + 4];
-    __shared__ float W1s[F_BK][F_BN + 4];
-    __shared__ float Wgs[F_BK][F_BN + 4];
-
-    const int tile_n = blockIdx.x, tile_m = blockIdx.y;
-    const int m0 = tile_m * F_BM, n0 = tile_n * F_BN;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int lrow = tid >> 2, lq = tid & 3;   // staging: row, float4 along k
-
-    const float *xp = (const float *)p.X + (int64_t)min(m0 + lrow, p.M - 1) * p.ldx + lq * 4;
-    const float *w1p = (const float *)p.W1 + (int64_t)min(n0 + lrow, p.F - 1) * p.ldw + lq * 4;
-    const float *wgp = GATED ? (const float *)p.Wg + (int64_t)min(n0 + lrow, p.F - 1) * p.ldw + lq * 4 : nullptr;
-
-    float g[4][4], u[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            g[i][j] = u[i][j] = 0.0f;
-
-    for (int k0 = 0; k0 < p.d; k0 += F_BK) {
-        const bool ok = k0 + lq * 4 < p.d;   // d is a multiple of 4
-        float4 vx = ok ? *(const float4 *)(xp + k0) : make_float4(0, 0, 0, 0);
-        float4 v1 = ok ? *(const float4 *)(w1p + k0) : make_float4(0, 0, 0, 0);
-        float4 vg = (GATED && ok) ? *(const float4 *)(wgp + k0) : make_float4(0, 0, 0, 0);
-        __syncthreads();
-        Xs[lq * 4 + 0][lrow] = vx.x; Xs[lq * 4 + 1][lrow] = vx.y; Xs[lq * 4 + 2][lrow] = vx.z; Xs[lq * 4 + 3][lrow] = vx.w;
-        W1s[lq * 4 + 0][lrow] = v1.x; W1s[lq * 4 + 1][lrow] = v1.y; W1s[lq * 4 + 2][lrow] = v1.z; W1s[lq * 4 + 3][lrow] = v1.w;
-        if (GATED) {
-            Wgs[lq * 4 + 0][lrow] = vg.x; Wgs[lq * 4 + 1][lrow] = vg.y; Wgs[lq * 4 + 2][lrow] = vg.z; Wgs[lq * 4 + 3][lrow] = vg.w;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < F_BK; ++kk) {
-            float a[4], b1v[4], bgv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = Xs[kk][ty * 4 + i];
-                b1v[i] = W1s[kk][tx * 4 + i];
-                bgv[i] = GATED ? Wgs[kk][tx * 4 + i] : 0.0f;
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    u[i][j] = fmaf(a[i], b1v[j], u[i][j]);
-                    if (GATED)
-                        g[i][j] = fmaf(a[i], bgv[j], g[i][j]);
-                }
-        }
-    }
-
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int grow = m0 + ty * 4 + i;
-        float sq = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int colj = n0 + tx * 4 + j;
-            if (colj < p.F) {
-                float uu = u[i][j] + (p.b1 ? ((const float *)p.b1)[colj] : 0.0f);
-                float z;
-                if (GATED)
-                    z = act_apply(act, g[i][j] + (p.bg ? ((const float *)p.bg)[colj] : 0.0f)) * uu;
-                else
-                    z = act_apply(act, uu);
-                sq = fmaf(z, z, sq);
-                if (grow < p.M)
-                    p.Z[(int64_t)grow * p.ldz + colj] = z;
-            }
-        }
-        // the 16 threads that share a row are one DPP row of the wavefront
-        sq = row16_sum(sq);
-        if (tx == 0 && grow < p.M)
-            p.rowpart[(int64_t)grow * p.nt + tile_n] = sq;
-    }
-}
-
 // ------------------------------------------------------------------------------------ short prompts: d in ranges
 // A short prompt has few token tiles, and few neuron tiles times few token tiles leave most of the chip without work
 // while the call has to read all the weights (40 tokens of a 4096 x 11008 block: 86 tiles for 256 CUs).  The contraction is
@@ -983,8 +900,7 @@ size_t ff1_slab_bytes(const griffin_layer &L, int64_t M)
 
 int ff1_ntiles(const griffin_layer &L)
 {
-    const int bn = L.dtype == GRIFFIN_BF16 ? G_BN : F_BN;
-    return (L.n + bn - 1) / bn;
+    return L.dtype == GRIFFIN_BF16 ? (L.n + G_BN - 1) / G_BN : f32_ntiles(L.n);
 }
 
 // one workgroup per CU (a multiple of 8, so that every XCD gets the same number), fewer if there are fewer tiles.
@@ -1124,13 +1040,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
         }
         return check_launch("ff1_bf16_mfma_kernel");
     }
-    p.mt = (int32_t)((M + F_BM - 1) / F_BM);
-    dim3 grid(p.nt, p.mt), block(256);
-    if (gated)
-        hipLaunchKernelGGL(ff1_f32_kernel<true>, grid, block, 0, st, p, L.act);
-    else
-        hipLaunchKernelGGL(ff1_f32_kernel<false>, grid, block, 0, st, p, L.act);
-    return check_launch("ff1_f32_kernel");
+    return launch_f32_ff1(L, X, ldx, M, Z, ldz, rowpart, st);
 }
 
 // C[s] = A B^T over the s-th range of the contraction, fp32, for s = 0 .. splits-1, on the

@@ -15,7 +15,7 @@
 //     bf16 on its way through registers into LDS, 16-byte loads, double-buffered, BK = 64, a
 //     256-token x 128-feature tile, 4 waves of 128 x 64, v_mfma_f32_32x32x16_bf16, XOR-swizzled
 //     LDS rows), with the same ranges and the same sum;
-//   * shapes the tiles cannot take (D_ff not a multiple of 8, fp32 blocks): a plain fp32 kernel.
+//   * shapes the tiles cannot take (D_ff not a multiple of 8, fp32 blocks): the fp32 kernel of f32.hip.
 #include "common.h"
 
 namespace griffin {
@@ -219,23 +219,6 @@ __global__ __launch_bounds__(256) void ff2_split_sum_kernel(Ff2Params p)
     y[2] = (uint16_t)f32_to_bf16_bits(a.z); y[3] = (uint16_t)f32_to_bf16_bits(a.w);
 }
 
-// plain fp32 path: one output per thread, 64 x 4 outputs per workgroup share the Z rows via L1
-template <bool BF16>
-__global__ __launch_bounds__(256) void ff2_plain_kernel(Ff2Params p)
-{
-    const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int row = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (col >= p.d || row >= p.M)
-        return;
-    const float *z = p.Z + (int64_t)row * p.ldz;
-    float acc = 0.0f;
-    for (int j = 0; j < p.F; ++j)
-        acc = fmaf(z[j], load_scalar<BF16>(p.W2p, (int64_t)col * p.ldw + j), acc);
-    if (p.b2)
-        acc += load_scalar<BF16>(p.b2, col);
-    store_scalar<BF16>(p.Y, (int64_t)row * p.ldy + col, acc);
-}
-
 // Z fp32 -> bf16 copy [M][F] (rounded to nearest even), 8 elements per thread
 __global__ __launch_bounds__(256) void ff2_z_to_bf16_kernel(const float *Z, int64_t ldz, int64_t M, int32_t F, uint16_t *Zb)
 {
@@ -346,13 +329,7 @@ int launch_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, boo
         hipLaunchKernelGGL(ff2_split_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p);
         return check_launch("ff2_split_sum_kernel");
     }
-    p.mt = p.nt = 0;
-    dim3 grid((d + 63) / 64, (unsigned)((M + 3) / 4));
-    if (bf16)
-        hipLaunchKernelGGL(ff2_plain_kernel<true>, grid, dim3(256), 0, st, p);
-    else
-        hipLaunchKernelGGL(ff2_plain_kernel<false>, grid, dim3(256), 0, st, p);
-    return check_launch("ff2_plain_kernel");
+    return launch_f32_ff2(Z, ldz, M, F, d, bf16, W2p, ldw, b2, Y, ldy, st);
 }
 
 }  // namespace griffin

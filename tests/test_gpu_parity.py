@@ -308,6 +308,8 @@ PREFILL_CASES = [
     (synth.DT_F32, 256, 688, [64], 344, synth.ACT_SILU, True, False),            # config 0 shape
     (synth.DT_F32, 72, 150, [70, 1, 33], 40, synth.ACT_GELU_TANH, True, True),   # ragged tiles, 3 seqs
     (synth.DT_F32, 64, 130, [9], 130, synth.ACT_RELU, False, True),              # Eq. 2, keep all
+    (synth.DT_F32, 136, 2050, [500, 21], 1000, synth.ACT_SILU, True, True),      # 64-token tiles, ragged both ways, d = 8.5 slices
+    (synth.DT_F32, 8, 33, [1], 16, synth.ACT_GELU_TANH, True, False),            # half a slice of d, one token
     (synth.DT_BF16, 512, 1000, [300], 500, synth.ACT_SILU, True, False),         # 3 x 8 tiles, ragged both
     (synth.DT_BF16, 136, 260, [129, 0, 200], 77, synth.ACT_GELU_TANH, True, True),  # k tail, empty seq
     (synth.DT_BF16, 256, 384, [256], 100, synth.ACT_RELU, False, False),         # Eq. 2 on the MFMA path
@@ -582,6 +584,11 @@ def test_shared_set_for_a_batch_end_to_end():
     (synth.DT_BF16, 136, 264, 70, False),      # k tail (264 = 4 * 64 + 8)
     (synth.DT_BF16, 64, 131, 9, True),         # D_ff not a multiple of 8: plain path
     (synth.DT_F32, 256, 688, 64, True),        # config-0 shape, fp32
+    (synth.DT_F32, 8, 1, 1, False),            # the fp32 kernel: one element, one slice
+    (synth.DT_F32, 40, 133, 33, True),         # ... D_ff not a multiple of 4 (element loads), two token tiles
+    (synth.DT_F32, 1048, 132, 1000, True),     # ... 64-token tiles (16 x 33 of them), last ones ragged
+    (synth.DT_BF16, 1032, 262, 1000, True),    # ... bf16 W_2, D_ff even, 64-token tiles
+    (synth.DT_BF16, 40, 268, 31, False),       # ... bf16 W_2 with 8-byte loads (D_ff a multiple of 4, not of 8)
 ])
 def test_prompt_output_uses_the_full_block(dtype, d, F, S, bias):
     act = synth.ACT_SILU
