@@ -179,8 +179,9 @@ int griffin_compact(const griffin_layer *L, const int32_t *idx, int32_t k,
  * for `batch` independent rows x[b] through the ONE block C (a compact block, or a full one
  * with n = D_FF, which is Eq. 1).  x, y: [batch][d] contiguous, C->dtype.  With batch > 1 the
  * rows share one selected set (Section 5.3, Eq. 7) and the weights are streamed once per
- * four rows; five rows and more of a bf16 block with d a multiple of 512 up to 5120 take the
- * matrix cores and stream them once per sixteen rows.
+ * four rows; five rows and more of a bf16 block (d from 64 to 8192; of small blocks whose d is not a
+ * multiple of 512 more than sixteen) take the matrix cores and stream them once per pass of 16 to 64
+ * rows, as many as the registers hold at that width (64 up to d = 2048, 48 up to 3072, 32 up to 5120).
  * workspace >= griffin_decode_workspace_bytes(d, n, batch) bytes, 256-byte aligned.
  */
 size_t griffin_decode_workspace_bytes(int32_t d, int32_t n, int32_t batch);
@@ -219,7 +220,8 @@ int griffin_ff_decode_multi(const griffin_layer *Cs, int32_t batch, const void *
  * With a workspace of griffin_decode_workspace_bytes(d, L->n, batch) bytes (sized for the whole
  * block rather than for k neurons) five rows and more take ONE pass over the whole block, every row
  * dropping the neurons outside its own set: the sets of a batch cover most of the block between them,
- * so this moves far fewer bytes than a pass per row (bf16, d a multiple of 512 up to 5120).
+ * so this moves far fewer bytes than a pass per row (bf16, d from 64 to 8192; widths that are not a
+ * multiple of 512 up to 5120 take it when the sets together hold at least 1.5 times the block).
  */
 int griffin_ff_decode_indexed(const griffin_layer *L, const int32_t *idx, int32_t k,
                               int32_t batch, const void *x, void *y, void *workspace,

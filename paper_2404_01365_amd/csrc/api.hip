@@ -360,14 +360,7 @@ size_t griffin_decode_workspace_bytes(int32_t d, int32_t n, int32_t batch)
 {
     if (d < 1 || n < 1 || batch < 1 || batch > GRIFFIN_MAX_BATCH)
         return 0;
-    size_t floats = (size_t)decode_parts(n, batch) * batch * d;
-    if (batch >= DEC_BATCH_MIN_ROWS && decode_batch_supported(d, n, true)) {
-        // also enough for the masked pass of griffin_ff_decode_indexed over a block of n neurons
-        const size_t fb = decode_masked_workspace_floats(d, n, batch);
-        if (fb > floats)
-            floats = fb;
-    }
-    return floats * sizeof(float);
+    return decode_wanted_floats(d, n, batch) * sizeof(float);
 }
 
 static int decode_common(const griffin_layer *L0, const griffin_layer *multi, const int32_t *idx, int32_t k,
@@ -381,7 +374,7 @@ static int decode_common(const griffin_layer *L0, const griffin_layer *multi, co
     if (!aligned16(x) || !aligned16(y))
         return GRIFFIN_ESHAPE;
     const int32_t n = idx ? k : L0->n;
-    if (!ws || ((uintptr_t)ws & 255) || ws_bytes < griffin_decode_workspace_bytes(L0->d, n, batch ? batch : 1))
+    if (!ws || ((uintptr_t)ws & 255) || ws_bytes < decode_least_floats(L0->d, n, batch ? batch : 1) * sizeof(float))
         return GRIFFIN_EWORKSPACE;
     if (batch == 0)
         return GRIFFIN_OK;
@@ -447,7 +440,7 @@ int griffin_ff_decode_indexed(const griffin_layer *L, const int32_t *idx, int32_
 // The partial rows of griffin_ff_decode live in a file-scope device array instead of a workspace the
 // caller allocated.  In host code the array's name is only a handle: its device address is asked for
 // once per device (with that device current) and that address is what the kernels are given.
-constexpr size_t STATIC_SCRATCH_BYTES = (size_t)8 << 20;
+constexpr size_t STATIC_SCRATCH_BYTES = DEC_STATIC_BYTES;
 constexpr int STATIC_MAX_DEVICES = 64;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 static std::atomic<void *> g_scratch_ptr[STATIC_MAX_DEVICES];

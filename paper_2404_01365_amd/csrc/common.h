@@ -169,15 +169,20 @@ int launch_decode(const DecodeJob &job, hipStream_t st);
 bool decode_split_supported(const DecodeJob &job);
 int launch_decode_split(const DecodeJob &job, hipStream_t st, hipEvent_t ev_mid);
 // rows 5.. of a batch through one shared block: matrix-core path (decode_batch.hip)
-bool decode_batch_supported(int32_t d, int32_t n, bool bf16);
-size_t decode_batch_workspace_floats(int32_t d, int32_t n, int32_t batch);
-size_t decode_masked_workspace_floats(int32_t d, int32_t n_src, int32_t batch);
-int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32_t *idx, int32_t k, int *NR_out,
+// floats of workspace it wants (0: it does not take the shape, or not within `have` floats); the front
+// leaves [batch][NR][d] partial rows
+size_t decode_batch_floats(int32_t d, int32_t n, int32_t batch, size_t have);
+int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32_t *idx, int32_t k, size_t have, int *NR_out,
                               hipStream_t st);
 int launch_index_sets_build(const int32_t *idx, int32_t k, int32_t batch, int32_t n_block, uint32_t *sets, hipStream_t st);
 size_t index_sets_words(int32_t n_block, int32_t batch);
+
 constexpr int DEC_BATCH_MIN_ROWS = 5;
 int decode_parts(int32_t n, int32_t batch);
+// floats of workspace that a decode has to be given, and that it makes use of
+size_t decode_least_floats(int32_t d, int32_t n, int32_t batch);
+size_t decode_wanted_floats(int32_t d, int32_t n, int32_t batch);
+constexpr size_t DEC_STATIC_BYTES = (size_t)8 << 20;     // the library's own scratch array (griffin_ff_decode_static)
 void set_decode_probe(hipEvent_t begin, hipEvent_t mid, hipEvent_t end);
 
 }  // namespace griffin

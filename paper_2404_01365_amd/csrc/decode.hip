@@ -382,6 +382,40 @@ int decode_parts(int32_t n, int32_t batch)
     return P < 1 ? 1 : P;
 }
 
+// What a decode has to be given: a partial row per workgroup and batch row; for the shapes whose batches have always run
+// on the matrix cores also what sixteen rows a pass need there (partial rows, Z and membership words).
+size_t decode_least_floats(int32_t d, int32_t n, int32_t batch)
+{
+    size_t floats = (size_t)decode_parts(n, batch) * batch * d;
+    if (batch >= DEC_BATCH_MIN_ROWS && d % 512 == 0 && d <= 5120 && n >= 64 && n <= 32768) {
+        int64_t nr = 256 / (d / 512);
+        if (nr > 64) nr = 64;
+        if (nr < (n + 479) / 480) nr = (n + 479) / 480;
+        const size_t fb = (size_t)batch * nr * d + (size_t)n * 17 + 128;
+        if (fb > floats)
+            floats = fb;
+    }
+    return floats;
+}
+
+// What it makes use of: more rows a pass want more room for their Z, and the matrix-core path also takes shapes that
+// it did not take before.  A decode that fits the library's own array goes on fitting it: the two entry points choose
+// their route by the shape alone.
+static size_t decode_route_floats(int32_t d, int32_t n, int32_t batch)
+{
+    const size_t least = decode_least_floats(d, n, batch), own = DEC_STATIC_BYTES / sizeof(float);
+    return batch < DEC_BATCH_MIN_ROWS ? 0 : decode_batch_floats(d, n, batch, least <= own ? own : (size_t)-1);
+}
+
+// rows of 1 KB pieces: the shapes whose batches have always run on the matrix cores
+static bool decode_whole_pieces(int32_t d) { return d % 512 == 0 && d <= 5120; }
+
+size_t decode_wanted_floats(int32_t d, int32_t n, int32_t batch)
+{
+    const size_t least = decode_least_floats(d, n, batch), route = decode_route_floats(d, n, batch);
+    return route > least ? route : least;
+}
+
 // one-shot instrumentation: events recorded around the streaming kernel of the next decode
 static thread_local hipEvent_t g_probe_begin = nullptr, g_probe_mid = nullptr, g_probe_end = nullptr;
 
@@ -398,17 +432,29 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
     if (R == 0)
         return GRIFFIN_EUNSUPPORTED;
     int P = decode_parts(job.n, job.batch);
-    // five rows and more through one shared block: the matrix-core path
-    const bool batch_path = !job.multi && !job.idx && job.batch >= DEC_BATCH_MIN_ROWS &&
-                            decode_batch_supported(job.d, job.n, job.bf16);
-    // five rows and more with their own sets inside one block: one masked pass over the whole block, if
-    // the caller's workspace was sized for the whole block (else row by row through the index lists)
-    const bool masked_path = !job.multi && job.idx && job.batch >= DEC_BATCH_MIN_ROWS && job.W2 &&
-                             decode_batch_supported(job.d, job.n_src, job.bf16) &&
-                             job.part_bytes >= decode_masked_workspace_floats(job.d, job.n_src, job.batch) * sizeof(float);
-    if (!masked_path &&
-        job.part_bytes < (batch_path ? decode_batch_workspace_floats(job.d, job.n, job.batch)
-                                     : (size_t)P * job.batch * job.d) * sizeof(float))
+    // A batch through one shared block takes the matrix-core path, with as many rows a pass as the workspace has room
+    // for; else rows go four at a time.  A batch whose rows have their own sets inside one block takes it as a masked pass
+    // over the whole block if the workspace was sized for the whole block; else rows go one by one through the index lists.
+    // Rows of other widths than whole 1 KB pieces up to 5120: a shared block of a few megabytes is cheaper four rows at a
+    // time as long as that is not many passes (two kernels instead of three; 704 x 1500 Eq. 2, 5 / 16 rows: 11.5 / 13.3 us against
+    // 13.1 / 14.0; 1152 x 2400: 17.7 / 28.0 against 16.4 / 18.2), and the masked pass, which reads the whole block, has to stand
+    // against rows that read the k neurons of their sets each (2752 x 15520, k = n/2: 3 rows 64 us one by one, 58 masked;
+    // 5 rows 112 / 59; 16 rows 330 / 62).
+    const int32_t nb = job.idx ? job.n_src : job.n;
+    const bool worth = decode_whole_pieces(job.d) || (job.idx ? 2 * (int64_t)job.batch * job.n >= 3 * (int64_t)nb
+                                                              : job.batch > 16 || (int64_t)nb * job.d >= (2 << 20));
+    size_t have = 0;
+    if (job.bf16 && !job.multi && job.W2 && job.batch >= DEC_BATCH_MIN_ROWS && worth) {
+        have = decode_route_floats(job.d, nb, job.batch);
+        if (job.idx && job.part_bytes < decode_wanted_floats(job.d, nb, job.batch) * sizeof(float))
+            have = 0;
+        if (have > job.part_bytes / sizeof(float))
+            have = job.part_bytes / sizeof(float);
+        if (!decode_batch_floats(job.d, nb, job.batch, have))
+            have = 0;
+    }
+    const bool batch_path = have > 0;
+    if (!batch_path && job.part_bytes < (size_t)P * job.batch * job.d * sizeof(float))
         return GRIFFIN_EWORKSPACE;
 
     DecodeParams p;
@@ -450,9 +496,9 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
     }
     if (!job.W2 && !job.multi)
         return GRIFFIN_EUNSUPPORTED;       // only the transposed copy is there and this call cannot use it
-    if (batch_path || masked_path) {
-        int rc = masked_path ? launch_decode_batch_front(job, job.n_src, job.idx, job.n, &P, st)
-                             : launch_decode_batch_front(job, job.n, nullptr, 0, &P, st);
+    if (batch_path) {
+        int rc = job.idx ? launch_decode_batch_front(job, job.n_src, job.idx, job.n, have, &P, st)
+                         : launch_decode_batch_front(job, job.n, nullptr, 0, have, &P, st);
         if (rc != GRIFFIN_OK)
             return rc;
         if (ev_mid && hipEventRecord(ev_mid, st) != hipSuccess)

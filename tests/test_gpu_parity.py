@@ -209,6 +209,34 @@ def test_indexed_decode_with_sets_built_once(d, n, k, B):
             assert max_rel(to_host(y1)[b], ref) <= TOL_OUT[dtype], (t, b)
 
 
+# The matrix-core path beyond one tile of sixteen rows and beyond whole 1 KB pieces: passes of 1 to 4 tiles, the last
+# pass narrower; blocks of d that end early or are not there; D_ff not a multiple of 8 and of the workgroups' shares.
+@pytest.mark.parametrize("d,n,B,gated,bias", [
+    (64, 1000, 17, True, True),       # one 64-element block per row, two tiles
+    (72, 70, 64, True, False),        # a block moved back to the end of the row; n = 8 * 8 + 6
+    (520, 4100, 33, False, True),     # Eq. 2, nine blocks, three tiles; a second column slice of 8
+    (1152, 4503, 49, True, True),     # four tiles, 18 blocks on 5 waves, n odd
+    (2048, 700, 64, True, False),     # four full tiles
+    (2752, 1037, 40, True, False),    # 43 blocks on 8 waves, three tiles
+    (3072, 8300, 48, True, True),     # three tiles at the widest, full groups and a rest
+    (4096, 333, 40, True, False),     # two passes: two tiles and one
+    (5120, 517, 31, False, True),     # two tiles at the widest, Eq. 2
+    (6000, 420, 7, True, True),       # wider than 5120, last block short
+    (8192, 260, 20, True, False),     # widest rows: a tile a pass
+])
+def test_ff_decode_batch_tiles_and_widths(d, n, B, gated, bias):
+    dtype, act = synth.DT_BF16, synth.ACT_SILU
+    c = synth.small_case(d * 3 + n, d, n, 4, dtype, T=B, with_bias=bias)
+    Wg = c["Wg"] if gated else None
+    bg = c.get("bg") if gated else None
+    L, _ = dev_layer(Wg, c["W1"], c["W2"], act, dtype, bg, c.get("b1"), c.get("b2"))
+    got = run_decode(L, to_dev(c["xt"], dtype), B)
+    assert np.all(np.isfinite(got))
+    for b in range(B):
+        ref = oracle.ff_decode(c["xt"][b], Wg, c["W1"], c["W2"], act, bg, c.get("b1"), c.get("b2"))
+        assert max_rel(got[b], ref) <= TOL_OUT[dtype], b
+
+
 # ------------------------------------------------------------------ compaction
 @pytest.mark.parametrize("interleaved", [False, True])
 @pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
@@ -868,3 +896,14 @@ def test_indexed_decode_masked_pass_matches_oracle(d, n, k, B, gated, bias):
     for b in range(B):
         ref = oracle.ff_decode(c["xt"][b], sub(Wg, b), c["W1"][idx[b]], c["W2"][idx[b]], act, sub(bg, b), sub(c.get("b1"), b), c.get("b2"))
         assert max_rel(got[b], ref) <= TOL_OUT[dtype], b
+
+
+@pytest.mark.parametrize("d,n,k,B,gated,bias", [
+    (1152, 1503, 700, 20, True, True),     # masked pass at a width that is not whole 1 KB pieces, two tiles
+    (2752, 517, 250, 40, False, True),     # ... three tiles, Eq. 2
+    (8192, 200, 130, 5, True, False),      # ... the widest rows
+    (2752, 517, 40, 6, True, False),       # small sets: row by row through the lists
+    (2048, 999, 400, 50, True, True),      # four tiles in one pass, the words of four groups
+])
+def test_indexed_decode_tiles_and_widths(d, n, k, B, gated, bias):
+    test_indexed_decode_masked_pass_matches_oracle(d, n, k, B, gated, bias)
