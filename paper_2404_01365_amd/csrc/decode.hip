@@ -13,8 +13,8 @@
 //     (s*NT + T)*G ... +G-1), so at any time the chip reads one contiguous window of rows
 //     per matrix (one window in all when the three rows of a neuron are stored side by
 //     side, i.e. Wg, W1, W2 interleaved with ld = 3d);
-//   * the two dot products are reduced inside the wave with DPP, combined across the team's
-//     waves through a few LDS words and one barrier per G neurons, and the loads of the next
+//   * the dot products (two per row of x) are reduced inside the wave with DPP, all together, combined across
+//     the team's waves through a few LDS words and one barrier per G neurons, and the loads of the next
 //     two steps are already in flight while that happens (three register sets; the loads are
 //     branch-free so the compiler waits for the oldest set only; with one step of lookahead a
 //     wave streams only one step's bytes per memory latency, which is what bounds narrow rows);
@@ -27,6 +27,7 @@ namespace griffin {
 
 constexpr int DEC_G = 1;                 // neurons per team step
 constexpr int DEC_MAX_WAVES = 16;        // waves per workgroup
+constexpr int DEC_MAX_TEAMS = 8;         // teams per workgroup
 constexpr int DEC_MAX_PARTS = 256;       // partial rows per batch row
 constexpr int DEC_NB_MAX = 4;            // rows of x sharing one pass over the weights
 constexpr int DEC_FOLD_FLOATS = 8192;    // LDS floats for folding teams (d <= 8192)
@@ -88,6 +89,100 @@ struct Chunk {
     }
 };
 
+// The sums of NV values (1, 2, 4 or 8) over the sixteen lanes of every DPP row, value i in the lanes whose index ends in
+// i (log2 NV bits).  Two values that are added over the same pair of lanes change places while they are added, so a step
+// halves the number of values: 22 instructions for eight values, where a sum of each over the wavefront takes 88 (which bound
+// the passes of three and four rows: three rows of 4096 x 5504 36.8 -> 29.1 us, of 3072 x 12288 68 -> 44, of a 4096 x 11008
+// Eq. 2 block 51.4 -> 37.8; a single row waits for memory either way).
+template <int CTRL>
+__device__ __forceinline__ float pair_step(float even, float odd, bool is_odd)
+{
+    return (is_odd ? odd : even) + dpp_f32<CTRL>(is_odd ? even : odd);
+}
+
+template <int NV>
+__device__ __forceinline__ float row16_sums(const float (&v)[NV], int lane)
+{
+    constexpr int XOR1 = 0xB1, XOR2 = 0x4E, ROR4 = 0x124, ROR8 = 0x128;
+    const bool o0 = lane & 1, o1 = lane & 2, o2 = lane & 4;
+    float a[4], b[2], c;
+    if (NV >= 2) {
+#pragma unroll
+        for (int i = 0; i < NV / 2; ++i)
+            a[i] = pair_step<XOR1>(v[(2 * i) % NV], v[(2 * i + 1) % NV], o0);
+    } else {
+        a[0] = v[0] + dpp_f32<XOR1>(v[0]);
+    }
+    if (NV >= 4) {
+#pragma unroll
+        for (int i = 0; i < NV / 4; ++i)
+            b[i] = pair_step<XOR2>(a[(2 * i) % 4], a[(2 * i + 1) % 4], o1);
+    } else {
+        b[0] = a[0] + dpp_f32<XOR2>(a[0]);
+    }
+    // a rotation by four brings a lane whose bit 2 differs and whose lower bits agree
+    c = NV >= 8 ? pair_step<ROR4>(b[0], b[1], o2) : b[0] + dpp_f32<ROR4>(b[0]);
+    return c + dpp_f32<ROR8>(c);
+}
+
+// z of the team's neuron for NB rows from the partial sums [value][4 per wave, zero up to 64] (value: gate and up of row 0, of
+// row 1, ...).  The lanes share the values out, 64 / NV lanes each; sigma is taken once for all rows where a row's gate and
+// up sums are in one DPP row.
+template <bool GATED, int NB>
+__device__ __forceinline__ void team_z(const float (*red)[64], int lane, int act, float bg, float b1, float (&z)[NB])
+{
+    constexpr int NV = (GATED ? 2 : 1) * NB, LPV = 64 / NV;
+    const float *src = &red[lane / LPV][(lane % LPV) * NV];
+    float q = 0.0f;
+    if (NV == 8) {
+        const f32x4 t = *(const f32x4 *)src, u = *(const f32x4 *)(src + 4);
+        q = ((t.x + t.y) + (t.z + t.w)) + ((u.x + u.y) + (u.z + u.w));
+    } else if (NV == 4) {
+        const f32x4 t = *(const f32x4 *)src;
+        q = (t.x + t.y) + (t.z + t.w);
+    } else if (NV == 2) {
+        const float2 t = *(const float2 *)src;
+        q = t.x + t.y;
+    } else {
+        q = *src;
+    }
+    q += dpp_f32<0xB1>(q);
+    q += dpp_f32<0x4E>(q);
+    q += dpp_f32<0x141>(q);          // eight lanes
+    if (NV == 8) {
+        // row nb: gate in its lanes 0-7, up in its lanes 8-15
+        const float u = dpp_f32<0x128>(q);
+        const float zl = act_apply(act, q + bg) * (u + b1);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            z[nb] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zl), 16 * nb));
+        return;
+    }
+    q += dpp_f32<0x140>(q);          // sixteen
+#define TEAM_ROW(r_) __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q), 16 * (r_)))
+    if (NV == 4 && !GATED) {
+        const float zl = act_apply(act, q + b1);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            z[nb] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zl), 16 * nb));
+    } else if (NV == 4) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            z[nb] = act_apply(act, TEAM_ROW(2 * nb) + bg) * (TEAM_ROW(2 * nb + 1) + b1);
+    } else if (NV == 2) {
+        const float s0 = TEAM_ROW(0) + TEAM_ROW(1), s1 = TEAM_ROW(2) + TEAM_ROW(3);
+        if (GATED) {
+            z[0] = act_apply(act, s0 + bg) * (s1 + b1);
+        } else {
+            z[0] = act_apply(act, s0 + b1);
+            z[NB - 1] = act_apply(act, s1 + b1);
+        }
+    } else {
+        z[0] = act_apply(act, (TEAM_ROW(0) + TEAM_ROW(1)) + (TEAM_ROW(2) + TEAM_ROW(3)) + b1);
+    }
+#undef TEAM_ROW
+}
+
 // GATED and INDEXED are compile-time so that the three row loads of a neuron are issued
 // back to back with no branch between them (a branch there makes the compiler wait for the
 // first load before issuing the next).
@@ -96,11 +191,12 @@ struct Chunk {
 template <bool BF16, bool GATED, bool INDEXED, bool BIAS, int NB>
 __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *Wg, const void *W1,
                                             const void *W2, const void *bg, const void *b1,
-                                            float (*red)[2 * DEC_G * DEC_NB_MAX][16], float *fold)
+                                            float (*red)[2 * DEC_NB_MAX][64], float *fold)
 {
     constexpr int E = Chunk<BF16>::E;
     constexpr int ES = BF16 ? 2 : 4;
-    constexpr int G = DEC_G;
+    constexpr int G = DEC_G, NMAT = GATED ? 2 : 1;
+    static_assert(G == 1, "the team's sums are those of one neuron");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, in an SGPR
     const int R = p.R;
@@ -128,8 +224,8 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
     const int nsteps = (p.n + NT * G - 1) / (NT * G);
     const int32_t *idx = INDEXED ? p.idx + (int64_t)b * p.n : nullptr;
     const int64_t row_bytes = p.ld * ES;
-    constexpr int NV = 2 * G * NB;                   // values to combine across the team per step
-    float(*myred)[2 * G * DEC_NB_MAX][16] = red + team * 2;   // [parity][value][wave of the team]
+    constexpr int NV = NMAT * NB;                    // values to combine across the team per step
+    float(*myred)[2 * DEC_NB_MAX][64] = red + team * 2;       // [parity][value][four partial sums per wave of the team]
 
 
     // Loads are branch-free (slots past the last neuron re-read the last row, which stays in
@@ -138,6 +234,9 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
     u32x4 buf[3][G][3];
     int rows[3][G];
     float bias[3][G][2];
+    // a bias that is not there is loaded from a matrix instead (at an element that exists) and not used: a branch around its load
+    // would make it, and the weights behind it, wait (4096 x 11008 Eq. 2 with biases, 3 rows: 45.0 us a call against 38.2)
+    const void *bgp = bg ? bg : W1, *b1p = b1 ? b1 : W1;
 
 // the weights are read once per call: non-temporal loads (no allocation in the caches on the way)
 // stream measurably faster than plain ones (135 MB: 20.4 us against 24.0 us in a bare read loop)
@@ -157,8 +256,9 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
             buf[B_][g][1] = DEC_STREAM_LOAD((const u32x4 *)((const char *)W1 + row_ * row_bytes) + cc);     \
             buf[B_][g][2] = DEC_STREAM_LOAD((const u32x4 *)((const char *)W2 + row_ * row_bytes) + cc);     \
             if (BIAS) {                                                                      \
-                bias[B_][g][0] = (GATED && bg) ? load_scalar<BF16>(bg, row_) : 0.0f;         \
-                bias[B_][g][1] = b1 ? load_scalar<BF16>(b1, row_) : 0.0f;                    \
+                if (GATED)                                                                   \
+                    bias[B_][g][0] = load_scalar<BF16>(bgp, row_);                           \
+                bias[B_][g][1] = load_scalar<BF16>(b1p, row_);                               \
             }                                                                                \
             rows[B_][g] = row_;                                                              \
         }                                                                                    \
@@ -168,37 +268,20 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
     {                                                                                        \
         float pv_[NV];                                                                       \
         _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                    \
-            _Pragma("unroll") for (int g = 0; g < G; ++g)                                    \
         {                                                                                    \
-            pv_[(nb * G + g) * 2] = GATED ? wave_sum(Chunk<BF16>::dot(buf[B_][g][0], xr[nb])) : 0.0f; \
-            pv_[(nb * G + g) * 2 + 1] = wave_sum(Chunk<BF16>::dot(buf[B_][g][1], xr[nb]));   \
+            if (GATED)                                                                       \
+                pv_[nb * NMAT] = Chunk<BF16>::dot(buf[B_][0][0], xr[nb]);                    \
+            pv_[nb * NMAT + NMAT - 1] = Chunk<BF16>::dot(buf[B_][0][1], xr[nb]);             \
         }                                                                                    \
-        if (lane == 0) {                                                                     \
-            _Pragma("unroll") for (int v = 0; v < NV; ++v) myred[(s_) & 1][v][wt] = pv_[v];  \
-        }                                                                                    \
+        const float part_ = row16_sums<NV>(pv_, lane);                                       \
+        if ((lane & 15) < NV)                                                                \
+            myred[(s_) & 1][lane & 15][wt * 4 + (lane >> 4)] = part_;                        \
         __syncthreads();                                                                     \
-        _Pragma("unroll") for (int q = 0; q < (NV + 3) / 4; ++q)                             \
-        {                                                                                    \
-            float q_ = q * 4 + (lane >> 4) < NV ? myred[(s_) & 1][q * 4 + (lane >> 4)][lane & 15] : 0.0f; \
-            q_ = row16_sum(q_);                                                              \
-            _Pragma("unroll") for (int h = 0; h < 2; ++h)                                    \
-            {                                                                                \
-                if (q * 4 + 2 * h < NV) {                                                    \
-                    const int pair_ = q * 2 + h;         /* = nb * G + g */                  \
-                    const int nb_ = pair_ / G, g_ = pair_ % G;                               \
-                    const int j_ = ((s_) * NT + T) * G + g_;                                 \
-                    float gg_ = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q_), 32 * h));      \
-                    float uu_ = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q_), 32 * h + 16)); \
-                    if (BIAS) {                                                              \
-                        gg_ += bias[B_][g_][0];                                              \
-                        uu_ += bias[B_][g_][1];                                              \
-                    }                                                                        \
-                    float z_ = GATED ? act_apply(p.act, gg_) * uu_ : act_apply(p.act, uu_);  \
-                    z_ = j_ < p.n ? z_ : 0.0f;                                               \
-                    Chunk<BF16>::axpy(z_, buf[B_][g_][2], ya[nb_]);                          \
-                }                                                                            \
-            }                                                                                \
-        }                                                                                    \
+        float z_[NB];                                                                        \
+        team_z<GATED, NB>(myred[(s_) & 1], lane, p.act, BIAS && GATED && bg ? bias[B_][0][0] : 0.0f, BIAS && b1 ? bias[B_][0][1] : 0.0f, z_); \
+        const int j_ = (s_) * NT + T;                                                        \
+        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                    \
+            Chunk<BF16>::axpy(j_ < p.n ? z_[nb] : 0.0f, buf[B_][0][2], ya[nb]);              \
     }
 
     if (nsteps > 0) {
@@ -206,8 +289,8 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
         DEC_LOAD(1, 1)             // steps past the end re-read the last row and contribute nothing
     }
     // zero the padding entries of the cross-wave buffers once (the first rows are already on their way)
-    for (int i = threadIdx.x; i < p.teams * 2 * 2 * G * DEC_NB_MAX * 16; i += blockDim.x)
-        (&red[0][0][0])[i] = 0.0f;
+    for (int i = threadIdx.x; i < p.teams * 2 * NV * 16; i += blockDim.x)
+        *(f32x4 *)&red[i / (NV * 16)][(i / 16) % NV][i % 16 * 4] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
     __syncthreads();
     for (int s = 0; s < nsteps; s += 3) {
         DEC_LOAD(2, s + 2)
@@ -270,7 +353,7 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
 template <bool BF16, bool GATED, bool INDEXED, bool BIAS, int NB>
 __global__ __launch_bounds__(DEC_MAX_WAVES * 64) void ff_decode_kernel(DecodeParams p)
 {
-    __shared__ float red[DEC_MAX_WAVES * 2][2 * DEC_G * DEC_NB_MAX][16];
+    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2 * DEC_NB_MAX][64];
     __shared__ __attribute__((aligned(16))) float fold[DEC_FOLD_FLOATS];
     decode_body<BF16, GATED, INDEXED, BIAS, NB>(p, p.Wg, p.W1, p.W2, p.bg, p.b1, red, fold);
 }
@@ -278,7 +361,7 @@ __global__ __launch_bounds__(DEC_MAX_WAVES * 64) void ff_decode_kernel(DecodePar
 template <bool BF16, bool GATED, bool BIAS>
 __global__ __launch_bounds__(DEC_MAX_WAVES * 64) void ff_decode_multi_kernel(DecodeParams p, MultiPtrs m)
 {
-    __shared__ float red[DEC_MAX_WAVES * 2][2 * DEC_G * DEC_NB_MAX][16];
+    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2 * DEC_NB_MAX][64];
     __shared__ __attribute__((aligned(16))) float fold[DEC_FOLD_FLOATS];
     const void *const *q = m.p[blockIdx.y];
     decode_body<BF16, GATED, false, BIAS, 1>(p, q[0], q[1], q[2], q[3], q[4], red, fold);
@@ -387,7 +470,7 @@ int decode_parts(int32_t n, int32_t batch)
 size_t decode_least_floats(int32_t d, int32_t n, int32_t batch)
 {
     size_t floats = (size_t)decode_parts(n, batch) * batch * d;
-    if (batch >= DEC_BATCH_MIN_ROWS && d % 512 == 0 && d <= 5120 && n >= 64 && n <= 32768) {
+    if (batch >= 5 && d % 512 == 0 && d <= 5120 && n >= 64 && n <= 32768) {
         int64_t nr = 256 / (d / 512);
         if (nr > 64) nr = 64;
         if (nr < (n + 479) / 480) nr = (n + 479) / 480;
@@ -441,8 +524,12 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
     // against rows that read the k neurons of their sets each (2752 x 15520, k = n/2: 3 rows 64 us one by one, 58 masked;
     // 5 rows 112 / 59; 16 rows 330 / 62).
     const int32_t nb = job.idx ? job.n_src : job.n;
-    const bool worth = decode_whole_pieces(job.d) || (job.idx ? 2 * (int64_t)job.batch * job.n >= 3 * (int64_t)nb
-                                                              : job.batch > 16 || (int64_t)nb * job.d >= (2 << 20));
+    // With the words at hand three and four rows are enough for the masked pass if their sets hold twice the block (4096 x 14336,
+    // k = n/2, 4 rows 120 us one by one, 67 masked; 1024 x 4496, 20 / 18); two never are.
+    const bool few = job.batch < 5;
+    const bool worth = few ? job.sets && (int64_t)job.batch * job.n >= 2 * (int64_t)nb
+                           : decode_whole_pieces(job.d) || (job.idx ? 2 * (int64_t)job.batch * job.n >= 3 * (int64_t)nb
+                                                                    : job.batch > 16 || (int64_t)nb * job.d >= (2 << 20));
     size_t have = 0;
     if (job.bf16 && !job.multi && job.W2 && job.batch >= DEC_BATCH_MIN_ROWS && worth) {
         have = decode_route_floats(job.d, nb, job.batch);

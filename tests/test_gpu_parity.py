@@ -898,6 +898,51 @@ def test_indexed_decode_masked_pass_matches_oracle(d, n, k, B, gated, bias):
         assert max_rel(got[b], ref) <= TOL_OUT[dtype], b
 
 
+@pytest.mark.parametrize("dtype,d,n,B,biases", [
+    (synth.DT_BF16, 8, 70, 3, "gu"),          # one lane of one wave, eight teams
+    (synth.DT_BF16, 520, 133, 4, "g"),        # two waves a team, four teams; a bias on the gate alone
+    (synth.DT_BF16, 1544, 90, 2, "u"),        # four waves a team; a bias on the up product alone
+    (synth.DT_BF16, 4096, 300, 3, ""),        # eight waves
+    (synth.DT_BF16, 8192, 65, 4, "gu"),       # sixteen waves: all partial sums in use
+    (synth.DT_F32, 4096, 40, 4, "gu"),        # the same in fp32
+    (synth.DT_F32, 72, 100, 2, "u"),
+])
+@pytest.mark.parametrize("gated", [True, False])
+def test_ff_decode_few_rows_reduce_together(dtype, d, n, B, biases, gated):
+    act = synth.ACT_GELU_TANH
+    c = synth.small_case(d + 5 * n, d, n, 4, dtype, T=B, with_bias=True)
+    Wg = c["Wg"] if gated else None
+    bg = c["bg"] if gated and "g" in biases else None
+    b1 = c["b1"] if "u" in biases else None
+    L, _ = dev_layer(Wg, c["W1"], c["W2"], act, dtype, bg, b1, c["b2"])
+    got = run_decode(L, to_dev(c["xt"], dtype), B)
+    for b in range(B):
+        ref = oracle.ff_decode(c["xt"][b], Wg, c["W1"], c["W2"], act, bg, b1, c["b2"])
+        assert max_rel(got[b], ref) <= TOL_OUT[dtype], b
+
+
+def test_indexed_decode_three_rows_take_the_masked_pass():
+    """Three rows whose sets hold more than twice the block, with and without the words: two routes, one result up to
+    the rounding of the output."""
+    dtype, act, d, n, k, B = synth.DT_BF16, synth.ACT_SILU, 1024, 301, 260, 3
+    c = synth.small_case(77, d, n, 4, dtype, T=B)
+    L, _ = dev_layer(c["Wg"], c["W1"], c["W2"], act, dtype)
+    rng = np.random.default_rng(3)
+    idx = np.stack([np.sort(rng.choice(n, k, replace=False)) for _ in range(B)]).astype(np.int32)
+    idx_dev = torch.from_numpy(idx).cuda()
+    sets = torch.zeros(G.griffin_index_sets_bytes(n, B) // 4, dtype=torch.int32, device="cuda")
+    G.griffin_index_sets_build(idx_dev, k, B, n, sets)
+    ws = workspace(G.griffin_decode_workspace_bytes(d, n, B))
+    x = to_dev(c["xt"], dtype)
+    y1, y2 = torch.empty_like(x), torch.empty_like(x)
+    G.griffin_ff_decode_indexed_sets(L, idx_dev, k, sets, B, x, y1, workspace=ws)
+    G.griffin_ff_decode_indexed(L, idx_dev, k, B, x, y2, workspace=ws)
+    sync()
+    for b in range(B):
+        ref = oracle.ff_decode(c["xt"][b], c["Wg"][idx[b]], c["W1"][idx[b]], c["W2"][idx[b]], act)
+        assert max_rel(to_host(y1)[b], ref) <= TOL_OUT[dtype] and max_rel(to_host(y2)[b], ref) <= TOL_OUT[dtype]
+
+
 @pytest.mark.parametrize("d,n,k,B,gated,bias", [
     (1152, 1503, 700, 20, True, True),     # masked pass at a width that is not whole 1 KB pieces, two tiles
     (2752, 517, 250, 40, False, True),     # ... three tiles, Eq. 2
