@@ -191,7 +191,7 @@ __device__ __forceinline__ void team_z(const float (*red)[64], int lane, int act
 template <bool BF16, bool GATED, bool INDEXED, bool BIAS, int NB>
 __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *Wg, const void *W1,
                                             const void *W2, const void *bg, const void *b1,
-                                            float (*red)[2 * DEC_NB_MAX][64], float *fold)
+                                            float (*red)[2 * NB][64], float *fold)
 {
     constexpr int E = Chunk<BF16>::E;
     constexpr int ES = BF16 ? 2 : 4;
@@ -225,7 +225,7 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
     const int32_t *idx = INDEXED ? p.idx + (int64_t)b * p.n : nullptr;
     const int64_t row_bytes = p.ld * ES;
     constexpr int NV = NMAT * NB;                    // values to combine across the team per step
-    float(*myred)[2 * DEC_NB_MAX][64] = red + team * 2;       // [parity][value][four partial sums per wave of the team]
+    float(*myred)[2 * NB][64] = red + team * 2;       // [parity][value][four partial sums per wave of the team]
 
 
     // Loads are branch-free (slots past the last neuron re-read the last row, which stays in
@@ -353,7 +353,7 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
 template <bool BF16, bool GATED, bool INDEXED, bool BIAS, int NB>
 __global__ __launch_bounds__(DEC_MAX_WAVES * 64) void ff_decode_kernel(DecodeParams p)
 {
-    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2 * DEC_NB_MAX][64];
+    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2 * NB][64];
     __shared__ __attribute__((aligned(16))) float fold[DEC_FOLD_FLOATS];
     decode_body<BF16, GATED, INDEXED, BIAS, NB>(p, p.Wg, p.W1, p.W2, p.bg, p.b1, red, fold);
 }
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(DEC_MAX_WAVES * 64) void ff_decode_kernel(DecodePar
 template <bool BF16, bool GATED, bool BIAS>
 __global__ __launch_bounds__(DEC_MAX_WAVES * 64) void ff_decode_multi_kernel(DecodeParams p, MultiPtrs m)
 {
-    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2 * DEC_NB_MAX][64];
+    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2][64];
     __shared__ __attribute__((aligned(16))) float fold[DEC_FOLD_FLOATS];
     const void *const *q = m.p[blockIdx.y];
     decode_body<BF16, GATED, false, BIAS, 1>(p, q[0], q[1], q[2], q[3], q[4], red, fold);
