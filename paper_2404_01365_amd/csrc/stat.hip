@@ -159,6 +159,62 @@ __global__ __launch_bounds__(64) void stat_finalize_kernel(const float *s2part, 
         s_out[(int64_t)seq * F + j] = v;
 }
 
+// Short sequences in one kernel: what bounds them is not Z (1.8 MB for 40 tokens of 11008 neurons) but the two dependent
+// dispatches and the latencies inside them.  A workgroup of sixteen wavefronts takes 64 columns of one sequence from end to end:
+// wave w has the rows w, w + 16, ... (at most eight of them: all its loads are on their way at once), forms their weights
+// itself and leaves its sums in LDS; they are added in wave order and the root is taken at once.  Every workgroup reads the
+// row partials of the whole sequence again, which is why longer ones (128 tokens x 86 partials are 44 KB) go in chunks, and so
+// do calls with more workgroups than the chip holds at once (512).  Whole selections, chunks and second kernel / this one:
+// 40 tokens of 4096 x 11008 64.9 / 60.7 us, 128 tokens 73.7 / 71.4, eight prompts of 40 tokens of 1024 x 4096 49.7 / 47.1, of
+// 4096 x 11008 (1376 workgroups) 119 / 130.
+constexpr int STAT_SHORT_ROWS = 128, STAT_SHORT_WAVES = 16;
+
+__global__ __launch_bounds__(STAT_SHORT_WAVES * 64) void stat_short_kernel(const float *Z, int64_t ldz, const float *rowpart, int nt,
+                                                                           int F, SeqTable seqs, float *s, float *s_out)
+{
+    constexpr int U = STAT_SHORT_ROWS / STAT_SHORT_WAVES;
+    __shared__ float part[STAT_SHORT_WAVES][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, seq = blockIdx.y;
+    const int j = blockIdx.x * 64 + lane, jc = j < F ? j : F - 1;
+    const int64_t s0 = seqs.cu[seq];
+    const int len = (int)(seqs.cu[seq + 1] - s0);
+    float acc = 0.0f;
+    if (wave < len) {                          // rows past the end repeat the wave's first row with weight 0
+        float z[U], a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = wave + STAT_SHORT_WAVES * u;
+            z[u] = Z[(s0 + (r < len ? r : wave)) * ldz + jc];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = wave + STAT_SHORT_WAVES * u;
+            const float *rp = rowpart + (s0 + (r < len ? r : wave)) * nt;
+            a[u] = 0.0f;
+            for (int t = lane; t < nt; t += 64)
+                a[u] += rp[t];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float v = wave_sum(a[u]);
+            const float w = (v > 0.0f && wave + STAT_SHORT_WAVES * u < len) ? 1.0f / v : 0.0f;
+            acc = fmaf(z[u] * z[u], w, acc);
+        }
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && j < F) {
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < STAT_SHORT_WAVES; ++w)
+            t += part[w][lane];
+        const float v = sqrtf(t);
+        s[(int64_t)seq * F + j] = v;
+        if (s_out)
+            s_out[(int64_t)seq * F + j] = v;
+    }
+}
+
 // Eq. 7: sbar_j = sum_b s[b][j] / sqrt(S_b), b ascending, empty sequences skipped
 __global__ __launch_bounds__(256) void stat_shared_kernel(const float *s, SeqTable seqs, int F, float *sbar)
 {
@@ -198,6 +254,14 @@ int launch_stat(const float *Z, int64_t ldz, const float *rowpart, int nt, int64
                 const SeqTable &seqs, float *s2part, float *s, float *s_out, hipStream_t st)
 {
     int rcode;
+    int32_t longest = 0;
+    for (int b = 0; b < seqs.n; ++b)
+        longest = seqs.cu[b + 1] - seqs.cu[b] > longest ? seqs.cu[b + 1] - seqs.cu[b] : longest;
+    if (longest <= STAT_SHORT_ROWS && (int64_t)((F + 63) / 64) * seqs.n <= 512) {
+        hipLaunchKernelGGL(stat_short_kernel, dim3((F + 63) / 64, seqs.n), dim3(STAT_SHORT_WAVES * 64), 0, st, Z, ldz, rowpart, nt, F,
+                           seqs, s, s_out);
+        return check_launch("stat_short_kernel");
+    }
     const int R = stat_rows_per_chunk(M, seqs.n, F);
     ChunkTable chunks;
     int32_t n_chunks = 0;

@@ -430,6 +430,15 @@ RANGE_CASES = [
 ]
 
 
+RANGE_CASES += [
+    # the statistic of short sequences in one kernel: up to 128 rows each and 512 workgroups, else in chunks
+    (synth.DT_BF16, 64, 260, [128, 0, 1, 17, 16], 100, synth.ACT_SILU, True, False),
+    (synth.DT_BF16, 64, 260, [129, 3], 100, synth.ACT_SILU, True, False),
+    (synth.DT_F32, 64, 4033, [20] * 8, 2000, synth.ACT_GELU_TANH, True, False),       # 64 x 8 workgroups, F odd
+    (synth.DT_F32, 64, 4097, [20] * 8, 2000, synth.ACT_GELU_TANH, True, False),       # 65 x 8: chunks
+]
+
+
 @pytest.mark.parametrize("dtype,d,F,lens,k,act,gated,bias", RANGE_CASES)
 def test_prefill_select_of_short_prompts_in_ranges(dtype, d, F, lens, k, act, gated, bias):
     test_prefill_select_matches_oracle(dtype, d, F, lens, k, act, gated, bias)
