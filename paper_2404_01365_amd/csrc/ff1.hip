@@ -112,7 +112,8 @@ __device__ __forceinline__ float ff1_acc_read(float a)
 }
 
 // EXTRA: the instantiation that also knows biases and the bf16 copy of Z; the lean one (most models: no FF
-// biases, selection alone) is 2 % faster for not carrying those branches and registers through the epilogue.
+// biases, selection alone) is 2 % faster for not carrying those branches and registers through the epilogue, and 9 % on the
+// wide tiles of Eq. 2 blocks, which spill 312 bytes a lane with them and 184 without (2048 tokens of 3072 x 24576: 375 -> 340 us).
 template <int ACT, bool GATED, int MI, bool PLAIN, bool EQ2W = false, bool EXTRA = true, bool DUAL = false>
 __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x16 (&accU)[MI][2], f32x16 (&accG)[MI][2],
                                                     float (*rs)[64 * MI], uint32_t rs_lds, uint32_t patch_lds, int m0, int n0,
@@ -939,7 +940,8 @@ static void launch_mfma(const Ff1Params &p, bool gated, bool wide, hipStream_t s
         else hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, false, false>), grid, block, 0, st, p);
     } else {
         if (ktail) hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, false, MI, true>), grid_all, block, 0, st, p);
-        else if (wide) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, true>), grid, block, 0, st, p);   // 256-column tiles
+        else if (wide && (p.Zb || p.b1)) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, true>), grid, block, 0, st, p);   // 256-column tiles
+        else if (wide) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, true, false>), grid, block, 0, st, p);
         else hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, false, MI, false>), grid, block, 0, st, p);
     }
 }

@@ -436,6 +436,8 @@ RANGE_CASES += [
     (synth.DT_BF16, 64, 260, [129, 3], 100, synth.ACT_SILU, True, False),
     (synth.DT_F32, 64, 4033, [20] * 8, 2000, synth.ACT_GELU_TANH, True, False),       # 64 x 8 workgroups, F odd
     (synth.DT_F32, 64, 4097, [20] * 8, 2000, synth.ACT_GELU_TANH, True, False),       # 65 x 8: chunks
+    # Eq. 2 without biases, 256-column tiles of 256 tokens: 6 x 65 = 390 tiles
+    (synth.DT_BF16, 128, 16520, [1300], 8000, synth.ACT_RELU, False, False),
 ]
 
 
