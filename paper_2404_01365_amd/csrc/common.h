@@ -14,13 +14,15 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// round-to-nearest-even; NaN stays NaN
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
+// round-to-nearest-even; NaN stays NaN (one v_cvt_pk_bf16_f32; the same bits as rounding in integers, all 2^32 inputs compared)
+__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+
+// two values rounded into one word, `lo` in its low half: one instruction
+__device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi)
 {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u)
-        return (u >> 16) | 0x40u;
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+    typedef __attribute__((ext_vector_type(2))) __bf16 pair_t;
+    const pair_t v = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(uint32_t, v);
 }
 
 template <bool BF16>

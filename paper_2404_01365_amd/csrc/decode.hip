@@ -432,8 +432,8 @@ __global__ __launch_bounds__(RED_WAVES * 64) void ff_decode_reduce_kernel(const 
         const int64_t o = (int64_t)b * d + c;
         if (BF16) {
             uint2 w;
-            w.x = f32_to_bf16_bits(s.x) | (f32_to_bf16_bits(s.y) << 16);
-            w.y = f32_to_bf16_bits(s.z) | (f32_to_bf16_bits(s.w) << 16);
+            w.x = f32x2_to_bf16x2(s.x, s.y);
+            w.y = f32x2_to_bf16x2(s.z, s.w);
             *(uint2 *)((uint16_t *)y + o) = w;
         } else {
             *(float4 *)((float *)y + o) = s;

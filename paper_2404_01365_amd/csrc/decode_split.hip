@@ -188,7 +188,7 @@ __global__ __launch_bounds__(1024) void ff_decode_down_kernel(SplitParams p)
             acc0 += bf16_bits_to_f32(((const uint16_t *)p.b2)[c]);
             acc1 += bf16_bits_to_f32(((const uint16_t *)p.b2)[c + 1]);
         }
-        ((uint32_t *)p.y)[c >> 1] = f32_to_bf16_bits(acc0) | (f32_to_bf16_bits(acc1) << 16);
+        ((uint32_t *)p.y)[c >> 1] = f32x2_to_bf16x2(acc0, acc1);
     }
 }
 

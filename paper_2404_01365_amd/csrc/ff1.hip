@@ -111,10 +111,10 @@ __device__ __forceinline__ float ff1_acc_read(float a)
     return v;
 }
 
-// EXTRA: the instantiation that also knows biases and the bf16 copy of Z; the lean one (most models: no FF
+// EXTRA: 2 also knows biases and the bf16 copy of Z, 1 the copy alone, 0 neither; the lean one (most models: no FF
 // biases, selection alone) is 2 % faster for not carrying those branches and registers through the epilogue, and 9 % on the
 // wide tiles of Eq. 2 blocks, which spill 312 bytes a lane with them and 184 without (2048 tokens of 3072 x 24576: 375 -> 340 us).
-template <int ACT, bool GATED, int MI, bool PLAIN, bool EQ2W = false, bool EXTRA = true, bool DUAL = false>
+template <int ACT, bool GATED, int MI, bool PLAIN, bool EQ2W = false, int EXTRA = 2, bool DUAL = false>
 __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x16 (&accU)[MI][2], f32x16 (&accG)[MI][2],
                                                     float (*rs)[64 * MI], uint32_t rs_lds, uint32_t patch_lds, int m0, int n0,
                                                     int tile_n)
@@ -129,7 +129,7 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x16 (
     // the last one and are never read
     const int FS = PLAIN ? (int)p.ldz : p.F;
     const bool vec = ((FS | (int32_t)p.ldz) & 3) == 0 && ((uintptr_t)p.Z & 15) == 0;
-    const bool hb = EXTRA && !PLAIN && (p.b1 != nullptr || (GLU && p.bg != nullptr));
+    const bool hb = EXTRA == 2 && !PLAIN && (p.b1 != nullptr || (GLU && p.bg != nullptr));
     const uint16_t *b1p = (const uint16_t *)p.b1, *bgp = (const uint16_t *)p.bg;
     const bool bias8 = (((uintptr_t)p.b1 | (uintptr_t)p.bg) & 7) == 0;       // four biases per 8-byte load
     if (vec && (!hb || bias8)) {
@@ -227,8 +227,8 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x16 (
                         *(f32x4_t *)(Zh + (int64_t)tok * p.ldz + ncol) = pv[j_];                     \
                     if (EXTRA && !PLAIN && p.Zb) {                                                   \
                         uint2 h_;                                                                    \
-                        h_.x = f32_to_bf16_bits(pv[j_][0]) | (f32_to_bf16_bits(pv[j_][1]) << 16);    \
-                        h_.y = f32_to_bf16_bits(pv[j_][2]) | (f32_to_bf16_bits(pv[j_][3]) << 16);    \
+                        h_.x = f32x2_to_bf16x2(pv[j_][0], pv[j_][1]);    \
+                        h_.y = f32x2_to_bf16x2(pv[j_][2], pv[j_][3]);    \
                         *(uint2 *)(p.Zb + (int64_t)tok * p.ldzb + ncol) = h_;                        \
                     }                                                                                \
                 }                                                                                    \
@@ -327,7 +327,7 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // slot swizzle of row r (rows of every stage section start at a multiple of 16)
 #define FF1_SWZ(r) (((r) >> 1) & 7)
 
-template <int ACT, bool GATED, int MI, bool PLAIN, bool EQ2W = false, bool EXTRA = true, bool DUAL = false>
+template <int ACT, bool GATED, int MI, bool PLAIN, bool EQ2W = false, int EXTRA = 2, bool DUAL = false>
 __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass has no buffer-descriptor builtins; it only needs the launch stub
@@ -823,8 +823,8 @@ __global__ __launch_bounds__(256) void ff1_act_kernel(Ff1ActParams p)
         }
         if (p.Zb) {                      // only with F, ldzb multiples of 4 (ff1_can_write_zb)
             uint2 h;
-            h.x = f32_to_bf16_bits(z[0]) | (f32_to_bf16_bits(z[1]) << 16);
-            h.y = f32_to_bf16_bits(z[2]) | (f32_to_bf16_bits(z[3]) << 16);
+            h.x = f32x2_to_bf16x2(z[0], z[1]);
+            h.y = f32x2_to_bf16x2(z[2], z[3]);
             *(uint2 *)(p.Zb + (int64_t)row * p.ldzb + j) = h;
         }
     }
@@ -936,12 +936,14 @@ static void launch_mfma(const Ff1Params &p, bool gated, bool wide, hipStream_t s
     const bool ktail = p.d % 64 != 0 || p.ldx > (1 << 21) || p.ldw > (1 << 21);
     if (gated) {
         if (ktail) hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, true, MI, true>), grid_all, block, 0, st, p);
-        else if (p.Zb || p.b1 || p.bg) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, false, false>), grid, block, 0, st, p);
+        else if (p.b1 || p.bg) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false>), grid, block, 0, st, p);
+        else if (p.Zb) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, false, 1>), grid, block, 0, st, p);
+        else hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, false, 0>), grid, block, 0, st, p);
     } else {
         if (ktail) hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, false, MI, true>), grid_all, block, 0, st, p);
-        else if (wide && (p.Zb || p.b1)) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, true>), grid, block, 0, st, p);   // 256-column tiles
-        else if (wide) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, true, false>), grid, block, 0, st, p);
+        else if (wide && p.b1) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, true>), grid, block, 0, st, p);   // 256-column tiles
+        else if (wide && p.Zb) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, true, 1>), grid, block, 0, st, p);
+        else if (wide) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, MI, false, true, 0>), grid, block, 0, st, p);
         else hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, false, MI, false>), grid, block, 0, st, p);
     }
 }
@@ -1005,11 +1007,11 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
             p.mt = (int32_t)(M > 128 ? (M + 255) / 256 : 1);
             const dim3 grid(ff1_grid(p.mt * p.nt * pl.splits, M <= 64 ? 2 : 1)), block(G_THREADS);
             if (M <= 64)
-                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 1, true, false, true, true>), grid, block, 0, st, p);
+                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 1, true, false, 2, true>), grid, block, 0, st, p);
             else if (M > 128)
-                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 4, true, false, true, true>), grid, block, 0, st, p);
+                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 4, true, false, 2, true>), grid, block, 0, st, p);
             else
-                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 2, true, false, true, true>), grid, block, 0, st, p);
+                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 2, true, false, 2, true>), grid, block, 0, st, p);
         } else {
             launch_gemm_nt_partials(X, ldx, L.W1, L.ld, M, L.n, L.d, pl.splits, pl.per, slabs, pl.ldu, st);
         }

@@ -38,7 +38,7 @@ constexpr int P_BM = 256, P_BN = 128, P_BK = 64;
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
-    return f32_to_bf16_bits(lo) | (f32_to_bf16_bits(hi) << 16);
+    return f32x2_to_bf16x2(lo, hi);
 }
 
 __global__ __launch_bounds__(256) void ff2_bf16_mfma_kernel(Ff2Params p)
