@@ -13,8 +13,8 @@
 //     (s*NT + T)*G ... +G-1), so at any time the chip reads one contiguous window of rows
 //     per matrix (one window in all when the three rows of a neuron are stored side by
 //     side, i.e. Wg, W1, W2 interleaved with ld = 3d);
-//   * the dot products (two per row of x) are reduced inside the wave with DPP, all together, combined across
-//     the team's waves through a few LDS words and one barrier per G neurons, and the loads of the next
+//   * the dot products (two per row of x) are reduced inside the wave with DPP, those of several rows together, combined
+//     across the team's waves through a few LDS words and one barrier per G neurons, and the loads of the next
 //     two steps are already in flight while that happens (three register sets; the loads are
 //     branch-free so the compiler waits for the oldest set only; with one step of lookahead a
 //     wave streams only one step's bytes per memory latency, which is what bounds narrow rows);
@@ -31,6 +31,9 @@ constexpr int DEC_MAX_TEAMS = 8;         // teams per workgroup
 constexpr int DEC_MAX_PARTS = 256;       // partial rows per batch row
 constexpr int DEC_NB_MAX = 4;            // rows of x sharing one pass over the weights
 constexpr int DEC_FOLD_FLOATS = 8192;    // LDS floats for folding teams (d <= 8192)
+
+// partial sums per value and team: one per wave where each value is summed over its wave, four where NB rows go together
+constexpr int dec_red_width(int NB) { return NB == 1 ? 16 : 64; }
 
 struct DecodeParams {
     const void *Wg, *W1, *W2, *bg, *b1;
@@ -89,11 +92,13 @@ struct Chunk {
     }
 };
 
-// The sums of NV values (1, 2, 4 or 8) over the sixteen lanes of every DPP row, value i in the lanes whose index ends in
-// i (log2 NV bits).  Two values that are added over the same pair of lanes change places while they are added, so a step
-// halves the number of values: 22 instructions for eight values, where a sum of each over the wavefront takes 88 (which bound
-// the passes of three and four rows: three rows of 4096 x 5504 36.8 -> 29.1 us, of 3072 x 12288 68 -> 44, of a 4096 x 11008
-// Eq. 2 block 51.4 -> 37.8; a single row waits for memory either way).
+// Passes of two to four rows.  The sums of NV values (2, 4 or 8) over the sixteen lanes of every DPP row, value i in the lanes
+// whose index ends in i (log2 NV bits).  Two values that are added over the same pair of lanes change places while they are
+// added, so a step halves the number of values: 22 instructions for eight values, where a sum of each over the wavefront takes 88
+// (which bound the passes of three and four rows: three rows of 4096 x 5504 36.8 -> 29.1 us, of 3072 x 12288 68 -> 44, of a
+// 4096 x 11008 Eq. 2 block 51.4 -> 37.8).  A row that goes alone has one or two values and waits for memory; it keeps the plain sum,
+// because the exchange takes its registers across a step of occupancy and a launch of 256 workgroups per row needs three of
+// them on a CU (three own-set rows, k = n/2, of 4096 x 14336 98 us with it and 88 without, of 2752 x 8000 49.8 and 37.7).
 template <int CTRL>
 __device__ __forceinline__ float pair_step(float even, float odd, bool is_odd)
 {
@@ -106,13 +111,9 @@ __device__ __forceinline__ float row16_sums(const float (&v)[NV], int lane)
     constexpr int XOR1 = 0xB1, XOR2 = 0x4E, ROR4 = 0x124, ROR8 = 0x128;
     const bool o0 = lane & 1, o1 = lane & 2, o2 = lane & 4;
     float a[4], b[2], c;
-    if (NV >= 2) {
 #pragma unroll
-        for (int i = 0; i < NV / 2; ++i)
-            a[i] = pair_step<XOR1>(v[(2 * i) % NV], v[(2 * i + 1) % NV], o0);
-    } else {
-        a[0] = v[0] + dpp_f32<XOR1>(v[0]);
-    }
+    for (int i = 0; i < NV / 2; ++i)
+        a[i] = pair_step<XOR1>(v[2 * i], v[2 * i + 1], o0);
     if (NV >= 4) {
 #pragma unroll
         for (int i = 0; i < NV / 4; ++i)
@@ -140,11 +141,9 @@ __device__ __forceinline__ void team_z(const float (*red)[64], int lane, int act
     } else if (NV == 4) {
         const f32x4 t = *(const f32x4 *)src;
         q = (t.x + t.y) + (t.z + t.w);
-    } else if (NV == 2) {
+    } else {
         const float2 t = *(const float2 *)src;
         q = t.x + t.y;
-    } else {
-        q = *src;
     }
     q += dpp_f32<0xB1>(q);
     q += dpp_f32<0x4E>(q);
@@ -169,16 +168,9 @@ __device__ __forceinline__ void team_z(const float (*red)[64], int lane, int act
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
             z[nb] = act_apply(act, TEAM_ROW(2 * nb) + bg) * (TEAM_ROW(2 * nb + 1) + b1);
-    } else if (NV == 2) {
-        const float s0 = TEAM_ROW(0) + TEAM_ROW(1), s1 = TEAM_ROW(2) + TEAM_ROW(3);
-        if (GATED) {
-            z[0] = act_apply(act, s0 + bg) * (s1 + b1);
-        } else {
-            z[0] = act_apply(act, s0 + b1);
-            z[NB - 1] = act_apply(act, s1 + b1);
-        }
-    } else {
-        z[0] = act_apply(act, (TEAM_ROW(0) + TEAM_ROW(1)) + (TEAM_ROW(2) + TEAM_ROW(3)) + b1);
+    } else {                         // two rows of an Eq. 2 block
+        z[0] = act_apply(act, TEAM_ROW(0) + TEAM_ROW(1) + b1);
+        z[NB - 1] = act_apply(act, TEAM_ROW(2) + TEAM_ROW(3) + b1);
     }
 #undef TEAM_ROW
 }
@@ -191,7 +183,7 @@ __device__ __forceinline__ void team_z(const float (*red)[64], int lane, int act
 template <bool BF16, bool GATED, bool INDEXED, bool BIAS, int NB>
 __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *Wg, const void *W1,
                                             const void *W2, const void *bg, const void *b1,
-                                            float (*red)[2 * NB][64], float *fold)
+                                            float (*red)[2 * NB][dec_red_width(NB)], float *fold)
 {
     constexpr int E = Chunk<BF16>::E;
     constexpr int ES = BF16 ? 2 : 4;
@@ -225,7 +217,8 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
     const int32_t *idx = INDEXED ? p.idx + (int64_t)b * p.n : nullptr;
     const int64_t row_bytes = p.ld * ES;
     constexpr int NV = NMAT * NB;                    // values to combine across the team per step
-    float(*myred)[2 * NB][64] = red + team * 2;       // [parity][value][four partial sums per wave of the team]
+    constexpr int RW = dec_red_width(NB);
+    float(*myred)[2 * NB][RW] = red + team * 2;       // [parity][value][partial sums of the team's waves]
 
 
     // Loads are branch-free (slots past the last neuron re-read the last row, which stays in
@@ -273,12 +266,25 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
                 pv_[nb * NMAT] = Chunk<BF16>::dot(buf[B_][0][0], xr[nb]);                    \
             pv_[nb * NMAT + NMAT - 1] = Chunk<BF16>::dot(buf[B_][0][1], xr[nb]);             \
         }                                                                                    \
-        const float part_ = row16_sums<NV>(pv_, lane);                                       \
-        if ((lane & 15) < NV)                                                                \
-            myred[(s_) & 1][lane & 15][wt * 4 + (lane >> 4)] = part_;                        \
-        __syncthreads();                                                                     \
+        const float bg_ = BIAS && GATED && bg ? bias[B_][0][0] : 0.0f, b1_ = BIAS && b1 ? bias[B_][0][1] : 0.0f; \
         float z_[NB];                                                                        \
-        team_z<GATED, NB>(myred[(s_) & 1], lane, p.act, BIAS && GATED && bg ? bias[B_][0][0] : 0.0f, BIAS && b1 ? bias[B_][0][1] : 0.0f, z_); \
+        if constexpr (NB == 1) {                                                             \
+            _Pragma("unroll") for (int v = 0; v < NV; ++v) pv_[v] = wave_sum(pv_[v]);        \
+            if (lane == 0) {                                                                 \
+                _Pragma("unroll") for (int v = 0; v < NV; ++v) myred[(s_) & 1][v][wt] = pv_[v]; \
+            }                                                                                \
+            __syncthreads();                                                                 \
+            const float q_ = row16_sum((lane >> 4) < NV ? myred[(s_) & 1][lane >> 4][lane & 15] : 0.0f); \
+            const float g_ = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q_), 0)); \
+            const float u_ = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q_), 16 * (NV - 1))); \
+            z_[0] = GATED ? act_apply(p.act, g_ + bg_) * (u_ + b1_) : act_apply(p.act, u_ + b1_); \
+        } else {                                                                             \
+            const float part_ = row16_sums<NV>(pv_, lane);                                   \
+            if ((lane & 15) < NV)                                                            \
+                myred[(s_) & 1][lane & 15][wt * 4 + (lane >> 4)] = part_;                    \
+            __syncthreads();                                                                 \
+            team_z<GATED, NB>(myred[(s_) & 1], lane, p.act, bg_, b1_, z_);                   \
+        }                                                                                    \
         const int j_ = (s_) * NT + T;                                                        \
         _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                    \
             Chunk<BF16>::axpy(j_ < p.n ? z_[nb] : 0.0f, buf[B_][0][2], ya[nb]);              \
@@ -289,8 +295,9 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
         DEC_LOAD(1, 1)             // steps past the end re-read the last row and contribute nothing
     }
     // zero the padding entries of the cross-wave buffers once (the first rows are already on their way)
-    for (int i = threadIdx.x; i < p.teams * 2 * NV * 16; i += blockDim.x)
-        *(f32x4 *)&red[i / (NV * 16)][(i / 16) % NV][i % 16 * 4] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int RQ = RW / 4;
+    for (int i = threadIdx.x; i < p.teams * 2 * NV * RQ; i += blockDim.x)
+        *(f32x4 *)&red[i / (NV * RQ)][(i / RQ) % NV][i % RQ * 4] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
     __syncthreads();
     for (int s = 0; s < nsteps; s += 3) {
         DEC_LOAD(2, s + 2)
@@ -353,7 +360,7 @@ __device__ __forceinline__ void decode_body(const DecodeParams &p, const void *W
 template <bool BF16, bool GATED, bool INDEXED, bool BIAS, int NB>
 __global__ __launch_bounds__(DEC_MAX_WAVES * 64) void ff_decode_kernel(DecodeParams p)
 {
-    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2 * NB][64];
+    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2 * NB][dec_red_width(NB)];
     __shared__ __attribute__((aligned(16))) float fold[DEC_FOLD_FLOATS];
     decode_body<BF16, GATED, INDEXED, BIAS, NB>(p, p.Wg, p.W1, p.W2, p.bg, p.b1, red, fold);
 }
@@ -361,7 +368,7 @@ __global__ __launch_bounds__(DEC_MAX_WAVES * 64) void ff_decode_kernel(DecodePar
 template <bool BF16, bool GATED, bool BIAS>
 __global__ __launch_bounds__(DEC_MAX_WAVES * 64) void ff_decode_multi_kernel(DecodeParams p, MultiPtrs m)
 {
-    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2][64];
+    __shared__ __attribute__((aligned(16))) float red[DEC_MAX_TEAMS * 2][2][dec_red_width(1)];
     __shared__ __attribute__((aligned(16))) float fold[DEC_FOLD_FLOATS];
     const void *const *q = m.p[blockIdx.y];
     decode_body<BF16, GATED, false, BIAS, 1>(p, q[0], q[1], q[2], q[3], q[4], red, fold);

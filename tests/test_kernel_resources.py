@@ -1,0 +1,72 @@
+"""Registers and LDS of the streaming decode kernels, read from the built library's own code-object metadata (no GPU):
+the forms that run 256 workgroups of eight wavefronts per row need several of them on a CU at a time."""
+import os
+import re
+import struct
+
+import pytest
+
+msgpack = pytest.importorskip("msgpack")
+
+import paper_2404_01365_amd as G
+
+LIB = os.path.join(os.path.dirname(G.__file__), "libgriffin.so")
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _notes(elf):
+    """msgpack metadata of an amdgpu code object (note type 32)"""
+    shoff, = struct.unpack_from("<Q", elf, 40)
+    shentsize, shnum = struct.unpack_from("<HH", elf, 58)
+    for i in range(shnum):
+        typ, = struct.unpack_from("<I", elf, shoff + i * shentsize + 4)
+        off, size = struct.unpack_from("<QQ", elf, shoff + i * shentsize + 24)
+        if typ != 7:
+            continue
+        namesz, descsz, ntype = struct.unpack_from("<III", elf, off)
+        if ntype == 32:
+            start = off + 12 + (namesz + 3) // 4 * 4
+            return msgpack.unpackb(elf[start:start + descsz])
+    return {}
+
+
+def kernels():
+    blob = open(LIB, "rb").read()
+    found = {}
+    for m in re.finditer(MAGIC, blob):
+        base = m.start()
+        count, = struct.unpack_from("<Q", blob, base + len(MAGIC))
+        at = base + len(MAGIC) + 8
+        if count > 8:
+            continue
+        for _ in range(count):
+            off, size, tlen = struct.unpack_from("<QQQ", blob, at)
+            triple = blob[at + 24:at + 24 + tlen]
+            at += 24 + tlen
+            if b"gfx950" in triple:
+                for k in _notes(blob[base + off:base + off + size]).get("amdhsa.kernels", []):
+                    found[k[".name"]] = k
+    return found
+
+
+# template arguments as the compiler mangles them: <BF16, GATED, INDEXED, BIAS, rows>, <BF16, GATED, BIAS> of the per-row blocks
+def name(kernel, *flags, rows=None):
+    args = "".join("Lb%dE" % f for f in flags) + ("" if rows is None else "Li%dE" % rows)
+    return r"%sI%sE" % (kernel, args)
+
+
+@pytest.mark.parametrize("pattern,vgprs", [
+    (name("ff_decode_kernel", 1, 1, 1, 0, rows=1), 80),        # own sets, bf16 Eq. 3: six waves a SIMD, three workgroups a CU
+    (name("ff_decode_kernel", 1, 0, 1, 0, rows=1), 72),        # ... Eq. 2
+    (name("ff_decode_kernel", 0, 1, 1, 1, rows=1), 72),        # ... fp32 with biases
+    (name("ff_decode_multi_kernel", 1, 1, 1), 80),             # per-row blocks, bf16 Eq. 3 with biases
+    (name("ff_decode_multi_kernel", 1, 0, 1), 64),             # ... Eq. 2: eight waves a SIMD, four workgroups a CU
+    (name("ff_decode_kernel", 1, 1, 0, 1, rows=1), 80),        # one row through one block, with biases
+])
+def test_rows_that_go_alone_keep_their_occupancy(pattern, vgprs):
+    hits = [k for n, k in kernels().items() if re.search(pattern, n)]
+    assert len(hits) == 1, pattern
+    k = hits[0]
+    assert k[".vgpr_count"] <= vgprs
+    assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0
+    assert k[".group_segment_fixed_size"] <= 40 * 1024         # four workgroups a CU
