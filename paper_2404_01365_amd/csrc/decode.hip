@@ -30,7 +30,11 @@ constexpr int DEC_MAX_WAVES = 16;        // waves per workgroup
 constexpr int DEC_MAX_TEAMS = 8;         // teams per workgroup
 constexpr int DEC_MAX_PARTS = 256;       // partial rows per batch row
 constexpr int DEC_NB_MAX = 4;            // rows of x sharing one pass over the weights
-constexpr int DEC_FOLD_FLOATS = 8192;    // LDS floats for folding teams (d <= 8192)
+constexpr int DEC_MAX_D = 8192;
+// LDS floats for folding teams: a workgroup has several only where a team has four waves at the most.  (Room for all 8192 columns
+// beside the partial sums of four rows makes 64 KB, two workgroups a CU where there were three: 25 fp32 rows of 120 x 191
+// 17.6 us a call against 14.1.)
+constexpr int DEC_FOLD_FLOATS = 4 * 64 * 8;
 
 // partial sums per value and team: one per wave where each value is summed over its wave, four where NB rows go together
 constexpr int dec_red_width(int NB) { return NB == 1 ? 16 : 64; }
@@ -456,7 +460,7 @@ static int decode_team_waves(int32_t d, bool bf16)
 {
     const int nch = d / (bf16 ? 8 : 4);
     const int R = (nch + 63) / 64;
-    return (R <= DEC_MAX_WAVES && d <= DEC_FOLD_FLOATS) ? R : 0;
+    return (R <= DEC_MAX_WAVES && d <= DEC_MAX_D) ? R : 0;
 }
 
 // workgroups (= partial rows) per batch row: enough to fill the chip when the rows of a batch

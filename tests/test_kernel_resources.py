@@ -70,3 +70,11 @@ def test_rows_that_go_alone_keep_their_occupancy(pattern, vgprs):
     assert k[".vgpr_count"] <= vgprs
     assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0
     assert k[".group_segment_fixed_size"] <= 40 * 1024         # four workgroups a CU
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+@pytest.mark.parametrize("gated", [0, 1])
+def test_rows_that_go_four_at_a_time_leave_room_for_three_workgroups(bf16, gated):
+    for bias in (0, 1):
+        hits = [k for n, k in kernels().items() if re.search(name("ff_decode_kernel", bf16, gated, 0, bias, rows=4), n)]
+        assert len(hits) == 1 and hits[0][".group_segment_fixed_size"] <= 48 * 1024
