@@ -236,9 +236,9 @@ int griffin_ff_decode_indexed(const griffin_layer *L, const int32_t *idx, int32_
  *          uint32, bit b of word j of group g set iff row 16 g + b holds neuron j; written by
  *          griffin_index_sets_build(idx, k, batch, L->n, ...), valid as long as idx does not change.
  * griffin_ff_decode_indexed_sets takes the same idx as well: when the one-pass route does not apply
- * (fewer than five rows whose sets together hold less than twice the block, one or two rows, a
- * workspace sized for k neurons only, a shape it does not cover) the rows
- * go through the index lists exactly as in griffin_ff_decode_indexed and sets is not read.
+ * (fewer than five rows, a workspace sized for k neurons only, a shape it does not cover) the rows
+ * go through the index lists exactly as in griffin_ff_decode_indexed and sets is not read; nor is it for
+ * d that is not a multiple of 512 up to 5120, where the one pass derives the words from idx.
  */
 size_t griffin_index_sets_bytes(int32_t n, int32_t batch);
 int griffin_index_sets_build(const int32_t *idx, int32_t k, int32_t batch, int32_t n, void *sets,

@@ -170,16 +170,16 @@ int launch_decode(const DecodeJob &job, hipStream_t st);
 // one row through a block that carries W2t: two pure streams, no partial rows (decode_split.hip)
 bool decode_split_supported(const DecodeJob &job);
 int launch_decode_split(const DecodeJob &job, hipStream_t st, hipEvent_t ev_mid);
-// rows 5.. of a batch through one shared block: matrix-core path (decode_batch.hip)
+// rows 5.. of a batch through one block: matrix-core path (decode_batch.hip)
 // floats of workspace it wants (0: it does not take the shape, or not within `have` floats); the front
 // leaves [batch][NR][d] partial rows
 size_t decode_batch_floats(int32_t d, int32_t n, int32_t batch, size_t have);
-int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32_t *idx, int32_t k, size_t have, int *NR_out,
-                              hipStream_t st);
+int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32_t *idx, int32_t k, const uint32_t *sets,
+                              size_t have, int *NR_out, hipStream_t st);
 int launch_index_sets_build(const int32_t *idx, int32_t k, int32_t batch, int32_t n_block, uint32_t *sets, hipStream_t st);
 size_t index_sets_words(int32_t n_block, int32_t batch);
 
-constexpr int DEC_BATCH_MIN_ROWS = 3;     // rows from which the path is considered (launch_decode)
+constexpr int DEC_BATCH_MIN_ROWS = 5;     // rows from which the path is considered (launch_decode)
 int decode_parts(int32_t n, int32_t batch);
 // floats of workspace that a decode has to be given, and that it makes use of
 size_t decode_least_floats(int32_t d, int32_t n, int32_t batch);

@@ -535,12 +535,8 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
     // against rows that read the k neurons of their sets each (2752 x 15520, k = n/2: 3 rows 64 us one by one, 58 masked;
     // 5 rows 112 / 59; 16 rows 330 / 62).
     const int32_t nb = job.idx ? job.n_src : job.n;
-    // With the words at hand three and four rows are enough for the masked pass if their sets hold twice the block (4096 x 14336,
-    // k = n/2, 4 rows 120 us one by one, 67 masked; 1024 x 4496, 20 / 18); two never are.
-    const bool few = job.batch < 5;
-    const bool worth = few ? job.sets && (int64_t)job.batch * job.n >= 2 * (int64_t)nb
-                           : decode_whole_pieces(job.d) || (job.idx ? 2 * (int64_t)job.batch * job.n >= 3 * (int64_t)nb
-                                                                    : job.batch > 16 || (int64_t)nb * job.d >= (2 << 20));
+    const bool worth = decode_whole_pieces(job.d) || (job.idx ? 2 * (int64_t)job.batch * job.n >= 3 * (int64_t)nb
+                                                              : job.batch > 16 || (int64_t)nb * job.d >= (2 << 20));
     size_t have = 0;
     if (job.bf16 && !job.multi && job.W2 && job.batch >= DEC_BATCH_MIN_ROWS && worth) {
         have = decode_route_floats(job.d, nb, job.batch);
@@ -595,8 +591,10 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
     if (!job.W2 && !job.multi)
         return GRIFFIN_EUNSUPPORTED;       // only the transposed copy is there and this call cannot use it
     if (batch_path) {
-        int rc = job.idx ? launch_decode_batch_front(job, job.n_src, job.idx, job.n, have, &P, st)
-                         : launch_decode_batch_front(job, job.n, nullptr, 0, have, &P, st);
+        // the caller's words are read where griffin.h says so; for other shapes they need not have been built
+        const uint32_t *sets = decode_whole_pieces(job.d) ? job.sets : nullptr;
+        int rc = job.idx ? launch_decode_batch_front(job, job.n_src, job.idx, job.n, sets, have, &P, st)
+                         : launch_decode_batch_front(job, job.n, nullptr, 0, nullptr, have, &P, st);
         if (rc != GRIFFIN_OK)
             return rc;
         if (ev_mid && hipEventRecord(ev_mid, st) != hipSuccess)

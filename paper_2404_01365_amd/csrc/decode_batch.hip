@@ -506,9 +506,10 @@ size_t index_sets_words(int32_t n_block, int32_t batch)
 }
 
 // Runs both kernels for every pass; leaves part[b][NR][d] for the reduce kernel.
-// n_block neurons in the block; idx (or NULL) [batch][k]: the rows' own sets inside that block.
-int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32_t *idx, int32_t k, size_t have, int *NR_out,
-                              hipStream_t st)
+// n_block neurons in the block; idx (or NULL) [batch][k]: the rows' own sets inside that block;
+// sets (or NULL): their membership words, else they are built here.
+int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32_t *idx, int32_t k, const uint32_t *sets,
+                              size_t have, int *NR_out, hipStream_t st)
 {
     const BatchPlan pl = batch_plan(job.d, n_block, job.batch, have);
     if (pl.T == 0)
@@ -537,8 +538,8 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
         const int T = (p.rows + BT_ROWS - 1) / BT_ROWS;                        // the last pass may have fewer tiles
         p.x = (const uint16_t *)job.x + (int64_t)r0 * job.d;
         p.part = job.part + (size_t)r0 * pl.NR * job.d;
-        if (job.sets) {
-            p.mask = job.sets + (size_t)(r0 / BT_ROWS) * n_block;      // built once per prompt by the caller
+        if (sets) {
+            p.mask = sets + (size_t)(r0 / BT_ROWS) * n_block;      // built once per prompt by the caller
         } else if (idx) {
             const int rcm = launch_index_sets_build(idx + (int64_t)r0 * k, k, p.rows, n_block, mask, st);
             if (rcm != GRIFFIN_OK)
