@@ -41,6 +41,9 @@ typedef __attribute__((address_space(1))) const void gbl_cvoid_b;
 
 constexpr int BT_ROWS = 16;              // rows of x per MFMA tile
 constexpr int BT_MAX_T = 4;              // tiles per pass
+constexpr int BT_MAX_N = 32768;          // neurons: a pass keeps the Z of all of them, and a partial row per range of a few hundred,
+                                         // which for wider blocks is far more than rows taken four at a time need (64 rows of
+                                         // 4096 x 65536: 147 MB against 32)
 constexpr int BT_WAVES = 8;              // waves per workgroup of the first kernel at the most
 constexpr int BT_COLS = 512;             // columns per workgroup of the second kernel
 constexpr int BT_WAVES2 = 8;             // waves per workgroup of the second kernel (64 columns each)
@@ -443,7 +446,7 @@ static BatchPlan batch_plan_tiles(int32_t d, int32_t n, int T)
             b.S = S;
             break;
         }
-    if (b.S == 0 || n < 64 || d < 64 || d % 8 != 0 || T * b.S > (b.S == 10 ? 20 : 18))
+    if (b.S == 0 || n < 64 || n > BT_MAX_N || d < 64 || d % 8 != 0 || T * b.S > (b.S == 10 ? 20 : 18))
         return b;
     b.W = (nblk + b.S - 1) / b.S;
     b.CS = (d + BT_COLS - 1) / BT_COLS;

@@ -226,6 +226,12 @@ def test_batch_decode_workspace_covers_the_matrix_core_path():
     assert G.griffin_decode_workspace_bytes(8192, 500, 16) == G.griffin_decode_workspace_bytes(8192, 500, 13) // 13 * 16
 
 
+@pytest.mark.parametrize("d,n", [(4096, 65536), (8192, 53248), (512, 1 << 20)])
+def test_decode_workspace_of_very_wide_blocks_is_a_partial_row_per_workgroup(d, n):
+    # rows go four at a time, 32 workgroups for each of 64 rows
+    assert G.griffin_decode_workspace_bytes(d, n, 64) == 32 * 64 * d * 4
+
+
 def test_decode_static_judges_sizes_before_it_touches_the_runtime():
     lib = G.lib
     assert G.griffin_ff_decode_static_max_bytes() == 8 << 20
