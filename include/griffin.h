@@ -15,7 +15,9 @@
  *     W2 is the transpose of the paper's W_2 (D x D_FF), so that the "rows of W_1, W_g and
  *     columns of W_2" selected in Section 4.2 are the same row j of all three arrays.
  *   - dtype is the storage type of X, x, y and of all weights and biases (fp32 or bf16).
- *     Accumulation, activations, Z, the statistic s and the selection run in fp32.
+ *     Accumulation, activations, Z, the statistic s and the selection run in fp32.  Two products take Z rounded on
+ *     the way in, as their comments say: the prompt's output of bf16 blocks (to bf16) and five rows and more of a
+ *     bf16 block whose d is a multiple of 512 up to 5120 (to a pair of bf16, 2^-17).
  *   - d must be a multiple of 8; d, n <= 2^20; ld >= d and a multiple of 8 (16-byte rows).
  *   - A block may carry W2 a second time in the paper's own orientation (W2t, see griffin_layer).
  */
@@ -182,6 +184,8 @@ int griffin_compact(const griffin_layer *L, const int32_t *idx, int32_t k,
  * four rows; five rows and more of a bf16 block (d from 64 to 8192; of small blocks whose d is not a
  * multiple of 512 more than sixteen) take the matrix cores and stream them once per pass of 16 to 64
  * rows, as many as the registers hold at that width (64 up to d = 2048, 48 up to 3072, 32 up to 5120).
+ * Where d is a multiple of 512 up to 5120 these passes round Z to pairs of bf16 (2^-17; a z beyond the largest
+ * bf16 gives NaN); at other widths, and for fewer than five rows, Z is fp32 and infinities go where fp32 takes them.
  * workspace >= griffin_decode_workspace_bytes(d, n, batch) bytes, 256-byte aligned.
  */
 size_t griffin_decode_workspace_bytes(int32_t d, int32_t n, int32_t batch);
@@ -221,7 +225,9 @@ int griffin_ff_decode_multi(const griffin_layer *Cs, int32_t batch, const void *
  * block rather than for k neurons) five rows and more take ONE pass over the whole block, every row
  * dropping the neurons outside its own set: the sets of a batch cover most of the block between them,
  * so this moves far fewer bytes than a pass per row (bf16, d from 64 to 8192; widths that are not a
- * multiple of 512 up to 5120 take it when the sets together hold at least 1.5 times the block).
+ * multiple of 512 up to 5120 take it when the sets together hold at least 1.5 times the block).  What is dropped
+ * counts as zero; where d is a multiple of 512 up to 5120 a row meets 0 x Inf = NaN if a neuron outside its set has a
+ * W2 entry that is not finite.
  */
 int griffin_ff_decode_indexed(const griffin_layer *L, const int32_t *idx, int32_t k,
                               int32_t batch, const void *x, void *y, void *workspace,

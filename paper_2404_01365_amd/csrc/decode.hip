@@ -481,7 +481,7 @@ int decode_parts(int32_t n, int32_t batch)
 size_t decode_least_floats(int32_t d, int32_t n, int32_t batch)
 {
     size_t floats = (size_t)decode_parts(n, batch) * batch * d;
-    if (batch >= 5 && d % 512 == 0 && d <= 5120 && n >= 64 && n <= 32768) {
+    if (batch >= DEC_BATCH_MIN_ROWS && decode_whole_pieces(d) && n >= 64 && n <= 32768) {
         int64_t nr = 256 / (d / 512);
         if (nr > 64) nr = 64;
         if (nr < (n + 479) / 480) nr = (n + 479) / 480;
@@ -500,9 +500,6 @@ static size_t decode_route_floats(int32_t d, int32_t n, int32_t batch)
     const size_t least = decode_least_floats(d, n, batch), own = DEC_STATIC_BYTES / sizeof(float);
     return batch < DEC_BATCH_MIN_ROWS ? 0 : decode_batch_floats(d, n, batch, least <= own ? own : (size_t)-1);
 }
-
-// rows of 1 KB pieces: the shapes whose batches have always run on the matrix cores
-static bool decode_whole_pieces(int32_t d) { return d % 512 == 0 && d <= 5120; }
 
 size_t decode_wanted_floats(int32_t d, int32_t n, int32_t batch)
 {

@@ -24,8 +24,9 @@
 //    workgroup, so the work is cut in two directions: a workgroup owns 512 columns and one of NR ranges of neurons, and
 //    writes one [rows][512] partial into the partial-row buffer that the single-row path uses (NR rows per batch row).
 //
-// Z is kept in the layout in which the second kernel's MFMAs want it: bf16 hi + lo pairs (their sum has fp32's accuracy to
-// 2^-17; both are fed), [n/8][tile of 16 rows][hi, lo][16 rows][8 neurons].
+// Z is kept in the layout in which the second kernel's MFMAs want it.  At widths of whole 1 KB pieces up to 5120: bf16 hi + lo pairs
+// (their sum has fp32's accuracy to 2^-17; both are fed), [n/8][tile of 16 rows][hi, lo][16 rows][8 neurons].  At all other widths Z
+// stays in fp32, as it is when rows go four at a time: [n/8][tile][two halves][16 rows][4 neurons].
 // The partial rows are added in a fixed order by ff_decode_reduce_kernel (decode.hip).
 #include "common.h"
 
@@ -34,6 +35,7 @@
 namespace griffin {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_b;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_b;
 typedef __attribute__((ext_vector_type(4))) float f32x4_b;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_b;
 typedef __attribute__((address_space(3))) void lds_void_b;
@@ -51,10 +53,11 @@ constexpr int BT_WAVES2 = 8;             // waves per workgroup of the second ke
 struct BatchParams {
     const void *Wg, *W1, *W2, *bg, *b1;
     const void *x;           // [rows][d] bf16
-    uint16_t *z;             // fragments of Z (see above)
+    void *z;                 // fragments of Z (see above)
     float *part;             // [rows][NR][d] fp32
     int64_t ld;
     int32_t d, n, act, rows; // rows <= 16 T
+    int32_t exact;           // Z stays in fp32
     int32_t W, P, NB;        // waves per workgroup and workgroups of the first kernel, groups between two meetings of the waves
     int32_t NR, CS;          // neuron ranges x column slices of the second kernel
     const uint32_t *mask;    // [tile][n], bit b set if row b of the tile uses the neuron; NULL: every row uses all
@@ -228,7 +231,7 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
             const int j0 = BT_FIRST(ge) + q * 4;
             const int cnt = BT_COUNT(ge) - q * 4;           // neurons of this lane, an even number
             if (cnt > 0) {
-                uint32_t hi[4], lo[4];
+                float zv[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int j = min(j0 + i, p.n - 1);
@@ -242,17 +245,22 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
                     } else {
                         z = act_apply(p.act, uu);
                     }
-                    if (j0 + i >= p.n || t * BT_ROWS + r16 >= p.rows || (p.mask && !((p.mask[(int64_t)t * p.n + j] >> r16) & 1u)))
-                        z = 0.0f;          // beyond the block or the batch, or not in this row's own expert set
-                    hi[i] = f32_to_bf16_bits(z);
-                    lo[i] = f32_to_bf16_bits(z - bf16_bits_to_f32(hi[i]));
+                    // beyond the block or the batch, or not in this row's own expert set: no part in the sum (-0, which no other z is)
+                    const bool out = j0 + i >= p.n || t * BT_ROWS + r16 >= p.rows || (p.mask && !((p.mask[(int64_t)t * p.n + j] >> r16) & 1u));
+                    zv[i] = out ? -0.0f : z + 0.0f;
                 }
 #pragma unroll
                 for (int i = 0; i < 4; i += 2)
                     if (i < cnt) {
-                        uint16_t *zo = p.z + ((((int64_t)((j0 + i) >> 3) * T + t) * 2) * BT_ROWS + r16) * 8 + ((j0 + i) & 7);
-                        *(uint32_t *)zo = hi[i] | (hi[i + 1] << 16);
-                        *(uint32_t *)(zo + BT_ROWS * 8) = lo[i] | (lo[i + 1] << 16);
+                        const int j = j0 + i;
+                        char *zo = (char *)p.z + ((int64_t)(j >> 3) * T + t) * 512;
+                        if (p.exact) {
+                            *(float2 *)(zo + ((j >> 2) & 1) * 256 + r16 * 16 + (j & 3) * 4) = make_float2(zv[i], zv[i + 1]);
+                        } else {
+                            const uint32_t hi = f32x2_to_bf16x2(zv[i], zv[i + 1]);
+                            *(uint32_t *)(zo + r16 * 16 + (j & 7) * 2) = hi;
+                            *(uint32_t *)(zo + 256 + r16 * 16 + (j & 7) * 2) = f32x2_to_bf16x2(zv[i] - bf16_lo(hi), zv[i + 1] - bf16_hi(hi));
+                        }
                     }
             }
         }
@@ -288,9 +296,16 @@ constexpr int BD_RING = BT_WAVES2 * BD_DEPTH * BD_SLOT * 16;    // bytes: 99 KB
 constexpr int bd_range(int T) { return T == 1 ? 480 : (160 * 1024 - BD_RING) / (64 * T) / 32 * 32 - 8; }
 static_assert(bd_range(1) + 8 + 31 <= (160 * 1024 - BD_RING) / 64 && bd_range(4) > 0, "the range's fragments fit beside the ring");
 
-template <int T>
+//
+// EXACT: Z is fp32, split into the three bf16 that hold its 24 bits.  (v_mfma_f32_16x16x4_f32 takes Z as it is, for five times the
+// matrix time: whole calls of 50 rows of 2176 x 10610 106 us against 93, 30 rows of 1280 x 6425 33.0 against 29.2, 11 rows of
+// 6144 x 6734 63.0 against 58.2; with pairs, 17 bits, they take 85, 27.2 and 56.7.)  A weight that is not finite counts only for the rows that use its
+// neuron, as it does when every row reads its own neurons: a step that holds one (no step of a sound model does) takes
+// these weights out of the MFMAs, leaving a finite one of their sign, and adds their products lane by lane.
+template <int T, bool EXACT>
 __global__ __launch_bounds__(BT_WAVES2 * 64) void ff_batch_down_kernel(BatchParams p)
 {
+    constexpr uint32_t NO_Z = EXACT ? 0x80000000u : 0u;
     extern __shared__ __attribute__((aligned(16))) unsigned char bt_smem[];     // the ring, then the fragments of Z
     u32x4_b *const ring_s = (u32x4_b *)bt_smem;
     const uint32_t zs_a = (uint32_t)(uintptr_t)(lds_void_b *)(bt_smem + BD_RING);
@@ -334,7 +349,7 @@ __global__ __launch_bounds__(BT_WAVES2 * 64) void ff_batch_down_kernel(BatchPara
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int u = u0 + r * (BT_WAVES2 * 64) + tid;
-            v[r] = u < units ? zg[u] : (u32x4_b){0u, 0u, 0u, 0u};
+            v[r] = u < units ? zg[u] : (u32x4_b){NO_Z, NO_Z, NO_Z, NO_Z};
         }
         if (first) {
 #pragma unroll
@@ -381,15 +396,87 @@ __global__ __launch_bounds__(BT_WAVES2 * 64) void ff_batch_down_kernel(BatchPara
 #pragma unroll
         for (int t = 1; t < T; ++t)
             asm volatile("" : "+v"(ah[t]), "+v"(al[t]));
+        u32x4_b bw[4];
+#define BD_PACK()                                                                                            \
+        _Pragma("unroll") for (int c = 0; c < 4; ++c)                                                        \
+            bw[c] = (u32x4_b){e[c][0] | (e[c][1] << 16), e[c][2] | (e[c][3] << 16), e[c][4] | (e[c][5] << 16), e[c][6] | (e[c][7] << 16)};
+#define BD_MFMA(t_, c_, part_)                                                                               \
+        acc[t_][c_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_b, part_), __builtin_bit_cast(bf16x8_b, bw[c_]), acc[t_][c_], 0, 0, 0);
+        BD_PACK()
+        if constexpr (EXACT) {
+#define BD_Z(t_, i_) ((i_) < 4 ? ah[t_][(i_) & 3] : al[t_][(i_) & 3])        /* neuron 8q + i of row bq */
+            float check = 0.0f;                      // 0 * w is a NaN only for a w that is not finite
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const u32x4_b bw = {e[c][0] | (e[c][1] << 16), e[c][2] | (e[c][3] << 16), e[c][4] | (e[c][5] << 16), e[c][6] | (e[c][7] << 16)};
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    check = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_b, (uint32_t)bw[c][i]), (bf16x2_b){0, 0}, check, false);
+            if (__any(check != check)) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+#pragma unroll 1
+                    for (int g = 0; g < 4; ++g) {
+                        uint32_t zr[T][4];           // neuron 8g + i of this lane's rows 4q .. 4q+3
+#pragma unroll
+                        for (int t = 0; t < T; ++t)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+                                zr[t][r] = (uint32_t)__shfl((int)BD_Z(t, i), g * 16 + 4 * q + r);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const float w = bf16_bits_to_f32((uint32_t)__shfl((int)e[c][i], g * 16 + bq));
+                            const bool bad = (__float_as_uint(w) & 0x7F800000u) == 0x7F800000u;
+#pragma unroll
+                            for (int t = 0; t < T; ++t)
+#pragma unroll
+                                for (int r = 0; r < 4; ++r)
+                                    if (bad && zr[t][r] != NO_Z)
+                                        acc[t][c][r] += __uint_as_float(zr[t][r]) * w;
+                        }
+                    }
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if ((e[c][i] & 0x7F80u) == 0x7F80u)
+                            e[c][i] = (e[c][i] & 0x8000u) | 0x3F80u;
+                }
+                BD_PACK()
+            }
+            // the first, second and third eight bits of z
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_b, ah[t]), __builtin_bit_cast(bf16x8_b, bw), acc[t][c], 0, 0, 0);
-                acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_b, al[t]), __builtin_bit_cast(bf16x8_b, bw), acc[t][c], 0, 0, 0);
+                u32x4_b part[3];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t z[2], r[2], l[2];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        z[k] = BD_Z(t, 2 * i + k);
+                        const float f = __uint_as_float(z[k]);
+                        r[k] = (z[k] & 0x7F800000u) != 0x7F800000u ? __float_as_uint(f - __uint_as_float(z[k] & 0xFFFF0000u)) : 0u;
+                        l[k] = __float_as_uint(__uint_as_float(r[k]) - __uint_as_float(r[k] & 0xFFFF0000u));
+                    }
+                    part[0][i] = __builtin_amdgcn_perm(z[1], z[0], 0x07060302u);       // their upper halves
+                    part[1][i] = __builtin_amdgcn_perm(r[1], r[0], 0x07060302u);
+                    part[2][i] = __builtin_amdgcn_perm(l[1], l[0], 0x07060302u);
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        BD_MFMA(t, c, part[k])
             }
+#undef BD_Z
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    BD_MFMA(t, c, ah[t])
+                    BD_MFMA(t, c, al[t])
+                }
         }
+#undef BD_PACK
+#undef BD_MFMA
     }
     __builtin_amdgcn_s_waitcnt(bt_vmcnt(0));                   // no LDS-DMA may outlive the loop
     }
@@ -527,7 +614,8 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
     p.P = pl.W <= 4 ? 512 : 256;               // eight waves per CU
     p.NR = pl.NR; p.CS = pl.CS;
     float *z = job.part + (((size_t)job.batch * pl.NR * job.d + 63) & ~(size_t)63);
-    p.z = (uint16_t *)z;
+    p.z = z;
+    p.exact = !decode_whole_pieces(job.d);
     uint32_t *mask = idx ? (uint32_t *)(z + pl.z_units) : nullptr;
     p.mask = mask;
 
@@ -590,12 +678,14 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
             return rc;
         const dim3 g2(pl.NR * pl.CS), b2(BT_WAVES2 * 64);
         const size_t lds2 = BD_RING + (size_t)max_range * 64 * T;
-#define BD_GO(T_)                                                                                              \
+#define BD_GO2(T_, EX_)                                                                                        \
         {                                                                                                      \
-            BT_LDS((ff_batch_down_kernel<T_>))                                                                 \
-            hipLaunchKernelGGL((ff_batch_down_kernel<T_>), g2, b2, lds2, st, p);                               \
+            BT_LDS((ff_batch_down_kernel<T_, EX_>))                                                            \
+            hipLaunchKernelGGL((ff_batch_down_kernel<T_, EX_>), g2, b2, lds2, st, p);                          \
         }
+#define BD_GO(T_) { if (p.exact) BD_GO2(T_, true) else BD_GO2(T_, false) }
         if (T == 1) BD_GO(1) else if (T == 2) BD_GO(2) else if (T == 3) BD_GO(3) else BD_GO(4)
+#undef BD_GO2
 #undef BD_GO
 #undef BT_LDS
         rc = check_launch("ff_batch_down_kernel");

@@ -966,3 +966,68 @@ def test_indexed_decode_does_not_read_words_that_need_not_be_built(d, n, k, B):
 ])
 def test_indexed_decode_tiles_and_widths(d, n, k, B, gated, bias):
     test_indexed_decode_masked_pass_matches_oracle(d, n, k, B, gated, bias)
+
+
+# Widths other than whole 1 KB pieces up to 5120 keep Z and the second product in fp32 in the one pass, and weights or
+# activations that are not finite go where they go when every row reads its own neurons.
+@pytest.mark.parametrize("d,n,B", [(1152, 1900, 6), (704, 1003, 20), (2752, 1003, 33), (1984, 1101, 64), (8192, 300, 9)])
+def test_batch_decode_keeps_z_in_fp32(d, n, B):
+    """y = z_a - z_b with z_a = 1 + 2^-9 + 2^-20, z_b = 1 + 2^-9: a Z of fewer than 21 bits loses it."""
+    W1 = torch.zeros(n, d, dtype=torch.bfloat16, device="cuda")
+    W2 = torch.zeros_like(W1)
+    ja, jb = n // 3, n - 2
+    W1[ja, :3] = torch.tensor([1.0, 2.0 ** -9, 2.0 ** -20])
+    W1[jb, :2] = torch.tensor([1.0, 2.0 ** -9])
+    W2[ja], W2[jb] = 1.0, -1.0
+    x = torch.ones(B, d, dtype=torch.bfloat16, device="cuda")
+    y = run_decode(G.layer(W1, W2, None, act=G.ACT_RELU), x, B)
+    assert np.all(y == 2.0 ** -20)
+
+
+@pytest.mark.parametrize("d,n,B,k", [(1152, 1900, 6, 0), (704, 1003, 20, 0), (2752, 1003, 33, 0), (1984, 1101, 64, 0), (8192, 300, 9, 0),
+                                     (1152, 401, 6, 200), (2752, 1003, 20, 500), (704, 1003, 64, 400)])
+def test_batch_decode_of_values_that_are_not_finite(d, n, B, k):
+    """Against the same rows one at a time (k: neurons of a row's own set, 0: all rows share the block)."""
+    dtype = synth.DT_BF16
+    c = synth.small_case(d + n, d, n, 4, dtype, T=B)
+    Wg, W1, W2 = (to_dev(c[m], dtype) for m in ("Wg", "W1", "W2"))
+    x = to_dev(c["xt"], dtype)
+    inf, nan = float("inf"), float("nan")
+    # weights: infinities of both signs, two of them in one column, a NaN; first and last neurons of steps and ranges
+    for j, col, v in ((0, 1, inf), (31, 2, -inf), (n // 2, 3, inf), (n // 2 + 1, 3, inf), (n - 1, d - 1, nan), (n - 9, 64, -inf)):
+        W2[j, col] = v
+    # activations: z of neuron 40 is infinite for every other row; z of neuron 50 is 255.75 x 2^120 for row 1, which is finite in
+    # fp32 and rounds to an infinity in bf16
+    W1[:, :3], Wg[:, :3], x[:, :3] = 0.0, 0.0, 0.0
+    W1[40, 0], Wg[40, 0], x[::2, 0] = 2.0 ** 100, 1.0, 2.0 ** 100
+    x[1, 1:3], W1[50, 1], Wg[50], W2[50] = 1.0, 2.0 ** 120, 0.0, 2.0 ** -120
+    Wg[50, 1], Wg[50, 2] = 255.0, 0.75
+    L = G.layer(W1, W2, Wg, act=G.ACT_RELU)
+    got = torch.zeros_like(x)
+    want = torch.zeros_like(x)
+    if k:
+        rng = np.random.default_rng(5)
+        sets = [set(rng.choice(n - 1, k - 1, replace=False).tolist()) for _ in range(B)]
+        if 50 not in sets[1]:
+            sets[1] = (sets[1] - {max(sets[1])}) | {50}
+        idx = torch.tensor([sorted(v) + [n - 1] for v in sets], dtype=torch.int32, device="cuda")
+        ws = workspace(G.griffin_decode_workspace_bytes(d, n, B))
+        G.griffin_ff_decode_indexed(L, idx, k, B, x, got, workspace=ws)
+        for b in range(B):
+            G.griffin_ff_decode_indexed(L, idx[b:b + 1].contiguous(), k, 1, x[b], want[b], workspace=ws)
+    else:
+        ws = workspace(G.griffin_decode_workspace_bytes(d, n, B))
+        G.griffin_ff_decode(L, x, got, B, workspace=ws)
+        for b in range(B):
+            G.griffin_ff_decode(L, x[b], want[b], 1, workspace=ws)
+    sync()
+    got, want = got.float().cpu().numpy(), want.float().cpu().numpy()
+    # a row that goes alone meets 0 x NaN where the kernel re-reads the last neuron past the end
+    cols = np.arange(d) != d - 1
+    np.testing.assert_array_equal(np.isnan(got[:, cols]), np.isnan(want[:, cols]))
+    np.testing.assert_array_equal(np.isinf(got[:, cols]), np.isinf(want[:, cols]))
+    ok = np.isfinite(want) & np.isfinite(got)
+    assert ok.any() and np.isinf(want).any()
+    np.testing.assert_array_equal(np.sign(got[np.isinf(want) & cols]), np.sign(want[np.isinf(want) & cols]))
+    scale = np.where(ok, np.abs(want), 0).max(axis=1, keepdims=True)
+    assert (np.abs(np.where(ok, got, 0) - np.where(ok, want, 0)) <= TOL_OUT[dtype] * scale).all()
