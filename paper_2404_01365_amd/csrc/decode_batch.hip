@@ -497,8 +497,8 @@ __global__ __launch_bounds__(BT_WAVES2 * 64) void ff_batch_down_kernel(BatchPara
 // Rows with their own expert sets through the FULL block in one pass (Section 4.2: every sample picks
 // its own neurons): the sets of a batch cover nearly every neuron between them (16 half-sets of a
 // 14336-neuron block: all of it), so streaming the block once and dropping, per row, the neurons its
-// set does not hold moves 8 times fewer bytes than streaming 16 compact blocks.  mask[j] collects,
-// for 16 rows, which of them selected neuron j.
+// set does not hold moves 8 times fewer bytes than streaming 16 compact blocks.  mask[g][j] collects,
+// for the rows 16 g .. 16 g + 15, which of them selected neuron j.
 __global__ __launch_bounds__(256) void batch_mask_zero_kernel(uint32_t *mask, int n)
 {
     const int j = blockIdx.x * 256 + threadIdx.x;
@@ -506,14 +506,14 @@ __global__ __launch_bounds__(256) void batch_mask_zero_kernel(uint32_t *mask, in
         mask[j] = 0u;
 }
 
-__global__ __launch_bounds__(256) void batch_mask_build_kernel(const int32_t *idx, int rows, int k, int n_src, uint32_t *mask)
+__global__ __launch_bounds__(256) void batch_mask_build_kernel(const int32_t *idx, int k, int n_src, uint32_t *mask)
 {
     const int t = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
-    if (t >= k || b >= rows)
+    if (t >= k)
         return;
     int j = idx[(int64_t)b * k + t];
     j = j < 0 ? 0 : (j >= n_src ? n_src - 1 : j);
-    atomicOr(&mask[j], 1u << b);
+    atomicOr(&mask[(int64_t)(b / BT_ROWS) * n_src + j], 1u << b % BT_ROWS);
 }
 
 // What the batch path would do with a shape.
@@ -576,23 +576,19 @@ size_t decode_batch_floats(int32_t d, int32_t n, int32_t batch, size_t have)
     return b.T ? batch_floats(b, d, n, batch) : 0;
 }
 
+size_t index_sets_words(int32_t n_block, int32_t batch)
+{
+    return (size_t)((batch + BT_ROWS - 1) / BT_ROWS) * n_block;
+}
+
 // The membership words of every group of 16 rows, [groups][n_block], for callers that build them once
 // per prompt (the sets do not change during generation, Section 4.2).
 int launch_index_sets_build(const int32_t *idx, int32_t k, int32_t batch, int32_t n_block, uint32_t *sets, hipStream_t st)
 {
-    for (int r0 = 0; r0 < batch; r0 += BT_ROWS) {
-        const int rows = batch - r0 < BT_ROWS ? batch - r0 : BT_ROWS;
-        uint32_t *mask = sets + (size_t)(r0 / BT_ROWS) * n_block;
-        hipLaunchKernelGGL(batch_mask_zero_kernel, dim3((n_block + 255) / 256), dim3(256), 0, st, mask, n_block);
-        hipLaunchKernelGGL(batch_mask_build_kernel, dim3((k + 255) / 256, rows), dim3(256), 0, st,
-                           idx + (int64_t)r0 * k, rows, k, n_block, mask);
-    }
+    const int words = (int)index_sets_words(n_block, batch);
+    hipLaunchKernelGGL(batch_mask_zero_kernel, dim3((words + 255) / 256), dim3(256), 0, st, sets, words);
+    hipLaunchKernelGGL(batch_mask_build_kernel, dim3((k + 255) / 256, batch), dim3(256), 0, st, idx, k, n_block, sets);
     return check_launch("batch_mask_build_kernel");
-}
-
-size_t index_sets_words(int32_t n_block, int32_t batch)
-{
-    return (size_t)((batch + BT_ROWS - 1) / BT_ROWS) * n_block;
 }
 
 // Runs both kernels for every pass; leaves part[b][NR][d] for the reduce kernel.
