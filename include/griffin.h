@@ -181,9 +181,9 @@ int griffin_compact(const griffin_layer *L, const int32_t *idx, int32_t k,
  * for `batch` independent rows x[b] through the ONE block C (a compact block, or a full one
  * with n = D_FF, which is Eq. 1).  x, y: [batch][d] contiguous, C->dtype.  With batch > 1 the
  * rows share one selected set (Section 5.3, Eq. 7) and the weights are streamed once per
- * four rows; five rows and more of a bf16 block (d from 64 to 8192; of small blocks whose d is not a
- * multiple of 512 more than sixteen) take the matrix cores and stream them once per pass of 16 to 64
- * rows, as many as the registers hold at that width (64 up to d = 2048, 48 up to 3072, 32 up to 5120).
+ * four rows; five rows and more of a bf16 block (n from 64 to 32768, d from 64 to 8192; where d is not a
+ * multiple of 512 up to 5120 if that spares enough bytes) take the matrix cores and stream them once per pass
+ * of 16 to 64 rows, as many as the registers hold at that width (64 up to d = 2048, 48 up to 3072, 32 up to 5120).
  * Where d is a multiple of 512 up to 5120 these passes round Z to pairs of bf16 (2^-17; a z beyond the largest
  * bf16 gives NaN); at other widths, and for fewer than five rows, Z is fp32 and infinities go where fp32 takes them.
  * workspace >= griffin_decode_workspace_bytes(d, n, batch) bytes, 256-byte aligned.
@@ -225,7 +225,7 @@ int griffin_ff_decode_multi(const griffin_layer *Cs, int32_t batch, const void *
  * block rather than for k neurons) five rows and more take ONE pass over the whole block, every row
  * dropping the neurons outside its own set: the sets of a batch cover most of the block between them,
  * so this moves far fewer bytes than a pass per row (bf16, d from 64 to 8192; widths that are not a
- * multiple of 512 up to 5120 take it when the sets together hold at least 1.5 times the block).  What is dropped
+ * multiple of 512 up to 5120 take it when it spares some tens of megabytes).  What is dropped
  * counts as zero; where d is a multiple of 512 up to 5120 a row meets 0 x Inf = NaN if a neuron outside its set has a
  * W2 entry that is not finite.
  */

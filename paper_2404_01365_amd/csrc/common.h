@@ -174,6 +174,8 @@ int launch_decode_split(const DecodeJob &job, hipStream_t st, hipEvent_t ev_mid)
 // floats of workspace it wants (0: it does not take the shape, or not within `have` floats); the front
 // leaves [batch][NR][d] partial rows
 size_t decode_batch_floats(int32_t d, int32_t n, int32_t batch, size_t have);
+// passes over the weights within `have` floats (0: it does not take the shape)
+int decode_batch_passes(int32_t d, int32_t n, int32_t batch, size_t have);
 int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32_t *idx, int32_t k, const uint32_t *sets,
                               size_t have, int *NR_out, hipStream_t st);
 int launch_index_sets_build(const int32_t *idx, int32_t k, int32_t batch, int32_t n_block, uint32_t *sets, hipStream_t st);

@@ -517,6 +517,28 @@ void set_decode_probe(hipEvent_t begin, hipEvent_t mid, hipEvent_t end)
     g_probe_end = end;
 }
 
+// Bytes that the matrix-core path has to spare against rows that go four at a time through a shared block, or one by one through
+// their own sets: it has three kernels instead of two, partial rows of its own and, for own sets, the membership words to form.
+//   * own sets: 40 MB and 600 bytes per row and column.  One by one / masked, us: 704 x 4000, k = n/2: 5 rows 16.2 / 21.4 (25 MB
+//     spared), 8 rows 23.0 / 22.3 (51); 40 rows of n/20: 1408 x 5632 32.5 / 39.7 (47), 1984 x 8000 47.3 / 47.9 (95); 2752 x 15520,
+//     k = n/2: 5 rows 112 / 63 (384);
+//   * a shared block, by the number of groups of four rows (three of them run slower than two or four).  Four at a time / matrix
+//     cores, us, Eq. 3: 704 wide, 8 rows n = 12784 25.5 / 26.0, 18465 32.6 / 30.6; 16 rows n = 2982 16.5 / 18.2, 4261 20.4 / 20.0;
+//     12 rows n = 568 15.0 / 16.2, 1420 18.6 / 16.6; 17 rows n = 568 16.1 / 18.0, 1420 19.2 / 18.1; 4288 wide, 8 rows n = 349
+//     20.3 / 22.1, 489 23.2 / 21.1; 16 rows n = 349 24.0 / 26.3, 489 26.3 / 25.6; 5632 wide (a pass per 16 rows), 17 rows n = 799 45.5 / 49.4,
+//     1065 55.0 / 52.0.
+static int64_t dec_batch_spare(int32_t d, int32_t batch, bool own_sets)
+{
+    const int groups = (batch + DEC_NB_MAX - 1) / DEC_NB_MAX;
+    if (own_sets)
+        return 40000000 + (int64_t)600 * batch * d;
+    if (groups > 4)
+        return 4000000 + (int64_t)600 * batch * d;
+    if (groups == 3)
+        return 8000000 + (int64_t)100 * batch * d;
+    return d <= 2800 ? 40000000 : groups == 2 ? 16000000 : 30000000;
+}
+
 int launch_decode(const DecodeJob &job, hipStream_t st)
 {
     const int R = decode_team_waves(job.d, job.bf16);
@@ -526,22 +548,19 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
     // A batch through one shared block takes the matrix-core path, with as many rows a pass as the workspace has room
     // for; else rows go four at a time.  A batch whose rows have their own sets inside one block takes it as a masked pass
     // over the whole block if the workspace was sized for the whole block; else rows go one by one through the index lists.
-    // Rows of other widths than whole 1 KB pieces up to 5120: a shared block of a few megabytes is cheaper four rows at a
-    // time as long as that is not many passes (two kernels instead of three; 704 x 1500 Eq. 2, 5 / 16 rows: 11.5 / 13.3 us against
-    // 13.1 / 14.0; 1152 x 2400: 17.7 / 28.0 against 16.4 / 18.2), and the masked pass, which reads the whole block, has to stand
-    // against rows that read the k neurons of their sets each (2752 x 15520, k = n/2: 3 rows 64 us one by one, 58 masked;
-    // 5 rows 112 / 59; 16 rows 330 / 62).
+    // Rows of other widths than whole 1 KB pieces up to 5120 take it when the bytes it spares pay for it (dec_batch_spare).
     const int32_t nb = job.idx ? job.n_src : job.n;
-    const bool worth = decode_whole_pieces(job.d) || (job.idx ? 2 * (int64_t)job.batch * job.n >= 3 * (int64_t)nb
-                                                              : job.batch > 16 || (int64_t)nb * job.d >= (2 << 20));
     size_t have = 0;
-    if (job.bf16 && !job.multi && job.W2 && job.batch >= DEC_BATCH_MIN_ROWS && worth) {
+    if (job.bf16 && !job.multi && job.W2 && job.batch >= DEC_BATCH_MIN_ROWS) {
         have = decode_route_floats(job.d, nb, job.batch);
         if (job.idx && job.part_bytes < decode_wanted_floats(job.d, nb, job.batch) * sizeof(float))
             have = 0;
         if (have > job.part_bytes / sizeof(float))
             have = job.part_bytes / sizeof(float);
-        if (!decode_batch_floats(job.d, nb, job.batch, have))
+        const int passes = decode_batch_passes(job.d, nb, job.batch, have);
+        const int64_t rows_read = job.idx ? (int64_t)job.batch * job.n : (int64_t)((job.batch + DEC_NB_MAX - 1) / DEC_NB_MAX) * nb;
+        const int64_t spared = (rows_read - (int64_t)passes * nb) * (job.Wg ? 6 : 4) * job.d;
+        if (passes == 0 || !(decode_whole_pieces(job.d) || spared > dec_batch_spare(job.d, job.batch, job.idx != nullptr)))
             have = 0;
     }
     const bool batch_path = have > 0;

@@ -569,6 +569,12 @@ static BatchPlan batch_plan(int32_t d, int32_t n, int32_t batch, size_t have)
     return BatchPlan{0, 0, 0, 0, 0, 0};
 }
 
+int decode_batch_passes(int32_t d, int32_t n, int32_t batch, size_t have)
+{
+    const BatchPlan b = batch_plan(d, n, batch, have);
+    return b.T ? (batch + b.T * BT_ROWS - 1) / (b.T * BT_ROWS) : 0;
+}
+
 // Floats that the path wants for a shape, 0 if it does not take it (or not within `have` floats).
 size_t decode_batch_floats(int32_t d, int32_t n, int32_t batch, size_t have)
 {
