@@ -521,25 +521,21 @@ void set_decode_probe(hipEvent_t begin, hipEvent_t mid, hipEvent_t end)
 }
 
 // Bytes that the matrix-core path has to spare against rows that go four at a time through a shared block, or one by one through
-// their own sets: it has three kernels instead of two, partial rows of its own and, for own sets, the membership words to form.
-//   * own sets: 40 MB and 600 bytes per row and column.  One by one / masked, us: 704 x 4000, k = n/2: 5 rows 16.2 / 21.4 (25 MB
-//     spared), 8 rows 23.0 / 22.3 (51); 40 rows of n/20: 1408 x 5632 32.5 / 39.7 (47), 1984 x 8000 47.3 / 47.9 (95); 2752 x 15520,
-//     k = n/2: 5 rows 112 / 63 (384);
-//   * a shared block, by the number of groups of four rows (three of them run slower than two or four).  Four at a time / matrix
-//     cores, us, Eq. 3: 704 wide, 8 rows n = 12784 25.5 / 26.0, 18465 32.6 / 30.6; 16 rows n = 2982 16.5 / 18.2, 4261 20.4 / 20.0;
-//     12 rows n = 568 15.0 / 16.2, 1420 18.6 / 16.6; 17 rows n = 568 16.1 / 18.0, 1420 19.2 / 18.1; 4288 wide, 8 rows n = 349
-//     20.3 / 22.1, 489 23.2 / 21.1; 16 rows n = 349 24.0 / 26.3, 489 26.3 / 25.6; 5632 wide (a pass per 16 rows), 17 rows n = 799 45.5 / 49.4,
-//     1065 55.0 / 52.0.
-static int64_t dec_batch_spare(int32_t d, int32_t batch, bool own_sets)
+// their own sets: it has three kernels instead of two, partial rows of its own (600 bytes per row and column pay for them) and,
+// for own sets, the membership words to form; groups of four run side by side and share what the caches hold, passes do not.
+//   * own sets, one by one / masked, us: 704 x 4000, k = n/2: 5 rows 15.8 / 22.1 (25 MB spared), 8 rows 22.7 / 23.0 (51), k = 3n/4:
+//     27.5 / 22.6 (84); 40 rows of 1408 x 5632, k = n/20 29.7 / 39.7 (47), k = n/10 43.8 / 39.3 (142); 5 rows of 2752 x 15520, k = n/3
+//     80 / 60 (167);
+//   * a shared Eq. 3 block, four at a time / matrix cores, us: 704 wide, 8 rows n = 12784 25.5 / 25.6 (54), 12 rows n = 6392
+//     21.1 / 19.9 (54), 16 rows n = 2982 16.5 / 16.5 (38), 33 rows n = 2130 20.7 / 21.5 (72); 4288 wide, 8 rows n = 349 22.0 / 21.6 (9),
+//     16 rows n = 489 26.2 / 25.1 (38), 33 rows (two passes) n = 1049 51.5 / 54.3 (189); 5632 wide, 17 rows (two passes) n = 2308
+//     62.8 / 63.4 (234), 33 rows (three) 95.0 / 97.1 (468).
+static int64_t dec_batch_spare(int32_t d, int32_t batch, int passes, bool own_sets)
 {
-    const int groups = (batch + DEC_NB_MAX - 1) / DEC_NB_MAX;
+    const int64_t partials = (int64_t)600 * batch * d;
     if (own_sets)
-        return 40000000 + (int64_t)600 * batch * d;
-    if (groups > 4)
-        return 4000000 + (int64_t)600 * batch * d;
-    if (groups == 3)
-        return 8000000 + (int64_t)100 * batch * d;
-    return d <= 2800 ? 40000000 : groups == 2 ? 16000000 : 30000000;
+        return 40000000 + partials;
+    return (d <= 2800 ? 50000000 : 16000000) + (batch > 16 ? partials : 0) + (int64_t)100000000 * (passes - 1);
 }
 
 int launch_decode(const DecodeJob &job, hipStream_t st)
@@ -563,7 +559,7 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
         const int passes = decode_batch_passes(job.d, nb, job.batch, have);
         const int64_t rows_read = job.idx ? (int64_t)job.batch * job.n : (int64_t)((job.batch + DEC_NB_MAX - 1) / DEC_NB_MAX) * nb;
         const int64_t spared = (rows_read - (int64_t)passes * nb) * (job.Wg ? 6 : 4) * job.d;
-        if (passes == 0 || !(decode_whole_pieces(job.d) || spared > dec_batch_spare(job.d, job.batch, job.idx != nullptr)))
+        if (passes == 0 || !(decode_whole_pieces(job.d) || spared > dec_batch_spare(job.d, job.batch, passes, job.idx != nullptr)))
             have = 0;
     }
     const bool batch_path = have > 0;
