@@ -30,6 +30,7 @@
 // The partial rows are added in a fixed order by ff_decode_reduce_kernel (decode.hip).
 #include "common.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace griffin {
@@ -554,7 +555,9 @@ static size_t batch_floats(const BatchPlan &b, int32_t d, int32_t n, int32_t bat
 }
 
 // Tiles per pass.  A pass reads all the weights, so as few passes as the registers allow (x of a pass lives in them:
-// 16 T rows with T S <= 18), the rows shared out evenly.  `have` floats of workspace bound it from above.
+// 16 T rows with T S <= 18), the rows shared out evenly.  `have` floats of workspace bound it from above: first the ranges get
+// longer, down to a quarter of what fills the chip (or to what the LDS holds), then the passes get narrower (in the library's own 8 MiB:
+// 64 rows of 960 x 3840 34.9 us with 28 ranges instead of 64, 48 four rows at a time; 33 rows of 704 x 12784 37.2 in one pass, 48.9 in two).
 static BatchPlan batch_plan(int32_t d, int32_t n, int32_t batch, size_t have)
 {
     const int tiles = (batch + BT_ROWS - 1) / BT_ROWS;
@@ -562,8 +565,13 @@ static BatchPlan batch_plan(int32_t d, int32_t n, int32_t batch, size_t have)
         const int T = (tiles + passes - 1) / passes;
         if (T > BT_MAX_T)
             continue;
-        const BatchPlan b = batch_plan_tiles(d, n, T);
-        if (b.T && batch_floats(b, d, n, batch) <= have)
+        BatchPlan b = batch_plan_tiles(d, n, T);
+        if (!b.T)
+            continue;
+        const int least = std::max((n + bd_range(T) - 1) / bd_range(T), b.NR / 4);
+        while (b.NR > least && batch_floats(b, d, n, batch) > have)
+            --b.NR;
+        if (batch_floats(b, d, n, batch) <= have)
             return b;
     }
     return BatchPlan{0, 0, 0, 0, 0, 0};

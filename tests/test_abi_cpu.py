@@ -226,6 +226,16 @@ def test_batch_decode_workspace_covers_the_matrix_core_path():
     assert G.griffin_decode_workspace_bytes(8192, 500, 16) == G.griffin_decode_workspace_bytes(8192, 500, 13) // 13 * 16
 
 
+@pytest.mark.parametrize("d,n,batch", [(576, 2304, 64), (768, 3072, 48), (960, 3840, 40), (960, 3840, 64), (1088, 4352, 33), (1088, 4352, 54)])
+def test_batches_that_nearly_fill_the_static_array_keep_the_matrix_core_path(d, n, batch):
+    # 8 MiB bound the partial rows, not the route: the query is more than a partial row per workgroup (at most 256 / (batch / 8))
+    # and row, and what fits the array at four rows at a time still fits it
+    four = 512 // -(-batch // 4) // 8 * 8 * batch * d * 4
+    need = G.griffin_decode_workspace_bytes(d, n, batch)
+    assert need > four
+    assert four > 8 << 20 or need <= 8 << 20
+
+
 @pytest.mark.parametrize("d,n", [(4096, 65536), (8192, 53248), (512, 1 << 20)])
 def test_decode_workspace_of_very_wide_blocks_is_a_partial_row_per_workgroup(d, n):
     # rows go four at a time, 32 workgroups for each of 64 rows

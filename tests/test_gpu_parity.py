@@ -223,6 +223,8 @@ def test_indexed_decode_with_sets_built_once(d, n, k, B):
     (5120, 517, 31, False, True),     # two tiles at the widest, Eq. 2
     (6000, 420, 7, True, True),       # wider than 5120, last block short
     (8192, 260, 20, True, False),     # widest rows: a tile a pass
+    (960, 3840, 64, True, False),     # within the 8 MiB of the library's own array: fewer, longer ranges
+    (1088, 4352, 54, False, True),
 ])
 def test_ff_decode_batch_tiles_and_widths(d, n, B, gated, bias):
     dtype, act = synth.DT_BF16, synth.ACT_SILU
@@ -1031,3 +1033,23 @@ def test_batch_decode_of_values_that_are_not_finite(d, n, B, k):
     np.testing.assert_array_equal(np.sign(got[np.isinf(want) & cols]), np.sign(want[np.isinf(want) & cols]))
     scale = np.where(ok, np.abs(want), 0).max(axis=1, keepdims=True)
     assert (np.abs(np.where(ok, got, 0) - np.where(ok, want, 0)) <= TOL_OUT[dtype] * scale).all()
+
+
+@pytest.mark.parametrize("d,n,B", [(960, 3840, 40), (704, 12784, 33), (512, 4000, 48), (1152, 1000, 17)])
+def test_static_decode_of_a_batch_is_bit_for_bit_the_same(d, n, B):
+    """The library's own array holds what a caller's workspace of the queried size (or a larger one) holds."""
+    dtype = synth.DT_BF16
+    g = torch.Generator(device="cuda").manual_seed(d + n)
+    m = [(torch.randn(n, d, generator=g, device="cuda") * d ** -0.5).bfloat16() for _ in range(3)]
+    x = torch.randn(B, d, generator=g, device="cuda").bfloat16()
+    L = G.layer(m[1], m[2], m[0], act=G.ACT_SILU)
+    need = G.griffin_decode_workspace_bytes(d, n, B)
+    assert need <= G.griffin_ff_decode_static_max_bytes()
+    ys = [torch.empty_like(x) for _ in range(3)]
+    G.griffin_ff_decode_static(L, x, ys[0], B)
+    for y, size in ((ys[1], need), (ys[2], 64 << 20)):
+        G.griffin_ff_decode(L, x, y, B, workspace=workspace(size))
+    sync()
+    assert torch.equal(ys[0], ys[1]) and torch.equal(ys[0], ys[2])
+    z = torch.nn.functional.silu(x.double() @ m[0].double().t()) * (x.double() @ m[1].double().t())
+    assert max_rel(to_host(ys[0]), (z @ m[2].double()).cpu().numpy()) <= TOL_OUT[dtype]
