@@ -552,8 +552,13 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
     size_t have = 0;
     if (job.bf16 && !job.multi && job.W2 && job.batch >= DEC_BATCH_MIN_ROWS) {
         have = decode_route_floats(job.d, nb, job.batch);
-        if (job.idx && job.part_bytes < decode_wanted_floats(job.d, nb, job.batch) * sizeof(float))
-            have = 0;
+        // own sets: a workspace sized for the whole block; where these batches have always run here, also the size that has always
+        // done, as long as it is not what a workspace for k neurons has
+        if (job.idx && job.part_bytes < decode_wanted_floats(job.d, nb, job.batch) * sizeof(float)) {
+            const bool least = decode_whole_pieces(job.d) && job.part_bytes >= decode_least_floats(job.d, nb, job.batch) * sizeof(float);
+            if (!least || (job.n < nb && job.part_bytes <= decode_wanted_floats(job.d, job.n, job.batch) * sizeof(float)))
+                have = 0;
+        }
         if (have > job.part_bytes / sizeof(float))
             have = job.part_bytes / sizeof(float);
         const int passes = decode_batch_passes(job.d, nb, job.batch, have);

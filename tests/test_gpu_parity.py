@@ -1053,3 +1053,42 @@ def test_static_decode_of_a_batch_is_bit_for_bit_the_same(d, n, B):
     assert torch.equal(ys[0], ys[1]) and torch.equal(ys[0], ys[2])
     z = torch.nn.functional.silu(x.double() @ m[0].double().t()) * (x.double() @ m[1].double().t())
     assert max_rel(to_host(ys[0]), (z @ m[2].double()).cpu().numpy()) <= TOL_OUT[dtype]
+
+
+def least_batch_floats(d, n, B):
+    """What a batch at d a multiple of 512 up to 5120 has always been given: partial rows, Z and words of sixteen rows a pass."""
+    ranges = max(min(256 // (d // 512), 64), -(-n // 480))
+    return max(B * ranges * d + 17 * n + 128, 512 // -(-B // 4) * B * d)
+
+
+@pytest.mark.parametrize("d,n,B", [(512, 900, 17), (1024, 2000, 40), (2048, 700, 64), (3072, 1001, 48), (5120, 300, 20)])
+def test_batch_decode_within_the_least_workspace(d, n, B):
+    """Fewer tiles a pass, shared and with own sets, and the same route: words that hold nothing leave nothing of the rows."""
+    dtype, act, k = synth.DT_BF16, synth.ACT_SILU, n // 8
+    c = synth.small_case(d + n, d, n, 4, dtype, T=B)
+    L, _ = dev_layer(c["Wg"], c["W1"], c["W2"], act, dtype)
+    x = to_dev(c["xt"], dtype)
+    size = 4 * least_batch_floats(d, n, B)
+    if size < G.griffin_decode_workspace_bytes(d, n, B):
+        small = workspace(size + 4096)
+        ws, guard = small[:size], small[size:]
+    else:
+        small = ws = workspace(size)
+        guard = small[:0]
+    small.fill_(0x7F)
+    y, y2 = torch.empty_like(x), torch.empty_like(x)
+    G.griffin_ff_decode(L, x, y, B, workspace=ws)
+    rng = np.random.default_rng(7)
+    idx = np.stack([np.sort(rng.choice(n, k, replace=False)) for _ in range(B)]).astype(np.int32)
+    idx_dev = torch.from_numpy(idx).cuda()
+    G.griffin_ff_decode_indexed(L, idx_dev, k, B, x, y2, workspace=ws)
+    sets = torch.zeros(G.griffin_index_sets_bytes(n, B) // 4, dtype=torch.int32, device="cuda")
+    y3 = torch.ones_like(x)
+    G.griffin_ff_decode_indexed_sets(L, idx_dev, k, sets, B, x, y3, workspace=ws)
+    sync()
+    assert torch.all(guard == 0x7F) and not torch.any(y3)
+    for b in range(0, B, 7):
+        ref = oracle.ff_decode(c["xt"][b], c["Wg"], c["W1"], c["W2"], act)
+        assert max_rel(to_host(y)[b], ref) <= TOL_OUT[dtype], b
+        ref = oracle.ff_decode(c["xt"][b], c["Wg"][idx[b]], c["W1"][idx[b]], c["W2"][idx[b]], act)
+        assert max_rel(to_host(y2)[b], ref) <= TOL_OUT[dtype], b
