@@ -1001,6 +1001,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
     if (slabs && pl.splits > 1 && ldx <= (1 << 21)) {
         const int nb = (L.n + ACT_COLS - 1) / ACT_COLS;
         *nt_out = nb;
+        int rc;
         if (gated) {
             p.Z = slabs; p.ldz = pl.ldu; p.Zb = nullptr; p.z_stream = 0;
             p.splits = pl.splits; p.kt_per_split = pl.per;
@@ -1012,10 +1013,10 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
                 hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 4, true, false, 2, true>), grid, block, 0, st, p);
             else
                 hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 2, true, false, 2, true>), grid, block, 0, st, p);
+            rc = check_launch("ff1_bf16_mfma_kernel");
         } else {
-            launch_gemm_nt_partials(X, ldx, L.W1, L.ld, M, L.n, L.d, pl.splits, pl.per, slabs, pl.ldu, st);
+            rc = launch_gemm_nt_partials(X, ldx, L.W1, L.ld, M, L.n, L.d, pl.splits, pl.per, slabs, pl.ldu, st);
         }
-        int rc = check_launch("ff1_bf16_mfma_kernel");
         if (rc != GRIFFIN_OK)
             return rc;
         Ff1ActParams a;
