@@ -18,6 +18,10 @@
  *     Accumulation, activations, Z, the statistic s and the selection run in fp32.  Two products take Z rounded on
  *     the way in, as their comments say: the prompt's output of bf16 blocks (to bf16) and five rows and more of a
  *     bf16 block whose d is a multiple of 512 up to 5120 (to a pair of bf16, 2^-17).
+ *   - *_workspace_bytes is what a call makes use of, and the size to give it.  griffin_prefill_select,
+ *     griffin_prompt_phase and griffin_ff_decode* also run in somewhat less (a short prompt's product
+ *     in one range, fewer rows a pass): another order of summation, so the last bits may differ from
+ *     those of the queried size.  Below what the smallest form needs they return GRIFFIN_EWORKSPACE.
  *   - d must be a multiple of 8; d, n <= 2^20; ld >= d and a multiple of 8 (16-byte rows).
  *   - A block may carry W2 a second time in the paper's own orientation (W2t, see griffin_layer).
  */
@@ -35,7 +39,7 @@ typedef enum {
     GRIFFIN_OK = 0,
     GRIFFIN_EINVAL = 1,        /* null pointer, negative size, bad enum                     */
     GRIFFIN_ESHAPE = 2,        /* sizes inconsistent with each other or with the alignment  */
-    GRIFFIN_EWORKSPACE = 3,    /* workspace missing or smaller than the *_workspace_bytes   */
+    GRIFFIN_EWORKSPACE = 3,    /* workspace missing, not aligned or too small (see below)   */
     GRIFFIN_EUNSUPPORTED = 4,  /* valid request this build has no kernel for                */
     GRIFFIN_EHIP = 5           /* the HIP runtime refused a launch                          */
 } griffin_status;
@@ -102,8 +106,8 @@ int32_t griffin_k_from_fraction(int32_t d_ff, double keep);
  *   Z_out           [total_tokens][L->n] fp32 with row stride ldz elements, or NULL (then Z
  *                   lives in the workspace).  Exposed because the prompt's own output uses the
  *                   full block (Section 5.1) and needs exactly this Z.
- *   workspace       at least griffin_prefill_workspace_bytes(L, total_tokens, n_seqs,
- *                   Z_out != NULL) bytes, 256-byte aligned
+ *   workspace       griffin_prefill_workspace_bytes(L, total_tokens, n_seqs, Z_out != NULL)
+ *                   bytes, 256-byte aligned
  * An empty sequence (length 0) selects indices 0 .. k-1 and reports s = 0.
  */
 size_t griffin_prefill_workspace_bytes(const griffin_layer *L, int64_t total_tokens,
@@ -186,7 +190,7 @@ int griffin_compact(const griffin_layer *L, const int32_t *idx, int32_t k,
  * of 16 to 64 rows, as many as the registers hold at that width (64 up to d = 2048, 48 up to 3072, 32 up to 5120).
  * Where d is a multiple of 512 up to 5120 these passes round Z to pairs of bf16 (2^-17; a z beyond the largest
  * bf16 gives NaN); at other widths, and for fewer than five rows, Z is fp32 and infinities go where fp32 takes them.
- * workspace >= griffin_decode_workspace_bytes(d, n, batch) bytes, 256-byte aligned.
+ * workspace: griffin_decode_workspace_bytes(d, n, batch) bytes or more, 256-byte aligned.
  */
 size_t griffin_decode_workspace_bytes(int32_t d, int32_t n, int32_t batch);
 int griffin_ff_decode(const griffin_layer *C, const void *x, void *y, int32_t batch,
@@ -195,7 +199,8 @@ int griffin_ff_decode(const griffin_layer *C, const void *x, void *y, int32_t ba
 /*
  * griffin_ff_decode for callers that cannot allocate device memory or carry a workspace around:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments, same kernels and bit for bit the same y as griffin_ff_decode, but the partial rows live
+ * arguments, same kernels and bit for bit the same y as griffin_ff_decode with a workspace of the queried
+ * size or more, but the partial rows live
  * in a device array inside the library (8 MiB per GPU, held from the first call on that GPU until the
  * process ends) instead of a caller workspace.  The call allocates and frees nothing.
  *   - A request whose griffin_decode_workspace_bytes(C->d, C->n, batch) exceeds
