@@ -229,10 +229,10 @@ int griffin_ff_decode_multi(const griffin_layer *Cs, int32_t batch, const void *
  * With a workspace of griffin_decode_workspace_bytes(d, L->n, batch) bytes (sized for the whole
  * block rather than for k neurons) five rows and more take ONE pass over the whole block, every row
  * dropping the neurons outside its own set: the sets of a batch cover most of the block between them,
- * so this moves far fewer bytes than a pass per row (bf16, d from 64 to 8192; widths that are not a
- * multiple of 512 up to 5120 take it when it spares some tens of megabytes).  What is dropped
- * counts as zero; where d is a multiple of 512 up to 5120 a row meets 0 x Inf = NaN if a neuron outside its set has a
- * W2 entry that is not finite.
+ * so this moves far fewer bytes than a pass per row (bf16, n from 64 to 32768, d from 64 to 8192; where
+ * d is not a multiple of 512 up to 5120, and three and four rows, if it spares some tens of megabytes).
+ * What is dropped counts as zero; five rows and more with d a multiple of 512 up to 5120 meet
+ * 0 x Inf = NaN if a neuron outside a row's set has a W2 entry that is not finite.
  */
 int griffin_ff_decode_indexed(const griffin_layer *L, const int32_t *idx, int32_t k,
                               int32_t batch, const void *x, void *y, void *workspace,
@@ -248,8 +248,8 @@ int griffin_ff_decode_indexed(const griffin_layer *L, const int32_t *idx, int32_
  *          griffin_index_sets_build(idx, k, batch, L->n, ...), valid as long as idx does not change.
  * griffin_ff_decode_indexed_sets takes the same idx as well: when the one-pass route does not apply
  * (fewer than five rows, a workspace sized for k neurons only, a shape it does not cover) the rows
- * go through the index lists exactly as in griffin_ff_decode_indexed and sets is not read; nor is it for
- * d that is not a multiple of 512 up to 5120, where the one pass derives the words from idx.
+ * go exactly as in griffin_ff_decode_indexed and sets is not read; nor is it for d that is not a
+ * multiple of 512 up to 5120, where the one pass derives the words from idx.
  */
 size_t griffin_index_sets_bytes(int32_t n, int32_t batch);
 int griffin_index_sets_build(const int32_t *idx, int32_t k, int32_t batch, int32_t n, void *sets,

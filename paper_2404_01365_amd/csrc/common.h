@@ -181,9 +181,10 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
 int launch_index_sets_build(const int32_t *idx, int32_t k, int32_t batch, int32_t n_block, uint32_t *sets, hipStream_t st);
 size_t index_sets_words(int32_t n_block, int32_t batch);
 
-// rows of whole 1 KB pieces: Z as bf16 pairs, and the caller's membership words are read
-inline bool decode_whole_pieces(int32_t d) { return d % 512 == 0 && d <= 5120; }
-constexpr int DEC_BATCH_MIN_ROWS = 5;     // rows from which the path is considered (launch_decode)
+constexpr int DEC_BATCH_MIN_ROWS = 5;     // rows from which the path is considered (launch_decode) ...
+constexpr int DEC_MASKED_MIN_ROWS = 3;    // ... and where the rows have their own sets
+// batches of whole 1 KB pieces: Z as bf16 pairs, and the caller's membership words are read
+inline bool decode_whole_pieces(int32_t d, int32_t batch) { return d % 512 == 0 && d <= 5120 && batch >= DEC_BATCH_MIN_ROWS; }
 int decode_parts(int32_t n, int32_t batch);
 // floats of workspace that a decode has to be given, and that it makes use of
 size_t decode_least_floats(int32_t d, int32_t n, int32_t batch);

@@ -484,7 +484,7 @@ int decode_parts(int32_t n, int32_t batch)
 size_t decode_least_floats(int32_t d, int32_t n, int32_t batch)
 {
     size_t floats = (size_t)decode_parts(n, batch) * batch * d;
-    if (batch >= DEC_BATCH_MIN_ROWS && decode_whole_pieces(d) && n >= 64 && n <= 32768) {
+    if (decode_whole_pieces(d, batch) && n >= 64 && n <= 32768) {
         int64_t nr = 256 / (d / 512);
         if (nr > 64) nr = 64;
         if (nr < (n + 479) / 480) nr = (n + 479) / 480;
@@ -501,7 +501,7 @@ size_t decode_least_floats(int32_t d, int32_t n, int32_t batch)
 static size_t decode_route_floats(int32_t d, int32_t n, int32_t batch)
 {
     const size_t least = decode_least_floats(d, n, batch), own = DEC_STATIC_BYTES / sizeof(float);
-    return batch < DEC_BATCH_MIN_ROWS ? 0 : decode_batch_floats(d, n, batch, least <= own ? own : (size_t)-1);
+    return batch < DEC_MASKED_MIN_ROWS ? 0 : decode_batch_floats(d, n, batch, least <= own ? own : (size_t)-1);
 }
 
 size_t decode_wanted_floats(int32_t d, int32_t n, int32_t batch)
@@ -525,7 +525,8 @@ void set_decode_probe(hipEvent_t begin, hipEvent_t mid, hipEvent_t end)
 // for own sets, the membership words to form; groups of four run side by side and share what the caches hold, passes do not.
 //   * own sets, one by one / masked, us: 704 x 4000, k = n/2: 5 rows 15.8 / 22.1 (25 MB spared), 8 rows 22.7 / 23.0 (51), k = 3n/4:
 //     27.5 / 22.6 (84); 40 rows of 1408 x 5632, k = n/20 29.7 / 39.7 (47), k = n/10 43.8 / 39.3 (142); 5 rows of 2752 x 15520, k = n/3
-//     80 / 60 (167);
+//     80 / 60 (167); three and four rows: 100 MB.  4 rows of 4096 x 14336, k = n/3 90 / 72 (141), k = n/2 120 / 72 (352); 3 rows of
+//     2752 x 15520, k = n/2 62 / 63 (110), 4 rows of 5632 x 12428, k = n/3 101 / 101 (168);
 //   * a shared Eq. 3 block, four at a time / matrix cores, us: 704 wide, 8 rows n = 12784 25.5 / 25.6 (54), 12 rows n = 6392
 //     21.1 / 19.9 (54), 16 rows n = 2982 16.5 / 16.5 (38), 33 rows n = 2130 20.7 / 21.5 (72); 4288 wide, 8 rows n = 349 22.0 / 21.6 (9),
 //     16 rows n = 489 26.2 / 25.1 (38), 33 rows (two passes) n = 1049 51.5 / 54.3 (189); 5632 wide, 17 rows (two passes) n = 2308
@@ -534,7 +535,7 @@ static int64_t dec_batch_spare(int32_t d, int32_t batch, int passes, bool own_se
 {
     const int64_t partials = (int64_t)600 * batch * d;
     if (own_sets)
-        return 40000000 + partials;
+        return batch < DEC_BATCH_MIN_ROWS ? 100000000 : 40000000 + partials;
     return (d <= 2800 ? 50000000 : 16000000) + (batch > 16 ? partials : 0) + (int64_t)100000000 * (passes - 1);
 }
 
@@ -550,12 +551,12 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
     // Rows of other widths than whole 1 KB pieces up to 5120 take it when the bytes it spares pay for it (dec_batch_spare).
     const int32_t nb = job.idx ? job.n_src : job.n;
     size_t have = 0;
-    if (job.bf16 && !job.multi && job.W2 && job.batch >= DEC_BATCH_MIN_ROWS) {
+    if (job.bf16 && !job.multi && job.W2 && job.batch >= (job.idx ? DEC_MASKED_MIN_ROWS : DEC_BATCH_MIN_ROWS)) {
         have = decode_route_floats(job.d, nb, job.batch);
         // own sets: a workspace sized for the whole block; where these batches have always run here, also the size that has always
         // done, as long as it is not what a workspace for k neurons has
         if (job.idx && job.part_bytes < decode_wanted_floats(job.d, nb, job.batch) * sizeof(float)) {
-            const bool least = decode_whole_pieces(job.d) && job.part_bytes >= decode_least_floats(job.d, nb, job.batch) * sizeof(float);
+            const bool least = decode_whole_pieces(job.d, job.batch) && job.part_bytes >= decode_least_floats(job.d, nb, job.batch) * sizeof(float);
             if (!least || (job.n < nb && job.part_bytes <= decode_wanted_floats(job.d, job.n, job.batch) * sizeof(float)))
                 have = 0;
         }
@@ -564,7 +565,7 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
         const int passes = decode_batch_passes(job.d, nb, job.batch, have);
         const int64_t rows_read = job.idx ? (int64_t)job.batch * job.n : (int64_t)((job.batch + DEC_NB_MAX - 1) / DEC_NB_MAX) * nb;
         const int64_t spared = (rows_read - (int64_t)passes * nb) * (job.Wg ? 6 : 4) * job.d;
-        if (passes == 0 || !(decode_whole_pieces(job.d) || spared > dec_batch_spare(job.d, job.batch, passes, job.idx != nullptr)))
+        if (passes == 0 || !(decode_whole_pieces(job.d, job.batch) || spared > dec_batch_spare(job.d, job.batch, passes, job.idx != nullptr)))
             have = 0;
     }
     const bool batch_path = have > 0;
@@ -612,7 +613,7 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
         return GRIFFIN_EUNSUPPORTED;       // only the transposed copy is there and this call cannot use it
     if (batch_path) {
         // the caller's words are read where griffin.h says so; for other shapes they need not have been built
-        const uint32_t *sets = decode_whole_pieces(job.d) ? job.sets : nullptr;
+        const uint32_t *sets = decode_whole_pieces(job.d, job.batch) ? job.sets : nullptr;
         int rc = job.idx ? launch_decode_batch_front(job, job.n_src, job.idx, job.n, sets, have, &P, st)
                          : launch_decode_batch_front(job, job.n, nullptr, 0, nullptr, have, &P, st);
         if (rc != GRIFFIN_OK)

@@ -24,9 +24,9 @@
 //    workgroup, so the work is cut in two directions: a workgroup owns 512 columns and one of NR ranges of neurons, and
 //    writes one [rows][512] partial into the partial-row buffer that the single-row path uses (NR rows per batch row).
 //
-// Z is kept in the layout in which the second kernel's MFMAs want it.  At widths of whole 1 KB pieces up to 5120: bf16 hi + lo pairs
-// (their sum has fp32's accuracy to 2^-17; both are fed), [n/8][tile of 16 rows][hi, lo][16 rows][8 neurons].  At all other widths Z
-// stays in fp32, as it is when rows go four at a time: [n/8][tile][two halves][16 rows][4 neurons].
+// Z is kept in the layout in which the second kernel's MFMAs want it.  Five rows and more at widths of whole 1 KB pieces up to 5120: bf16
+// hi + lo pairs (their sum has fp32's accuracy to 2^-17; both are fed), [n/8][tile of 16 rows][hi, lo][16 rows][8 neurons].  At all
+// other widths, and for fewer rows, Z stays in fp32, as it is in decode.hip: [n/8][tile][two halves][16 rows][4 neurons].
 // The partial rows are added in a fixed order by ff_decode_reduce_kernel (decode.hip).
 #include "common.h"
 
@@ -625,7 +625,7 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
     p.NR = pl.NR; p.CS = pl.CS;
     float *z = job.part + (((size_t)job.batch * pl.NR * job.d + 63) & ~(size_t)63);
     p.z = z;
-    p.exact = !decode_whole_pieces(job.d);
+    p.exact = !decode_whole_pieces(job.d, job.batch);
     uint32_t *mask = idx ? (uint32_t *)(z + pl.z_units) : nullptr;
     p.mask = mask;
 

@@ -936,6 +936,7 @@ def test_ff_decode_few_rows_reduce_together(dtype, d, n, B, biases, gated):
 
 @pytest.mark.parametrize("d,n,k,B", [
     (1024, 301, 260, 1), (1024, 301, 260, 3), (1024, 301, 260, 4),      # fewer than five rows, most of the block in every set
+    (4096, 3000, 2990, 4), (5120, 3601, 3000, 3), (2752, 5003, 5000, 3),      # ... enough of it for the one pass, which derives the words
     (1152, 301, 200, 6), (2752, 517, 400, 20), (5632, 130, 100, 5),     # widths whose one pass derives the words from idx
 ])
 def test_indexed_decode_does_not_read_words_that_need_not_be_built(d, n, k, B):
@@ -987,7 +988,7 @@ def test_batch_decode_keeps_z_in_fp32(d, n, B):
 
 
 @pytest.mark.parametrize("d,n,B,k", [(1152, 1900, 6, 0), (704, 1003, 20, 0), (2752, 1003, 33, 0), (1984, 1101, 64, 0), (8192, 300, 9, 0),
-                                     (1152, 401, 6, 200), (2752, 1003, 20, 500), (704, 1003, 64, 400)])
+                                     (1152, 5001, 6, 2500), (2752, 1003, 20, 500), (704, 1003, 64, 400), (4096, 3001, 4, 2900), (5120, 3601, 3, 3000)])
 def test_batch_decode_of_values_that_are_not_finite(d, n, B, k):
     """Against the same rows one at a time (k: neurons of a row's own set, 0: all rows share the block)."""
     dtype = synth.DT_BF16
