@@ -319,7 +319,7 @@ int griffin_prompt_phase(const griffin_layer *L, const void *W2p, int64_t ldw, c
         return GRIFFIN_ESHAPE;
     const bool bf16 = L->dtype == GRIFFIN_BF16;
     const bool tiles = bf16 && L->n % 8 == 0 && L->d % 4 == 0 && ldw % 8 == 0 && aligned16(W2p);
-    if (!tiles && total > ((int64_t)1 << 18))
+    if (!tiles && total > ((int64_t)1 << 18))          // the documented limit of the fp32 path
         return GRIFFIN_EUNSUPPORTED;
     const PrefillPlan pl = plan_prefill(*L, total, n_seqs, false);
     const size_t second = total > 0 ? ff2_workspace_bytes(total, L->n, L->d) : 0;

@@ -14,7 +14,7 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// round-to-nearest-even; NaN stays NaN (one v_cvt_pk_bf16_f32; the same bits as rounding in integers, all 2^32 inputs compared)
+// round-to-nearest-even; NaN stays NaN (one v_cvt_pk_bf16_f32)
 __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 // two values rounded into one word, `lo` in its low half: one instruction

@@ -14,12 +14,13 @@
 //    lines of eight neurons an instruction, R blocks ahead; the lanes of two such instructions then trade halves, so that a
 //    register holds sixteen neurons as the MFMA wants them: a kilobyte of weights costs one load and one MFMA per sixteen
 //    rows of the batch and touches no LDS.  A wave's partial tiles go to LDS; the waves meet as seldom as the LDS allows (a
-//    barrier per group would tie their load streams to the slowest: 47 us instead of 42.5 on 4096 x 14336), add the
+//    barrier per group would tie their load streams to the slowest: 75 us a masked call instead of 71 on 4096 x 14336), add the
 //    tiles in wave order, apply sigma, the gating product and the membership bits, and store Z.  Workgroups start at different
 //    blocks, so that row strides of a power of two do not send them all to the same memory channels at a time.
-//    Measured on the gate and up rows: 5120 x 6912 (142 MB), 16 rows 32.5 us (38.0 before, when rows were streamed through
-//    LDS two neurons at a time with two of sixteen MFMA columns in use; 42 with loads of sixteen half lines instead of
-//    eight whole ones); 3072 x 12288, 40 rows 37 us (three passes of 32 before); 4096 x 14336 masked 42.5 us (43.9 before).
+//    Measured on the gate and up rows (medians of the kernel trace, each with the ~4 us of a dependent dispatch in it):
+//    5120 x 6912 (142 MB), 16 rows 34 us (38 when rows were streamed through LDS two neurons at a time with two of sixteen
+//    MFMA columns in use; 42 with loads of sixteen half lines instead of eight whole ones); 3072 x 12288, 40 rows 37 us (three
+//    passes of 32 in that form); 4096 x 14336 masked 44 us, as in that form.
 //  * ff_batch_down_kernel: the second line.  Giving every workgroup all d columns would cost one [rows][d] partial per
 //    workgroup, so the work is cut in two directions: a workgroup owns 512 columns and one of NR ranges of neurons, and
 //    writes one [rows][512] partial into the partial-row buffer that the single-row path uses (NR rows per batch row).

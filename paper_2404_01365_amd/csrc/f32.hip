@@ -12,7 +12,7 @@
 // each, took 89 us where this takes 8 for the output of the same prompt; the whole prompt phase of 256 tokens through a
 // 1024 x 4096 block 2021 -> 123 us, of 1500 tokens through a bf16 1024 x 4002 block 10046 -> 465 us.)  Operands come out of
 // the L2s once per tile, which is what bounds long prompts: they take 64-token tiles as soon as those fill the chip
-// (selection from 2048 tokens of a 1024 x 4096 block: 584 us with 32, 470 with 64).
+// (selection from 2048 tokens of a 1024 x 4096 block: 584 us with 32, 472 with 64).
 #include "common.h"
 
 namespace griffin {
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
 
 int f32_ntiles(int32_t n) { return (n + FN_COLS - 1) / FN_COLS; }
 
-// 64-token tiles when they still give every CU two workgroups
+// 64-token tiles when there are two for every CU (the gated form's LDS holds one at a time)
 static bool f32_tall(int64_t M, int nt) { return (M + 63) / 64 * nt >= 512; }
 
 int launch_f32_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz, float *rowpart,
