@@ -2,6 +2,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <atomic>
 #include <stdint.h>
 
 #include "griffin.h"
@@ -110,6 +112,22 @@ struct SeqTable {            // passed to kernels by value
 
 int set_hip_error(hipError_t e, const char *what);   // records text, returns GRIFFIN_EHIP
 int check_launch(const char *what);                  // hipGetLastError -> status
+
+// A kernel may ask for more LDS than its code names once its limit is raised; needed once per kernel and device.  The enclosing
+// function returns the status if the runtime refuses.
+#define RAISE_LDS_LIMIT(KERNEL, BYTES)                                                                                 \
+    {                                                                                                                  \
+        static std::atomic<uint64_t> raised_{0};                                                                       \
+        int dev_ = 0;                                                                                                  \
+        if (hipGetDevice(&dev_) != hipSuccess)                                                                         \
+            return set_hip_error(hipGetLastError(), "hipGetDevice");                                                   \
+        const uint64_t bit_ = 1ull << (dev_ & 63);                                                                     \
+        if (!(raised_.load(std::memory_order_acquire) & bit_)) {                                                       \
+            if (hipFuncSetAttribute((const void *)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES) != hipSuccess) \
+                return set_hip_error(hipGetLastError(), "hipFuncSetAttribute");                                        \
+            raised_.fetch_or(bit_, std::memory_order_release);                                                         \
+        }                                                                                                              \
+    }
 
 // launchers (one per source file); all return a griffin_status
 // slabs (optional): room of ff1_slab_bytes() for the raw products of ranges of d.  Zb (optional): a bf16 copy of Z [M][ldzb] written by the same epilogue when ff1_can_write_zb() says so

@@ -642,10 +642,20 @@ int launch_decode(const DecodeJob &job, hipStream_t st)
         else if (NB == 2) DEC_GO1(BF, GA, false, BI, 2);               \
         else DEC_GO1(BF, GA, false, BI, DEC_NB_MAX);                   \
     }
-#define DEC_GO_MULTI(BF, GA, BI) hipLaunchKernelGGL((ff_decode_multi_kernel<BF, GA, BI>), grid, block, 0, st, p, m)
+    // Per-row blocks of more than eight waves a team: one workgroup a CU, by asking for more than half of its LDS.  Two of ten waves
+    // each, at the registers of these kernels, stream 10 % slower (5120 x 6912 Eq. 3, 4 / 8 rows: with biases 152 / 301 us against
+    // 136 / 277, without 151 / 295 against 138 / 276; Eq. 2 98 / 204 against 95 / 186; 6144 x 5500 135 / 270 against 130 / 260; 8192
+    // wide, where two do not fit, the same; up to 4096 wide two and three are the better number).
+    const int alone = R > 8 ? 72 * 1024 : 0;
+#define DEC_GO_MULTI(BF, GA, BI)                                                                                   \
+    {                                                                                                              \
+        if (alone)                                                                                                 \
+            RAISE_LDS_LIMIT((ff_decode_multi_kernel<BF, GA, BI>), alone)                                           \
+        hipLaunchKernelGGL((ff_decode_multi_kernel<BF, GA, BI>), grid, block, alone, st, p, m);                    \
+    }
 #define DEC_PICK3(BF, GA, IX) { if (bias) DEC_GO(BF, GA, IX, true) else DEC_GO(BF, GA, IX, false) }
 #define DEC_PICK2(BF, GA) { if (indexed) DEC_PICK3(BF, GA, true) else DEC_PICK3(BF, GA, false) }
-#define DEC_PICKM(BF, GA) { if (bias) DEC_GO_MULTI(BF, GA, true); else DEC_GO_MULTI(BF, GA, false); }
+#define DEC_PICKM(BF, GA) { if (bias) DEC_GO_MULTI(BF, GA, true) else DEC_GO_MULTI(BF, GA, false) }
     if (job.multi) {
         if (job.bf16) { if (gated) DEC_PICKM(true, true) else DEC_PICKM(true, false) }
         else          { if (gated) DEC_PICKM(false, true) else DEC_PICKM(false, false) }

@@ -32,7 +32,6 @@
 #include "common.h"
 
 #include <algorithm>
-#include <atomic>
 
 namespace griffin {
 
@@ -630,10 +629,6 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
     uint32_t *mask = idx ? (uint32_t *)(z + pl.z_units) : nullptr;
     p.mask = mask;
 
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess)
-        return set_hip_error(hipGetLastError(), "hipGetDevice");
-    const uint64_t dev_bit = 1ull << (dev & 63);
     const int max_range = ((n_block + pl.NR - 1) / pl.NR + 7 + 31) & ~31;      // of any range, in whole steps of 32
     for (int r0 = 0; r0 < job.batch; r0 += pl.T * BT_ROWS) {
         p.rows = job.batch - r0 < pl.T * BT_ROWS ? job.batch - r0 : pl.T * BT_ROWS;
@@ -647,16 +642,6 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
             if (rcm != GRIFFIN_OK)
                 return rcm;
         }
-/* raising the dynamic LDS limit is needed once per kernel and device */
-#define BT_LDS(KERNEL)                                                                                         \
-        {                                                                                                      \
-            static std::atomic<uint64_t> attr_set_{0};                                                         \
-            if (!(attr_set_.load(std::memory_order_acquire) & dev_bit)) {                                      \
-                if (hipFuncSetAttribute((const void *)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) \
-                    return set_hip_error(hipGetLastError(), "hipFuncSetAttribute");                            \
-                attr_set_.fetch_or(dev_bit, std::memory_order_release);                                        \
-            }                                                                                                  \
-        }
         // the waves of a workgroup meet as seldom as the LDS (of a CU, shared by two workgroups of up to four waves) allows
         const int group_bytes = pl.W * T * (gated ? 2 : 1) * 1024, groups = ((n_block + 7) / 8 * 4 + 8 * p.P - 1) / (8 * p.P);
         p.NB = (p.P > 256 ? 72 : 144) * 1024 / group_bytes;
@@ -666,10 +651,10 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
 #define BT_GO(S_, T_)                                                                                          \
         case S_ * 8 + T_:                                                                                      \
             if (gated) {                                                                                       \
-                BT_LDS((ff_batch_gu_kernel<true, S_, T_>))                                                     \
+                RAISE_LDS_LIMIT((ff_batch_gu_kernel<true, S_, T_>), 160 * 1024)                                                     \
                 hipLaunchKernelGGL((ff_batch_gu_kernel<true, S_, T_>), dim3(p.P), dim3(p.W * 64), lds1, st, p); \
             } else {                                                                                           \
-                BT_LDS((ff_batch_gu_kernel<false, S_, T_>))                                                    \
+                RAISE_LDS_LIMIT((ff_batch_gu_kernel<false, S_, T_>), 160 * 1024)                                                    \
                 hipLaunchKernelGGL((ff_batch_gu_kernel<false, S_, T_>), dim3(p.P), dim3(p.W * 64), lds1, st, p); \
             }                                                                                                  \
             break;
@@ -691,14 +676,13 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
         const size_t lds2 = BD_RING + (size_t)max_range * 64 * T;
 #define BD_GO2(T_, EX_)                                                                                        \
         {                                                                                                      \
-            BT_LDS((ff_batch_down_kernel<T_, EX_>))                                                            \
+            RAISE_LDS_LIMIT((ff_batch_down_kernel<T_, EX_>), 160 * 1024)                                                            \
             hipLaunchKernelGGL((ff_batch_down_kernel<T_, EX_>), g2, b2, lds2, st, p);                          \
         }
 #define BD_GO(T_) { if (p.exact) BD_GO2(T_, true) else BD_GO2(T_, false) }
         if (T == 1) BD_GO(1) else if (T == 2) BD_GO(2) else if (T == 3) BD_GO(3) else BD_GO(4)
 #undef BD_GO2
 #undef BD_GO
-#undef BT_LDS
         rc = check_launch("ff_batch_down_kernel");
         if (rc != GRIFFIN_OK)
             return rc;
