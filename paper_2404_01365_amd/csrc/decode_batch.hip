@@ -651,10 +651,10 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
 #define BT_GO(S_, T_)                                                                                          \
         case S_ * 8 + T_:                                                                                      \
             if (gated) {                                                                                       \
-                RAISE_LDS_LIMIT((ff_batch_gu_kernel<true, S_, T_>), 160 * 1024)                                                     \
+                RAISE_LDS_LIMIT((ff_batch_gu_kernel<true, S_, T_>), 160 * 1024)                                \
                 hipLaunchKernelGGL((ff_batch_gu_kernel<true, S_, T_>), dim3(p.P), dim3(p.W * 64), lds1, st, p); \
             } else {                                                                                           \
-                RAISE_LDS_LIMIT((ff_batch_gu_kernel<false, S_, T_>), 160 * 1024)                                                    \
+                RAISE_LDS_LIMIT((ff_batch_gu_kernel<false, S_, T_>), 160 * 1024)                               \
                 hipLaunchKernelGGL((ff_batch_gu_kernel<false, S_, T_>), dim3(p.P), dim3(p.W * 64), lds1, st, p); \
             }                                                                                                  \
             break;
@@ -676,7 +676,7 @@ int launch_decode_batch_front(const DecodeJob &job, int32_t n_block, const int32
         const size_t lds2 = BD_RING + (size_t)max_range * 64 * T;
 #define BD_GO2(T_, EX_)                                                                                        \
         {                                                                                                      \
-            RAISE_LDS_LIMIT((ff_batch_down_kernel<T_, EX_>), 160 * 1024)                                                            \
+            RAISE_LDS_LIMIT((ff_batch_down_kernel<T_, EX_>), 160 * 1024)                                       \
             hipLaunchKernelGGL((ff_batch_down_kernel<T_, EX_>), g2, b2, lds2, st, p);                          \
         }
 #define BD_GO(T_) { if (p.exact) BD_GO2(T_, true) else BD_GO2(T_, false) }

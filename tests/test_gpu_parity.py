@@ -302,6 +302,38 @@ def test_indexed_and_multi_decode_match_compact_decode():
     assert np.array_equal(y_idx, y_multi)   # same rows, same order of operations
 
 
+@pytest.mark.parametrize("dtype,d,gated,bias", [
+    (synth.DT_BF16, 4096, True, True),      # eight waves a team: the LDS limit stays
+    (synth.DT_BF16, 4160, True, True),      # nine, the last one nearly empty
+    (synth.DT_BF16, 4160, False, False),
+    (synth.DT_BF16, 8192, True, False),     # sixteen
+    (synth.DT_F32, 2112, True, True),
+    (synth.DT_F32, 4096, False, True),
+])
+def test_multi_decode_of_wide_blocks(dtype, d, gated, bias):
+    """Per-row blocks wider than eight waves a team are launched with more than half of a CU's LDS."""
+    n, k, B = 96, 70, 3
+    c = synth.small_case(57, d, n, 2, dtype, T=B, with_bias=bias)
+    act = synth.ACT_SILU if gated else synth.ACT_RELU
+    bg, b1, b2 = (c["bg"] if gated else None, c["b1"], c["b2"]) if bias else (None, None, None)
+    L, t = dev_layer(c["Wg"] if gated else None, c["W1"], c["W2"], act, dtype, bg, b1, b2)
+    rng = np.random.default_rng(6)
+    Cs, keep, refs = [], [], []
+    for b in range(B):
+        idx = np.sort(rng.choice(n, k, replace=False)).astype(np.int32)
+        C, ct = empty_compact(L, k, t)
+        G.griffin_compact(L, torch.from_numpy(idx).cuda(), k, C)
+        Cs.append(C); keep.append(ct)
+        refs.append(oracle.ff_decode(c["xt"][b], c["Wg"][idx] if gated else None, c["W1"][idx], c["W2"][idx], act,
+                                     bg[idx] if bg is not None else None, b1[idx] if bias else None, b2))
+    x = to_dev(c["xt"], dtype)
+    y = torch.full_like(x, float("nan"))
+    G.griffin_ff_decode_multi(Cs, x, y, workspace=workspace(G.griffin_decode_workspace_bytes(d, k, B)))
+    sync()
+    for b in range(B):
+        assert max_rel(to_host(y)[b], refs[b]) <= TOL_OUT[dtype]
+
+
 # ------------------------------------------------------------------ top-k
 @pytest.mark.parametrize("n,k", [(1, 1), (7, 3), (64, 64), (688, 344), (1000, 1), (5000, 4999), (24576, 12288),
                                  (8200, 4100), (36864, 20000), (40000, 777)])   # 8 loads + tail; the largest cached row; uncached
