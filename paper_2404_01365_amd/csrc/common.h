@@ -104,6 +104,16 @@ __device__ __forceinline__ float wave_sum(float v)
     return (a + b) + (c + d);
 }
 
+// Sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48; all four end with it (lane swaps, no LDS).
+__device__ __forceinline__ float lane_groups_sum(float v)
+{
+    typedef __attribute__((ext_vector_type(2))) uint32_t pair_t;
+    pair_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r.x) + __uint_as_float(r.y);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+
 // ------------------------------------------------------------------ host side
 struct SeqTable {            // passed to kernels by value
     int32_t n;
