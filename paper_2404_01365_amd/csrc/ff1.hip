@@ -14,32 +14,16 @@
 // variant takes the shapes it cannot (d not a multiple of 64).
 //
 // fp32 blocks: f32.hip.
-#include "common.h"
+#include "ff1_kernel.h"
 
 #include <atomic>
 
 namespace griffin {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // one 16-byte chunk (8 bf16)
+template <> void launch_ff1_tiles<GRIFFIN_ACT_SILU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
+template <> void launch_ff1_tiles<GRIFFIN_ACT_GELU_TANH>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
+template <> void launch_ff1_tiles<GRIFFIN_ACT_RELU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
 
-constexpr int G_BN = 128, G_BK = 64;
-constexpr int G_THREADS = 256;
-// s_waitcnt immediate that waits for vmcnt <= n only (expcnt / lgkmcnt fields left at "no wait")
-constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
-
-struct Ff1Params {
-    const void *X, *Wg, *W1, *bg, *b1;
-    float *Z, *rowpart;
-    uint16_t *Zb;                    // optional bf16 copy of Z [M][ldzb] for the prompt-output product, or NULL
-    int64_t ldx, ldw, ldz, ldzb;
-    int32_t M, F, d, nt, mt;
-    int32_t splits, kt_per_split;    // ranges of the contraction (1 for the activations) and 64-wide k-tiles per range
-    int32_t z_stream;                // Z leaves with the non-temporal hint (see launch_ff1)
-};
-
-// Epilogue shared by the MFMA kernels: sigma, gating, store of Z, row sums of z^2.
 // Lane holds column (neuron) l31 of each 32x32 tile and rows (i>>2)*8 + lh*4 + (i&3), i = 0..15.
 template <int ACT, bool GATED, int MI>
 __device__ __forceinline__ void ff1_mfma_epilogue(const Ff1Params &p, f32x16 (&accU)[MI][2], f32x16 (&accG)[MI][2],
@@ -89,554 +73,6 @@ __device__ __forceinline__ void ff1_mfma_epilogue(const Ff1Params &p, f32x16 (&a
     for (int r = tid; r < BM; r += G_THREADS)
         if (m0 + r < p.M)
             p.rowpart[(int64_t)(m0 + r) * p.nt + tile_n] = rs[0][r] + rs[1][r];
-}
-
-// ------------------------------------------------------------------------------------ bf16 / MFMA, direct-to-LDS
-// Epilogue of the main kernel.  Its MFMAs take the weight fragment as the first operand, so the
-// accumulator tiles are transposed: a lane holds ONE token (column lane & 15 of the 16x16 tile) and four consecutive
-// neurons, (lane >> 4) * 4 + i.  Z is then written 16 bytes at a time and a token's sum of squares needs two lane swaps only.
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
-// PLAIN: the kernel serves as a plain C = A B^T with fp32 output (one range of a split contraction):
-// no activation, no biases, no row sums; Z points at that range's [M][F] slab.
-// One accumulator value out of its AGPR, at the point of use.  Left to itself the compiler copies all
-// 256 accumulator registers into VGPRs at the end of the k loop and spills a hundred of them around
-// the epilogue; the asm operand keeps each value in the accumulation file until it is wanted.
-__device__ __forceinline__ float ff1_acc_read(float a)
-{
-    float v;
-    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
-    return v;
-}
-
-// EXTRA: 2 also knows biases and the bf16 copy of Z, 1 the copy alone, 0 neither; the lean one (most models: no FF
-// biases, selection alone) does not carry those branches and registers through the epilogue.
-//
-// A wave's tile leaves in steps of sixteen tokens x 16 NI neurons through two private LDS patches that take turns (16 rows of
-// 256 B, 16-byte chunk c of row r at c ^ r: writes and reads both spread evenly over the banks): sigma and the gating product of
-// one step run while the other patch is on its way back, and a step leaves as 16-byte stores that cover whole 64 NI-byte row
-// pieces (stores straight from the accumulator layout would touch 16 different rows with 64 bytes each).  Every
-// LDS access here is inline asm: the next tile's first LDS-DMA loads are in flight, and an access the compiler knows about
-// would wait for them (and for the Z stores).
-// -> true if every wave of a tile inside the matrix has issued the usual number of stores (EPI_STORES of the kernel)
-template <int ACT, bool GATED, int TI, int NI, bool PLAIN, bool EQ2W, int EXTRA, bool DUAL>
-__device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x4_t (&accU)[TI][NI], f32x4_t (&accG)[TI][NI],
-                                                    uint32_t patch_lds, int m0, int n0, int tile_n)
-{
-    constexpr int BM = 32 * TI, BN = 32 * NI, WN = 16 * NI;   // tile; columns of a wave
-    // one B matrix (the plain product, or an Eq. 2 block) over a tile twice as wide: accG = columns n0 + BN ..
-    constexpr bool WIDE = (PLAIN && GATED) || EQ2W;         // two column halves to store
-    constexpr bool GLU = GATED && !PLAIN && !EQ2W;          // accG is the gate (Eq. 3)
-    constexpr int HV = WIDE ? 2 : 1;
-    int tid = threadIdx.x;
-    // what follows is worked out here, tile by tile: kept over the k loop it would cost the registers that are not there
-    asm volatile("" : "+v"(tid));
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1, l15 = lane & 15, lq = lane >> 4;
-    // slabs of raw products (PLAIN) are whole rows of ldz columns, a multiple of 4: the columns past F hold repeats of
-    // the last one and are never read
-    const int FS = PLAIN ? (int)p.ldz : p.F;
-    const bool vec = ((FS | (int32_t)p.ldz) & 3) == 0 && ((uintptr_t)p.Z & 15) == 0;
-    const bool hb = EXTRA == 2 && !PLAIN && (p.b1 != nullptr || (GLU && p.bg != nullptr));
-    const uint16_t *b1p = (const uint16_t *)p.b1, *bgp = (const uint16_t *)p.bg;
-    const bool bias8 = (((uintptr_t)p.b1 | (uintptr_t)p.bg) & 7) == 0;       // four biases per 8-byte load
-    const bool usual = vec && (!hb || bias8) && p.ldz <= (1 << 20);         // (32-bit byte offsets inside a tile)
-    const uint32_t patch = patch_lds + (uint32_t)(wave * 2 * 4096);
-    float sq[TI];                          // sums of squares of the lane's tokens 16 ti + l15 over its neurons
-#pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
-        sq[ti] = 0.0f;
-    if (usual) {
-        const uint32_t wr = patch + (uint32_t)(l15 * 256);
-        // a step's 16 rows of 4 NI chunks: the lane writes NI of them, and takes numbers lane + 64 j on their way out: row rrow (of
-        // the step; none if the column is past the end), byte offset vo from the step's first element
-        int rrow[HV][NI];
-        uint32_t rd[NI], wc[NI], vo[NI], vob[NI];
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const int row = (lane + 64 * j) / (4 * NI), col = (lane + 64 * j) % (4 * NI) * 4;
-#pragma unroll
-            for (int h = 0; h < HV; ++h)
-                rrow[h][j] = n0 + (DUAL ? 0 : h * BN) + wn * WN + col < FS ? row : 1 << 30;
-            rd[j] = patch + (uint32_t)(row * 256 + ((col >> 2) ^ row) * 16);
-            wc[j] = wr + (uint32_t)(((4 * j + lq) ^ l15) * 16);
-            vo[j] = (uint32_t)(row * (int)p.ldz + col) * 4;
-            vob[j] = (uint32_t)(row * (int)p.ldzb + col) * 2;
-        }
-        // biases of this lane's 4 NI columns (four consecutive ones per register pair), fetched before any store
-        // of Z leaves: a load behind the stores would wait for them all
-        uint2 b1w[NI], bgw[NI];
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni) {
-            const int c = min(n0 + wn * WN + ni * 16 + lq * 4, p.F - 4);
-            b1w[ni] = (hb && b1p) ? *(const uint2 *)(b1p + c) : make_uint2(0u, 0u);
-            if (EQ2W)       // the second half's b1, 128 columns further on
-                bgw[ni] = (hb && b1p) ? *(const uint2 *)(b1p + min(c + BN, p.F - 4)) : make_uint2(0u, 0u);
-            else
-                bgw[ni] = (hb && GLU && bgp) ? *(const uint2 *)(bgp + c) : make_uint2(0u, 0u);
-        }
-        f32x4_t pv[NI];
-// step s_: token block s_ / HV, column half s_ % HV (the second half: the second set of accumulators, 128 columns further on)
-#define FF1_EPI_COMPUTE(s_)                                                                                       \
-        {                                                                                                         \
-            const int ti_ = (s_) / HV, half_ = (s_) % HV;                                                         \
-            const int nh_ = n0 + (DUAL ? 0 : half_ * BN);                                                       \
-            _Pragma("unroll") for (int ni = 0; ni < NI; ++ni)                                                      \
-            {                                                                                                     \
-                f32x4_t v;                                                                                        \
-                _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                     \
-                {                                                                                                 \
-                    float u = ff1_acc_read(half_ == 0 ? accU[ti_][ni][e] : accG[ti_][ni][e]);                     \
-                    float gt = GLU ? ff1_acc_read(accG[ti_][ni][e]) : 0.0f;                                       \
-                    if (hb) {                                                                                     \
-                        const uint2 &bu = (EQ2W && half_ == 1) ? bgw[ni] : b1w[ni];                               \
-                        const uint32_t wu = e < 2 ? bu.x : bu.y, wg2 = e < 2 ? bgw[ni].x : bgw[ni].y;             \
-                        u += __uint_as_float((e & 1) ? (wu & 0xFFFF0000u) : (wu << 16));                          \
-                        if (GLU)                                                                                  \
-                            gt += __uint_as_float((e & 1) ? (wg2 & 0xFFFF0000u) : (wg2 << 16));                   \
-                    }                                                                                             \
-                    v[e] = PLAIN ? u : (GLU ? act_apply_t<ACT>(gt) * u : act_apply_t<ACT>(u));                    \
-                }                                                                                                 \
-                if (nh_ + wn * WN + ni * 16 + lq * 4 >= FS)                                                       \
-                    v = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};                                                        \
-                if (!PLAIN) {                                                                                     \
-                    sq[ti_] = fmaf(v[0], v[0], sq[ti_]); sq[ti_] = fmaf(v[1], v[1], sq[ti_]);                     \
-                    sq[ti_] = fmaf(v[2], v[2], sq[ti_]); sq[ti_] = fmaf(v[3], v[3], sq[ti_]);                     \
-                }                                                                                                 \
-                asm volatile("ds_write_b128 %0, %1 offset:%2" :: "v"(wc[ni]), "v"(v), "n"(((s_) & 1) * 4096) : "memory"); \
-                /* keep the groups apart: left alone, the scheduler pulls the accumulator reads of all groups */  \
-                /* to the front and spills a hundred registers */                                                 \
-                __builtin_amdgcn_sched_barrier(0);                                                                \
-            }                                                                                                     \
-        }
-#if defined(__HIP_DEVICE_COMPILE__)      /* the host pass has no buffer builtins */
-        // the wave's rows and columns of Z (of either half) and of its bf16 copy as raw buffers
-        const int64_t zrow0 = m0 + wm * (16 * TI);
-        const int zcol0 = n0 + wn * WN;
-        float *const z0 = p.Z + zrow0 * p.ldz + zcol0, *const z1 = z0 + (DUAL ? (int64_t)p.M * p.ldz : (int64_t)BN);
-        const __amdgpu_buffer_rsrc_t zr0 = __builtin_amdgcn_make_buffer_rsrc((void *)z0, 0, 0x7FFFFFFE, 0x00020000),
-                                     zr1 = __builtin_amdgcn_make_buffer_rsrc((void *)z1, 0, 0x7FFFFFFE, 0x00020000),
-                                     zrb = __builtin_amdgcn_make_buffer_rsrc((void *)(p.Zb + zrow0 * p.ldzb + zcol0), 0, 0x7FFFFFFE, 0x00020000);
-// Z of chunk j_ of step s_, and its bf16 copy; cache-policy bit 1 = non-temporal (the two flavours must stay two instructions)
-#define FF1_Z_STORE(s_, j_)                                                                                       \
-        {                                                                                                         \
-            const u32x4 v_ = __builtin_bit_cast(u32x4, pv[j_]);                                                   \
-            const int so_ = (s_) / HV * 16 * (int)p.ldz * 4;                                                      \
-            if (p.z_stream)                                                                                       \
-                __builtin_amdgcn_raw_buffer_store_b128(v_, (s_) % HV ? zr1 : zr0, vo[j_], so_, 2);                \
-            else                                                                                                  \
-                __builtin_amdgcn_raw_buffer_store_b128(v_, (s_) % HV ? zr1 : zr0, vo[j_], so_, 0);                \
-            if (EXTRA && !PLAIN && p.Zb) {                                                                        \
-                typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_;                                      \
-                const u32x2_ h_ = {f32x2_to_bf16x2(pv[j_][0], pv[j_][1]), f32x2_to_bf16x2(pv[j_][2], pv[j_][3])}; \
-                __builtin_amdgcn_raw_buffer_store_b64(h_, zrb, vob[j_], ((s_) / HV * 16 * (int)p.ldzb + (s_) % HV * BN) * 2, 0); \
-            }                                                                                                     \
-        }
-#else
-#define FF1_Z_STORE(s_, j_) {}
-#endif
-        FF1_EPI_COMPUTE(0)
-#pragma unroll
-        for (int s = 0; s < TI * HV; ++s) {
-            // the rows of step s come back while the next step is computed (LDS accesses of a wave are performed in order)
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-                asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(pv[j]) : "v"(rd[j]), "n"((s & 1) * 4096) : "memory");
-            if (s + 1 < TI * HV) {
-                FF1_EPI_COMPUTE(s + 1)
-                asm volatile("s_waitcnt lgkmcnt(%0)" :: "n"(NI) : "memory");
-            } else {
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            }
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-                asm volatile("" : "+v"(pv[j]) :: "memory");
-            const int left = p.M - (m0 + wm * (16 * TI) + (s / HV) * 16);       // rows of the matrix in this step
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                if (rrow[s % HV][j] < left)
-                    FF1_Z_STORE(s, j)
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-#undef FF1_Z_STORE
-#undef FF1_EPI_COMPUTE
-    } else {
-        // rows of Z that 16-byte stores cannot take, or biases that 8-byte loads cannot: element by element
-#pragma unroll
-        for (int ti = 0; ti < TI; ++ti) {
-            const int tok = m0 + wm * (16 * TI) + ti * 16 + l15;
-            const bool rowok = tok < p.M;
-            float *zrow = p.Z + (int64_t)min(tok, p.M - 1) * p.ldz;
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int col = n0 + wn * WN + ni * 16 + lq * 4 + i;
-                    const int cj = min(col, p.F - 1);
-                    float u = ff1_acc_read(accU[ti][ni][i]);
-                    float gt = GATED ? ff1_acc_read(accG[ti][ni][i]) : 0.0f;
-                    if (!PLAIN && b1p) u += bf16_bits_to_f32(b1p[cj]);
-                    if (GLU && bgp) gt += bf16_bits_to_f32(bgp[cj]);
-                    if (EQ2W && b1p) gt += bf16_bits_to_f32(b1p[min(col + BN, p.F - 1)]);
-                    const float z = PLAIN ? u : (GLU ? act_apply_t<ACT>(gt) * u : act_apply_t<ACT>(u));
-                    if (col < p.F) {
-                        sq[ti] = fmaf(z, z, sq[ti]);
-                        if (rowok)
-                            zrow[col] = z;
-                    }
-                    if (WIDE && col + BN < p.F) {
-                        const float z2 = EQ2W ? act_apply_t<ACT>(gt) : gt;
-                        sq[ti] = fmaf(z2, z2, sq[ti]);
-                        if (rowok)
-                            zrow[col + BN] = z2;
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        }
-    }
-    if (PLAIN)
-        return usual;
-    // row sums: the four lanes of a token by lane swaps, the two waves of a token through the patches
-#pragma unroll
-    for (int ti = 0; ti < TI; ++ti) {
-        sq[ti] = lane_groups_sum(sq[ti]);
-        asm volatile("ds_write_b32 %0, %1 offset:%2" :: "v"(patch + (uint32_t)(l15 * 4)), "v"(sq[ti]), "n"(ti * 64) : "memory");
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    static_assert(BM <= G_THREADS, "a thread per token");
-    if (tid < BM) {
-        float q0, q1;
-        const uint32_t ra = patch_lds + (uint32_t)((tid / (16 * TI)) * 4 * 4096 + (tid % (16 * TI)) * 4);
-        asm volatile("ds_read_b32 %0, %1" : "=v"(q0) : "v"(ra));
-        asm volatile("ds_read_b32 %0, %1 offset:8192" : "=v"(q1) : "v"(ra));
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(q0), "+v"(q1));
-        if (m0 + tid < p.M)
-            p.rowpart[(int64_t)(m0 + tid) * p.nt + tile_n] = q0 + q1;
-    }
-    return usual;
-}
-
-// Main path (d a multiple of 64).  Operand tiles go from global memory straight into LDS
-// (buffer_load_dwordx4 ... lds: lane l of a wave instruction fills 16-byte slot l of a 1 KB
-// region; no VGPR staging, no ds_write).  A k-tile is BK = 64 elements = one whole 128-byte
-// cache line per row: with half lines the other half is evicted from the 32 KB vector L1
-// before the next k-tile asks for it, every line crosses the L2->L1 path twice and that path
-// (64 B/clk) becomes the bound.  An instruction covers 8 rows x 128 B.  A row
-// of a stage is 8 slots (128 B, half of the 256 bytes the LDS banks span), logical chunk c of
-// row r in slot c ^ ((r >> 1) & 7): sixteen consecutive rows then land on sixteen different
-// 16-byte bank groups, which keeps the ds_read_b128 operand fetches conflict-free (with
-// c ^ (r & 7) rows two apart collide and the bank-conflict counter showed the LDS stalled for
-// half of its active cycles); the swizzle is applied by choosing which global chunk each lane
-// loads.  Per k-tile: two k-steps of 32 on fragments that were read one k-step ahead.  Between them, a counted
-// vmcnt + one bare s_barrier say that the next k-tile has landed for every wave and that every wave has read its last
-// fragment of this one; the second k-step then sends X of the k-tile two ahead into the stage just read, and the first k-step of
-// the next k-tile the weights of the one three ahead of this (three stages of weights and two of X fill the LDS: 160 KB).
-// Loads past the last k-tile re-read the last one into a dead stage, which keeps the loop body branch-free.
-//
-// What bounds it and what that decided (256 x 128 x 2 tiles, 2048 tokens of 3072 x 24576, one call after another):
-//   * power.  A loop of nothing but these MFMAs on random data runs at 1.77 PFLOP/s with v_mfma_f32_32x32x16 and at 2.05
-//     with v_mfma_f32_16x16x32 (2.4 with zeros, either way): hence the smaller instruction, neighbours sharing an operand.
-//   * the loads' issue.  One LDS-DMA instruction per 64 clocks of MFMA and no more: two of them 416 -> 446 us
-//     (without the epilogue); spread out like that they need a stage more than two to land in.
-//   * 32x32x16, two stages, loads under half of the time: 502 us; this: 473 (zeros 455 -> 397).  1024 tokens of 5120 x 13824
-//     254 -> 232 us, whole selections 564 -> 522, 3999 -> 3880 (4096 x 14336, 20600 tokens).
-//   * the epilogue is 55 us of 473: 25 of sigma and lane work, 28 of stores that all workgroups send at about the same time.
-//     (Starting the workgroups of an XCD up to 7 us apart, or letting the stores drain under one k-tile more: no faster.)
-typedef __attribute__((address_space(3))) void lds_void_t;
-// slot swizzle of row r (rows of every stage section start at a multiple of 16)
-#define FF1_SWZ(r) (((r) >> 1) & 7)
-
-template <int ACT, bool GATED, int TI, int NI, bool PLAIN, bool EQ2W = false, int EXTRA = 2, bool DUAL = false>
-__global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
-{
-#if defined(__HIP_DEVICE_COMPILE__)   // the host pass has no buffer-descriptor builtins; it only needs the launch stub
-    constexpr int BM = 32 * TI, BN = 32 * NI, BK = 64;
-    constexpr int XQ = BM / 32, WQ = BN / 32;                // 8-row regions per wave per k-tile
-    constexpr int WL = (GATED ? 2 : 1) * WQ;                   // LDS-DMA instructions per wave and k-tile: XQ of X, WL of the weights
-    constexpr int X_ST = BM * 8, W_ST = (GATED ? 2 : 1) * BN * 8;    // 16-byte slots per stage
-    // Stages: two workgroups share a CU with 64-token tiles; 256-token tiles of two weight sections fill the LDS with two stages of X
-    // and three of the weights (the ones that come from HBM); everything else has three of both.
-    constexpr int NXS = TI == 2 || TI > 4 ? 2 : 3, NWS = TI == 2 ? 2 : 3;
-    // The plain product has one B matrix: its tile is 256 columns wide and the "gate" half of the
-    // machinery (LDS section, fragments, accumulators) takes columns n0 + 128 .. n0 + 255, which
-    // halves the X traffic per flop exactly as the dual product does.
-    // DUAL: the plain kernel over both matrices of a gated block (raw products of one range of d, two slabs per range);
-    // the gate's section holds Wg again and the tile is 128 columns of both.
-    constexpr bool WIDE = (PLAIN && GATED && !DUAL) || EQ2W;        // EQ2W: an Eq. 2 block (no gate) through the same machinery
-    static_assert(!DUAL || (PLAIN && GATED), "DUAL is a form of the plain product");
-    static_assert(!EQ2W || (GATED && !PLAIN), "the Eq. 2 wide tile uses both LDS sections and both accumulator sets");
-    constexpr int TILE_N = WIDE ? 2 * BN : BN;
-    // The epilogue's patches (32 KB) live in the last weight stage, which nothing is loaded into before the k loop of the next
-    // tile; blocks with one weight section have room for patches of their own.
-    constexpr int W_BASE = NXS * X_ST, PATCH = W_BASE + (GATED ? (NWS - 1) * W_ST : NWS * W_ST), PATCH_SLOTS = 4 * 2 * 256;
-    constexpr int LDS_SLOTS = PATCH + PATCH_SLOTS > W_BASE + NWS * W_ST ? PATCH + PATCH_SLOTS : W_BASE + NWS * W_ST;
-    static_assert(LDS_SLOTS * 16 <= 160 * 1024, "fits the LDS of a CU");
-    __shared__ u32x4 lds[LDS_SLOTS];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-
-    // XCD-aware tile order (workgroup ids congruent mod 8 share an XCD: each XCD walks its own
-    // contiguous range of tiles, its workgroups side by side); with a split contraction the ranges
-    // of one tile are `ntile` ids apart.  The grid holds one workgroup per CU and every workgroup
-    // walks through its tiles itself, so that the first loads of the next tile can go out before
-    // the epilogue of this one (a workgroup per tile leaves the CU idle while the next one starts).
-    const int ntile = p.mt * p.nt, nblk = ntile * p.splits;
-    // Order of the tiles: panels of PANEL_M token tiles; inside a panel the token tile runs fastest, then the
-    // neuron tile.  The 32 workgroups of an XCD then work on 8 token tiles x 4 neuron tiles at any time (12
-    // operand slices stream through its L2 per k-tile) instead of 32 token tiles x 1 neuron tile (33 slices)
-    // when the prompt batch is long; a last panel of fewer token tiles is walked the same way.  With at most
-    // PANEL_M token tiles this is the plain order "token tile fastest".
-    constexpr int PANEL_M = 8;
-    const int full_m = (p.mt / PANEL_M) * PANEL_M, full_tiles = full_m * p.nt;
-    const int per_xcd = (nblk + 7) / 8;
-    const int wg_per_xcd = gridDim.x >> 3;
-    int slot = blockIdx.x >> 3;
-    if (slot >= per_xcd || (int)(blockIdx.x & 7) * per_xcd + slot >= nblk)
-        return;
-
-    // per-tile addressing: the loader maps lane -> (row of the 8-row region, slot in the row) ->
-    // global chunk (un-swizzled); byte offsets are relative to the tile's first row and fit 32 bits
-    // (checked at launch).  Raw buffer descriptors (32-bit data format word of gfx9-family raw
-    // buffers); every access is in range by construction, the record count is not relied upon.
-    constexpr int RSRC_FLAGS = 0x00020000, RSRC_RECORDS = 0x7FFFFFFE;
-    int m0, n0, tile_n, kt0, KT;
-    float *Zt;
-    uint32_t xvo[XQ], wvo[WQ], wgvo[WQ];
-    __amdgpu_buffer_rsrc_t rX, rW1, rWg;
-#define FF1_TILE_ADDR(logical_)                                                                          \
-    {                                                                                                    \
-        int al_ = lane;                                                                                  \
-        asm volatile("" : "+v"(al_));          /* nothing of this is to be kept over the k loop */       \
-        const int lrow = al_ >> 3;                                                                       \
-        const int split_ = (logical_) / ntile, tile_ = (logical_) % ntile;                               \
-        {                                                                                                \
-            const int in_full_ = tile_ < full_tiles ? 1 : 0;                                             \
-            const int w_ = in_full_ ? tile_ % (PANEL_M * p.nt) : tile_ - full_tiles;                     \
-            const int pm_ = in_full_ ? PANEL_M : p.mt - full_m;                                          \
-            tile_n = w_ / pm_;                                                                           \
-            m0 = ((in_full_ ? (tile_ / (PANEL_M * p.nt)) * PANEL_M : full_m) + w_ % pm_) * BM;           \
-        }                                                                                                \
-        n0 = tile_n * TILE_N;                                                                            \
-        Zt = PLAIN ? p.Z + (int64_t)split_ * (DUAL ? 2 : 1) * p.M * p.ldz : p.Z;                         \
-        _Pragma("unroll") for (int q = 0; q < XQ; ++q)                                                   \
-            xvo[q] = __umul24(min((wave * XQ + q) * 8 + lrow, p.M - 1 - m0), (uint32_t)(p.ldx * 2)) +    \
-                     (uint32_t)(((al_ & 7) ^ FF1_SWZ((wave * XQ + q) * 8 + lrow)) * 16);                 \
-        _Pragma("unroll") for (int q = 0; q < WQ; ++q)                                                   \
-        {                                                                                                \
-            wvo[q] = __umul24(min((wave * WQ + q) * 8 + lrow, p.F - 1 - n0), (uint32_t)(p.ldw * 2)) +    \
-                     (uint32_t)(((al_ & 7) ^ FF1_SWZ((wave * WQ + q) * 8 + lrow)) * 16);                 \
-            wgvo[q] = WIDE ? __umul24(min(BN + (wave * WQ + q) * 8 + lrow, p.F - 1 - n0), (uint32_t)(p.ldw * 2)) +\
-                             (uint32_t)(((al_ & 7) ^ FF1_SWZ((wave * WQ + q) * 8 + lrow)) * 16)          \
-                           : wvo[q];                                                                     \
-        }                                                                                                \
-        rX = __builtin_amdgcn_make_buffer_rsrc((void *)((const uint16_t *)p.X + (int64_t)m0 * p.ldx), 0, \
-                                               RSRC_RECORDS, RSRC_FLAGS);                                \
-        rW1 = __builtin_amdgcn_make_buffer_rsrc((void *)((const uint16_t *)p.W1 + (int64_t)n0 * p.ldw), 0,\
-                                                RSRC_RECORDS, RSRC_FLAGS);                               \
-        rWg = __builtin_amdgcn_make_buffer_rsrc((void *)((const uint16_t *)((GATED && (!PLAIN || DUAL) && !EQ2W) ? p.Wg : p.W1) + (int64_t)n0 * p.ldw), 0,\
-                                                RSRC_RECORDS, RSRC_FLAGS);                               \
-        kt0 = split_ * p.kt_per_split;                                                                   \
-        KT = min(p.kt_per_split, p.d / BK - kt0);      /* k-tiles of this range (>= 1 by construction) */\
-    }
-    FF1_TILE_ADDR((int)(blockIdx.x & 7) * per_xcd + slot)
-
-// LDS-DMA instruction number q of the X part (0 .. XQ-1) or of the weights (0 .. WL-1: W1, then Wg) of k-tile kt_, into the stage
-// at slot st_.  The weight tiles carry the non-temporal hint (each is used by one wave of tiles and then never
-// again; measured 3 % faster), the X tiles, which every column of tiles re-reads, do not.
-#define FF1_SO(kt_) ((kt0 + min((kt_), KT - 1)) * (BK * 2))
-#define FF1_LOAD_X(kt_, st_, q)                                                                          \
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rX, (lds_void_t *)(lds + (st_) + (wave * XQ + (q)) * 64), 16, xvo[q], FF1_SO(kt_), 0, 0);
-#define FF1_LOAD_W(kt_, st_, q)                                                                          \
-    {                                                                                                    \
-        if ((q) < WQ)                                                                                    \
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rW1, (lds_void_t *)(lds + W_BASE + (st_) + (wave * WQ + (q) % WQ) * 64), 16, \
-                                                     wvo[(q) % WQ], FF1_SO(kt_), 0, 2);                  \
-        else                                                                                             \
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rWg, (lds_void_t *)(lds + W_BASE + (st_) + BN * 8 + (wave * WQ + (q) % WQ) * 64), 16, \
-                                                     wgvo[(q) % WQ], FF1_SO(kt_), 0, 2);                 \
-    }
-// Operand fragments are fetched with ds_read_b128 written as inline asm: the compiler makes every
-// LDS load it knows about wait for ALL LDS-DMA in flight (it cannot tell the stages apart), which
-// would serialise the pipeline.  The asm reads are invisible to that logic; their completion is
-// awaited explicitly (FF1_WAIT_FRAGS names the registers, so the MFMAs that use them stay behind
-// it), and sched_barrier keeps the hand-made interleaving of reads, DMA issues and MFMAs.
-#define FF1_DS_READ(dst, addr, off) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
-#define FF1_BARRIER()                                                                                    \
-    {                                                                                                    \
-        asm volatile("" ::: "memory");                                                                   \
-        __builtin_amdgcn_s_barrier();                                                                    \
-        asm volatile("" ::: "memory");                                                                   \
-    }
-#define FF1_PIN() __builtin_amdgcn_sched_barrier(0)
-
-    f32x4_t accU[TI][NI], accG[TI][NI];            // a wave's tile: TI blocks of sixteen tokens x NI of sixteen neurons
-
-    const int l15 = lane & 15, lq = lane >> 4, sw = FF1_SWZ(l15);
-    // LDS byte addresses of this lane's fragment rows in stage 0, per k-step of 32
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t *)lds;
-    uint32_t abase[2], bbase[2];
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-        const int ch = (4 * kk + lq) ^ sw;
-        abase[kk] = lds0 + (uint32_t)(((wm * (16 * TI) + l15) * 8 + ch) * 16);
-        bbase[kk] = lds0 + (uint32_t)((W_BASE + (wn * (16 * NI) + l15) * 8 + ch) * 16);
-    }
-    u32x4 fa[2][TI], f1[2][NI], fg[2][NI];
-    constexpr int NREADS = TI + (GATED ? 2 : 1) * NI;
-    constexpr int NSLOTS = TI * NI < 16 ? TI * NI : TI * NI % 16 == 0 ? 16 : 12;          // interleaving slots per k-step ...
-    constexpr int MPS = TI * NI / NSLOTS;                      // ... with so many pairs of MFMAs (up, gate) or singles each
-    static_assert(NREADS <= NSLOTS * 2 && XQ <= NSLOTS && WL <= NSLOTS && TI * NI == NSLOTS * MPS, "a k-step has a slot for everything");
-
-// read number r (0 .. NREADS-1) of fragment set F_ (16 rows = 2048 B apart): the weights first
-#define FF1_READ_ONE(F_, r, sa_, sb_)                                                          \
-    {                                                                                          \
-        if ((r) < NI) FF1_DS_READ(f1[F_][(r) % NI], sb_, ((r) % NI) * 2048);                   \
-        else if (GATED && (r) < 2 * NI) FF1_DS_READ(fg[F_][(r) % NI], sb_, BN * 128 + ((r) % NI) * 2048); \
-        else FF1_DS_READ(fa[F_][((r) - (GATED ? 2 : 1) * NI) % TI], sa_, (((r) - (GATED ? 2 : 1) * NI) % TI) * 2048); \
-    }
-// MFMA(s) number m (0 .. TI NI - 1) of fragment set F_: tile (ti, ni) of the up product and, gated, of the gate product; weights
-// first, so the result tile is neurons x tokens.  Inline asm keeps every accumulator where it is: with the builtin the compiler, which
-// has no accumulation register left to turn round in, moves some eighty of them to and fro in every k-tile.  It also sees no
-// MFMA hazards then: the accumulators are written well before the first and read well after the last (FF1_MFMA_GAP), and operands
-// come from the LDS behind a wait.
-#define FF1_MFMA_ONE(F_, m)                                                                    \
-    {                                                                                          \
-        const int ti_ = (m) / NI, ni_ = (ti_ & 1) ? NI - 1 - (m) % NI : (m) % NI;              \
-        if (GATED && (ti_ & 1))                                                                \
-            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(accG[ti_][ni_]) : "v"(fg[F_][ni_]), "v"(fa[F_][ti_])); \
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(accU[ti_][ni_]) : "v"(f1[F_][ni_]), "v"(fa[F_][ti_])); \
-        if (GATED && !(ti_ & 1))                                                               \
-            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(accG[ti_][ni_]) : "v"(fg[F_][ni_]), "v"(fa[F_][ti_])); \
-    }
-#define FF1_MFMA_GAP() asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-#define FF1_WAIT_FRAGS(F_)                                                                     \
-    {                                                                                          \
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                                     \
-        _Pragma("unroll") for (int n_ = 0; n_ < NI; ++n_) asm volatile("" : "+v"(f1[F_][n_])); \
-        if (GATED) { _Pragma("unroll") for (int n_ = 0; n_ < NI; ++n_) asm volatile("" : "+v"(fg[F_][n_])); } \
-        _Pragma("unroll") for (int t_ = 0; t_ < TI; ++t_) asm volatile("" : "+v"(fa[F_][t_])); \
-    }
-// one k-step: MFMAs on fragment set FM_, the reads of set FR_ (k-step KR_ of the stages at slots xs_, ws_) two a slot, and the
-// loads one a slot: LX_ a k-tile of X, else one of the weights, LT_ into the stage at slot ls_
-#define FF1_KSTEP(FM_, FR_, xs_, ws_, KR_, LX_, LT_, ls_)                                      \
-    {                                                                                          \
-        const uint32_t sa = abase[KR_] + (uint32_t)((xs_) * 16), sb = bbase[KR_] + (uint32_t)((ws_) * 16); \
-        FF1_PIN();                                                                             \
-        _Pragma("unroll") for (int m = 0; m < NSLOTS; ++m)                                     \
-        {                                                                                      \
-            _Pragma("unroll") for (int z_ = 0; z_ < 2; ++z_)                                   \
-                if (m * 2 + z_ < NREADS)                                                       \
-                    FF1_READ_ONE(FR_, m * 2 + z_, sa, sb)                                      \
-            if ((LX_) && m < XQ)                                                               \
-                FF1_LOAD_X(LT_, ls_, m < XQ ? m : 0)                                           \
-            if (!(LX_) && m < WL)                                                              \
-                FF1_LOAD_W(LT_, ls_, m)                                                        \
-            _Pragma("unroll") for (int z_ = 0; z_ < MPS; ++z_)                                 \
-                FF1_MFMA_ONE(FM_, m * MPS + z_)                                                \
-            FF1_PIN();                                                                         \
-        }                                                                                      \
-    }
-
-    // What a tile loads before its k loop: X of the first NXS k-tiles, the weights of the first NWS - 1; k-tile 0 first.
-    constexpr int AFTER0 = (NXS - 1) * XQ + (NWS - 2) * WL;    // loads behind those of k-tile 0
-    // ... and what of it the wait in the middle of a k-tile may leave on its way: the last X (three stages) and weights (three)
-    constexpr int MID = (NXS == 3 ? XQ : 0) + (NWS == 3 ? WL : 0);
-    static_assert(NXS <= NWS, "the wait in the middle counts on it");
-    // Global store instructions that EVERY wave issues in the epilogue's usual path on a tile that lies
-    // wholly inside the matrix (NI per 16-token block and column half, plus the row sums when all four waves write them).
-    // The wait for k-tile 0 of the next tile may leave that many operations outstanding, no more: a
-    // wave that issued fewer stores than the wait allows would sail through before its loads landed.
-    constexpr int Z_STORES = TI * NI * (WIDE || DUAL ? 2 : 1), EPI_STORES = Z_STORES + ((!PLAIN && BM == G_THREADS) ? 1 : 0);
-#define FF1_FIRST_LOADS()                                                                      \
-    {                                                                                          \
-        _Pragma("unroll") for (int q = 0; q < XQ; ++q) FF1_LOAD_X(0, 0, q)                     \
-        _Pragma("unroll") for (int q = 0; q < WL; ++q) FF1_LOAD_W(0, 0, q)                     \
-        if (NXS == 3) { _Pragma("unroll") for (int q = 0; q < XQ; ++q) FF1_LOAD_X(1, X_ST, q) } \
-        if (NWS == 3) { _Pragma("unroll") for (int q = 0; q < WL; ++q) FF1_LOAD_W(1, W_ST, q) } \
-        _Pragma("unroll") for (int q = 0; q < XQ; ++q) FF1_LOAD_X(NXS - 1, (NXS - 1) * X_ST, q) \
-    }
-    FF1_FIRST_LOADS()
-    bool stores_known = false;         // the tile before was whole and took the epilogue's usual path
-    for (;;) {
-        // k-tile 0 has landed when only the loads behind it and (from the second tile on) the
-        // epilogue's stores, all issued after it, are still outstanding
-        constexpr int W0 = AFTER0 + EPI_STORES, W1 = W0 + Z_STORES;
-        if (stores_known && EXTRA && !PLAIN && p.Zb)      // twice the Z stores (more than the counter holds: 63 is as good)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(W1 > 63 ? 63 : W1));
-        else if (stores_known)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(W0 > 63 ? 63 : W0));
-        else
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(AFTER0));
-        FF1_BARRIER()
-#pragma unroll
-        for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-                accU[ti][ni] = accG[ti][ni] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-        {
-            const uint32_t sa = abase[0], sb = bbase[0];
-#pragma unroll
-            for (int r = 0; r < NREADS; ++r)
-                FF1_READ_ONE(0, r, sa, sb)
-        }
-        FF1_MFMA_GAP()
-        int xs = 0, ws = 0, wp = (NWS - 1) * W_ST;             // stages (slots) of this k-tile, and the weights' of the one before
-        for (int kt = 0; kt < KT; ++kt) {
-            const int xn = xs == (NXS - 1) * X_ST ? 0 : xs + X_ST, wnx = ws == (NWS - 1) * W_ST ? 0 : ws + W_ST;
-            FF1_WAIT_FRAGS(0)
-            FF1_KSTEP(0, 1, xs, ws, 1, false, kt + NWS - 1, wp)
-            FF1_WAIT_FRAGS(1)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(MID));        // tile kt+1 has landed (this wave's part)
-            FF1_BARRIER()                                      // ... every wave's part; tile kt is read out
-            FF1_KSTEP(1, 0, xn, wnx, 0, true, kt + NXS, xs)
-            wp = ws;
-            ws = wnx;
-            xs = xn;
-        }
-        FF1_MFMA_GAP()
-        FF1_WAIT_FRAGS(0)                                 // the reads issued for the tile past the end
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));         // no LDS-DMA of this tile is left in flight
-        FF1_BARRIER()
-
-        // this tile's coordinates for the epilogue; then the next tile's first loads go out
-        Ff1Params pt = p;
-        pt.Z = Zt;
-        const int m0c = m0, n0c = n0, tile_nc = tile_n;
-        const bool whole = m0 + BM <= p.M && n0 + TILE_N <= p.F;
-        slot += wg_per_xcd;
-        const int logical_n = (int)(blockIdx.x & 7) * per_xcd + slot;
-        const bool more = slot < per_xcd && logical_n < nblk;
-        if (more) {
-            FF1_TILE_ADDR(logical_n)
-            FF1_FIRST_LOADS()
-        }
-        const bool usual = ff1_mfma_epilogue_t<ACT, GATED, TI, NI, PLAIN, EQ2W, EXTRA, DUAL>(pt, accU, accG, lds0 + (uint32_t)(PATCH * 16), m0c, n0c, tile_nc);
-        if (!more)
-            break;
-        FF1_BARRIER()              // every wave is done with its patches
-        stores_known = usual && whole;
-    }
-#undef FF1_SO
-#undef FF1_LOAD_X
-#undef FF1_LOAD_W
-#undef FF1_MFMA_GAP
-#undef FF1_TILE_ADDR
-#undef FF1_FIRST_LOADS
-#undef FF1_BARRIER
-#undef FF1_DS_READ
-#undef FF1_PIN
-#undef FF1_READ_ONE
-#undef FF1_MFMA_ONE
-#undef FF1_WAIT_FRAGS
-#undef FF1_KSTEP
-#endif
 }
 
 // ------------------------------------------------------------------------------------ bf16 / MFMA, register-staged
@@ -953,20 +389,12 @@ template <int ACT, int MI>
 static void launch_mfma(const Ff1Params &p, bool gated, bool wide, hipStream_t st)
 {
     const int nblk = p.mt * p.nt;
-    dim3 grid(ff1_grid(nblk)), block(G_THREADS);
-    dim3 grid_all(((nblk + 7) / 8) * 8);           // the register-staged kernel takes one tile per workgroup
     // the direct-to-LDS kernel wants whole 64-element k-tiles and 32-bit byte offsets inside a tile
-    const bool ktail = p.d % 64 != 0 || p.ldx > (1 << 21) || p.ldw > (1 << 21);
-    if (gated) {
-        if (ktail) hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, true, MI, true>), grid_all, block, 0, st, p);
-        else if (p.b1 || p.bg) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, 2 * MI, 4, false>), grid, block, 0, st, p);
-        else if (p.Zb) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, 2 * MI, 4, false, false, 1>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, 2 * MI, 4, false, false, 0>), grid, block, 0, st, p);
-    } else {
-        if (ktail) hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, false, MI, true>), grid_all, block, 0, st, p);
-        else if (wide) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, true, 2 * MI, 4, false, true>), grid, block, 0, st, p);   // 256-column tiles
-        else hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, false, 2 * MI, 4, false>), grid, block, 0, st, p);
-    }
+    if (!(p.d % 64 != 0 || p.ldx > (1 << 21) || p.ldw > (1 << 21)))
+        return launch_ff1_tiles<ACT>(p, 2 * MI, 4, gated, wide, ff1_grid(nblk), st);
+    const dim3 grid(((nblk + 7) / 8) * 8), block(G_THREADS);           // the register-staged kernel takes one tile per workgroup
+    if (gated) hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, true, MI, true>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, false, MI, true>), grid, block, 0, st, p);
 }
 
 template <int MI>
