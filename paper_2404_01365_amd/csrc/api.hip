@@ -136,7 +136,7 @@ size_t griffin_prefill_workspace_bytes(const griffin_layer *L, int64_t total_tok
 {
     if (check_layer(L) != GRIFFIN_OK || total_tokens < 0 || n_seqs < 1 || n_seqs > GRIFFIN_MAX_SEQS)
         return 0;
-    return plan_prefill(*L, total_tokens, n_seqs, have_z_out != 0).total + align256(ff1_slab_bytes(*L, total_tokens));
+    return plan_prefill(*L, total_tokens, n_seqs, have_z_out != 0).total + align256(ff1_tail_bytes(*L, total_tokens));
 }
 
 int griffin_prefill_select(const griffin_layer *L, const void *X, int64_t ldx,
@@ -172,9 +172,10 @@ int griffin_prefill_select(const griffin_layer *L, const void *X, int64_t ldx,
     float *s = (float *)(ws + pl.off_s);
 
     int32_t nt = 0;
-    // the slabs of a short prompt lie behind the rest; a workspace without room for them takes the product in one range
-    float *slabs = workspace_bytes >= pl.total + ff1_slab_bytes(*L, total) ? (float *)(ws + pl.total) : nullptr;
-    if ((rc = launch_ff1(*L, X, ldx, total, Z, zld, rowpart, &nt, st, nullptr, 0, slabs)) != GRIFFIN_OK)
+    // the slabs of a short prompt, or the row partials of narrow tiles, lie behind the rest; a workspace without room for them
+    // takes the product in one range of 128-neuron tiles
+    float *tail = workspace_bytes >= pl.total + ff1_tail_bytes(*L, total) ? (float *)(ws + pl.total) : nullptr;
+    if ((rc = launch_ff1(*L, X, ldx, total, Z, zld, &rowpart, &nt, st, nullptr, 0, tail)) != GRIFFIN_OK)
         return rc;
     if ((rc = launch_stat(Z, zld, rowpart, nt, total, L->n, seqs, s2part, s, s_out, st)) != GRIFFIN_OK)
         return rc;
@@ -296,7 +297,7 @@ size_t griffin_prompt_phase_workspace_bytes(const griffin_layer *L, int64_t tota
         return 0;
     const size_t first = plan_prefill(*L, total_tokens, n_seqs, false).total;
     return first + align256(total_tokens > 0 ? ff2_workspace_bytes(total_tokens, L->n, L->d) : 0) +
-           align256(ff1_slab_bytes(*L, total_tokens));
+           align256(ff1_tail_bytes(*L, total_tokens));
 }
 
 int griffin_prompt_phase(const griffin_layer *L, const void *W2p, int64_t ldw, const void *X, int64_t ldx,
@@ -340,8 +341,8 @@ int griffin_prompt_phase(const griffin_layer *L, const void *W2p, int64_t ldw, c
                       ff1_can_write_zb(*L, ldx, Z, L->n);
     int32_t nt = 0;
     const size_t before = pl.total + align256(second);
-    float *slabs = workspace_bytes >= before + ff1_slab_bytes(*L, total) ? (float *)(ws + before) : nullptr;
-    if ((rc = launch_ff1(*L, X, ldx, total, Z, L->n, rowpart, &nt, st, fuse ? (uint16_t *)ws2 : nullptr, L->n, slabs)) != GRIFFIN_OK)
+    float *tail = workspace_bytes >= before + ff1_tail_bytes(*L, total) ? (float *)(ws + before) : nullptr;
+    if ((rc = launch_ff1(*L, X, ldx, total, Z, L->n, &rowpart, &nt, st, fuse ? (uint16_t *)ws2 : nullptr, L->n, tail)) != GRIFFIN_OK)
         return rc;
     if ((rc = launch_stat(Z, L->n, rowpart, nt, total, L->n, seqs, s2part, s, s_out, st)) != GRIFFIN_OK)
         return rc;

@@ -5,7 +5,7 @@
 // norms of Section 4.1 are finished elsewhere.
 //
 // bf16: a dense contraction, so it runs on the matrix cores.  One workgroup (4 wavefronts, 2x2)
-// owns a 256-token (128 for short prompts) x 128-neuron tile of BOTH products: the X tile is
+// owns a tile of up to 256 tokens x 128 neurons of BOTH products: the X tile is
 // staged once in LDS and feeds two sets of v_mfma_f32_16x16x32_bf16 accumulators (gate and up),
 // so the epilogue finds g_ij and u_ij in the same lane and applies sigma, the gating product,
 // the store of Z and the row sum-of-squares without another pass.  Workgroup ids are remapped so
@@ -16,14 +16,17 @@
 // fp32 blocks: f32.hip.
 #include "ff1_kernel.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace griffin {
 
+// compiled in files of their own
 template <> void launch_ff1_tiles<GRIFFIN_ACT_SILU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
 template <> void launch_ff1_tiles<GRIFFIN_ACT_GELU_TANH>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
 template <> void launch_ff1_tiles<GRIFFIN_ACT_RELU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
 
+// Epilogue of the register-staged kernel: sigma, gating, store of Z, row sums of z^2.
 // Lane holds column (neuron) l31 of each 32x32 tile and rows (i>>2)*8 + lh*4 + (i&3), i = 0..15.
 template <int ACT, bool GATED, int MI>
 __device__ __forceinline__ void ff1_mfma_epilogue(const Ff1Params &p, f32x16 (&accU)[MI][2], f32x16 (&accG)[MI][2],
@@ -295,37 +298,96 @@ __global__ __launch_bounds__(256) void ff1_act_kernel(Ff1ActParams p)
         p.rowpart[(int64_t)row * gridDim.x + blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
+struct Ff1Tile {
+    int ti, ni;              // 32 ti tokens x 32 ni neurons
+    double cost;             // of the whole product, in rounds of 256 x 128 tiles on every CU
+};
+
+// The shape of the tiles, by what M tokens x n neurons cost on 256 CUs (an Eq. 2 block's tiles are
+// twice as wide).  A round of tiles of a shape takes the time FF1_SHAPES states, whatever part of the chip it fills, but for 0.3 of it:
+// matrix cores that idle leave the others power to run faster.  Selections (us) with 256 x 128 tiles / the shape this chooses:
+// 512 tokens of 4096 x 11008 110 / 100 (256 x 96: 230 tiles instead of 172), 777 of 5120 x 13824 254 / 230 (224 x 128: the last
+// tokens need no whole tile), 700 of 4096 x 14336 202 / 169, 1500 of 4096 x 11008 300 / 258, 3000 of 1536 x 6000 160 / 136 (256 x 96),
+// 1000 of 1024 x 4096 54 / 46 and 256 of 2048 x 8192 64 / 51 (256 x 64), 40 of 4096 x 11008 72 / 52 (128 x 128 / 64 x 64).
+static Ff1Tile ff1_tile(int64_t M, int32_t n, bool gated, bool any_width, bool sums_apart)
+{
+    const int64_t units = gated ? (n + 31) / 32 : (n + 63) / 64;
+    Ff1Tile best = {0, 0, 0.0};
+#define FF1_SHAPE_COST(TI_, NI_, COST_)                                                                         \
+    if ((gated ? NI_ == 4 || any_width : FF1_SHAPE_EQ2(TI_, NI_)) && (!sums_apart || FF1_SUMS_APART(TI_, NI_))) { \
+        const int64_t tiles = ((M + 32 * TI_ - 1) / (32 * TI_)) * ((units + NI_ - 1) / NI_);                    \
+        const double cost = COST_ * (0.7 * (double)((tiles + 255) / 256) + 0.3 / 256 * (double)tiles);          \
+        if (best.ti == 0 || cost < best.cost)                                                                   \
+            best = {TI_, NI_, cost};                                                                            \
+    }
+    FF1_SHAPES(FF1_SHAPE_COST)
+#undef FF1_SHAPE_COST
+    return best;
+}
+
+// The 128-column tiles of an Eq. 2 block, 256 tokens or 128: half the matrix work of a tile of both products, and bound by the L2->L1
+// path (~1400 clocks per k-tile against ~2550).
+static double ff1_narrow_cost(int64_t M, int32_t n)
+{
+    const int64_t mt = M > 128 ? (M + 255) / 256 : (M + 127) / 128, tiles = mt * ((n + G_BN - 1) / G_BN);
+    return (M > 128 ? 0.55 : 0.42) * (0.7 * (double)((tiles + 255) / 256) + 0.3 / 256 * (double)tiles);
+}
+
+// The plain product (128 columns of two matrices, or 256 of one): no more token tiles than of 256 tokens (128, 64 for prompts that
+// fit one), each as low as the tokens allow.
+struct Ff1Plain { int ti; double cost; };    // cost of a tile, 256 tokens = 1
+static Ff1Plain ff1_plain_tile(int64_t M)
+{
+    const int64_t mt = (M + 255) / 256, need = (M + 32 * mt - 1) / (32 * mt);
+    if (M <= 64) return {2, 0.45};
+    return need > 7 ? Ff1Plain{8, 1.0} : need > 6 ? Ff1Plain{7, 0.865} : need > 4 ? Ff1Plain{6, 0.785} : Ff1Plain{4, 0.91};
+}
+
+template <bool DUAL>
+static void launch_plain(const Ff1Params &p, int ti, int grid, hipStream_t st)
+{
+#define FF1_PLAIN_GO(TI_) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, TI_, 4, true, false, 2, DUAL>), dim3(grid), dim3(G_THREADS), 0, st, p)
+    switch (ti) {
+    case 2: FF1_PLAIN_GO(2); break;
+    case 4: FF1_PLAIN_GO(4); break;
+    case 6: FF1_PLAIN_GO(6); break;
+    case 7: FF1_PLAIN_GO(7); break;
+    default: FF1_PLAIN_GO(8); break;
+    }
+#undef FF1_PLAIN_GO
+}
+
 struct Ff1Plan {
-    int splits, per;         // ranges of d, k-tiles per range; 1 range: the epilogue of the product does it all
+    int splits;              // ranges of d; 1 range: the epilogue of the product does it all
+    int per;                 // k-tiles that are summed apart: those of a range, or of one that 128-neuron tiles would have taken
+    int room;                // ranges whose slabs the workspace has room for (what 128-neuron tiles would want: queries do not shrink)
     int64_t ldu;             // columns of a slab's row
 };
 
 // How many ranges: the cheapest by a cost in microseconds, from (measured) the time of a k-tile on a CU with its item's
 // fixed part in k-tiles, the weights at the rate the loop draws them from HBM, the slabs written and read again, and the
 // second kernel:
-//   * the whole product: a k-tile 1.15 us (256 tokens; 1.05 with up to 128; an Eq. 2 block's 128-column tiles 0.95 / 0.8), 8 (3)
-//     k-tiles of prologue and epilogue;
+//   * the whole product on 128-neuron tiles: a k-tile 1.15 us (256 tokens; 1.05 with up to 128; an Eq. 2 block's 128-column tiles
+//     0.95 / 0.8), 8 (3) k-tiles of prologue and epilogue; on the tiles of ff1_tile see below;
 //   * in ranges: the same without sigma in the epilogue (5, 3); up to 64 tokens 1.0 us, 1.25 us where two workgroups share a CU.
-// Whole selections of a 4096 x 11008 block, in one range / in 2, 3, 4, 5, 8 ranges (us): 40 tokens 96 / 70, 69, 64, 65, 70;
+// Whole selections of a 4096 x 11008 block, in one range of 256 x 128 (128 x 128) tiles / in 2, 3, 4, 5, 8 ranges (us): 40 tokens 96 / 70, 69, 64, 65, 70;
 // 128 tokens 97 / 75, 97, 87, 84, 102; 256 tokens 111 / 88, 120, 114, 112, 138; 512 tokens 115 / 152, 178, ...; of a 2048 x 8192
 // block: 40 tokens 58 / 45, 42, 41, 44, 46; 256 tokens 70 / 60, 58, 59, 83, 89; of a 8192 x 8192 Eq. 2 block: 40 tokens
 // 127 / 92, 73, 64, 58, 52; 512 tokens 151 / 120, 101, 107, 134, 125.
 static Ff1Plan ff1_plan(const griffin_layer &L, int64_t M)
 {
     const int KT = L.d / 64;
-    Ff1Plan pl = {1, KT, ((int64_t)L.n + 3) & ~(int64_t)3};
+    Ff1Plan pl = {1, KT, 1, ((int64_t)L.n + 3) & ~(int64_t)3};
     if (L.dtype != GRIFFIN_BF16 || L.d % 64 != 0 || L.ld > (1 << 21) || M < 1 || M > 2048)
         return pl;
     const bool gated = L.Wg != nullptr;
     const int64_t mt = M > 128 ? (M + 255) / 256 : 1;
     const int64_t n128 = mt * ((L.n + G_BN - 1) / G_BN), n256 = mt * ((L.n + 2 * G_BN - 1) / (2 * G_BN));
     const int fix_whole = M > 128 ? 8 : 3, fix_raw = M > 128 ? 5 : 3;
-    const double kt_us = M > 128 ? 1.15 : 1.05, kt_narrow_us = M > 128 ? 0.95 : 0.8;
-    double best = (double)((n128 + 255) / 256) * (KT + fix_whole) * (gated ? kt_us : kt_narrow_us);
-    if (!gated) {
-        const double wide = (double)((n256 + 255) / 256) * (KT + fix_whole) * kt_us;
-        best = wide < best ? wide : best;
-    }
+    const double whole_us = M > 128 ? 1.15 : 1.05, whole_narrow_us = M > 128 ? 0.95 : 0.8, kt_us = 1.15 * ff1_plain_tile(M).cost;
+    double best = (double)((n128 + 255) / 256) * (KT + fix_whole) * (gated ? whole_us : whole_narrow_us);
+    if (!gated)
+        best = std::min(best, (double)((n256 + 255) / 256) * (KT + fix_whole) * whole_us);
     const int64_t ntile = gated ? n128 : n256;
     const double hbm_us = (double)(gated ? 2 : 1) * L.n * L.d * 2 / 6.9e6;
     for (int s = 2; s <= 16; ++s) {
@@ -345,17 +407,30 @@ static Ff1Plan ff1_plan(const griffin_layer &L, int64_t M)
         t = (t > hbm_us ? t : hbm_us) + slab * 2 / 7e6 + 5.0;
         if (t < best) {
             best = t;
-            pl.splits = used;
+            pl.splits = pl.room = used;
             pl.per = per;
         }
     }
+    // One range on small tiles that keep the ranges' sums apart in registers computes the same, and needs no slabs; a round of them takes
+    // 1.25 us a k-tile where few tokens leave it waiting for the weights.  In ranges / so, selections (us): 40 tokens of 4096 x 11008
+    // 59.8 / 54.5, 163 of 2048 x 7872 55.2 / 46.6, 32 of 704 x 2384 25.2 / 22.0; but 81 of 7744 x 9040 88.2 / 91.9.  An Eq. 2 block's
+    // slabs are half as large, so it has to be cheaper by more: 50 tokens of 1088 x 3072 (compacted, too) 34.3 / 35.1, 34 of 512 x 1328 21.0 / 19.6.
+    if (pl.splits > 1 && ff1_tile(M, L.n, gated, true, true).cost * (KT + 8) * (gated ? 1.25 : 2.0) <= best)
+        pl.splits = 1;
     return pl;
 }
 
-size_t ff1_slab_bytes(const griffin_layer &L, int64_t M)
+// One range whose tiles are narrower than 128 neurons has more row partials than ff1_ntiles: they go there, too.
+size_t ff1_tail_bytes(const griffin_layer &L, int64_t M)
 {
     const Ff1Plan pl = ff1_plan(L, M);
-    return pl.splits > 1 ? (size_t)pl.splits * (L.Wg ? 2 : 1) * M * pl.ldu * sizeof(float) : 0;
+    const size_t slabs = pl.room > 1 ? (size_t)pl.room * (L.Wg ? 2 : 1) * M * pl.ldu * sizeof(float) : 0;
+    if (pl.splits > 1)
+        return slabs;
+    if (L.dtype != GRIFFIN_BF16 || L.d % 64 != 0 || L.ld > (1 << 21) || !L.Wg || M < 1)
+        return slabs;
+    const int ni = ff1_tile(M, L.n, true, true, pl.room > 1).ni;
+    return std::max(slabs, ni < 4 ? (size_t)M * ((L.n + 32 * ni - 1) / (32 * ni)) * sizeof(float) : 0);
 }
 
 int ff1_ntiles(const griffin_layer &L)
@@ -385,25 +460,19 @@ static int ff1_grid(int nblk, int per_cu = 1)
     return want < cus * per_cu ? want : cus * per_cu;
 }
 
-template <int ACT, int MI>
-static void launch_mfma(const Ff1Params &p, bool gated, bool wide, hipStream_t st)
+// the register-staged kernel takes one tile per workgroup
+template <int ACT>
+static void launch_staged(Ff1Params p, bool gated, hipStream_t st)
 {
-    const int nblk = p.mt * p.nt;
-    // the direct-to-LDS kernel wants whole 64-element k-tiles and 32-bit byte offsets inside a tile
-    if (!(p.d % 64 != 0 || p.ldx > (1 << 21) || p.ldw > (1 << 21)))
-        return launch_ff1_tiles<ACT>(p, 2 * MI, 4, gated, wide, ff1_grid(nblk), st);
-    const dim3 grid(((nblk + 7) / 8) * 8), block(G_THREADS);           // the register-staged kernel takes one tile per workgroup
-    if (gated) hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, true, MI, true>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, false, MI, true>), grid, block, 0, st, p);
-}
-
-template <int MI>
-static void launch_mfma_act(const Ff1Params &p, int act, bool gated, bool wide, hipStream_t st)
-{
-    switch (act) {
-    case GRIFFIN_ACT_SILU: launch_mfma<GRIFFIN_ACT_SILU, MI>(p, gated, wide, st); break;
-    case GRIFFIN_ACT_GELU_TANH: launch_mfma<GRIFFIN_ACT_GELU_TANH, MI>(p, gated, wide, st); break;
-    default: launch_mfma<GRIFFIN_ACT_RELU, MI>(p, gated, wide, st); break;
+    const int bm = p.M > 128 ? 256 : 128;
+    p.mt = (p.M + bm - 1) / bm;
+    const dim3 grid((p.mt * p.nt + 7) / 8 * 8), block(G_THREADS);
+    if (p.M > 128) {
+        if (gated) hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, true, 4, true>), grid, block, 0, st, p);
+        else hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, false, 4, true>), grid, block, 0, st, p);
+    } else {
+        if (gated) hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, true, 2, true>), grid, block, 0, st, p);
+        else hipLaunchKernelGGL((ff1_bf16_mfma_staged_kernel<ACT, false, 2, true>), grid, block, 0, st, p);
     }
 }
 
@@ -418,16 +487,16 @@ bool ff1_can_write_zb(const griffin_layer &L, int64_t ldx, const float *Z, int64
 }
 
 int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz,
-               float *rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb, float *slabs)
+               float **rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb, float *tail)
 {
     Ff1Params p;
     p.X = X; p.Wg = L.Wg; p.W1 = L.W1; p.bg = L.bg; p.b1 = L.b1;
-    p.Z = Z; p.rowpart = rowpart;
+    p.Z = Z; p.rowpart = *rowpart;
     p.Zb = (Zb && ff1_can_write_zb(L, ldx, Z, ldz)) ? Zb : nullptr;
     p.ldzb = ldzb;
     p.ldx = ldx; p.ldw = L.ld; p.ldz = ldz;
     p.M = (int32_t)M; p.F = L.n; p.d = L.d;
-    p.splits = 1; p.kt_per_split = L.d / 64;
+    p.splits = 1; p.kt_per_split = p.kt_per_sum = L.d / 64;
     // Z is read again at once by the statistic kernel.  While it fits the 256 MB Infinity Cache, plain stores leave it
     // there for that kernel; a Z several times that size is better sent past the caches (measured, statistic kernel
     // after plain / non-temporal stores: 201 MB of Z 38.3 / 44.6 us, 57 MB 14.5 / 16.4 us, 1.18 GB 284 / 243 us; the
@@ -435,41 +504,25 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
     p.z_stream = ((int64_t)M * L.n * 4 > ((int64_t)384 << 20) && ldz <= (1 << 20)) ? 1 : 0;   // (32-bit byte offsets inside a tile)
     p.nt = ff1_ntiles(L);
     const bool gated = L.Wg != nullptr;
-    // An Eq. 2 block on the direct-to-LDS kernel takes 256-column tiles (one row-sum partial per tile) when that
-    // is the faster way to fill the chip: a 128-column tile of one product is bound by the L2->L1 path (~1400
-    // clocks per k-tile), a 256-column tile by the matrix cores (~2550), and either comes in rounds of one tile per CU.
-    bool wide = false;
-    if (L.dtype == GRIFFIN_BF16 && !gated && !(L.d % 64 != 0 || ldx > (1 << 21) || L.ld > (1 << 21))) {
-        const int64_t mt = M > 128 ? (M + 255) / 256 : (M + 127) / 128;
-        const int64_t tn = mt * p.nt, tw = mt * ((L.n + 2 * G_BN - 1) / (2 * G_BN));
-        wide = ((tw + 255) / 256) * 2550 < ((tn + 255) / 256) * 1400;
-        if (wide)
-            p.nt = (L.n + 2 * G_BN - 1) / (2 * G_BN);
-    }
     const Ff1Plan pl = ff1_plan(L, M);
-    if (slabs && pl.splits > 1 && ldx <= (1 << 21)) {
+    if (tail && pl.splits > 1 && ldx <= (1 << 21)) {
         const int nb = (L.n + ACT_COLS - 1) / ACT_COLS;
         *nt_out = nb;
         int rc;
         if (gated) {
-            p.Z = slabs; p.ldz = pl.ldu; p.Zb = nullptr; p.z_stream = 0;
+            p.Z = tail; p.ldz = pl.ldu; p.Zb = nullptr; p.z_stream = 0;
             p.splits = pl.splits; p.kt_per_split = pl.per;
-            p.mt = (int32_t)(M > 128 ? (M + 255) / 256 : 1);
-            const dim3 grid(ff1_grid(p.mt * p.nt * pl.splits, M <= 64 ? 2 : 1)), block(G_THREADS);
-            if (M <= 64)
-                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 2, 4, true, false, 2, true>), grid, block, 0, st, p);
-            else if (M > 128)
-                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 8, 4, true, false, 2, true>), grid, block, 0, st, p);
-            else
-                hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 4, 4, true, false, 2, true>), grid, block, 0, st, p);
+            const int ti = ff1_plain_tile(M).ti;
+            p.mt = (int32_t)((M + 32 * ti - 1) / (32 * ti));
+            launch_plain<true>(p, ti, ff1_grid(p.mt * p.nt * pl.splits, M <= 64 ? 2 : 1), st);
             rc = check_launch("ff1_bf16_mfma_kernel");
         } else {
-            rc = launch_gemm_nt_partials(X, ldx, L.W1, L.ld, M, L.n, L.d, pl.splits, pl.per, slabs, pl.ldu, st);
+            rc = launch_gemm_nt_partials(X, ldx, L.W1, L.ld, M, L.n, L.d, pl.splits, pl.per, tail, pl.ldu, st);
         }
         if (rc != GRIFFIN_OK)
             return rc;
         Ff1ActParams a;
-        a.U = slabs; a.bg = L.bg; a.b1 = L.b1; a.Z = Z; a.rowpart = rowpart;
+        a.U = tail; a.bg = L.bg; a.b1 = L.b1; a.Z = Z; a.rowpart = *rowpart;
         a.Zb = (Zb && ff1_can_write_zb(L, ldx, Z, ldz)) ? Zb : nullptr;
         a.ldu = pl.ldu; a.ldz = ldz; a.ldzb = ldzb;
         a.M = (int32_t)M; a.F = L.n; a.act = L.act; a.splits = pl.splits;
@@ -480,21 +533,47 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
             hipLaunchKernelGGL(ff1_act_kernel<false>, agrid, dim3(256), 0, st, a);
         return check_launch("ff1_act_kernel");
     }
+    // the direct-to-LDS kernel wants whole 64-element k-tiles and 32-bit byte offsets inside a tile
+    const bool staged = L.d % 64 != 0 || ldx > (1 << 21) || L.ld > (1 << 21);
+    Ff1Tile t = {8, 4, 0.0};
+    bool wide = false;
+    const bool apart = tail && pl.room > 1;
+    p.kt_per_sum = apart ? pl.per : L.d / 64;
+    if (L.dtype == GRIFFIN_BF16 && !staged && M > 0) {
+        if (gated) {
+            t = ff1_tile(M, L.n, true, tail != nullptr, apart);
+            p.nt = (L.n + 32 * t.ni - 1) / (32 * t.ni);
+            if (t.ni < 4)
+                p.rowpart = *rowpart = tail;
+        } else {
+            t = ff1_tile(M, L.n, false, true, apart);
+            wide = apart || t.cost < ff1_narrow_cost(M, L.n);
+            if (wide)
+                p.nt = (L.n + 64 * t.ni - 1) / (64 * t.ni);
+            else
+                t = {M > 128 ? 8 : 4, 4, 0.0};
+        }
+        p.mt = (int32_t)((M + 32 * t.ti - 1) / (32 * t.ti));
+    }
     *nt_out = p.nt;
     if (M == 0)
         return GRIFFIN_OK;
     if (L.dtype == GRIFFIN_BF16) {
-        // 256-token tiles halve the LDS traffic per flop; short prompts keep 128
-        if (M > 128) {
-            p.mt = (int32_t)((M + 255) / 256);
-            launch_mfma_act<4>(p, L.act, gated, wide, st);
-        } else {
-            p.mt = (int32_t)((M + 127) / 128);
-            launch_mfma_act<2>(p, L.act, gated, wide, st);
+        const int grid = staged ? 0 : ff1_grid(p.mt * p.nt);
+#define FF1_ACT(ACT_)                                                                          \
+    {                                                                                          \
+        if (staged) launch_staged<ACT_>(p, gated, st);                                         \
+        else launch_ff1_tiles<ACT_>(p, t.ti, t.ni, gated, wide, grid, st);                     \
+    }
+        switch (L.act) {
+        case GRIFFIN_ACT_SILU: FF1_ACT(GRIFFIN_ACT_SILU) break;
+        case GRIFFIN_ACT_GELU_TANH: FF1_ACT(GRIFFIN_ACT_GELU_TANH) break;
+        default: FF1_ACT(GRIFFIN_ACT_RELU) break;
         }
+#undef FF1_ACT
         return check_launch("ff1_bf16_mfma_kernel");
     }
-    return launch_f32_ff1(L, X, ldx, M, Z, ldz, rowpart, st);
+    return launch_f32_ff1(L, X, ldx, M, Z, ldz, *rowpart, st);
 }
 
 // C[s] = A B^T over the s-th range of the contraction, fp32, for s = 0 .. splits-1, on the
@@ -542,21 +621,12 @@ int launch_gemm_nt_partials(const void *A, int64_t lda, const void *B, int64_t l
     p.Zb = nullptr; p.ldzb = 0;
     p.ldx = lda; p.ldw = ldb; p.ldz = ldc;
     p.M = (int32_t)M; p.F = N; p.d = K;
-    p.splits = splits; p.kt_per_split = kt_per_split;
+    p.splits = splits; p.kt_per_split = p.kt_per_sum = kt_per_split;
     p.z_stream = 0;
     p.nt = (N + 2 * G_BN - 1) / (2 * G_BN);        // 256-column tiles: both sets of accumulators hold columns of B
-    if (M > 128) {
-        p.mt = (int32_t)((M + 255) / 256);
-        const int nblk = p.mt * p.nt * splits;
-        hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 8, 4, true>), dim3(ff1_grid(nblk)), dim3(G_THREADS), 0, st, p);
-    } else if (M <= 64) {
-        p.mt = 1;
-        hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 2, 4, true>), dim3(ff1_grid(p.nt * splits, 2)), dim3(G_THREADS), 0, st, p);
-    } else {
-        p.mt = (int32_t)((M + 127) / 128);
-        const int nblk = p.mt * p.nt * splits;
-        hipLaunchKernelGGL((ff1_bf16_mfma_kernel<GRIFFIN_ACT_RELU, true, 4, 4, true>), dim3(ff1_grid(nblk)), dim3(G_THREADS), 0, st, p);
-    }
+    const int ti = ff1_plain_tile(M).ti;
+    p.mt = (int32_t)((M + 32 * ti - 1) / (32 * ti));
+    launch_plain<false>(p, ti, ff1_grid(p.mt * p.nt * splits, M <= 64 ? 2 : 1), st);
     return check_launch("ff1_bf16_mfma_kernel");
 }
 

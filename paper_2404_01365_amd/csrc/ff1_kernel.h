@@ -22,6 +22,7 @@ struct Ff1Params {
     int64_t ldx, ldw, ldz, ldzb;
     int32_t M, F, d, nt, mt;
     int32_t splits, kt_per_split;    // ranges of the contraction (1 for the activations) and 64-wide k-tiles per range
+    int32_t kt_per_sum;              // k-tiles that are summed apart and then added (FF1_SUMS_APART shapes)
     int32_t z_stream;                // Z leaves with the non-temporal hint (see launch_ff1)
 };
 
@@ -286,6 +287,10 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // slot swizzle of row r (rows of every stage section start at a multiple of 16)
 #define FF1_SWZ(r) (((r) >> 1) & 7)
 
+// Tiles whose accumulators leave the registers for a second set: every kt_per_sum k-tiles the products go to partial sums, which are added
+// in ascending order.  That is what ranges of d (ff1_plan) compute, bit for bit, without slabs and a kernel that adds them.
+#define FF1_SUMS_APART(ti_, ni_) ((ti_) * (ni_) <= 16)
+
 template <int ACT, bool GATED, int TI, int NI, bool PLAIN, bool EQ2W = false, int EXTRA = 2, bool DUAL = false>
 __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
 {
@@ -294,9 +299,12 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     constexpr int XQ = BM / 32, WQ = BN / 32;                // 8-row regions per wave per k-tile
     constexpr int WL = (GATED ? 2 : 1) * WQ;                   // LDS-DMA instructions per wave and k-tile: XQ of X, WL of the weights
     constexpr int X_ST = BM * 8, W_ST = (GATED ? 2 : 1) * BN * 8;    // 16-byte slots per stage
-    // Stages: two workgroups share a CU with 64-token tiles; 256-token tiles of two weight sections fill the LDS with two stages of X
-    // and three of the weights (the ones that come from HBM); everything else has three of both.
-    constexpr int NXS = TI == 2 || TI > 4 ? 2 : 3, NWS = TI == 2 ? 2 : 3;
+    // Stages: tiles of up to 128 tokens x 64 neurons, which are for little work, are bound by the latency of the weights and take as
+    // many as the LDS holds (40 tokens of 4096 x 11008, 64 x 64 tiles: whole selections 78 us with two stages, 52 with six).  Else
+    // two workgroups share a CU with 64-token tiles; from 160 tokens on two stages of X and three of the weights (the ones that come
+    // from HBM) fill the LDS; everything else has three of both.
+    constexpr bool DEEP = TI <= 4 && NI == 2;
+    constexpr int NXS = DEEP ? 8 - (TI == 2 ? 2 : TI) : TI == 2 || TI > 4 ? 2 : 3, NWS = DEEP ? NXS : TI == 2 ? 2 : 3;
     // The plain product has one B matrix: its tile is 256 columns wide and the "gate" half of the
     // machinery (LDS section, fragments, accumulators) takes columns n0 + 128 .. n0 + 255, which
     // halves the X traffic per flop exactly as the dual product does.
@@ -412,6 +420,8 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
 #define FF1_PIN() __builtin_amdgcn_sched_barrier(0)
 
     f32x4_t accU[TI][NI], accG[TI][NI];            // a wave's tile: TI blocks of sixteen tokens x NI of sixteen neurons
+    constexpr bool APART = GATED && !PLAIN && FF1_SUMS_APART(TI, NI);
+    f32x4_t sumU[APART ? TI : 1][APART ? NI : 1], sumG[APART ? TI : 1][APART ? NI : 1];
 
     const int l15 = lane & 15, lq = lane >> 4, sw = FF1_SWZ(l15);
     // LDS byte addresses of this lane's fragment rows in stage 0, per k-step of 32
@@ -425,8 +435,8 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     }
     u32x4 fa[2][TI], f1[2][NI], fg[2][NI];
     constexpr int NREADS = TI + (GATED ? 2 : 1) * NI;
-    constexpr int NSLOTS = TI * NI < 16 ? TI * NI : TI * NI % 16 == 0 ? 16 : 12;          // interleaving slots per k-step ...
-    constexpr int MPS = TI * NI / NSLOTS;                      // ... with so many pairs of MFMAs (up, gate) or singles each
+    // interleaving slots per k-step, with MPS pairs of MFMAs (up, gate) or singles each
+    constexpr int NSLOTS = TI * NI < 16 ? TI * NI : TI * NI % 16 == 0 ? 16 : TI * NI / 2, MPS = TI * NI / NSLOTS;
     static_assert(NREADS <= NSLOTS * 2 && XQ <= NSLOTS && WL <= NSLOTS && TI * NI == NSLOTS * MPS, "a k-step has a slot for everything");
 
 // read number r (0 .. NREADS-1) of fragment set F_ (16 rows = 2048 B apart): the weights first
@@ -481,9 +491,10 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
 
     // What a tile loads before its k loop: X of the first NXS k-tiles, the weights of the first NWS - 1; k-tile 0 first.
     constexpr int AFTER0 = (NXS - 1) * XQ + (NWS - 2) * WL;    // loads behind those of k-tile 0
-    // ... and what of it the wait in the middle of a k-tile may leave on its way: the last X (three stages) and weights (three)
-    constexpr int MID = (NXS == 3 ? XQ : 0) + (NWS == 3 ? WL : 0);
-    static_assert(NXS <= NWS, "the wait in the middle counts on it");
+    // ... and what the wait in the middle of a k-tile may leave on its way: all that was issued behind the next k-tile's
+    constexpr int MID = (NXS - 2) * XQ + (NWS - 2) * WL;
+    static_assert(AFTER0 <= 63 && MID <= 63, "the counter holds them");
+    static_assert(NXS == NWS || NXS == NWS - 1, "the wait in the middle counts on it");
     // Global store instructions that EVERY wave issues in the epilogue's usual path on a tile that lies
     // wholly inside the matrix (NI per 16-token block and column half, plus the row sums when all four waves write them).
     // The wait for k-tile 0 of the next tile may leave that many operations outstanding, no more: a
@@ -493,8 +504,11 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     {                                                                                          \
         _Pragma("unroll") for (int q = 0; q < XQ; ++q) FF1_LOAD_X(0, 0, q)                     \
         _Pragma("unroll") for (int q = 0; q < WL; ++q) FF1_LOAD_W(0, 0, q)                     \
-        if (NXS == 3) { _Pragma("unroll") for (int q = 0; q < XQ; ++q) FF1_LOAD_X(1, X_ST, q) } \
-        if (NWS == 3) { _Pragma("unroll") for (int q = 0; q < WL; ++q) FF1_LOAD_W(1, W_ST, q) } \
+        _Pragma("unroll") for (int k = 1; k < NWS - 1; ++k)                                    \
+        {                                                                                      \
+            if (k < NXS - 1) { _Pragma("unroll") for (int q = 0; q < XQ; ++q) FF1_LOAD_X(k, k * X_ST, q) } \
+            _Pragma("unroll") for (int q = 0; q < WL; ++q) FF1_LOAD_W(k, k * W_ST, q)          \
+        }                                                                                      \
         _Pragma("unroll") for (int q = 0; q < XQ; ++q) FF1_LOAD_X(NXS - 1, (NXS - 1) * X_ST, q) \
     }
     FF1_FIRST_LOADS()
@@ -523,7 +537,9 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
         }
         FF1_MFMA_GAP()
         int xs = 0, ws = 0, wp = (NWS - 1) * W_ST;             // stages (slots) of this k-tile, and the weights' of the one before
-        for (int kt = 0; kt < KT; ++kt) {
+        int kt = 0;
+        for (int ke = APART ? min(p.kt_per_sum, KT) : KT;; ke = min(ke + p.kt_per_sum, KT)) {
+        for (; kt < ke; ++kt) {
             const int xn = xs == (NXS - 1) * X_ST ? 0 : xs + X_ST, wnx = ws == (NWS - 1) * W_ST ? 0 : ws + W_ST;
             FF1_WAIT_FRAGS(0)
             FF1_KSTEP(0, 1, xs, ws, 1, false, kt + NWS - 1, wp)
@@ -534,6 +550,28 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
             wp = ws;
             ws = wnx;
             xs = xn;
+        }
+        if (!APART || (ke == KT && ke <= p.kt_per_sum))       // one sum
+            break;
+        // the sums so far; behind the last they go back to where the epilogue expects them
+        FF1_MFMA_GAP()
+        const bool first = ke <= p.kt_per_sum, last = ke == KT;
+#pragma unroll
+        for (int ti = 0; ti < (APART ? TI : 0); ++ti)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float u = ff1_acc_read(accU[ti][ni][e]), g = ff1_acc_read(accG[ti][ni][e]);
+                    sumU[ti][ni][e] = first ? u : sumU[ti][ni][e] + u;
+                    sumG[ti][ni][e] = first ? g : sumG[ti][ni][e] + g;
+                }
+                accU[ti][ni] = last ? sumU[ti][ni] : (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+                accG[ti][ni] = last ? sumG[ti][ni] : (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+            }
+        FF1_MFMA_GAP()
+        if (last)
+            break;
         }
         FF1_MFMA_GAP()
         FF1_WAIT_FRAGS(0)                                 // the reads issued for the tile past the end
@@ -574,18 +612,26 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
 #endif
 }
 
-// The whole product with its activation on this kernel, tiles of 32 ti tokens x 32 ni neurons (`wide`: an Eq. 2 block on tiles twice as
-// wide; without it the tiles of such a block are 128 x 128).  The caller has set p.mt and p.nt accordingly.
+// The whole product with its activation on this kernel, tiles of 32 ti tokens x 32 ni neurons (`wide`: an Eq. 2 block, on tiles of
+// 64 ni neurons; without it the tiles of such a block are 32 ti x 128).  The caller has set p.mt and p.nt accordingly.
 template <int ACT>
 void launch_ff1_tiles(const Ff1Params &p, int ti, int ni, bool gated, bool wide, int grid, hipStream_t st);
 
-#define FF1_TILES(...) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, __VA_ARGS__>), dim3(grid), dim3(G_THREADS), 0, st, p)
-#define FF1_TILES_CASE(TI_, NI_)                                                                                \
+// The tile shapes that are compiled: X(ti, ni, time of a round of them, 256 x 128 = 1).  ff1_tile (ff1.hip) chooses among them.
+#define FF1_SHAPES(X)                                                                                           \
+    X(8, 4, 1.0) X(7, 4, 0.89) X(6, 4, 0.8) X(8, 3, 0.785) X(4, 4, 0.7) X(6, 3, 0.635) X(8, 2, 0.585)       \
+    X(6, 2, 0.56) X(4, 2, 0.5) X(3, 2, 0.46) X(2, 2, 0.39)
+
+// An Eq. 2 block takes the narrow tiles in place of these.
+#define FF1_SHAPE_EQ2(ti_, ni_) ((ni_) > 2 || (ti_) <= 3)
+
+#define FF1_GO(...) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, __VA_ARGS__>), dim3(grid), dim3(G_THREADS), 0, st, p)
+#define FF1_TILES_CASE(TI_, NI_, COST_)                                                                         \
     if (ti == TI_ && ni == NI_) {                                                                               \
-        if (gated && (p.b1 || p.bg)) FF1_TILES(true, TI_, NI_, false);                                     \
-        else if (gated && p.Zb) FF1_TILES(true, TI_, NI_, false, false, 1);                                \
-        else if (gated) FF1_TILES(true, TI_, NI_, false, false, 0);                                        \
-        else FF1_TILES(true, TI_, NI_, false, true);                                                       \
+        if (gated && (p.b1 || p.bg)) FF1_GO(true, TI_, NI_, false);                                             \
+        else if (gated && (p.Zb || NI_ == 2)) FF1_GO(true, TI_, NI_, false, false, 1);                          \
+        else if (gated) FF1_GO(true, TI_, NI_, false, false, NI_ == 2 ? 1 : 0);                                 \
+        else if constexpr (FF1_SHAPE_EQ2(TI_, NI_)) FF1_GO(true, TI_, NI_, false, true);                        \
         return;                                                                                                 \
     }
 #define FF1_TILES_OF(ACT_)                                                                                      \
@@ -594,12 +640,11 @@ void launch_ff1_tiles(const Ff1Params &p, int ti, int ni, bool gated, bool wide,
     {                                                                                                           \
         constexpr int ACT = ACT_;                                                                               \
         if (!gated && !wide) {                                                                                  \
-            if (ti == 8) FF1_TILES(false, 8, 4, false);                                                      \
-            else FF1_TILES(false, 4, 4, false);                                                              \
+            if (ti == 8) FF1_GO(false, 8, 4, false);                                                            \
+            else FF1_GO(false, 4, 4, false);                                                                    \
             return;                                                                                             \
         }                                                                                                       \
-        FF1_TILES_CASE(8, 4)                                                                                    \
-        FF1_TILES_CASE(4, 4)                                                                                    \
+        FF1_SHAPES(FF1_TILES_CASE)                                                                              \
     }
 
 }  // namespace griffin

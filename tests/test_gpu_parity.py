@@ -480,6 +480,54 @@ def test_prefill_select_of_short_prompts_in_ranges(dtype, d, F, lens, k, act, ga
     test_prefill_select_matches_oracle(dtype, d, F, lens, k, act, gated, bias)
 
 
+# ------------------------------------------------------------------ prefill: every shape of the product's tiles
+# The shape (tokens x neurons of both products; of an Eq. 2 block twice the neurons) follows from the sizes; last tiles ragged both
+# ways, one to three k-tiles where up to six stages are loaded ahead, and walks of several tiles where the shape is taken for them.
+SHAPE_CASES = [
+    # dtype, d, F, lens, k, act, gated, bias
+    (synth.DT_BF16, 64, 700, [30], 350, synth.ACT_SILU, True, False),             # 64 x 64
+    (synth.DT_BF16, 448, 1001, [5, 8], 500, synth.ACT_GELU_TANH, True, True),     # 64 x 64, seven k-tiles, F odd
+    (synth.DT_BF16, 128, 9004, [65], 4000, synth.ACT_SILU, True, True),           # 96 x 64
+    (synth.DT_BF16, 192, 9004, [97], 4000, synth.ACT_RELU, True, False),          # 128 x 64
+    (synth.DT_BF16, 320, 9004, [130], 4000, synth.ACT_SILU, True, False),         # 192 x 64
+    (synth.DT_BF16, 128, 9004, [200], 4000, synth.ACT_GELU_TANH, True, True),     # 256 x 64
+    (synth.DT_BF16, 64, 16604, [130], 8000, synth.ACT_SILU, True, True),          # 192 x 96
+    (synth.DT_BF16, 128, 16604, [300], 8000, synth.ACT_GELU_TANH, True, False),   # 192 x 96, 346 tiles
+    (synth.DT_BF16, 64, 16604, [399], 8000, synth.ACT_SILU, True, False),         # 256 x 96, 346 tiles
+    (synth.DT_BF16, 64, 16603, [400], 8000, synth.ACT_RELU, True, True),          # the same, F odd, biases
+    (synth.DT_BF16, 64, 8188, [700, 5], 4000, synth.ACT_SILU, True, False),       # 192 x 128, 256 tiles
+    (synth.DT_BF16, 64, 16604, [600], 8000, synth.ACT_SILU, True, True),          # 224 x 128, 390 tiles
+    (synth.DT_BF16, 128, 5000, [777], 2500, synth.ACT_GELU_TANH, True, False),    # 256 x 96, 212 tiles
+    (synth.DT_BF16, 64, 700, [30], 350, synth.ACT_RELU, False, False),            # Eq. 2: 64 x 128
+    (synth.DT_BF16, 512, 16604, [65], 8000, synth.ACT_RELU, False, True),         # Eq. 2: 128 x 128
+    (synth.DT_BF16, 64, 16604, [777], 8000, synth.ACT_RELU, False, True),         # Eq. 2: 192 x 192, 435 tiles
+    (synth.DT_BF16, 64, 16604, [1000], 8000, synth.ACT_GELU_TANH, False, False),  # Eq. 2: 256 x 192, 348 tiles
+    (synth.DT_BF16, 64, 16604, [1100], 8000, synth.ACT_RELU, False, False),       # Eq. 2: 192 x 256, 390 tiles
+    (synth.DT_BF16, 64, 16604, [1500], 8000, synth.ACT_RELU, False, True),        # Eq. 2: 224 x 256, 455 tiles
+    (synth.DT_BF16, 4096, 900, [400], 450, synth.ACT_SILU, True, False),          # ranges of d on 224-token tiles
+    # sums of several ranges kept apart in registers, the last range shorter
+    (synth.DT_BF16, 1088, 3001, [33], 1500, synth.ACT_SILU, True, True),          # 64 x 64
+    (synth.DT_BF16, 1024, 9004, [70], 4000, synth.ACT_SILU, True, False),         # 96 x 64
+    (synth.DT_BF16, 1088, 9004, [128], 4000, synth.ACT_GELU_TANH, True, False),   # 128 x 64
+    (synth.DT_BF16, 1088, 9004, [250], 4000, synth.ACT_SILU, True, True),         # 256 x 64
+]
+
+
+@pytest.mark.parametrize("dtype,d,F,lens,k,act,gated,bias", SHAPE_CASES)
+def test_prefill_select_on_every_tile_shape(dtype, d, F, lens, k, act, gated, bias):
+    test_prefill_select_matches_oracle(dtype, d, F, lens, k, act, gated, bias)
+
+
+@pytest.mark.parametrize("d,F,lens,k,gated,bias", [
+    (64, 704, [30], 300, True, False),           # 64 x 64
+    (64, 16608, [399], 8000, True, False),       # 256 x 96, 346 tiles; the second product on 224-token tiles
+    (64, 16608, [250], 8000, True, True),        # 256 x 96
+    (128, 2048, [300], 1000, True, True),        # the second product on 192-token tiles
+])
+def test_prompt_phase_on_narrow_and_low_tiles(d, F, lens, k, gated, bias):
+    test_prompt_phase_is_selection_plus_prompt_output_from_one_z(synth.DT_BF16, d, F, lens, k, gated, bias)
+
+
 def test_prefill_takes_a_workspace_without_room_for_the_slabs():
     """The slabs are a convenience: the least workspace that is accepted gives the same answer in one range."""
     dtype, d, F, S, k = synth.DT_BF16, 1024, 1000, 40, 500
