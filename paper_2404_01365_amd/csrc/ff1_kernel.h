@@ -620,10 +620,10 @@ void launch_ff1_tiles(const Ff1Params &p, int ti, int ni, bool gated, bool wide,
 // The tile shapes that are compiled: X(ti, ni, time of a round of them, 256 x 128 = 1).  ff1_tile (ff1.hip) chooses among them.
 #define FF1_SHAPES(X)                                                                                           \
     X(8, 4, 1.0) X(7, 4, 0.89) X(6, 4, 0.8) X(8, 3, 0.785) X(4, 4, 0.7) X(6, 3, 0.635) X(8, 2, 0.585)       \
-    X(6, 2, 0.56) X(4, 2, 0.5) X(3, 2, 0.46) X(2, 2, 0.39)
+    X(6, 2, 0.56) X(4, 2, 0.48) X(3, 2, 0.46) X(2, 2, 0.39)
 
 // An Eq. 2 block takes the narrow tiles in place of these.
-#define FF1_SHAPE_EQ2(ti_, ni_) ((ni_) > 2 || (ti_) <= 3)
+#define FF1_SHAPE_EQ2(ti_, ni_) ((ni_) > 2 || (ti_) == 2)
 
 #define FF1_GO(...) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, __VA_ARGS__>), dim3(grid), dim3(G_THREADS), 0, st, p)
 #define FF1_TILES_CASE(TI_, NI_, COST_)                                                                         \
