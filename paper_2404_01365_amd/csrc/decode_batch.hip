@@ -69,12 +69,13 @@ constexpr int BT_NT = 2;
 
 constexpr int bt_vmcnt(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
-// blocks of a wave that are on their way at once: a divisor of S (the ring's registers have to be named at compile time),
-// about 64 KB per CU
+// Blocks of a wave that are on their way at once, a divisor of S (the ring's registers have to be named at compile time).  Two blocks of an
+// Eq. 3 block are 64 KB per CU; four or five, 128 to 160 KB, are slower: whole calls of sixteen rows of 5120 x 6912 54.4 / 52.1 us with two, of
+// 7680 x 7000 76.5 / 74.8, eight of 4096 x 5504 37.9 / 36.8, the masked pass of 4096 x 14336 70.4 / 69.6.
 constexpr int bt_ring(bool gated, int S, int T)
 {
-    if (T > 1)
-        return 2;            // beside x of several tiles more is slower (3072 x 12288, 40 rows: 66.7 us against 65.4), or does not fit
+    if (gated || T > 1)
+        return 2;
     return S % 4 == 0 ? 4 : S % 3 == 0 ? 3 : S % 5 == 0 ? 5 : 2;
 }
 
