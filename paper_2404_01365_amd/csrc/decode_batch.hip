@@ -11,14 +11,14 @@
 //    blocks of a row (wave w has the blocks w, w + W, ...: at any time the workgroup reads one window of W x 128
 //    bytes that marches along sixteen rows), and a wave keeps its blocks of all the rows of x in registers, as operand
 //    fragments of v_mfma_f32_16x16x32_bf16.  The weights go from global memory straight into registers, whole 128-byte
-//    lines of eight neurons an instruction, R blocks ahead; the lanes of two such instructions then trade halves, so that a
+//    lines of eight neurons an instruction, R blocks ahead (bt_ring); the lanes of two such instructions then trade halves, so that a
 //    register holds sixteen neurons as the MFMA wants them: a kilobyte of weights costs one load and one MFMA per sixteen
 //    rows of the batch and touches no LDS.  A wave's partial tiles go to LDS; the waves meet as seldom as the LDS allows (a
 //    barrier per group would tie their load streams to the slowest: 75 us a masked call instead of 71 on 4096 x 14336), add the
 //    tiles in wave order, apply sigma, the gating product and the membership bits, and store Z.  Workgroups start at different
 //    blocks, so that row strides of a power of two do not send them all to the same memory channels at a time.
 //    Measured on the gate and up rows (medians of the kernel trace, each with the ~4 us of a dependent dispatch in it):
-//    5120 x 6912 (142 MB), 16 rows 34 us (38 when rows were streamed through LDS two neurons at a time with two of sixteen
+//    5120 x 6912 (142 MB), 16 rows 31 us (34 with five blocks ahead; 38 when rows were streamed through LDS two neurons at a time with two of sixteen
 //    MFMA columns in use; 42 with loads of sixteen half lines instead of eight whole ones); 3072 x 12288, 40 rows 37 us (three
 //    passes of 32 in that form); 4096 x 14336 masked 44 us, as in that form.
 //  * ff_batch_down_kernel: the second line.  Giving every workgroup all d columns would cost one [rows][d] partial per
@@ -288,15 +288,19 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
 // every wave brings its own 32-neuron x 64-column pieces (whole 128-byte lines, 8 rows per
 // LDS-DMA instruction) into a private LDS ring and gathers the operands with 16-bit LDS reads, once for all tiles of rows.
 // No wave waits for another after the first barrier.
-constexpr int BD_DEPTH = 3;              // ring slots per wave (a fourth, fitted into the LDS by trimming the tables, changed nothing)
+// Ring slots per wave: the pieces of one step are on their way while those of another are used, 32 KB a CU.  With three (64 KB) whole
+// calls of 16 rows of 1024 x 5504 take 19.5 us (18.7 with two), 40 of 3072 x 12288 63.3 (61.9), 60 of 2048 x 9000 48.9 (47.3), 16 of 5120 x 6912
+// 52.2 (51.5); the masked pass of 4096 x 14336 and Eq. 2 blocks are the same either way.
+constexpr int BD_DEPTH = 2;
 constexpr int BD_REGION = 66;            // 16-byte units per 8-row region: 1 KB of rows + 32 B, so that the four
                                          // regions a gather touches (rows 8q + i) start on different LDS banks
 constexpr int BD_SLOT = 4 * BD_REGION;   // a slot: 32 rows x 128 B in four regions
-constexpr int BD_RING = BT_WAVES2 * BD_DEPTH * BD_SLOT * 16;    // bytes: 99 KB
+constexpr int BD_RING = BT_WAVES2 * BD_DEPTH * BD_SLOT * 16;    // bytes: 66 KB
 // neurons of a range before rounding to multiples of 8: its fragments, 64 T bytes a neuron in steps of 32, go into the
-// 61 KB that the ring leaves of the LDS (480 with one tile, 472, 312 and 216 with two, three and four)
-constexpr int bd_range(int T) { return T == 1 ? 480 : (160 * 1024 - BD_RING) / (64 * T) / 32 * 32 - 8; }
-static_assert(bd_range(1) + 8 + 31 <= (160 * 1024 - BD_RING) / 64 && bd_range(4) > 0, "the range's fragments fit beside the ring");
+// LDS beside the ring, 61 KB of it (480 with one tile, 472, 312 and 216 with two, three and four)
+constexpr int BD_Z_BYTES = 62464;
+constexpr int bd_range(int T) { return T == 1 ? 480 : BD_Z_BYTES / (64 * T) / 32 * 32 - 8; }
+static_assert(bd_range(1) + 8 + 31 <= BD_Z_BYTES / 64 && BD_Z_BYTES + BD_RING <= 160 * 1024, "the range's fragments fit beside the ring");
 
 //
 // EXACT: Z is fp32, split into the three bf16 that hold its 24 bits.  (v_mfma_f32_16x16x4_f32 takes Z as it is, for five times the
