@@ -272,7 +272,8 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x4_t 
 // vmcnt + one bare s_barrier say that the next k-tile has landed for every wave and that every wave has read its last
 // fragment of this one; the second k-step then sends X of the k-tile two ahead into the stage just read, and the first k-step of
 // the next k-tile the weights of the one three ahead of this (three stages of weights and two of X fill the LDS: 160 KB).
-// Loads past the last k-tile re-read the last one into a dead stage, which keeps the loop body branch-free.
+// Loads past the last k-tile re-read the last one into a dead stage, which keeps the loop body branch-free.  (With two stages of both the
+// weights leave along with X.)
 //
 // What bounds it and what that decided (256 x 128 x 2 tiles, 2048 tokens of 3072 x 24576, one call after another):
 //   * power.  A loop of nothing but these MFMAs on random data runs at 1.77 PFLOP/s with v_mfma_f32_32x32x16 and at 2.05
@@ -469,8 +470,8 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
         _Pragma("unroll") for (int t_ = 0; t_ < TI; ++t_) asm volatile("" : "+v"(fa[F_][t_])); \
     }
 // one k-step: MFMAs on fragment set FM_, the reads of set FR_ (k-step KR_ of the stages at slots xs_, ws_) two a slot, and the
-// loads one a slot: LX_ a k-tile of X, else one of the weights, LT_ into the stage at slot ls_
-#define FF1_KSTEP(FM_, FR_, xs_, ws_, KR_, LX_, LT_, ls_)                                      \
+// loads LPS of a kind a slot: if LX_, k-tile XT_ of X into the stage at slot xd_, if LW_, k-tile WT_ of the weights into the one at wd_
+#define FF1_KSTEP(FM_, FR_, xs_, ws_, KR_, LX_, XT_, xd_, LW_, WT_, wd_)                       \
     {                                                                                          \
         const uint32_t sa = abase[KR_] + (uint32_t)((xs_) * 16), sb = bbase[KR_] + (uint32_t)((ws_) * 16); \
         FF1_PIN();                                                                             \
@@ -479,10 +480,18 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
             _Pragma("unroll") for (int z_ = 0; z_ < 2; ++z_)                                   \
                 if (m * 2 + z_ < NREADS)                                                       \
                     FF1_READ_ONE(FR_, m * 2 + z_, sa, sb)                                      \
-            if ((LX_) && m < XQ)                                                               \
-                FF1_LOAD_X(LT_, ls_, m < XQ ? m : 0)                                           \
-            if (!(LX_) && m < WL)                                                              \
-                FF1_LOAD_W(LT_, ls_, m)                                                        \
+            if (m * LPS < XQ && (LX_))                                                         \
+            {                                                                                  \
+                _Pragma("unroll") for (int z_ = 0; z_ < LPS; ++z_)                             \
+                    if (m * LPS + z_ < XQ)                                                     \
+                        FF1_LOAD_X(XT_, xd_, m * LPS + z_ < XQ ? m * LPS + z_ : 0)             \
+            }                                                                                  \
+            if (m * LPS < WL && (LW_))                                                         \
+            {                                                                                  \
+                _Pragma("unroll") for (int z_ = 0; z_ < LPS; ++z_)                             \
+                    if (m * LPS + z_ < WL)                                                     \
+                        FF1_LOAD_W(WT_, wd_, m * LPS + z_)                                     \
+            }                                                                                  \
             _Pragma("unroll") for (int z_ = 0; z_ < MPS; ++z_)                                 \
                 FF1_MFMA_ONE(FM_, m * MPS + z_)                                                \
             FF1_PIN();                                                                         \
@@ -493,7 +502,15 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     constexpr int AFTER0 = (NXS - 1) * XQ + (NWS - 2) * WL;    // loads behind those of k-tile 0
     // ... and what the wait in the middle of a k-tile may leave on its way: all that was issued behind the next k-tile's
     constexpr int MID = (NXS - 2) * XQ + (NWS - 2) * WL;
-    static_assert(AFTER0 <= 63 && MID <= 63, "the counter holds them");
+    // Two stages of weights, two workgroups a CU: the first k-step is too late for the weights of the next k-tile, which are waited for
+    // behind it.  They leave a k-step earlier, along with X, and those of k-tile 1 when the epilogue has left their stage; as the wait in
+    // the middle is for everything, loads past the last k-tile can be left out.  With the weights in the first k-step / so (us): Eq. 2 selections, 57
+    // tokens of 6144 x 16276 72.6 / 69.1, 5 of 6656 x 10384 51.8 / 50.0; outputs, 64 tokens of 5120 x 13824 47.1 / 44.6, 13 of 2560 x 7552
+    // 33.5 / 30.4.
+    constexpr bool PAIR = NWS == 2;
+    static_assert(!PAIR || (NXS == 2 && MID == 0), "the wait in the middle is for everything");
+    constexpr int LPS = PAIR ? 4 : 1;
+    static_assert(AFTER0 + (PAIR ? WL : 0) <= 63 && MID <= 63, "the counter holds them");
     static_assert(NXS == NWS || NXS == NWS - 1, "the wait in the middle counts on it");
     // Global store instructions that EVERY wave issues in the epilogue's usual path on a tile that lies
     // wholly inside the matrix (NI per 16-token block and column half, plus the row sums when all four waves write them).
@@ -516,13 +533,18 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     for (;;) {
         // k-tile 0 has landed when only the loads behind it and (from the second tile on) the
         // epilogue's stores, all issued after it, are still outstanding
-        constexpr int W0 = AFTER0 + EPI_STORES, W1 = W0 + Z_STORES;
+        constexpr int BEHIND = PAIR ? WL : 0, W0 = AFTER0 + BEHIND + EPI_STORES, W1 = W0 + Z_STORES;
+        if (PAIR) {
+#pragma unroll
+            for (int q = 0; q < WL; ++q)
+                FF1_LOAD_W(1, W_ST, q)
+        }
         if (stores_known && EXTRA && !PLAIN && p.Zb)      // twice the Z stores (more than the counter holds: 63 is as good)
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(W1 > 63 ? 63 : W1));
         else if (stores_known)
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(W0 > 63 ? 63 : W0));
         else
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(AFTER0));
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(AFTER0 + BEHIND));
         FF1_BARRIER()
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti)
@@ -542,11 +564,11 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
         for (; kt < ke; ++kt) {
             const int xn = xs == (NXS - 1) * X_ST ? 0 : xs + X_ST, wnx = ws == (NWS - 1) * W_ST ? 0 : ws + W_ST;
             FF1_WAIT_FRAGS(0)
-            FF1_KSTEP(0, 1, xs, ws, 1, false, kt + NWS - 1, wp)
+            FF1_KSTEP(0, 1, xs, ws, 1, false, 0, 0, !PAIR, kt + NWS - 1, wp)
             FF1_WAIT_FRAGS(1)
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(MID));        // tile kt+1 has landed (this wave's part)
             FF1_BARRIER()                                      // ... every wave's part; tile kt is read out
-            FF1_KSTEP(1, 0, xn, wnx, 0, true, kt + NXS, xs)
+            FF1_KSTEP(1, 0, xn, wnx, 0, !PAIR || kt + NXS < KT, kt + NXS, xs, PAIR && kt + NWS < KT, kt + NWS, ws)
             wp = ws;
             ws = wnx;
             xs = xn;

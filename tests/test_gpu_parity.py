@@ -599,6 +599,29 @@ def test_prompt_output_when_workgroups_walk_tiles(d, F, S, bias):
         assert max_rel(got, oracle.ff2(Z.astype(np.float64), W2, b2)) <= TOL_OUT[dtype]
 
 
+@pytest.mark.parametrize("d,F,S", [
+    (136, 64, 1),                 # one k-tile, two, three, five: what is loaded ahead ends with the last of them
+    (260, 128, 40),
+    (1000, 192, 64),
+    (520, 320, 33),
+    (131404, 128, 5),             # 514 feature tiles: workgroups, two a CU, walk two of them
+    (131404, 320, 64),
+    (264, 4096, 50),              # in ranges
+])
+def test_prompt_output_of_few_tokens(d, F, S):
+    """The second product on 64-token tiles, which have two stages of LDS instead of three."""
+    dtype = synth.DT_BF16
+    g = np.random.default_rng(d + F + S)
+    Z = (g.standard_normal((S, F)) * (g.random((S, F)) < 0.7)).astype(np.float32)
+    W2 = synth.round_to_bf16((g.standard_normal((F, d)) * F ** -0.5).astype(np.float32))     # neuron-major
+    Y = torch.full((S, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    G.griffin_ff_prompt_out(torch.from_numpy(Z).cuda(), to_dev(np.ascontiguousarray(W2.T), dtype), Y,
+                            workspace=workspace(G.griffin_prompt_out_workspace_bytes(S, F, d)))
+    sync()
+    # Z is rounded to bf16 on its way into the matrix cores, in the reference too: what is left is the rounding of Y
+    assert max_rel(to_host(Y), oracle.ff2(synth.round_to_bf16(Z).astype(np.float64), W2, None)) <= 2.0 ** -8
+
+
 def test_prefill_with_biases_at_odd_addresses():
     """Biases need no alignment beyond their element size: vectors that start 2 bytes past an 8-byte boundary
     take the element-wise store path of the first product and give the same sets and statistic."""
