@@ -300,6 +300,7 @@ __global__ __launch_bounds__(256) void ff1_act_kernel(Ff1ActParams p)
 
 struct Ff1Tile {
     int ti, ni;              // 32 ti tokens x 32 ni neurons
+    int64_t tiles;
     double cost;             // of the whole product, in rounds of 256 x 128 tiles on every CU
 };
 
@@ -312,13 +313,13 @@ struct Ff1Tile {
 static Ff1Tile ff1_tile(int64_t M, int32_t n, bool gated, bool any_width, bool sums_apart)
 {
     const int64_t units = gated ? (n + 31) / 32 : (n + 63) / 64;
-    Ff1Tile best = {0, 0, 0.0};
+    Ff1Tile best = {0, 0, 0, 0.0};
 #define FF1_SHAPE_COST(TI_, NI_, COST_)                                                                         \
     if ((gated ? NI_ == 4 || any_width : FF1_SHAPE_EQ2(TI_, NI_)) && (!sums_apart || FF1_SUMS_APART(TI_, NI_))) { \
         const int64_t tiles = ((M + 32 * TI_ - 1) / (32 * TI_)) * ((units + NI_ - 1) / NI_);                    \
         const double cost = COST_ * (0.7 * (double)((tiles + 255) / 256) + 0.3 / 256 * (double)tiles);          \
         if (best.ti == 0 || cost < best.cost)                                                                   \
-            best = {TI_, NI_, cost};                                                                            \
+            best = {TI_, NI_, tiles, cost};                                                                            \
     }
     FF1_SHAPES(FF1_SHAPE_COST)
 #undef FF1_SHAPE_COST
@@ -415,8 +416,17 @@ static Ff1Plan ff1_plan(const griffin_layer &L, int64_t M)
     // 1.25 us a k-tile where few tokens leave it waiting for the weights.  In ranges / so, selections (us): 40 tokens of 4096 x 11008
     // 59.8 / 54.5, 163 of 2048 x 7872 55.2 / 46.6, 32 of 704 x 2384 25.2 / 22.0; but 81 of 7744 x 9040 88.2 / 91.9.  An Eq. 2 block's
     // slabs are half as large, so it has to be cheaper by more: 50 tokens of 1088 x 3072 (compacted, too) 34.3 / 35.1, 34 of 512 x 1328 21.0 / 19.6.
-    if (pl.splits > 1 && ff1_tile(M, L.n, gated, true, true).cost * (KT + 8) * (gated ? 1.25 : 2.0) <= best)
-        pl.splits = 1;
+    // So do tiles of an Eq. 3 block whose rounds wait longer than FF1_SHAPES says when the sums are apart (in ranges / so): 256 x 64
+    // tiles, 196 tokens of 3648 x 9488 75.2 / 80.0, 237 of 2048 x 8912 62.9 / 65.6; 128 x 64 tiles, 100 of 6144 x 16288 105.1 / 121.3 (but 108 of
+    // 8128 x 12304, five ranges with their slabs, 130.5 / 124.1); 128 x 128 tiles with half of their tokens or less, 24 of 2816 x 18128 65.8 / 89.1,
+    // 1 of 2560 x 24768 92.4 / 99.4; 64 x 64 tiles for a quarter of the chip, 14 of 1600 x 2992 26.8 / 28.4, 1 of 1280 x 3120 27.1 / 28.6 (but 62
+    // of 896 x 4192 30.5 / 28.5).
+    if (pl.splits > 1) {
+        const Ff1Tile t = ff1_tile(M, L.n, gated, true, true);
+        const bool few = t.ti == 2 && t.ni == 2 && t.tiles <= 64, low = t.ti == 4 && (t.ni == 2 ? pl.room <= 4 : M <= 64);
+        if (t.cost * (KT + 8) * (!gated || t.ti == 8 ? 2.0 : few ? 1.7 : low ? 1.45 : 1.25) <= best)
+            pl.splits = 1;
+    }
     return pl;
 }
 
@@ -535,7 +545,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
     }
     // the direct-to-LDS kernel wants whole 64-element k-tiles and 32-bit byte offsets inside a tile
     const bool staged = L.d % 64 != 0 || ldx > (1 << 21) || L.ld > (1 << 21);
-    Ff1Tile t = {8, 4, 0.0};
+    Ff1Tile t = {8, 4, 0, 0.0};
     bool wide = false;
     const bool apart = tail && pl.room > 1;
     p.kt_per_sum = apart ? pl.per : L.d / 64;
@@ -551,7 +561,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
             if (wide)
                 p.nt = (L.n + 64 * t.ni - 1) / (64 * t.ni);
             else
-                t = {M > 128 ? 8 : 4, 4, 0.0};
+                t = {M > 128 ? 8 : 4, 4, 0, 0.0};
         }
         p.mt = (int32_t)((M + 32 * t.ti - 1) / (32 * t.ti));
     }
