@@ -493,7 +493,7 @@ bool ff1_can_write_zb(const griffin_layer &L, int64_t ldx, const float *Z, int64
     const bool ktail = L.d % 64 != 0 || ldx > (1 << 21) || L.ld > (1 << 21);
     const bool vec = ((L.n | (int32_t)ldz) & 3) == 0 && ((uintptr_t)Z & 15) == 0;
     const bool bias8 = (((uintptr_t)L.b1 | (uintptr_t)L.bg) & 7) == 0;
-    return L.dtype == GRIFFIN_BF16 && !ktail && vec && bias8 && ldz <= (1 << 20);
+    return L.dtype == GRIFFIN_BF16 && !ktail && vec && bias8 && ldz <= FF1_LDZ_MAX;
 }
 
 int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz,

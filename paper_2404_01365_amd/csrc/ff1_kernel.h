@@ -15,6 +15,10 @@ constexpr int G_THREADS = 256;
 // s_waitcnt immediate that waits for vmcnt <= n only (expcnt / lgkmcnt fields left at "no wait")
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
+// Longest row stride of Z that the usual epilogue takes: the byte offsets inside a wave's 128 rows fit 31 bits.
+constexpr int64_t FF1_LDZ_MAX = 1 << 22;
+static_assert((127 * FF1_LDZ_MAX + 256) * 4 < 0x7FFFFFFE, "as do those of its buffer descriptors");
+
 struct Ff1Params {
     const void *X, *Wg, *W1, *bg, *b1;
     float *Z, *rowpart;
@@ -76,7 +80,7 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x4_t 
     const bool hb = EXTRA == 2 && !PLAIN && (p.b1 != nullptr || (GLU && p.bg != nullptr));
     const uint16_t *b1p = (const uint16_t *)p.b1, *bgp = (const uint16_t *)p.bg;
     const bool bias8 = (((uintptr_t)p.b1 | (uintptr_t)p.bg) & 7) == 0;       // four biases per 8-byte load
-    const bool usual = vec && (!hb || bias8) && p.ldz <= (1 << 20);         // (32-bit byte offsets inside a tile)
+    const bool usual = vec && (!hb || bias8) && p.ldz <= FF1_LDZ_MAX;
     const uint32_t patch = patch_lds + (uint32_t)(wave * 2 * 4096);
     float sq[TI];                          // sums of squares of the lane's tokens 16 ti + l15 over its neurons
 #pragma unroll
@@ -199,7 +203,10 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x4_t 
 #undef FF1_Z_STORE
 #undef FF1_EPI_COMPUTE
     } else {
-        // rows of Z that 16-byte stores cannot take, or biases that 8-byte loads cannot: element by element
+        // rows of Z that 16-byte stores cannot take or that are too far apart, or biases that 8-byte loads cannot: straight from the
+        // accumulators, 16 bytes at a time where the rows can take them.  (Rows 2^22 floats apart and more, selections, us, element by element / so /
+        // with rows that the path above takes: 512 tokens of 4096 x 11008 106.7 / 103.5 / 100.1, 1024 of 4096 x 14336 245 / 233 / 220, 1000 of an Eq. 2
+        // block of 4096 x 16384 163 / 153 / 142.)
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) {
             const int tok = m0 + wm * (16 * TI) + ti * 16 + l15;
@@ -207,28 +214,34 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x4_t 
             float *zrow = p.Z + (int64_t)min(tok, p.M - 1) * p.ldz;
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
+                const int col0 = n0 + wn * WN + ni * 16 + lq * 4;
+                f32x4_t z[HV];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int col = n0 + wn * WN + ni * 16 + lq * 4 + i;
+                    const int col = col0 + i;
                     const int cj = min(col, p.F - 1);
                     float u = ff1_acc_read(accU[ti][ni][i]);
                     float gt = GATED ? ff1_acc_read(accG[ti][ni][i]) : 0.0f;
                     if (!PLAIN && b1p) u += bf16_bits_to_f32(b1p[cj]);
                     if (GLU && bgp) gt += bf16_bits_to_f32(bgp[cj]);
                     if (EQ2W && b1p) gt += bf16_bits_to_f32(b1p[min(col + BN, p.F - 1)]);
-                    const float z = PLAIN ? u : (GLU ? act_apply_t<ACT>(gt) * u : act_apply_t<ACT>(u));
-                    if (col < p.F) {
-                        sq[ti] = fmaf(z, z, sq[ti]);
-                        if (rowok)
-                            zrow[col] = z;
-                    }
-                    if (WIDE && col + BN < p.F) {
-                        const float z2 = EQ2W ? act_apply_t<ACT>(gt) : gt;
-                        sq[ti] = fmaf(z2, z2, sq[ti]);
-                        if (rowok)
-                            zrow[col + BN] = z2;
-                    }
+                    z[0][i] = PLAIN ? u : (GLU ? act_apply_t<ACT>(gt) * u : act_apply_t<ACT>(u));
+                    if (WIDE)
+                        z[HV - 1][i] = EQ2W ? act_apply_t<ACT>(gt) : gt;
+#pragma unroll
+                    for (int h = 0; h < HV; ++h)
+                        if (col + h * BN < p.F) {
+                            sq[ti] = fmaf(z[h][i], z[h][i], sq[ti]);
+                            if (rowok && !vec)
+                                zrow[col + h * BN] = z[h][i];
+                        }
                     __builtin_amdgcn_sched_barrier(0);
+                }
+                if (vec) {                  // F is a multiple of four: all of a lane's columns are inside, or none
+#pragma unroll
+                    for (int h = 0; h < HV; ++h)
+                        if (rowok && col0 + h * BN < p.F)
+                            *(f32x4_t *)(zrow + col0 + h * BN) = z[h];
                 }
             }
         }

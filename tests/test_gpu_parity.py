@@ -622,6 +622,29 @@ def test_prompt_output_of_few_tokens(d, F, S):
     assert max_rel(to_host(Y), oracle.ff2(synth.round_to_bf16(Z).astype(np.float64), W2, None)) <= 2.0 ** -8
 
 
+@pytest.mark.parametrize("ldz", [(1 << 20) + 4, 1 << 22, (1 << 22) + 4, (1 << 22) + 6])
+@pytest.mark.parametrize("d,F,S,gated", [(128, 9004, 200, True), (64, 16604, 1000, False)])      # 256-token tiles
+def test_prefill_into_rows_of_z_far_apart(d, F, S, gated, ldz):
+    """Rows of Z as far apart as 32-bit offsets inside a tile reach (2^22 floats), and further: the same Z."""
+    c = synth.small_case(d + F, d, F, S, synth.DT_BF16, with_bias=True)
+    L, _ = dev_layer(c["Wg"] if gated else None, c["W1"], c["W2"], synth.ACT_SILU, synth.DT_BF16, c["bg"] if gated else None, c["b1"], c["b2"])
+    X = to_dev(c["X"], synth.DT_BF16)
+    out = []
+    for stride in (F, ldz):
+        Z = torch.empty(S * stride, dtype=torch.float32, device="cuda").view(S, stride)[:, :F]
+        Z.fill_(float("nan"))
+        idx = torch.full((1, 500), -1, dtype=torch.int32, device="cuda")
+        s = torch.full((1, F), -1.0, dtype=torch.float32, device="cuda")
+        G.griffin_prefill_select(L, X, [0, S], 500, idx, s_out=s, Z_out=Z, ldz=stride,
+                                 workspace=workspace(G.griffin_prefill_workspace_bytes(L, S, 1, True)))
+        out.append((Z, s))
+    sync()
+    (Z, s), (Zf, sf) = out
+    assert torch.equal(Z, Zf)
+    assert max_rel(Z[::37].cpu().numpy(), oracle.ff1(c["X"][::37], c["Wg"] if gated else None, c["W1"], synth.ACT_SILU, c["bg"] if gated else None, c["b1"])) <= TOL_Z
+    assert max_rel(sf.cpu().numpy(), s.cpu().numpy()) <= 1e-6      # row sums of squares in another order
+
+
 def test_prefill_with_biases_at_odd_addresses():
     """Biases need no alignment beyond their element size: vectors that start 2 bytes past an 8-byte boundary
     take the element-wise store path of the first product and give the same sets and statistic."""
