@@ -416,15 +416,24 @@ static Ff1Plan ff1_plan(const griffin_layer &L, int64_t M)
     // 1.25 us a k-tile where few tokens leave it waiting for the weights.  In ranges / so, selections (us): 40 tokens of 4096 x 11008
     // 59.8 / 54.5, 163 of 2048 x 7872 55.2 / 46.6, 32 of 704 x 2384 25.2 / 22.0; but 81 of 7744 x 9040 88.2 / 91.9.  An Eq. 2 block's
     // slabs are half as large, so it has to be cheaper by more: 50 tokens of 1088 x 3072 (compacted, too) 34.3 / 35.1, 34 of 512 x 1328 21.0 / 19.6.
-    // So do tiles of an Eq. 3 block whose rounds wait longer than FF1_SHAPES says when the sums are apart (in ranges / so): 256 x 64
-    // tiles, 196 tokens of 3648 x 9488 75.2 / 80.0, 237 of 2048 x 8912 62.9 / 65.6; 128 x 64 tiles, 100 of 6144 x 16288 105.1 / 121.3 (but 108 of
-    // 8128 x 12304, five ranges with their slabs, 130.5 / 124.1); 128 x 128 tiles with half of their tokens or less, 24 of 2816 x 18128 65.8 / 89.1,
-    // 1 of 2560 x 24768 92.4 / 99.4; 64 x 64 tiles for a quarter of the chip, 14 of 1600 x 2992 26.8 / 28.4, 1 of 1280 x 3120 27.1 / 28.6 (but 62
-    // of 896 x 4192 30.5 / 28.5).
+    // So does a single row of tiles of an Eq. 3 block of some shapes, whose rounds wait longer than FF1_SHAPES says when the sums are apart.  In
+    // ranges / so: 256 x 64, 196 tokens of 3648 x 9488 73.3 / 80.2, 219 of 3072 x 8816 64.7 / 73.6 (1728 x 3456, 585 tokens 53.2 / 52.3; 220 of 4416 x 15856, 248 tiles, 104.9 / 101.8); 128 x 64, 112
+    // of 4096 x 9280 58.1 / 66.9, 111 of 5120 x 13680 82.5 / 87.5 (196 of 3072 x 8176, two rows, 63.9 / 58.8; 108 of 8128 x 12304, five ranges
+    // with their slabs, 130.5 / 124.1); 128 x 128 with half of their tokens or less, 47 of 2560 x 17424 68.5 / 73.6, 1 of 3072 x 22800 74.5 / 77.8 (57
+    // of 3584 x 19536, two ranges, 91.7 / 86.6); 64 x 64 on a quarter of the chip, 3 of 1536 x 3072 24.1 / 26.9, 4 of 1152 x 3152 23.6 / 24.6 (4 of
+    // 1024 x 3360 23.7 / 23.7).
     if (pl.splits > 1) {
         const Ff1Tile t = ff1_tile(M, L.n, gated, true, true);
-        const bool few = t.ti == 2 && t.ni == 2 && t.tiles <= 64, low = t.ti == 4 && (t.ni == 2 ? pl.room <= 4 : M <= 64);
-        if (t.cost * (KT + 8) * (!gated || t.ti == 8 ? 2.0 : few ? 1.7 : low ? 1.45 : 1.25) <= best)
+        double line = gated ? 1.25 : 2.0;
+        if (gated && t.ti == 8 && M <= 256 && t.tiles < 224)
+            line = 1.8;
+        else if (gated && t.ti == 4 && t.ni == 2 && M <= 128 && pl.room <= 3)
+            line = 1.45;
+        else if (gated && t.ti == 4 && t.ni == 4 && M <= (pl.room == 2 ? 32 : 64))
+            line = 1.3;
+        else if (gated && t.ti == 2 && t.ni == 2 && t.tiles <= 64)
+            line = 1.7;
+        if (t.cost * (KT + 8) * line <= best)
             pl.splits = 1;
     }
     return pl;

@@ -10,13 +10,17 @@ def routes(calls):
 PARTS = [
     (4096, 11008, 40, "64x64 Eq. 3 copy", 4),
     (4608, 21712, 316, "128x128 Eq. 3", 2),
+    (3648, 9488, 196, "224x128 raw Eq. 3", 1),        # not 75 x 2 tiles of 256 x 64
+    (1728, 3456, 585, "256x64 Eq. 3 copy", 3),
+    (4416, 15856, 220, "256x64 Eq. 3 copy", 2),
+    (6144, 16288, 100, "128x128 raw Eq. 3", 1),       # not one row of 128 x 64
+    (3072, 8176, 196, "128x64 Eq. 3 copy", 4),
     (8128, 12304, 108, "128x64 Eq. 3 copy", 5),
-    (3648, 9488, 196, "224x128 raw Eq. 3", 1),        # 256 x 64 tiles would wait
-    (2048, 8912, 237, "256x128 raw Eq. 3", 1),
-    (6144, 16288, 100, "128x128 raw Eq. 3", 1),       # 128 x 64 tiles would
-    (2816, 18128, 24, "64x128 raw Eq. 3", 1),         # 128 x 128 tiles of which 24 tokens are there
-    (2560, 24768, 1, "64x128 raw Eq. 3", 1),
-    (1600, 2992, 14, "64x128 raw Eq. 3", 1),          # 47 tiles of 64 x 64
+    (2560, 17424, 47, "64x128 raw Eq. 3", 1),         # not 128 x 128 of which 47 tokens are there
+    (3072, 22800, 1, "64x128 raw Eq. 3", 1),
+    (3584, 19536, 57, "128x128 Eq. 3", 2),
+    (1536, 3072, 3, "64x128 raw Eq. 3", 1),           # not 48 tiles of 64 x 64
+    (1536, 4176, 3, "64x64 Eq. 3 copy", 6),
 ]
 
 
