@@ -22,9 +22,9 @@
 namespace griffin {
 
 // compiled in files of their own
-template <> void launch_ff1_tiles<GRIFFIN_ACT_SILU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
-template <> void launch_ff1_tiles<GRIFFIN_ACT_GELU_TANH>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
-template <> void launch_ff1_tiles<GRIFFIN_ACT_RELU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
+template <> int launch_ff1_tiles<GRIFFIN_ACT_SILU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
+template <> int launch_ff1_tiles<GRIFFIN_ACT_GELU_TANH>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
+template <> int launch_ff1_tiles<GRIFFIN_ACT_RELU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
 
 // Epilogue of the register-staged kernel: sigma, gating, store of Z, row sums of z^2.
 // Lane holds column (neuron) l31 of each 32x32 tile and rows (i>>2)*8 + lh*4 + (i&3), i = 0..15.
@@ -579,10 +579,11 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
         return GRIFFIN_OK;
     if (L.dtype == GRIFFIN_BF16) {
         const int grid = staged ? 0 : ff1_grid(p.mt * p.nt);
+        int rc = GRIFFIN_OK;
 #define FF1_ACT(ACT_)                                                                          \
     {                                                                                          \
         if (staged) launch_staged<ACT_>(p, gated, st);                                         \
-        else launch_ff1_tiles<ACT_>(p, t.ti, t.ni, gated, wide, grid, st);                     \
+        else rc = launch_ff1_tiles<ACT_>(p, t.ti, t.ni, gated, wide, grid, st);                \
     }
         switch (L.act) {
         case GRIFFIN_ACT_SILU: FF1_ACT(GRIFFIN_ACT_SILU) break;
@@ -590,7 +591,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
         default: FF1_ACT(GRIFFIN_ACT_RELU) break;
         }
 #undef FF1_ACT
-        return check_launch("ff1_bf16_mfma_kernel");
+        return rc != GRIFFIN_OK ? rc : check_launch("ff1_bf16_mfma_kernel");
     }
     return launch_f32_ff1(L, X, ldx, M, Z, ldz, *rowpart, st);
 }

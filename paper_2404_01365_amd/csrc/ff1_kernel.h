@@ -648,9 +648,10 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
 }
 
 // The whole product with its activation on this kernel, tiles of 32 ti tokens x 32 ni neurons (`wide`: an Eq. 2 block, on tiles of
-// 64 ni neurons; without it the tiles of such a block are 32 ti x 128).  The caller has set p.mt and p.nt accordingly.
+// 64 ni neurons; without it the tiles of such a block are 32 ti x 128).  The caller has set p.mt and p.nt accordingly.  Nothing is launched for
+// a shape that is not compiled: GRIFFIN_EUNSUPPORTED.
 template <int ACT>
-void launch_ff1_tiles(const Ff1Params &p, int ti, int ni, bool gated, bool wide, int grid, hipStream_t st);
+int launch_ff1_tiles(const Ff1Params &p, int ti, int ni, bool gated, bool wide, int grid, hipStream_t st);
 
 // The tile shapes that are compiled: X(ti, ni, time of a round of them, 256 x 128 = 1).  ff1_tile (ff1.hip) chooses among them.
 #define FF1_SHAPES(X)                                                                                           \
@@ -663,23 +664,34 @@ void launch_ff1_tiles(const Ff1Params &p, int ti, int ni, bool gated, bool wide,
 #define FF1_GO(...) hipLaunchKernelGGL((ff1_bf16_mfma_kernel<ACT, __VA_ARGS__>), dim3(grid), dim3(G_THREADS), 0, st, p)
 #define FF1_TILES_CASE(TI_, NI_, COST_)                                                                         \
     if (ti == TI_ && ni == NI_) {                                                                               \
-        if (gated && (p.b1 || p.bg)) FF1_GO(true, TI_, NI_, false);                                             \
-        else if (gated && (p.Zb || NI_ == 2)) FF1_GO(true, TI_, NI_, false, false, 1);                          \
-        else if (gated) FF1_GO(true, TI_, NI_, false, false, NI_ == 2 ? 1 : 0);                                 \
-        else if constexpr (FF1_SHAPE_EQ2(TI_, NI_)) FF1_GO(true, TI_, NI_, false, true);                        \
-        return;                                                                                                 \
+        if (!gated) {                                                                                           \
+            if constexpr (!FF1_SHAPE_EQ2(TI_, NI_)) return GRIFFIN_EUNSUPPORTED;                                \
+            else FF1_GO(true, TI_, NI_, false, true);                                                           \
+        } else if (p.b1 || p.bg) {                                                                              \
+            FF1_GO(true, TI_, NI_, false);                                                                      \
+        } else {                                                                                                \
+            if constexpr (NI_ != 2)                                                                             \
+                if (!p.Zb) {                                                                                    \
+                    FF1_GO(true, TI_, NI_, false, false, 0);                                                    \
+                    return GRIFFIN_OK;                                                                          \
+                }                                                                                               \
+            FF1_GO(true, TI_, NI_, false, false, 1);                                                            \
+        }                                                                                                       \
+        return GRIFFIN_OK;                                                                                      \
     }
 #define FF1_TILES_OF(ACT_)                                                                                      \
     template <>                                                                                                 \
-    void launch_ff1_tiles<ACT_>(const Ff1Params &p, int ti, int ni, bool gated, bool wide, int grid, hipStream_t st) \
+    int launch_ff1_tiles<ACT_>(const Ff1Params &p, int ti, int ni, bool gated, bool wide, int grid, hipStream_t st) \
     {                                                                                                           \
         constexpr int ACT = ACT_;                                                                               \
         if (!gated && !wide) {                                                                                  \
-            if (ti == 8) FF1_GO(false, 8, 4, false);                                                            \
-            else FF1_GO(false, 4, 4, false);                                                                    \
-            return;                                                                                             \
+            if (ti == 8 && ni == 4) FF1_GO(false, 8, 4, false);                                                 \
+            else if (ti == 4 && ni == 4) FF1_GO(false, 4, 4, false);                                            \
+            else return GRIFFIN_EUNSUPPORTED;                                                                   \
+            return GRIFFIN_OK;                                                                                  \
         }                                                                                                       \
         FF1_SHAPES(FF1_TILES_CASE)                                                                              \
+        return GRIFFIN_EUNSUPPORTED;                                                                            \
     }
 
 }  // namespace griffin

@@ -1,5 +1,10 @@
 """Which form of the prompt product a call takes, and what it makes of it (no GPU: tests/launches.py)."""
+import ctypes
+
+import pytest
+
 import launches
+import paper_2404_01365_amd as G
 
 
 def routes(calls):
@@ -27,3 +32,13 @@ PARTS = [
 def test_sums_stay_apart_in_registers_only_where_that_is_faster():
     got = routes([dict(entry="select", d=d, n=F, lens=[S]) for d, F, S, *_ in PARTS])
     assert [(*c[:3], r[0][0], r[0][3]) for c, r in zip(PARTS, got)] == PARTS
+
+
+@pytest.mark.parametrize("act", [G.ACT_SILU, G.ACT_GELU_TANH, G.ACT_RELU])
+@pytest.mark.parametrize("ti,ni,gated,wide", [(5, 4, 1, 0), (8, 1, 1, 0), (0, 0, 1, 0), (8, 2, 0, 1), (6, 2, 0, 1), (8, 3, 0, 0), (6, 4, 0, 0)])
+def test_a_shape_that_is_not_compiled_is_refused(act, ti, ni, gated, wide):
+    """The rule that chooses shapes and the list of those compiled are apart: a launch of nothing must not look like success."""
+    launch = getattr(G.lib, "_ZN7griffin16launch_ff1_tilesILi%dEEEiRKNS_9Ff1ParamsEiibbiP12ihipStream_t" % act)
+    launch.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.c_bool, ctypes.c_int, ctypes.c_void_p]
+    p = launches.Ff1Params()
+    assert launch(ctypes.byref(p), ti, ni, bool(gated), bool(wide), 8, None) == G.EUNSUPPORTED
