@@ -372,15 +372,14 @@ PREFILL_CASES = [
     (synth.DT_F32, 64, 130, [9], 130, synth.ACT_RELU, False, True),              # Eq. 2, keep all
     (synth.DT_F32, 136, 2050, [500, 21], 1000, synth.ACT_SILU, True, True),      # 64-token tiles, ragged both ways, d = 8.5 slices
     (synth.DT_F32, 8, 33, [1], 16, synth.ACT_GELU_TANH, True, False),            # half a slice of d, one token
-    (synth.DT_BF16, 512, 1000, [300], 500, synth.ACT_SILU, True, False),         # 3 x 8 tiles, ragged both
+    (synth.DT_BF16, 512, 1000, [300], 500, synth.ACT_SILU, True, False),         # 5 x 16 tiles of 64 x 64, ragged both, two sums each
     (synth.DT_BF16, 136, 260, [129, 0, 200], 77, synth.ACT_GELU_TANH, True, True),  # k tail, empty seq
     (synth.DT_BF16, 256, 384, [256], 100, synth.ACT_RELU, False, False),         # Eq. 2 on the MFMA path
-    (synth.DT_BF16, 64, 131, [1, 2, 130], 7, synth.ACT_SILU, True, False),       # one-token prompts, D_ff odd, KT = 2
+    (synth.DT_BF16, 64, 131, [1, 2, 130], 7, synth.ACT_SILU, True, False),       # one-token prompts, D_ff odd, one k-tile
     (synth.DT_BF16, 32, 40, [5], 40, synth.ACT_GELU_TANH, True, True),           # a single k-tile, keep all
-    (synth.DT_BF16, 1024, 2500, [700], 1, synth.ACT_SILU, True, False),          # k = 1, three 256-token tiles
-    (synth.DT_BF16, 64, 16520, [300], 8000, synth.ACT_RELU, False, True),        # Eq. 2 with biases, enough tiles for the
-                                                                                 # 256-column tiles; the last tile 136 wide
-    (synth.DT_BF16, 64, 33000, [100], 3000, synth.ACT_GELU_TANH, False, False),  # the same with 128-token tiles, last tile 232 wide
+    (synth.DT_BF16, 1024, 2500, [700], 1, synth.ACT_SILU, True, False),          # k = 1, 128 x 64 tiles
+    (synth.DT_BF16, 64, 16520, [300], 8000, synth.ACT_RELU, False, True),        # Eq. 2 with biases, 192 x 192 tiles, the last 8 wide
+    (synth.DT_BF16, 64, 33000, [100], 3000, synth.ACT_GELU_TANH, False, False),  # the same without biases, the last 168 wide
 ]
 
 
@@ -417,24 +416,23 @@ def test_prefill_select_matches_oracle(dtype, d, F, lens, k, act, gated, bias):
 # The matrix-core kernel runs one workgroup per CU; with more tiles than CUs (every full-size config) each
 # workgroup walks through several tiles, sends the next tile's first loads before the epilogue of the
 # current one and decides from the kind of tile it just finished (whole, or ragged in tokens or neurons)
-# how many stores may still be outstanding when it starts to read.  These cases have 280 to 780 tiles at a
-# small model width, so that the oracle stays cheap, two or three k-tiles, ragged last tiles in both
-# directions, and a token-tile count coprime to the walking stride so that whole and ragged tiles alternate
-# within one workgroup.
+# how many stores may still be outstanding when it starts to read.  These cases have more tiles than CUs (but for
+# one that says so) at a small model width, so that the oracle stays cheap, one to three k-tiles, ragged last tiles in both
+# directions.
 WALK_CASES = [
     # dtype, d, F, lens, k, act, gated, bias
-    (synth.DT_BF16, 192, 11000, [1700], 5500, synth.ACT_SILU, True, False),        # 7 x 86 = 602 tiles, lean kernel
+    (synth.DT_BF16, 192, 11000, [1700], 5500, synth.ACT_SILU, True, False),        # 224 x 128: 8 x 86 = 688 tiles, lean kernel
     (synth.DT_BF16, 128, 11000, [900, 800], 4000, synth.ACT_GELU_TANH, True, True),  # the same walk with biases, two prompts
-    (synth.DT_BF16, 128, 16600, [1000], 8000, synth.ACT_RELU, False, True),        # Eq. 2, 128-column tiles: 4 x 130 = 520
-    (synth.DT_BF16, 128, 16520, [1300], 8000, synth.ACT_GELU_TANH, False, True),   # Eq. 2, 256-column tiles: 6 x 65 = 390
-    (synth.DT_BF16, 128, 33000, [100], 9000, synth.ACT_SILU, True, False),         # 128-token tiles: 258 of them, lean
-    (synth.DT_BF16, 64, 40000, [128], 20000, synth.ACT_SILU, True, True),          # 128-token tiles with biases: 313
-    (synth.DT_BF16, 64, 66000, [90], 30000, synth.ACT_RELU, False, False),         # Eq. 2, 128-token tiles, 516 narrow tiles
-    (synth.DT_BF16, 64, 128000, [70], 50000, synth.ACT_SILU, False, True),         # Eq. 2, 128-token tiles, 500 wide tiles
+    (synth.DT_BF16, 128, 16600, [1000], 8000, synth.ACT_RELU, False, True),        # Eq. 2, 256 x 192: 4 x 87 = 348
+    (synth.DT_BF16, 128, 16520, [1300], 8000, synth.ACT_GELU_TANH, False, True),   # Eq. 2, 192 x 256: 7 x 65 = 455
+    (synth.DT_BF16, 128, 33000, [100], 9000, synth.ACT_SILU, True, False),         # 192 x 96: 344 of them, lean
+    (synth.DT_BF16, 64, 40000, [128], 20000, synth.ACT_SILU, True, True),          # 192 x 96 with biases: 417
+    (synth.DT_BF16, 64, 66000, [90], 30000, synth.ACT_RELU, False, False),         # Eq. 2, 128 x 128: 516 narrow tiles
+    (synth.DT_BF16, 64, 128000, [70], 50000, synth.ACT_SILU, False, True),         # Eq. 2, 128 x 256: 500 wide tiles
     # more than eight token tiles: the tiles are walked in panels of eight token tiles, the last panel narrower
-    (synth.DT_BF16, 64, 4000, [1500, 1190], 2000, synth.ACT_SILU, True, False),    # 11 x 32 = 352 tiles: one panel of 8, one of 3, ragged both ways
-    (synth.DT_BF16, 64, 2100, [4100], 1000, synth.ACT_GELU_TANH, True, True),      # 17 x 17 = 289 tiles: two panels of 8, one of 1
-    (synth.DT_BF16, 64, 2500, [2560], 1200, synth.ACT_RELU, False, True),          # Eq. 2, wide tiles: 10 x 10 = 100 tiles, panels of 8 and 2, no walk
+    (synth.DT_BF16, 64, 4000, [1500, 1190], 2000, synth.ACT_SILU, True, False),    # 256 x 96: 11 x 42 = 462 tiles: one panel of 8, one of 3, ragged both ways
+    (synth.DT_BF16, 64, 2100, [4100], 1000, synth.ACT_GELU_TANH, True, True),      # 192 x 96: 22 x 22 = 484 tiles: two panels of 8, one of 6
+    (synth.DT_BF16, 64, 2500, [2560], 1200, synth.ACT_RELU, False, True),          # Eq. 2, 256 x 128 narrow: 10 x 20 = 200 tiles, panels of 8 and 2, no walk
     # Z of 406 MB, more than the product keeps in the caches: it leaves through the streaming stores (24 x 130 tiles)
     (synth.DT_BF16, 64, 16640, [3100, 3000], 8000, synth.ACT_SILU, True, False),
 ]
@@ -447,20 +445,20 @@ def test_prefill_select_when_workgroups_walk_tiles(dtype, d, F, lens, k, act, ga
 
 # ------------------------------------------------------------------ prefill: short prompts, d cut into ranges
 # Few token tiles times few neuron tiles: the product runs over ranges of d that leave raw slabs, and a second kernel adds
-# them and applies sigma (64-, 128- and 256-token tiles; slabs' rows padded to four columns; the last range shorter).
+# them and applies sigma (slabs' rows padded to four columns; the last range shorter), or small tiles keep the ranges' sums apart in registers.
 RANGE_CASES = [
     # dtype, d, F, lens, k, act, gated, bias
-    (synth.DT_BF16, 1024, 1001, [1], 500, synth.ACT_SILU, True, True),             # one token, F odd (scalar stores of Z)
-    (synth.DT_BF16, 1088, 700, [40, 0, 23], 350, synth.ACT_GELU_TANH, True, False),  # 17 k-tiles, 63 tokens in three prompts
+    (synth.DT_BF16, 1024, 1001, [1], 500, synth.ACT_SILU, True, True),             # one token, F odd (scalar stores of Z), apart
+    (synth.DT_BF16, 1088, 700, [40, 0, 23], 350, synth.ACT_GELU_TANH, True, False),  # 17 k-tiles, 63 tokens in three prompts, apart
     (synth.DT_BF16, 2048, 130, [64], 65, synth.ACT_SILU, True, False),             # 64-token tile full, last neuron tile of 2
     (synth.DT_BF16, 2048, 515, [65], 200, synth.ACT_SILU, True, True),             # 128-token tile, one row more than 64
-    (synth.DT_BF16, 1024, 2000, [128], 999, synth.ACT_RELU, True, False),
-    (synth.DT_BF16, 2048, 1500, [129], 700, synth.ACT_SILU, True, False),          # 256-token tile
-    (synth.DT_BF16, 4096, 900, [300, 13], 450, synth.ACT_GELU_TANH, True, True),   # two token tiles, ragged
+    (synth.DT_BF16, 1024, 2000, [128], 999, synth.ACT_RELU, True, False),          # apart
+    (synth.DT_BF16, 2048, 1500, [129], 700, synth.ACT_SILU, True, False),          # apart, 64 x 64
+    (synth.DT_BF16, 4096, 900, [300, 13], 450, synth.ACT_GELU_TANH, True, True),   # two 192-token tiles, ragged
     (synth.DT_BF16, 2048, 1030, [33], 500, synth.ACT_RELU, False, True),           # Eq. 2: 256-column tiles, last one 6 wide
     (synth.DT_BF16, 2048, 1029, [100], 500, synth.ACT_GELU_TANH, False, False),    # Eq. 2, F odd
     (synth.DT_BF16, 2048, 2100, [260], 500, synth.ACT_RELU, False, True),          # Eq. 2, two token tiles
-    (synth.DT_BF16, 4096, 19197, [70], 9000, synth.ACT_SILU, True, False),         # 450 items: workgroups walk two of them
+    (synth.DT_BF16, 4096, 19197, [70], 9000, synth.ACT_SILU, True, False),         # 128 x 128 tiles, three sums apart
 ]
 
 
@@ -470,7 +468,7 @@ RANGE_CASES += [
     (synth.DT_BF16, 64, 260, [129, 3], 100, synth.ACT_SILU, True, False),
     (synth.DT_F32, 64, 4033, [20] * 8, 2000, synth.ACT_GELU_TANH, True, False),       # 64 x 8 workgroups, F odd
     (synth.DT_F32, 64, 4097, [20] * 8, 2000, synth.ACT_GELU_TANH, True, False),       # 65 x 8: chunks
-    # Eq. 2 without biases, 256-column tiles of 256 tokens: 6 x 65 = 390 tiles
+    # Eq. 2 without biases, 192 x 256: 7 x 65 = 455 tiles
     (synth.DT_BF16, 128, 16520, [1300], 8000, synth.ACT_RELU, False, False),
 ]
 
@@ -482,7 +480,7 @@ def test_prefill_select_of_short_prompts_in_ranges(dtype, d, F, lens, k, act, ga
 
 # ------------------------------------------------------------------ prefill: every shape of the product's tiles
 # The shape (tokens x neurons of both products; of an Eq. 2 block twice the neurons) follows from the sizes; last tiles ragged both
-# ways, one to three k-tiles where up to six stages are loaded ahead, and walks of several tiles where the shape is taken for them.
+# ways, fewer k-tiles than stages are loaded ahead, and walks of several tiles where the shape is taken for them.
 SHAPE_CASES = [
     # dtype, d, F, lens, k, act, gated, bias
     (synth.DT_BF16, 64, 700, [30], 350, synth.ACT_SILU, True, False),             # 64 x 64
@@ -505,7 +503,7 @@ SHAPE_CASES = [
     (synth.DT_BF16, 64, 16604, [1100], 8000, synth.ACT_RELU, False, False),       # Eq. 2: 192 x 256, 390 tiles
     (synth.DT_BF16, 64, 16604, [1500], 8000, synth.ACT_RELU, False, True),        # Eq. 2: 224 x 256, 455 tiles
     (synth.DT_BF16, 4096, 900, [400], 450, synth.ACT_SILU, True, False),          # ranges of d on 224-token tiles
-    # sums of several ranges kept apart in registers, the last range shorter
+    # sums of several ranges kept apart in registers, the last range shorter (of the first two; the others have one sum)
     (synth.DT_BF16, 1088, 3001, [33], 1500, synth.ACT_SILU, True, True),          # 64 x 64
     (synth.DT_BF16, 1024, 9004, [70], 4000, synth.ACT_SILU, True, False),         # 96 x 64
     (synth.DT_BF16, 1088, 9004, [128], 4000, synth.ACT_GELU_TANH, True, False),   # 128 x 64
@@ -518,9 +516,121 @@ def test_prefill_select_on_every_tile_shape(dtype, d, F, lens, k, act, gated, bi
     test_prefill_select_matches_oracle(dtype, d, F, lens, k, act, gated, bias)
 
 
+# Every compiled form of the product (test_prompt_routes.py holds the list against the library and says, without a GPU, that these sizes take
+# these routes): enough k-tiles for the rings of stages to go round and more tiles than CUs, together where the oracle's time allows it, and sums
+# kept apart where the form can; last tiles ragged.
+FORM_CASES = [
+    # d, F, tokens, act, gated, bias, form, tiles, k-tiles of a tile, sums of a tile
+    (512, 104, 35, synth.ACT_RELU, False, True, "64x128 Eq. 2", 1, 8, 1),
+    (832, 112, 38, synth.ACT_GELU_TANH, False, True, "64x128 Eq. 2", 1, 13, 4),
+    (320, 12728, 580, synth.ACT_GELU_TANH, False, True, "128x256 Eq. 2", 250, 5, 1),
+    (64, 24904, 580, synth.ACT_GELU_TANH, False, True, "128x256 Eq. 2", 490, 1, 1),
+    (384, 34320, 99, synth.ACT_RELU, False, False, "192x192 Eq. 2", 179, 6, 1),
+    (64, 37240, 268, synth.ACT_GELU_TANH, False, True, "192x192 Eq. 2", 388, 1, 1),
+    (320, 26392, 262, synth.ACT_RELU, False, True, "192x256 Eq. 2", 208, 5, 1),
+    (64, 17293, 1043, synth.ACT_GELU_TANH, False, True, "192x256 Eq. 2", 408, 1, 1),
+    (64, 36322, 600, synth.ACT_GELU_TANH, False, False, "224x256 Eq. 2", 426, 1, 1),
+    (320, 13184, 821, synth.ACT_RELU, False, False, "224x256 Eq. 2", 208, 5, 1),
+    (320, 33904, 234, synth.ACT_GELU_TANH, False, True, "256x192 Eq. 2", 177, 5, 1),
+    (64, 38464, 386, synth.ACT_RELU, False, True, "256x192 Eq. 2", 402, 1, 1),
+    (64, 18880, 1368, synth.ACT_GELU_TANH, False, False, "256x256 Eq. 2", 444, 1, 1),
+    (320, 17608, 691, synth.ACT_GELU_TANH, False, False, "256x256 Eq. 2", 207, 5, 1),
+    (320, 6680, 69, synth.ACT_RELU, False, True, "128x128 Eq. 2 narrow", 53, 5, 1),
+    (320, 264, 5586, synth.ACT_RELU, False, False, "256x128 Eq. 2 narrow", 66, 5, 1),
+    (64, 10824, 1387, synth.ACT_GELU_TANH, False, False, "256x128 Eq. 2 narrow", 510, 1, 1),
+    (320, 24752, 69, synth.ACT_GELU_TANH, True, False, "128x128 Eq. 3", 194, 5, 1),
+    (128, 12568, 577, synth.ACT_RELU, True, False, "128x128 Eq. 3", 495, 2, 1),
+    (1408, 16812, 260, synth.ACT_GELU_TANH, True, False, "128x128 Eq. 3", 396, 22, 2),
+    (320, 33624, 109, synth.ACT_SILU, True, False, "192x96 Eq. 3", 351, 5, 1),
+    (320, 25841, 271, synth.ACT_GELU_TANH, True, False, "192x128 Eq. 3", 404, 5, 1),
+    (384, 8224, 594, synth.ACT_SILU, True, False, "224x128 Eq. 3", 195, 6, 1),
+    (64, 26696, 385, synth.ACT_GELU_TANH, True, False, "224x128 Eq. 3", 418, 1, 1),
+    (320, 9816, 799, synth.ACT_SILU, True, False, "256x96 Eq. 3", 412, 5, 1),
+    (320, 12856, 454, synth.ACT_GELU_TANH, True, False, "256x128 Eq. 3", 202, 5, 1),
+    (64, 24760, 490, synth.ACT_RELU, True, False, "256x128 Eq. 3", 388, 1, 1),
+    (512, 37728, 34, synth.ACT_GELU_TANH, True, True, "64x64 Eq. 3 biases", 590, 8, 1),
+    (768, 35536, 34, synth.ACT_RELU, True, True, "64x64 Eq. 3 biases", 556, 12, 3),
+    (576, 9880, 65, synth.ACT_RELU, True, True, "96x64 Eq. 3 biases", 155, 9, 1),
+    (512, 5536, 135, synth.ACT_SILU, True, True, "96x64 Eq. 3 biases", 174, 8, 2),
+    (512, 144, 6038, synth.ACT_SILU, True, True, "128x64 Eq. 3 biases", 144, 8, 1),
+    (576, 3432, 291, synth.ACT_GELU_TANH, True, True, "128x64 Eq. 3 biases", 162, 9, 2),
+    (448, 25712, 65, synth.ACT_SILU, True, True, "128x128 Eq. 3 biases", 201, 7, 1),
+    (64, 12648, 577, synth.ACT_RELU, True, True, "128x128 Eq. 3 biases", 495, 1, 1),
+    (320, 8560, 169, synth.ACT_RELU, True, True, "192x64 Eq. 3 biases", 134, 5, 1),
+    (640, 8280, 147, synth.ACT_SILU, True, True, "192x64 Eq. 3 biases", 130, 10, 2),
+    (384, 34032, 101, synth.ACT_GELU_TANH, True, True, "192x96 Eq. 3 biases", 355, 6, 1),
+    (320, 30136, 281, synth.ACT_RELU, True, True, "192x128 Eq. 3 biases", 472, 5, 1),
+    (320, 24904, 399, synth.ACT_RELU, True, True, "224x128 Eq. 3 biases", 390, 5, 1),
+    (320, 8525, 199, synth.ACT_GELU_TANH, True, True, "256x64 Eq. 3 biases", 134, 5, 1),
+    (64, 5432, 1389, synth.ACT_RELU, True, True, "256x64 Eq. 3 biases", 510, 1, 1),
+    (1024, 4472, 415, synth.ACT_SILU, True, True, "256x64 Eq. 3 biases", 140, 16, 2),
+    (320, 33858, 196, synth.ACT_GELU_TANH, True, True, "256x96 Eq. 3 biases", 353, 5, 1),
+    (320, 12504, 455, synth.ACT_SILU, True, True, "256x128 Eq. 3 biases", 196, 5, 1),
+    (64, 24648, 476, synth.ACT_GELU_TANH, True, True, "256x128 Eq. 3 biases", 386, 1, 1),
+    (576, 34114, 44, synth.ACT_SILU, True, False, "64x64 Eq. 3 copy", 534, 9, 1),
+    (768, 37352, 34, synth.ACT_GELU_TANH, True, False, "64x64 Eq. 3 copy", 584, 12, 3),
+    (896, 34256, 33, synth.ACT_SILU, True, False, "64x64 Eq. 3 copy", 536, 14, 3),
+    (512, 8427, 66, synth.ACT_GELU_TANH, True, False, "96x64 Eq. 3 copy", 132, 8, 1),
+    (512, 5648, 145, synth.ACT_RELU, True, False, "96x64 Eq. 3 copy", 178, 8, 2),
+    (512, 152, 5651, synth.ACT_RELU, True, False, "128x64 Eq. 3 copy", 135, 8, 1),
+    (512, 4541, 206, synth.ACT_SILU, True, False, "128x64 Eq. 3 copy", 142, 8, 2),
+    (384, 9568, 129, synth.ACT_GELU_TANH, True, False, "192x64 Eq. 3 copy", 150, 6, 1),
+    (640, 8720, 148, synth.ACT_RELU, True, False, "192x64 Eq. 3 copy", 137, 10, 2),
+    (384, 1545, 5074, synth.ACT_GELU_TANH, True, False, "256x64 Eq. 3 copy", 500, 6, 1),
+    (960, 4600, 393, synth.ACT_RELU, True, False, "256x64 Eq. 3 copy", 144, 15, 2),
+    (2112, 3817, 38, synth.ACT_RELU, True, True, "64x128 raw Eq. 3", 210, 5, 1),
+    (1856, 2008, 115, synth.ACT_SILU, True, True, "128x128 raw Eq. 3", 96, 5, 1),
+    (1600, 622, 325, synth.ACT_RELU, True, True, "192x128 raw Eq. 3", 50, 5, 1),
+    (2304, 16496, 129, synth.ACT_RELU, True, False, "192x128 raw Eq. 3", 387, 12, 1),
+    (1920, 168, 1305, synth.ACT_GELU_TANH, True, True, "224x128 raw Eq. 3", 72, 5, 1),
+    (2048, 105, 249, synth.ACT_GELU_TANH, True, True, "256x128 raw Eq. 3", 8, 4, 1),
+    (3200, 900, 249, synth.ACT_SILU, True, False, "256x128 raw Eq. 3", 80, 5, 1),
+    (896, 34256, 7, synth.ACT_SILU, True, False, "64x128 raw Eq. 3", 804, 5, 1),
+    (1088, 33300, 40, synth.ACT_RELU, False, True, "64x256 raw one matrix", 393, 6, 1),
+]
+FORM_PHASE_CASES = [
+    # d, F, tokens, form of the first product, tiles, k-tiles, sums
+    (384, 27328, 102, "128x128 Eq. 3 copy", 214, 6, 1),
+    (64, 12608, 587, "128x128 Eq. 3 copy", 495, 1, 1),
+    (384, 20480, 268, "192x96 Eq. 3 copy", 428, 6, 1),
+    (320, 6464, 940, "192x128 Eq. 3 copy", 255, 5, 1),
+    (64, 16576, 526, "192x128 Eq. 3 copy", 390, 1, 1),
+    (64, 3648, 3469, "224x128 Eq. 3 copy", 464, 1, 1),
+    (320, 12736, 430, "224x128 Eq. 3 copy", 200, 5, 1),
+    (320, 19712, 427, "256x96 Eq. 3 copy", 412, 5, 1),
+    (320, 15168, 504, "256x128 Eq. 3 copy", 238, 5, 1),
+    (64, 10944, 1177, "256x128 Eq. 3 copy", 430, 1, 1),
+]
+FORM_OUT_CASES = [
+    # d, F, tokens, form, tiles, k-tiles
+    (32, 384, 35, "64x256 raw one matrix", 1, 6),
+    (81376, 320, 74, "128x256 raw one matrix", 318, 5),
+    (36, 320, 152, "192x256 raw one matrix", 1, 5),
+    (36, 384, 193, "224x256 raw one matrix", 1, 6),
+    (16488, 64, 773, "224x256 raw one matrix", 260, 1),
+    (32, 320, 229, "256x256 raw one matrix", 1, 5),
+    (9520, 64, 1571, "256x256 raw one matrix", 266, 1),
+]
+
+
+@pytest.mark.parametrize("d,F,S,act,gated,bias", [c[:6] for c in FORM_CASES])
+def test_prefill_select_on_every_form(d, F, S, act, gated, bias):
+    test_prefill_select_matches_oracle(synth.DT_BF16, d, F, [S], F // 2, act, gated, bias)
+
+
+@pytest.mark.parametrize("d,F,S", [c[:3] for c in FORM_PHASE_CASES])
+def test_prompt_phase_on_every_form(d, F, S):
+    test_prompt_phase_is_selection_plus_prompt_output_from_one_z(synth.DT_BF16, d, F, [S], F // 2, True, False)
+
+
+@pytest.mark.parametrize("d,F,S", [c[:3] for c in FORM_OUT_CASES])
+def test_prompt_output_on_every_form(d, F, S):
+    test_prompt_output_of_few_tokens(d, F, S)
+
+
 @pytest.mark.parametrize("d,F,lens,k,gated,bias", [
     (64, 704, [30], 300, True, False),           # 64 x 64
-    (64, 16608, [399], 8000, True, False),       # 256 x 96, 346 tiles; the second product on 224-token tiles
+    (64, 16608, [399], 8000, True, False),       # 256 x 96, 346 tiles
     (64, 16608, [250], 8000, True, True),        # 256 x 96
     (128, 2048, [300], 1000, True, True),        # the second product on 192-token tiles
 ])
@@ -560,10 +670,41 @@ def test_prefill_takes_a_workspace_without_room_for_the_slabs():
     np.testing.assert_array_equal(idx.cpu().numpy()[0], oracle.topk(s_ref[0], k))
 
 
+def test_a_workspace_without_room_for_the_partials_of_narrow_tiles():
+    """256 x 96 tiles leave a third more row partials than 128-neuron tiles, behind the rest of the workspace: the least that is accepted
+    gives the same answer on 128-neuron tiles, in a selection and in a prompt phase (with the bf16 copy of Z)."""
+    d, F, S, k = 64, 16576, 399, 8000
+    c = synth.small_case(7, d, F, S, synth.DT_BF16)
+    W1 = c["W1"].copy()
+    _, (s_ref,) = open_margin([c["X"]], c["Wg"], W1, synth.ACT_SILU, synth.DT_BF16, [k])
+    L, _ = dev_layer(c["Wg"], W1, c["W2"], synth.ACT_SILU, synth.DT_BF16)
+    X, W2p = to_dev(c["X"], synth.DT_BF16), to_dev(np.ascontiguousarray(c["W2"].T), synth.DT_BF16)
+    partials = (S * ((F + 95) // 96) * 4 + 255) // 256 * 256
+    Ys = []
+    for phase in (False, True):
+        query = G.griffin_prompt_phase_workspace_bytes(L, S, 1) if phase else G.griffin_prefill_workspace_bytes(L, S, 1, False)
+        for nbytes in (query, query - partials):
+            idx = torch.full((1, k), -1, dtype=torch.int32, device="cuda")
+            s = torch.full((1, F), -1.0, dtype=torch.float32, device="cuda")
+            Y = torch.full((S, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+            ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+            if phase:
+                G.griffin_prompt_phase(L, W2p, X, [0, S], k, idx, Y, s_out=s, workspace=ws)
+                Ys.append(Y)
+            else:
+                G.griffin_prefill_select(L, X, [0, S], k, idx, s_out=s, workspace=ws)
+            sync()
+            assert max_rel(s.cpu().numpy()[0], s_ref) <= TOL_S
+            np.testing.assert_array_equal(idx.cpu().numpy()[0], oracle.topk(s_ref, k))
+    assert torch.equal(*Ys)          # Z does not depend on the tiles
+    Z_ref = oracle.ff1(c["X"], c["Wg"], W1, synth.ACT_SILU)
+    assert max_rel(to_host(Ys[0]), oracle.ff2(Z_ref, c["W2"], None)) <= TOL_OUT[synth.DT_BF16]
+
+
 @pytest.mark.parametrize("d,F,lens,k,gated,bias", [
-    (192, 11000, [1700], 5000, True, False),     # the first product leaves the bf16 copy of Z while it walks 602 tiles
+    (192, 11000, [1700], 5000, True, False),     # 224 x 128, 688 tiles (no bf16 copy of Z: 11000 is no whole number of k-tiles)
     (128, 11000, [1000, 700], 5000, True, True), # the same with biases
-    (64, 40000, [100], 20000, True, False),      # 128-token tiles, 313 of them
+    (64, 40000, [100], 20000, True, False),      # 192 x 96 with the bf16 copy, 417 of them
 ])
 def test_prompt_phase_when_workgroups_walk_tiles(d, F, lens, k, gated, bias):
     test_prompt_phase_is_selection_plus_prompt_output_from_one_z(synth.DT_BF16, d, F, lens, k, gated, bias)

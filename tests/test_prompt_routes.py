@@ -5,6 +5,8 @@ import pytest
 
 import launches
 import paper_2404_01365_amd as G
+import test_gpu_parity as cases
+import test_kernel_resources as resources
 
 
 def routes(calls):
@@ -42,3 +44,28 @@ def test_a_shape_that_is_not_compiled_is_refused(act, ti, ni, gated, wide):
     launch.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.c_bool, ctypes.c_int, ctypes.c_void_p]
     p = launches.Ff1Params()
     assert launch(ctypes.byref(p), ti, ni, bool(gated), bool(wide), 8, None) == G.EUNSUPPORTED
+
+
+def test_the_gpu_cases_reach_every_form_as_they_say():
+    calls = [dict(entry="select", d=d, n=F, lens=[S], act=act, gated=gated, bias=bias) for d, F, S, act, gated, bias, *_ in cases.FORM_CASES]
+    calls += [dict(entry="phase", d=d, n=F, lens=[S]) for d, F, S, *_ in cases.FORM_PHASE_CASES]
+    calls += [dict(entry="out", d=d, n=F, lens=[S]) for d, F, S, *_ in cases.FORM_OUT_CASES]
+    listed = [c[6:] for c in cases.FORM_CASES] + [c[3:] for c in cases.FORM_PHASE_CASES] + [(*c[3:], 1) for c in cases.FORM_OUT_CASES]
+    got = [r[0] for r in routes(calls)]
+    assert [(c, r) for c, r in zip(calls, got) if r not in listed] == []
+    assert got == listed
+    # ... and the second product of a prompt phase, and outputs of few tokens, in the lists that have been there
+    got += [r for rs in routes([dict(entry="out", d=d, n=F, lens=[S]) for d, F, S in ((4200, 320, 6000), (2048, 128, 300), (131404, 128, 5))]) for r in rs]
+    compiled = {launches.form(n) for n in resources.kernels()} - {None}
+    assert compiled - {r[0] for r in got} == set()
+    for form in compiled:
+        _, tiles, kts, sums = zip(*(r for r in got if r[0] == form))
+        deep = form.startswith(("64x64", "96x64", "128x64", "64x128 Eq. 2"))       # four stages or more
+        assert max(kts) >= (8 if deep else 5), form
+
+
+def test_the_least_workspace_takes_tiles_of_128_neurons():
+    calls = [dict(entry=e, d=64, n=16576, lens=[399], least=least) for e in ("select", "phase") for least in (False, True)]
+    assert [r[0][0] for r in routes(calls)] == ["256x96 Eq. 3", "192x128 Eq. 3", "256x96 Eq. 3 copy", "192x128 Eq. 3 copy"]
+    calls = [dict(entry="select", d=1024, n=1000, lens=[40], least=least) for least in (False, True)]
+    assert [r[0][::3] for r in routes(calls)] == [("64x64 Eq. 3 copy", 4), ("128x128 Eq. 3", 1)]
