@@ -19,8 +19,8 @@
 //    blocks, so that row strides of a power of two do not send them all to the same memory channels at a time.
 //    Measured on the gate and up rows (medians of the kernel trace, each with the ~4 us of a dependent dispatch in it):
 //    5120 x 6912 (142 MB), 16 rows 31 us (34 with five blocks ahead; 38 when rows were streamed through LDS two neurons at a time with two of sixteen
-//    MFMA columns in use; 42 with loads of sixteen half lines instead of eight whole ones); 3072 x 12288, 40 rows 37 us (three
-//    passes of 32 in that form); 4096 x 14336 masked 44 us, as in that form.
+//    MFMA columns in use; 42 with loads of sixteen half lines instead of eight whole ones); 3072 x 12288, 40 rows 35 us (three
+//    passes of 32 in that form); 4096 x 14336 masked 41 us (44).
 //  * ff_batch_down_kernel: the second line.  Giving every workgroup all d columns would cost one [rows][d] partial per
 //    workgroup, so the work is cut in two directions: a workgroup owns 512 columns and one of NR ranges of neurons, and
 //    writes one [rows][512] partial into the partial-row buffer that the single-row path uses (NR rows per batch row).
@@ -290,7 +290,8 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
 // No wave waits for another after the first barrier.
 // Ring slots per wave: the pieces of one step are on their way while those of another are used, 32 KB a CU.  With three (64 KB) whole
 // calls of 16 rows of 1024 x 5504 take 19.5 us (18.7 with two), 40 of 3072 x 12288 63.3 (61.9), 60 of 2048 x 9000 48.9 (47.3), 16 of 5120 x 6912
-// 52.2 (51.5); the masked pass of 4096 x 14336 and Eq. 2 blocks are the same either way.
+// 52.2 (51.5); the masked pass of 4096 x 14336 is the same either way.  With Z in fp32: 50 of 2176 x 10610 90.2 (88.3), of its Eq. 2 block 77.1
+// (75.0), 30 of 1280 x 6425 31.3 (30.2), 11 of 6144 x 6734 57.5 (56.9), 16 of 7680 x 7000 75.9 (75.0).
 constexpr int BD_DEPTH = 2;
 constexpr int BD_REGION = 66;            // 16-byte units per 8-row region: 1 KB of rows + 32 B, so that the four
                                          // regions a gather touches (rows 8q + i) start on different LDS banks

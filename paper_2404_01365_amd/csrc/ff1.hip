@@ -605,6 +605,8 @@ bool gemm_nt_partials_ok(int64_t M, int32_t N, int32_t K, int64_t lda, int64_t l
            lda <= (1 << 21) && ldb <= (1 << 21);
 }
 
+// The ranges are priced for tiles of 256 or 128 tokens, one workgroup a CU, whatever launch_plain takes of lower ones: they also decide the workspace
+// that a call has to bring, which stays what it was.
 void gemm_nt_split_plan(int64_t M, int32_t N, int32_t K, int *splits, int *kt_per_split)
 {
     const int bm = M > 128 ? 256 : 128;

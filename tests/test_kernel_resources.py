@@ -78,3 +78,19 @@ def test_rows_that_go_four_at_a_time_leave_room_for_three_workgroups(bf16, gated
     for bias in (0, 1):
         hits = [k for n, k in kernels().items() if re.search(name("ff_decode_kernel", bf16, gated, 0, bias, rows=4), n)]
         assert len(hits) == 1 and hits[0][".group_segment_fixed_size"] <= 48 * 1024
+
+
+def test_forms_of_the_prompt_product_keep_their_registers():
+    """One wave a SIMD: nothing in scratch but for the largest tile of an Eq. 2 block.  Raw products of 64 tokens go two workgroups a CU."""
+    import launches
+    seen = 0
+    for n, k in kernels().items():
+        form = launches.form(n)
+        if form is None:
+            continue
+        seen += 1
+        assert k[".private_segment_fixed_size"] <= (64 if form == "256x256 Eq. 2" else 0), n
+        assert k[".group_segment_fixed_size"] <= 160 * 1024
+        if form in ("64x128 raw Eq. 3", "64x256 raw one matrix"):
+            assert k[".vgpr_count"] <= 256 and k[".group_segment_fixed_size"] <= 80 * 1024
+    assert seen == 121                   # 37 of each activation and ten raw products
