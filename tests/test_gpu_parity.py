@@ -351,6 +351,23 @@ def test_topk_matches_oracle(n, k):
         np.testing.assert_array_equal(got[r], oracle.topk(s[r], k))
 
 
+# row lengths at both sides of the lines between the forms of the top-k kernel, and of the piece that a wavefront has in them
+@pytest.mark.parametrize("n", [1, 63, 64, 257, 1023, 4095, 4097, 8192, 12289, 16384, 20479, 24577, 28672, 28673, 32767, 32768, 32769])
+def test_topk_of_rows_that_fill_few_bins(n):
+    """Rows whose range is one outlier, whose k-th value ties with thousands, that are all alike, of denormals, over the whole exponent."""
+    rng = np.random.default_rng(n)
+    s = np.stack([np.where(np.arange(n) == n // 2, 1e30, 1 + rng.integers(0, 50, n) * 2.0 ** -23), rng.integers(0, 4, n) * 0.25, np.full(n, 0.7),
+                  rng.integers(0, 3, n) * 2.0 ** -149, np.exp(40 * rng.standard_normal(n)).clip(1e-38, 3e38)]).astype(np.float32)
+    for k in sorted({1, (n + 2) // 3, max(1, n - 1), n}):
+        out = torch.full((s.shape[0] + 1, k), -1, dtype=torch.int32, device="cuda")
+        G.griffin_topk(torch.from_numpy(s).cuda(), k, out[:-1])
+        sync()
+        got = out.cpu().numpy()
+        for r in range(s.shape[0]):
+            np.testing.assert_array_equal(got[r], oracle.topk(s[r], k))
+        assert (got[-1] == -1).all()          # nothing behind the last row
+
+
 def test_stat_shared_matches_oracle():
     rng = np.random.default_rng(8)
     n, B = 1000, 4
