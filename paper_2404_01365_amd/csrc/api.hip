@@ -346,9 +346,8 @@ int griffin_prompt_phase(const griffin_layer *L, const void *W2p, int64_t ldw, c
         return rc;
     if ((rc = launch_stat(Z, L->n, rowpart, nt, total, L->n, seqs, s2part, s, s_out, st)) != GRIFFIN_OK)
         return rc;
-    if ((rc = launch_topk(s, n_seqs, L->n, k, idx_out, st)) != GRIFFIN_OK)
-        return rc;
-    return launch_ff2(Z, L->n, total, L->n, L->d, bf16, W2p, ldw, L->b2, Y, ldy, ws2, second, st, fuse);
+    const TopkJob topk = {s, idx_out, n_seqs, L->n, k};
+    return launch_ff2(Z, L->n, total, L->n, L->d, bf16, W2p, ldw, L->b2, Y, ldy, ws2, second, st, fuse, &topk);
 }
 
 int griffin_trace_next_decode(void *event_begin, void *event_mid, void *event_end)

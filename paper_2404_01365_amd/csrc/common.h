@@ -139,6 +139,13 @@ int check_launch(const char *what);                  // hipGetLastError -> statu
         }                                                                                                              \
     }
 
+// top-k of rows of scores [rows][n], on its own or in the launch of other work that does not need it
+struct TopkJob {
+    const float *scores;
+    int32_t *idx;            // [rows][k]
+    int32_t rows, n, k;
+};
+
 // launchers (one per source file); all return a griffin_status
 // rowpart: room of ff1_ntiles() floats a token, on return where the nt_out partials of each are.  tail (optional): room of
 // ff1_tail_bytes().  Zb (optional): a bf16 copy of Z [M][ldzb] written by the same epilogue when ff1_can_write_zb() says so
@@ -153,7 +160,7 @@ int f32_ntiles(int32_t n);
 int launch_f32_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz, float *rowpart,
                    hipStream_t st);
 int launch_f32_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, bool bf16, const void *W2p, int64_t ldw,
-                   const void *b2, void *Y, int64_t ldy, hipStream_t st);
+                   const void *b2, void *Y, int64_t ldy, hipStream_t st, const TopkJob *topk);
 int launch_stat(const float *Z, int64_t ldz, const float *rowpart, int nt, int64_t M, int32_t F,
                 const SeqTable &seqs, float *s2part, float *s, float *s_out, hipStream_t st);
 int64_t stat_max_chunks(int64_t total_tokens, int32_t n_seqs, int32_t F);
@@ -170,10 +177,11 @@ bool gemm_nt_partials_ok(int64_t M, int32_t N, int32_t K, int64_t lda, int64_t l
 void gemm_nt_split_plan(int64_t M, int32_t N, int32_t K, int *splits, int *kt_per_split);
 int launch_gemm_nt_partials(const void *A, int64_t lda, const void *B, int64_t ldb, int64_t M, int32_t N, int32_t K,
                             int splits, int kt_per_split, float *C, int64_t ldc, hipStream_t st);
-// zb_ready: the bf16 copy of Z already sits at the head of ws (written by the first GEMM's epilogue)
+// zb_ready: the bf16 copy of Z already sits at the head of ws (written by the first GEMM's epilogue).  topk (optional) is done
+// as well, in the last launch where that can carry it
 int launch_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, bool bf16, const void *W2p,
                int64_t ldw, const void *b2, void *Y, int64_t ldy, float *ws, size_t ws_bytes, hipStream_t st,
-               bool zb_ready = false);
+               bool zb_ready = false, const TopkJob *topk = nullptr);
 bool ff2_takes_zb(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, bool bf16, const void *W2p, int64_t ldw);
 size_t ff2_workspace_bytes(int64_t M, int32_t F, int32_t d);
 

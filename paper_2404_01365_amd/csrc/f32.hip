@@ -9,11 +9,11 @@
 // and component c of them is its operand of the c-th MFMA: the order of the contraction differs from memory order in the
 // same way on both sides.  (A 64 x 64 FMA tile staged through LDS in 16-element steps, one latency per step and 11
 // workgroups, took 30 us where this takes 7 on 64 tokens of a 256 x 688 block; one thread per output, 688 uncoalesced steps
-// each, took 89 us where this takes 8 for the output of the same prompt; the whole prompt phase of 256 tokens through a
+// each, took 89 us where this took 8 for the output of the same prompt; the whole prompt phase of 256 tokens through a
 // 1024 x 4096 block 2021 -> 123 us, of 1500 tokens through a bf16 1024 x 4002 block 10046 -> 465 us.)  Operands come out of
 // the L2s once per tile, which is what bounds long prompts: they take 64-token tiles as soon as those fill the chip
 // (selection from 2048 tokens of a 1024 x 4096 block: 584 us with 32, 472 with 64).
-#include "common.h"
+#include "topk_row.h"
 
 namespace griffin {
 
@@ -62,53 +62,55 @@ __device__ __forceinline__ f32x4_f fn_load(const void *row, int k, int K)
 
 // ACT: sigma and the row sums of the first contraction; else a plain product.  BBF16: B, the biases and a plain
 // product's C are bf16.  MT: 16-token tiles per workgroup.
-template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT>
-__global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
+// WAVES: wavefronts of the workgroup, of which each has every WAVES-th slice.
+// CT: its 16-column tiles (two, or one of a plain product).
+template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT, int WAVES, int CT = 2>
+__device__ __forceinline__ void f32_nt_tile(const F32NtParams &p, int bx, int by, float (*part)[GATED ? 2 : 1][MT * 16][FN_LD])
 {
     constexpr int NMAT = GATED ? 2 : 1, ES = BBF16 ? 2 : 4, S = 2;
-    __shared__ float part[FN_WAVES][NMAT][MT * 16][FN_LD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, q = lane >> 4;
-    const int m0 = blockIdx.x * (MT * 16), n0 = blockIdx.y * FN_COLS;
+    const int m0 = bx * (MT * 16), n0 = by * (CT * 16);
+    static_assert(CT * 16 == FN_COLS || !ACT, "rowpart has one sum of FN_COLS columns");
 
     // rows past the end repeat the last one; what they give is not stored
     const float *ar[MT];
-    const char *br[NMAT][2];
+    const char *br[NMAT][CT];
 #pragma unroll
     for (int t = 0; t < MT; ++t)
         ar[t] = p.A + (int64_t)min(m0 + t * 16 + r16, p.M - 1) * p.lda;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < CT; ++t) {
         const int64_t bo = (int64_t)min(n0 + t * 16 + r16, p.N - 1) * p.ldb * ES;
         br[0][t] = (const char *)p.B + bo;
         if (GATED)
             br[NMAT - 1][t] = (const char *)p.Bg + bo;
     }
-    f32x4_f acc[NMAT][MT][2];
+    f32x4_f acc[NMAT][MT][CT];
 #pragma unroll
     for (int m = 0; m < NMAT; ++m)
 #pragma unroll
-        for (int t = 0; t < 2 * MT; ++t)
-            acc[m][t >> 1][t & 1] = (f32x4_f){0.0f, 0.0f, 0.0f, 0.0f};
+        for (int t = 0; t < CT * MT; ++t)
+            acc[m][t / CT][t % CT] = (f32x4_f){0.0f, 0.0f, 0.0f, 0.0f};
 
-    f32x4_f a0[S][MT], a1[S][MT], b0[S][NMAT][2], b1[S][NMAT][2];
-// S slices from number s_ on (slices of this wave are FN_WAVES apart)
+    f32x4_f a0[S][MT], a1[S][MT], b0[S][NMAT][CT], b1[S][NMAT][CT];
+// S slices from number s_ on (slices of this wave are WAVES apart)
 #define FN_LOAD(a_, b_, s_)                                                                          \
     _Pragma("unroll") for (int u = 0; u < S; ++u)                                                    \
     {                                                                                                \
-        const int k_ = (((s_) + u) * FN_WAVES + wave) * FN_K + q * 4;                                \
+        const int k_ = (((s_) + u) * WAVES + wave) * FN_K + q * 4;                                \
         _Pragma("unroll") for (int t = 0; t < MT; ++t) a_[u][t] = fn_load<false, VEC>(ar[t], k_, p.K); \
-        _Pragma("unroll") for (int t = 0; t < 2 * NMAT; ++t)                                         \
-            b_[u][t >> 1][t & 1] = fn_load<BBF16, VEC>(br[t >> 1][t & 1], k_, p.K);                  \
+        _Pragma("unroll") for (int t = 0; t < CT * NMAT; ++t)                                        \
+            b_[u][t / CT][t % CT] = fn_load<BBF16, VEC>(br[t / CT][t % CT], k_, p.K);                \
     }
 #define FN_MFMA(a_, b_)                                                                              \
     _Pragma("unroll") for (int u = 0; u < S; ++u)                                                    \
         _Pragma("unroll") for (int c = 0; c < 4; ++c)                                                \
             _Pragma("unroll") for (int m = 0; m < NMAT; ++m)                                         \
-                _Pragma("unroll") for (int t = 0; t < 2 * MT; ++t)                                      \
-                    acc[m][t >> 1][t & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_[u][t >> 1][c], b_[u][m][t & 1][c], acc[m][t >> 1][t & 1], 0, 0, 0);
+                _Pragma("unroll") for (int t = 0; t < CT * MT; ++t)                                  \
+                    acc[m][t / CT][t % CT] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_[u][t / CT][c], b_[u][m][t % CT][c], acc[m][t / CT][t % CT], 0, 0, 0);
 
-    const int steps = ((p.K + FN_K - 1) / FN_K + FN_WAVES - 1) / FN_WAVES;
+    const int steps = ((p.K + FN_K - 1) / FN_K + WAVES - 1) / WAVES;
     FN_LOAD(a0, b0, 0)
     int s = 0;
     for (; s + 2 * S < steps; s += 2 * S) {
@@ -131,11 +133,23 @@ __global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
 #pragma unroll
     for (int m = 0; m < NMAT; ++m)
 #pragma unroll
-        for (int t = 0; t < 2 * MT; ++t)
+        for (int t = 0; t < CT * MT; ++t)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                part[wave][m][(t >> 1) * 16 + q * 4 + i][(t & 1) * 16 + r16] = acc[m][t >> 1][t & 1][i];
+                part[wave][m][(t / CT) * 16 + q * 4 + i][(t % CT) * 16 + r16] = acc[m][t / CT][t % CT][i];
     __syncthreads();
+    if (!ACT) {               // a thread has one element
+        for (int e = tid; e < MT * 16 * CT * 16; e += WAVES * 64) {
+            const int row = e / (CT * 16), c = e % (CT * 16), col = n0 + c;
+            float t = 0.0f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w)
+                t += part[w][0][row][c];
+            if (m0 + row < p.M && col < p.N)
+                store_scalar<BBF16>(p.C, (int64_t)(m0 + row) * p.ldc + col, t + (p.b ? load_scalar<BBF16>(p.b, col) : 0.0f));
+        }
+        return;
+    }
     // thread: two neighbouring columns of one row; the sixteen threads of a row are one DPP row of the wavefront
     const int c0 = (tid & 15) * 2;
 #pragma unroll
@@ -148,7 +162,7 @@ __global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
             for (int e = 0; e < 2; ++e) {
                 float t = 0.0f;
 #pragma unroll
-                for (int w = 0; w < FN_WAVES; ++w)
+                for (int w = 0; w < WAVES; ++w)
                     t += part[w][m][row][c0 + e];
                 v[m][e] = t;
             }
@@ -157,23 +171,46 @@ __global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
             const int col = n0 + c0 + e;
             if (col < p.N) {
                 float u = v[0][e] + (p.b ? load_scalar<BBF16>(p.b, col) : 0.0f);
-                if (ACT) {
-                    if (GATED)
-                        u = act_apply(p.act, v[NMAT - 1][e] + (p.bg ? load_scalar<BBF16>(p.bg, col) : 0.0f)) * u;
-                    else
-                        u = act_apply(p.act, u);
-                    sq = fmaf(u, u, sq);
-                }
+                if (GATED)
+                    u = act_apply(p.act, v[NMAT - 1][e] + (p.bg ? load_scalar<BBF16>(p.bg, col) : 0.0f)) * u;
+                else
+                    u = act_apply(p.act, u);
+                sq = fmaf(u, u, sq);
                 if (grow < p.M)
                     store_scalar<BBF16>(p.C, (int64_t)grow * p.ldc + col, u);
             }
         }
-        if (ACT) {
-            sq = row16_sum(sq);
-            if ((tid & 15) == 0 && grow < p.M)
-                p.rowpart[(int64_t)grow * p.nt + blockIdx.y] = sq;
-        }
+        sq = row16_sum(sq);
+        if ((tid & 15) == 0 && grow < p.M)
+            p.rowpart[(int64_t)grow * p.nt + by] = sq;
     }
+}
+
+template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT>
+__global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
+{
+    __shared__ float part[FN_WAVES][GATED ? 2 : 1][MT * 16][FN_LD];
+    f32_nt_tile<ACT, GATED, BBF16, VEC, MT, FN_WAVES>(p, blockIdx.x, blockIdx.y, part);
+}
+
+// Outputs of little work (at most a 32 x 32 tile for every CU): sixteen wavefronts halve the chain of loads, T = 1 has tiles of 16 x 16 (a
+// CU takes its two operands in at some 24 B a clock: 64 tokens of 256 x 688 are 16 tiles of 176 KB, or 64 of 88), and the top-k
+// of a prompt phase, which needs one CU a sequence and nothing of the product, goes in the first workgroups.  Whole prompt phases, us, eight
+// wavefronts and the top-k before / so: 64 tokens of 256 x 688 23.0 / 16.8 (16 x 16 tiles; 21.9 with 32 x 32), 77 of a bf16 512 x 1001 41.7 / 25.6,
+// 200 of 1024 x 4096 113 / 103 (832 tiles of 16 x 16, more bytes a CU: 32 x 32).
+constexpr int FN_WIDE_WAVES = TOPK_THREADS / 64;
+template <bool BBF16, bool VEC, int T, int KPT>
+__global__ __launch_bounds__(TOPK_THREADS) void f32_out_topk_kernel(F32NtParams p, TopkJob t)
+{
+    __shared__ union {
+        float part[FN_WIDE_WAVES][1][T * 16][FN_LD];
+        TopkShared topk;
+    } sh;
+    const int b = (int)blockIdx.x - t.rows, mt = (p.M + T * 16 - 1) / (T * 16);
+    if (b < 0)
+        topk_row<KPT>(sh.topk, t.scores + (int64_t)blockIdx.x * t.n, t.n, t.k, t.idx + (int64_t)blockIdx.x * t.k);
+    else
+        f32_nt_tile<false, false, BBF16, VEC, T, FN_WIDE_WAVES, T>(p, b % mt, b / mt, sh.part);
 }
 
 int f32_ntiles(int32_t n) { return (n + FN_COLS - 1) / FN_COLS; }
@@ -201,7 +238,7 @@ int launch_f32_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M
 }
 
 int launch_f32_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, bool bf16, const void *W2p, int64_t ldw,
-                   const void *b2, void *Y, int64_t ldy, hipStream_t st)
+                   const void *b2, void *Y, int64_t ldy, hipStream_t st, const TopkJob *topk)
 {
     F32NtParams p;
     p.A = Z; p.B = W2p; p.Bg = nullptr; p.b = b2; p.bg = nullptr; p.C = Y; p.rowpart = nullptr;
@@ -210,6 +247,31 @@ int launch_f32_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d,
     const bool tall = f32_tall(M, p.nt);
     const dim3 grid((unsigned)((M + (tall ? 63 : 31)) / (tall ? 64 : 32)), p.nt), block(FN_WAVES * 64);
     const bool vec = F % 4 == 0 && ldz % 4 == 0 && ldw % 4 == 0 && ((uintptr_t)Z & 15) == 0 && ((uintptr_t)W2p & (bf16 ? 7 : 15)) == 0;
+    const int64_t tiles = (M + 31) / 32 * p.nt, small = (M + 15) / 16 * ((d + 15) / 16);
+    if (tiles <= 256) {
+        const TopkJob t = topk ? *topk : TopkJob{nullptr, nullptr, 0, 0, 0};
+#define FN_OUT_GO(BF_, VEC_, KPT_)                                                                                          \
+        {                                                                                                                   \
+            if (small <= 256) hipLaunchKernelGGL((f32_out_topk_kernel<BF_, VEC_, 1, KPT_>), dim3((unsigned)(t.rows + small)), dim3(TOPK_THREADS), 0, st, p, t); \
+            else hipLaunchKernelGGL((f32_out_topk_kernel<BF_, VEC_, 2, KPT_>), dim3((unsigned)(t.rows + tiles)), dim3(TOPK_THREADS), 0, st, p, t); \
+        }
+#define FN_OUT(KPT_)                                                                                                        \
+        {                                                                                                                   \
+            if (bf16 && vec) FN_OUT_GO(true, true, KPT_)                                                                    \
+            else if (bf16) FN_OUT_GO(true, false, KPT_)                                                                     \
+            else if (vec) FN_OUT_GO(false, true, KPT_)                                                                      \
+            else FN_OUT_GO(false, false, KPT_)                                                                              \
+        }
+        TOPK_RIDE(t.n, FN_OUT)
+#undef FN_OUT
+#undef FN_OUT_GO
+        return check_launch("f32_out_topk_kernel");
+    }
+    if (topk) {
+        const int rc = launch_topk(topk->scores, topk->rows, topk->n, topk->k, topk->idx, st);
+        if (rc != GRIFFIN_OK)
+            return rc;
+    }
     if (bf16) { if (vec) FN_GO(false, false, true, true) else FN_GO(false, false, true, false) }
     else      { if (vec) FN_GO(false, false, false, true) else FN_GO(false, false, false, false) }
 #undef FN_GO

@@ -16,7 +16,7 @@
 //     256-token x 128-feature tile, 4 waves of 128 x 64, v_mfma_f32_32x32x16_bf16, XOR-swizzled
 //     LDS rows), with the same ranges and the same sum;
 //   * shapes the tiles cannot take (D_ff not a multiple of 8, fp32 blocks): the fp32 kernel of f32.hip.
-#include "common.h"
+#include "topk_row.h"
 
 namespace griffin {
 
@@ -196,11 +196,10 @@ __global__ __launch_bounds__(256) void ff2_bf16_mfma_kernel(Ff2Params p)
     }
 }
 
-// Y = sum over the splits (ascending, deterministic) + b2, converted to bf16
-__global__ __launch_bounds__(256) void ff2_split_sum_kernel(Ff2Params p)
+// Y = sum over the splits (ascending, deterministic) + b2, converted to bf16: four elements from number i on
+__device__ __forceinline__ void ff2_split_sum(const Ff2Params &p, int64_t i)
 {
     const int64_t total = (int64_t)p.M * p.d;
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= total)
         return;
     float4 a = *(const float4 *)(p.part + i);
@@ -217,6 +216,37 @@ __global__ __launch_bounds__(256) void ff2_split_sum_kernel(Ff2Params p)
     uint16_t *y = (uint16_t *)p.Y + (int64_t)row * p.ldy + col;
     y[0] = (uint16_t)f32_to_bf16_bits(a.x); y[1] = (uint16_t)f32_to_bf16_bits(a.y);
     y[2] = (uint16_t)f32_to_bf16_bits(a.z); y[3] = (uint16_t)f32_to_bf16_bits(a.w);
+}
+
+__global__ __launch_bounds__(256) void ff2_split_sum_kernel(Ff2Params p)
+{
+    ff2_split_sum(p, ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4);
+}
+
+// ... and, in the first workgroups, the top-k of a prompt phase: it needs one CU a sequence and nothing of the product, and on its own it
+// is a dispatch more (prompt phase of 1024 tokens of 5120 x 13824 385 -> 374 us with it here and faster, of 333 tokens of 1024 x 24576 117 -> 105).
+template <int KPT>
+__global__ __launch_bounds__(TOPK_THREADS) void ff2_split_sum_topk_kernel(Ff2Params p, TopkJob t)
+{
+    __shared__ TopkShared sh;
+    if ((int)blockIdx.x < t.rows)
+        topk_row<KPT>(sh, t.scores + (int64_t)blockIdx.x * t.n, t.n, t.k, t.idx + (int64_t)blockIdx.x * t.k);
+    else
+        ff2_split_sum(p, ((int64_t)(blockIdx.x - t.rows) * TOPK_THREADS + threadIdx.x) * 4);
+}
+
+static int launch_split_sum(const Ff2Params &p, const TopkJob *topk, hipStream_t st)
+{
+    const int64_t quads = (int64_t)p.M * p.d / 4;
+    if (topk) {
+        const dim3 grid((unsigned)(topk->rows + (quads + TOPK_THREADS - 1) / TOPK_THREADS));
+#define FF2_GO(KPT_) hipLaunchKernelGGL(ff2_split_sum_topk_kernel<KPT_>, grid, dim3(TOPK_THREADS), 0, st, p, *topk);
+        TOPK_RIDE(topk->n, FF2_GO)
+#undef FF2_GO
+        return check_launch("ff2_split_sum_topk_kernel");
+    }
+    hipLaunchKernelGGL(ff2_split_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p);
+    return check_launch("ff2_split_sum_kernel");
 }
 
 // Z fp32 -> bf16 copy [M][F] (rounded to nearest even), 8 elements per thread
@@ -284,8 +314,14 @@ bool ff2_takes_zb(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, 
 
 int launch_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, bool bf16, const void *W2p,
                int64_t ldw, const void *b2, void *Y, int64_t ldy, float *ws, size_t ws_bytes, hipStream_t st,
-               bool zb_ready)
+               bool zb_ready, const TopkJob *topk)
 {
+    int rc = GRIFFIN_OK;
+    if (topk && (M == 0 || !topk_rides(topk))) {
+        if ((rc = launch_topk(topk->scores, topk->rows, topk->n, topk->k, topk->idx, st)) != GRIFFIN_OK)
+            return rc;
+        topk = nullptr;
+    }
     if (M == 0)
         return GRIFFIN_OK;
     Ff2Params p;
@@ -301,7 +337,6 @@ int launch_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, boo
             return GRIFFIN_EWORKSPACE;
         uint16_t *Zb = (uint16_t *)ws;
         p.part = (float *)((char *)ws + zb_bytes);
-        int rc = GRIFFIN_OK;
         if (!zb_ready) {
             const int64_t oct = M * F / 8;
             hipLaunchKernelGGL(ff2_z_to_bf16_kernel, dim3((unsigned)((oct + 255) / 256)), dim3(256), 0, st, Z, ldz, M, F, Zb);
@@ -310,9 +345,7 @@ int launch_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, boo
         }
         if ((rc = launch_gemm_nt_partials(Zb, F, W2p, ldw, M, d, F, p.splits, per, p.part, d, st)) != GRIFFIN_OK)
             return rc;
-        const int64_t quads = (int64_t)M * d / 4;
-        hipLaunchKernelGGL(ff2_split_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p);
-        return check_launch("ff2_split_sum_kernel");
+        return launch_split_sum(p, topk, st);
     }
     if (ff2_tiles_ok(Z, ldz, F, d, bf16, W2p, ldw)) {
         ff2_split_plan(M, F, d, &p.splits, &p.kt_per_split);
@@ -322,14 +355,13 @@ int launch_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d, boo
         p.nt = (d + P_BN - 1) / P_BN;
         const int nblk = p.mt * p.nt * p.splits;
         hipLaunchKernelGGL(ff2_bf16_mfma_kernel, dim3(((nblk + 7) / 8) * 8), dim3(256), 0, st, p);
-        int rc = check_launch("ff2_bf16_mfma_kernel");
-        if (rc != GRIFFIN_OK || p.splits == 1)
+        if ((rc = check_launch("ff2_bf16_mfma_kernel")) != GRIFFIN_OK)
             return rc;
-        const int64_t quads = (int64_t)M * d / 4;
-        hipLaunchKernelGGL(ff2_split_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, p);
-        return check_launch("ff2_split_sum_kernel");
+        if (p.splits == 1)
+            return topk ? launch_topk(topk->scores, topk->rows, topk->n, topk->k, topk->idx, st) : GRIFFIN_OK;
+        return launch_split_sum(p, topk, st);
     }
-    return launch_f32_ff2(Z, ldz, M, F, d, bf16, W2p, ldw, b2, Y, ldy, st);
+    return launch_f32_ff2(Z, ldz, M, F, d, bf16, W2p, ldw, b2, Y, ldy, st, topk);
 }
 
 }  // namespace griffin

@@ -289,4 +289,14 @@ __device__ __forceinline__ void topk_row(TopkShared &sh, const float *row, int n
 #undef TOPK_IDX
 }
 
+// Kernels that carry the rows of a TopkJob in their first workgroups (of TOPK_THREADS threads) come in four lengths of row.
+inline bool topk_rides(const TopkJob *t) { return t && t->n <= TOPK_REG_KEYS; }
+#define TOPK_RIDE(n_, GO_)                                                                            \
+    {                                                                                                 \
+        if ((n_) <= 4 * TOPK_THREADS) GO_(4)                                                          \
+        else if ((n_) <= 8 * TOPK_THREADS) GO_(8)                                                     \
+        else if ((n_) <= 16 * TOPK_THREADS) GO_(16)                                                   \
+        else GO_(32)                                                                                  \
+    }
+
 }  // namespace griffin

@@ -986,6 +986,23 @@ def test_prompt_phase_is_selection_plus_prompt_output_from_one_z(dtype, d, F, le
     assert np.array_equal(to_host(Y), to_host(Y2))
 
 
+@pytest.mark.parametrize("dtype,d,F,lens,gated", [
+    (synth.DT_F32, 40, 100, [17], True),                # tiles of 16 x 16, ragged both ways, the top-k in the same launch
+    (synth.DT_F32, 520, 300, [190, 10], True),          # 32 x 32 on the same kernel
+    (synth.DT_F32, 1024, 72, [300], False),             # more than 256 of those: the top-k goes first, on its own
+    (synth.DT_F32, 16, 16500, [5], True),               # a row of scores beyond 16 a thread
+    (synth.DT_BF16, 64, 1003, [30, 5], True),           # neurons that come neither in eights nor in fours: fp32 product of a bf16 block
+    (synth.DT_BF16, 72, 1004, [100], True),             # ... in fours
+    (synth.DT_BF16, 64, 200, [40], True),               # register-staged tiles in one range: nothing to add, the top-k on its own
+    (synth.DT_BF16, 64, 4104, [40], True),              # ... in ranges, the top-k beside the kernel that adds them, 8 scores a thread
+    (synth.DT_BF16, 64, 8256, [33, 0, 2], True),        # 16 scores a thread
+    (synth.DT_BF16, 64, 32768, [9], True),              # 32
+    (synth.DT_BF16, 64, 32832, [9], True),              # more than registers hold: the top-k on its own
+])
+def test_prompt_phase_top_k_beside_the_output(dtype, d, F, lens, gated):
+    test_prompt_phase_is_selection_plus_prompt_output_from_one_z(dtype, d, F, lens, F // 3, gated, False)
+
+
 # ------------------------------------------------------------------ static and sampled selectors, set similarity
 @pytest.mark.parametrize("dtype,d,F,gated", [
     (synth.DT_BF16, 512, 1000, True), (synth.DT_BF16, 8, 5, True), (synth.DT_BF16, 4096, 700, False),
