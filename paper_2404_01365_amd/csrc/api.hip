@@ -174,8 +174,8 @@ int griffin_prefill_select(const griffin_layer *L, const void *X, int64_t ldx,
     int32_t nt = 0;
     // the slabs of a short prompt, or the row partials of narrow tiles, lie behind the rest; a workspace without room for them
     // takes the product in one range of 128-neuron tiles
-    float *tail = workspace_bytes >= pl.total + ff1_tail_bytes(*L, total) ? (float *)(ws + pl.total) : nullptr;
-    if ((rc = launch_ff1(*L, X, ldx, total, Z, zld, &rowpart, &nt, st, nullptr, 0, tail)) != GRIFFIN_OK)
+    float *tail = workspace_bytes >= pl.total + ff1_tail_least(*L, total) ? (float *)(ws + pl.total) : nullptr;
+    if ((rc = launch_ff1(*L, X, ldx, total, Z, zld, &rowpart, &nt, st, nullptr, 0, tail, workspace_bytes - pl.total)) != GRIFFIN_OK)
         return rc;
     if ((rc = launch_stat(Z, zld, rowpart, nt, total, L->n, seqs, s2part, s, s_out, st)) != GRIFFIN_OK)
         return rc;
@@ -341,8 +341,9 @@ int griffin_prompt_phase(const griffin_layer *L, const void *W2p, int64_t ldw, c
                       ff1_can_write_zb(*L, ldx, Z, L->n);
     int32_t nt = 0;
     const size_t before = pl.total + align256(second);
-    float *tail = workspace_bytes >= before + ff1_tail_bytes(*L, total) ? (float *)(ws + before) : nullptr;
-    if ((rc = launch_ff1(*L, X, ldx, total, Z, L->n, &rowpart, &nt, st, fuse ? (uint16_t *)ws2 : nullptr, L->n, tail)) != GRIFFIN_OK)
+    float *tail = workspace_bytes >= before + ff1_tail_least(*L, total) ? (float *)(ws + before) : nullptr;
+    if ((rc = launch_ff1(*L, X, ldx, total, Z, L->n, &rowpart, &nt, st, fuse ? (uint16_t *)ws2 : nullptr, L->n, tail,
+                         workspace_bytes - before)) != GRIFFIN_OK)
         return rc;
     if ((rc = launch_stat(Z, L->n, rowpart, nt, total, L->n, seqs, s2part, s, s_out, st)) != GRIFFIN_OK)
         return rc;

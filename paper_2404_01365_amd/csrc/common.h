@@ -148,12 +148,14 @@ struct TopkJob {
 
 // launchers (one per source file); all return a griffin_status
 // rowpart: room of ff1_ntiles() floats a token, on return where the nt_out partials of each are.  tail (optional): room of
-// ff1_tail_bytes().  Zb (optional): a bf16 copy of Z [M][ldzb] written by the same epilogue when ff1_can_write_zb() says so
+// ff1_tail_least() or more, `room` bytes.  Zb (optional): a bf16 copy of Z [M][ldzb] written by the same epilogue when ff1_can_write_zb() says so
 int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz,
-               float **rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb, float *tail);
+               float **rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb, float *tail, size_t room);
 // bytes that the product makes use of beside Z and rowpart (0: none): the slabs of a short prompt's ranges of d, or the row partials
 // of tiles narrower than 128 neurons; without them it runs in one range of wider tiles
 size_t ff1_tail_bytes(const griffin_layer &L, int64_t M);
+// what the product on one shape of tiles, or in ranges, makes use of
+size_t ff1_tail_least(const griffin_layer &L, int64_t M);
 bool ff1_can_write_zb(const griffin_layer &L, int64_t ldx, const float *Z, int64_t ldz);
 int ff1_ntiles(const griffin_layer &L);
 int f32_ntiles(int32_t n);

@@ -25,6 +25,9 @@ namespace griffin {
 template <> int launch_ff1_tiles<GRIFFIN_ACT_SILU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
 template <> int launch_ff1_tiles<GRIFFIN_ACT_GELU_TANH>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
 template <> int launch_ff1_tiles<GRIFFIN_ACT_RELU>(const Ff1Params &, int, int, bool, bool, int, hipStream_t);
+template <> int launch_ff1_two_shapes<GRIFFIN_ACT_SILU>(const Ff1Params &, const Ff1Params &, int, int, hipStream_t);
+template <> int launch_ff1_two_shapes<GRIFFIN_ACT_GELU_TANH>(const Ff1Params &, const Ff1Params &, int, int, hipStream_t);
+template <> int launch_ff1_two_shapes<GRIFFIN_ACT_RELU>(const Ff1Params &, const Ff1Params &, int, int, hipStream_t);
 
 // Epilogue of the register-staged kernel: sigma, gating, store of Z, row sums of z^2.
 // Lane holds column (neuron) l31 of each 32x32 tile and rows (i>>2)*8 + lh*4 + (i&3), i = 0..15.
@@ -326,6 +329,45 @@ static Ff1Tile ff1_tile(int64_t M, int32_t n, bool gated, bool any_width, bool s
     return best;
 }
 
+// Two shapes in one launch, of one height: `wide` columns of tiles 128 neurons wide, then `narrow` of 96 (ti = 0: not for this call).  One shape
+// seldom fills its last round on 256 CUs; of two, as few wide ones as the rounds of wide tiles alone have room for beside narrow
+// ones make the last round a cheaper one, with hardly a CU idle in it.  (A single shape that FF1_SHAPES does not have, 160 tokens or 224 x 96, comes
+// out of this too, beyond a round of it: within one the weights' latency counts, 463 tokens of 3072 x 8256 on 195 tiles of 160 x 128 79.2 us, on
+// 172 of 256 x 96 76.3.)
+// Where the line lies: whole selections and prompt phases, one shape / two (us), by the ratio that the model gives.  0.83 to 0.9: 788 tokens of
+// 6144 x 11392 270 / 230, 774 of 4096 x 17088 251 / 218; 0.9 to 0.95: 1026 of 5120 x 13664 302 / 277, 864 of 2048 x 9872 100 / 96; 0.95 to
+// 0.97: 1285 of 4096 x 17088 347 / 341, 3748 of 1536 x 7776 207 / 199; 0.97 to 0.98: 491 of 3072 x 18832 138.2 / 137.8, 3979 of 4096 x 17088 935 / 901;
+// from 0.99 on as often slower as faster (723 of 2560 x 7392 70.8 / 75.3).  Going over to the second shape costs a tile's first loads, which nothing
+// hides, so short k loops gain nothing: d = 512 31.7 / 31.6 at 0.95, 128 55.2 / 54.7 at 0.94; 768 144 / 142 at 0.97.
+constexpr int FF1_TWO_MIN_D = 768;
+constexpr double FF1_TWO_LINE = 0.97;
+struct Ff1Two {
+    int ti;
+    int64_t wide, narrow;
+    double cost;             // as Ff1Tile's
+};
+static Ff1Two ff1_two(int64_t M, int32_t n)
+{
+    Ff1Two best = {0, 0, 0, 0.0};
+#define FF1_TWO_COST(TI_, WIDE_, NARROW_)                                                                       \
+    {                                                                                                           \
+        const int64_t mt = (M + 32 * TI_ - 1) / (32 * TI_), all = (n + 127) / 128;                              \
+        const int64_t columns = (all * mt + 255) / 256 * 256 / mt;      /* of tiles, in that many rounds */     \
+        int64_t wide = std::min(all, std::max((int64_t)0, (n - 96 * columns + 31) / 32));                       \
+        for (int i = 0; i < 2; ++i) {           /* the fewest wide ones, then as many as take no round more */  \
+            const int64_t rounds = (wide * mt + 255) / 256, narrow = std::max((int64_t)0, (n - 128 * wide + 95) / 96); \
+            const double cost = 0.7 * (WIDE_ * rounds + NARROW_ * std::max((int64_t)0, ((wide + narrow) * mt + 255) / 256 - rounds)) + \
+                                0.3 / 256 * (double)mt * (WIDE_ * wide + NARROW_ * narrow);                     \
+            if ((best.ti == 0 || cost < best.cost) && (wide * narrow > 0 || (wide + narrow) * mt > 256))        \
+                best = {TI_, wide, narrow, cost};                                                               \
+            wide = std::min(all, rounds * 256 / mt);                                                            \
+        }                                                                                                       \
+    }
+    FF1_TWO_SHAPES(FF1_TWO_COST)
+#undef FF1_TWO_COST
+    return best;
+}
+
 // The 128-column tiles of an Eq. 2 block, 256 tokens or 128: half the matrix work of a tile of both products, and bound by the L2->L1
 // path (~1400 clocks per k-tile against ~2550).
 static double ff1_narrow_cost(int64_t M, int32_t n)
@@ -439,8 +481,18 @@ static Ff1Plan ff1_plan(const griffin_layer &L, int64_t M)
     return pl;
 }
 
+// Does the product go on two shapes of tiles?
+static Ff1Two ff1_takes_two(const griffin_layer &L, int64_t M, const Ff1Plan &pl)
+{
+    const Ff1Two none = {0, 0, 0, 0.0};
+    if (L.dtype != GRIFFIN_BF16 || L.d % 64 != 0 || L.d < FF1_TWO_MIN_D || L.ld > (1 << 21) || !L.Wg || L.b1 || L.bg || M < 1 || pl.room > 1)
+        return none;
+    const Ff1Two two = ff1_two(M, L.n);
+    return two.ti && two.cost < FF1_TWO_LINE * ff1_tile(M, L.n, true, true, false).cost ? two : none;
+}
+
 // One range whose tiles are narrower than 128 neurons has more row partials than ff1_ntiles: they go there, too.
-size_t ff1_tail_bytes(const griffin_layer &L, int64_t M)
+size_t ff1_tail_least(const griffin_layer &L, int64_t M)
 {
     const Ff1Plan pl = ff1_plan(L, M);
     const size_t slabs = pl.room > 1 ? (size_t)pl.room * (L.Wg ? 2 : 1) * M * pl.ldu * sizeof(float) : 0;
@@ -450,6 +502,16 @@ size_t ff1_tail_bytes(const griffin_layer &L, int64_t M)
         return slabs;
     const int ni = ff1_tile(M, L.n, true, true, pl.room > 1).ni;
     return std::max(slabs, ni < 4 ? (size_t)M * ((L.n + 32 * ni - 1) / (32 * ni)) * sizeof(float) : 0);
+}
+
+// ... and so has the product on two shapes
+static size_t ff1_two_bytes(const Ff1Two &two, int64_t M) { return (size_t)M * (two.wide + two.narrow) * sizeof(float); }
+
+size_t ff1_tail_bytes(const griffin_layer &L, int64_t M)
+{
+    const Ff1Two two = ff1_takes_two(L, M, ff1_plan(L, M));
+    const size_t least = ff1_tail_least(L, M);
+    return two.ti ? std::max(least, ff1_two_bytes(two, M)) : least;
 }
 
 int ff1_ntiles(const griffin_layer &L)
@@ -506,7 +568,7 @@ bool ff1_can_write_zb(const griffin_layer &L, int64_t ldx, const float *Z, int64
 }
 
 int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz,
-               float **rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb, float *tail)
+               float **rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb, float *tail, size_t room)
 {
     Ff1Params p;
     p.X = X; p.Wg = L.Wg; p.W1 = L.W1; p.bg = L.bg; p.b1 = L.b1;
@@ -554,6 +616,24 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
     }
     // the direct-to-LDS kernel wants whole 64-element k-tiles and 32-bit byte offsets inside a tile
     const bool staged = L.d % 64 != 0 || ldx > (1 << 21) || L.ld > (1 << 21);
+    const Ff1Two two = tail && !staged ? ff1_takes_two(L, M, pl) : Ff1Two{0, 0, 0, 0.0};
+    if (two.ti && room >= ff1_two_bytes(two, M)) {
+        const int64_t split = std::min((int64_t)L.n, two.wide * 128);
+        p.mt = (int32_t)((M + 32 * two.ti - 1) / (32 * two.ti));
+        p.rowpart = *rowpart = tail;
+        p.nt_row = *nt_out = (int32_t)(two.wide + two.narrow);
+        Ff1Params b = p;
+        p.F = (int32_t)split; p.nt = (int32_t)two.wide;
+        b.F = L.n - p.F; b.nt = (int32_t)two.narrow;
+        b.W1 = (const uint16_t *)p.W1 + split * p.ldw; b.Wg = (const uint16_t *)p.Wg + split * p.ldw;
+        b.Z = p.Z + split; b.rowpart = p.rowpart + p.nt;
+        b.Zb = p.Zb ? p.Zb + split : nullptr;
+        const int grid = ff1_grid(p.mt * p.nt_row);
+        const int rc = L.act == GRIFFIN_ACT_SILU ? launch_ff1_two_shapes<GRIFFIN_ACT_SILU>(p, b, two.ti, grid, st)
+                     : L.act == GRIFFIN_ACT_GELU_TANH ? launch_ff1_two_shapes<GRIFFIN_ACT_GELU_TANH>(p, b, two.ti, grid, st)
+                     : launch_ff1_two_shapes<GRIFFIN_ACT_RELU>(p, b, two.ti, grid, st);
+        return rc != GRIFFIN_OK ? rc : check_launch("ff1_bf16_two_shapes_kernel");
+    }
     Ff1Tile t = {8, 4, 0, 0.0};
     bool wide = false;
     const bool apart = tail && pl.room > 1;
@@ -574,7 +654,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
         }
         p.mt = (int32_t)((M + 32 * t.ti - 1) / (32 * t.ti));
     }
-    *nt_out = p.nt;
+    *nt_out = p.nt_row = p.nt;
     if (M == 0)
         return GRIFFIN_OK;
     if (L.dtype == GRIFFIN_BF16) {
@@ -644,7 +724,7 @@ int launch_gemm_nt_partials(const void *A, int64_t lda, const void *B, int64_t l
     p.ldx = lda; p.ldw = ldb; p.ldz = ldc;
     p.M = (int32_t)M; p.F = N; p.d = K;
     p.splits = splits; p.kt_per_split = p.kt_per_sum = kt_per_split;
-    p.z_stream = 0;
+    p.z_stream = p.nt_row = 0;
     p.nt = (N + 2 * G_BN - 1) / (2 * G_BN);        // 256-column tiles: both sets of accumulators hold columns of B
     const int ti = ff1_plain_tile(M).ti;
     p.mt = (int32_t)((M + 32 * ti - 1) / (32 * ti));

@@ -28,6 +28,7 @@ struct Ff1Params {
     int32_t splits, kt_per_split;    // ranges of the contraction (1 for the activations) and 64-wide k-tiles per range
     int32_t kt_per_sum;              // k-tiles that are summed apart and then added (FF1_SUMS_APART shapes)
     int32_t z_stream;                // Z leaves with the non-temporal hint (see launch_ff1)
+    int32_t nt_row;                  // row partials of a token (nt, or those of both parts of a product on two shapes of tiles)
 };
 
 
@@ -265,7 +266,7 @@ __device__ __forceinline__ bool ff1_mfma_epilogue_t(const Ff1Params &p, f32x4_t 
         asm volatile("ds_read_b32 %0, %1 offset:8192" : "=v"(q1) : "v"(ra));
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(q0), "+v"(q1));
         if (m0 + tid < p.M)
-            p.rowpart[(int64_t)(m0 + tid) * p.nt + tile_n] = q0 + q1;
+            p.rowpart[(int64_t)(m0 + tid) * p.nt_row + tile_n] = q0 + q1;
     }
     return usual;
 }
@@ -305,20 +306,34 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // in ascending order.  That is what ranges of d (ff1_plan) compute, bit for bit, without slabs and a kernel that adds them.
 #define FF1_SUMS_APART(ti_, ni_) ((ti_) * (ni_) <= 16)
 
-template <int ACT, bool GATED, int TI, int NI, bool PLAIN, bool EQ2W = false, int EXTRA = 2, bool DUAL = false>
-__global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
+// What a tile of a shape has in LDS, in 16-byte slots.  Stages: tiles of up to 128 tokens x 64 neurons, which are for little work, are bound by the
+// latency of the weights and take as many as the LDS holds (40 tokens of 4096 x 11008, 64 x 64 tiles: whole selections 78 us with two
+// stages, 52 with six).  Else two workgroups share a CU with 64-token tiles; from 160 tokens on two stages of X and three of the weights (the ones
+// that come from HBM) fill the LDS; everything else has three of both.
+template <bool GATED, int TI, int NI>
+struct Ff1Stages {
+    static constexpr int BM = 32 * TI, BN = 32 * NI;
+    static constexpr int X_ST = BM * 8, W_ST = (GATED ? 2 : 1) * BN * 8;    // slots per stage
+    static constexpr bool DEEP = TI <= 4 && NI == 2;
+    static constexpr int NXS = DEEP ? 8 - (TI == 2 ? 2 : TI) : TI == 2 || TI > 4 ? 2 : 3, NWS = DEEP ? NXS : TI == 2 ? 2 : 3;
+    // The epilogue's patches (32 KB) live in the last weight stage, which nothing is loaded into before the k loop of the next
+    // tile; blocks with one weight section have room for patches of their own.
+    static constexpr int W_BASE = NXS * X_ST, PATCH = W_BASE + (GATED ? (NWS - 1) * W_ST : NWS * W_ST), PATCH_SLOTS = 4 * 2 * 256;
+    static constexpr int SLOTS = PATCH + PATCH_SLOTS > W_BASE + NWS * W_ST ? PATCH + PATCH_SLOTS : W_BASE + NWS * W_ST;
+    static_assert(SLOTS * 16 <= 160 * 1024, "fits the LDS of a CU");
+};
+
+// A workgroup's tiles of one shape: of the `count` of its XCD, which are consecutive from `first` on, number `slot` and every (workgroups of
+// the XCD)-th after it.
+template <int ACT, bool GATED, int TI, int NI, bool PLAIN, bool EQ2W, int EXTRA, bool DUAL>
+__device__ __forceinline__ void ff1_walk(const Ff1Params &p, u32x4 *lds, const int first, const int count, int slot)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass has no buffer-descriptor builtins; it only needs the launch stub
+    using Stages = Ff1Stages<GATED, TI, NI>;
     constexpr int BM = 32 * TI, BN = 32 * NI, BK = 64;
     constexpr int XQ = BM / 32, WQ = BN / 32;                // 8-row regions per wave per k-tile
     constexpr int WL = (GATED ? 2 : 1) * WQ;                   // LDS-DMA instructions per wave and k-tile: XQ of X, WL of the weights
-    constexpr int X_ST = BM * 8, W_ST = (GATED ? 2 : 1) * BN * 8;    // 16-byte slots per stage
-    // Stages: tiles of up to 128 tokens x 64 neurons, which are for little work, are bound by the latency of the weights and take as
-    // many as the LDS holds (40 tokens of 4096 x 11008, 64 x 64 tiles: whole selections 78 us with two stages, 52 with six).  Else
-    // two workgroups share a CU with 64-token tiles; from 160 tokens on two stages of X and three of the weights (the ones that come
-    // from HBM) fill the LDS; everything else has three of both.
-    constexpr bool DEEP = TI <= 4 && NI == 2;
-    constexpr int NXS = DEEP ? 8 - (TI == 2 ? 2 : TI) : TI == 2 || TI > 4 ? 2 : 3, NWS = DEEP ? NXS : TI == 2 ? 2 : 3;
+    constexpr int X_ST = Stages::X_ST, W_ST = Stages::W_ST, NXS = Stages::NXS, NWS = Stages::NWS;
     // The plain product has one B matrix: its tile is 256 columns wide and the "gate" half of the
     // machinery (LDS section, fragments, accumulators) takes columns n0 + 128 .. n0 + 255, which
     // halves the X traffic per flop exactly as the dual product does.
@@ -328,12 +343,7 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     static_assert(!DUAL || (PLAIN && GATED), "DUAL is a form of the plain product");
     static_assert(!EQ2W || (GATED && !PLAIN), "the Eq. 2 wide tile uses both LDS sections and both accumulator sets");
     constexpr int TILE_N = WIDE ? 2 * BN : BN;
-    // The epilogue's patches (32 KB) live in the last weight stage, which nothing is loaded into before the k loop of the next
-    // tile; blocks with one weight section have room for patches of their own.
-    constexpr int W_BASE = NXS * X_ST, PATCH = W_BASE + (GATED ? (NWS - 1) * W_ST : NWS * W_ST), PATCH_SLOTS = 4 * 2 * 256;
-    constexpr int LDS_SLOTS = PATCH + PATCH_SLOTS > W_BASE + NWS * W_ST ? PATCH + PATCH_SLOTS : W_BASE + NWS * W_ST;
-    static_assert(LDS_SLOTS * 16 <= 160 * 1024, "fits the LDS of a CU");
-    __shared__ u32x4 lds[LDS_SLOTS];
+    constexpr int W_BASE = Stages::W_BASE, PATCH = Stages::PATCH;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -344,7 +354,7 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     // of one tile are `ntile` ids apart.  The grid holds one workgroup per CU and every workgroup
     // walks through its tiles itself, so that the first loads of the next tile can go out before
     // the epilogue of this one (a workgroup per tile leaves the CU idle while the next one starts).
-    const int ntile = p.mt * p.nt, nblk = ntile * p.splits;
+    const int ntile = p.mt * p.nt;
     // Order of the tiles: panels of PANEL_M token tiles; inside a panel the token tile runs fastest, then the
     // neuron tile.  The 32 workgroups of an XCD then work on 8 token tiles x 4 neuron tiles at any time (12
     // operand slices stream through its L2 per k-tile) instead of 32 token tiles x 1 neuron tile (33 slices)
@@ -352,10 +362,8 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     // PANEL_M token tiles this is the plain order "token tile fastest".
     constexpr int PANEL_M = 8;
     const int full_m = (p.mt / PANEL_M) * PANEL_M, full_tiles = full_m * p.nt;
-    const int per_xcd = (nblk + 7) / 8;
     const int wg_per_xcd = gridDim.x >> 3;
-    int slot = blockIdx.x >> 3;
-    if (slot >= per_xcd || (int)(blockIdx.x & 7) * per_xcd + slot >= nblk)
+    if (slot >= count)
         return;
 
     // per-tile addressing: the loader maps lane -> (row of the 8-row region, slot in the row) ->
@@ -402,7 +410,7 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
         kt0 = split_ * p.kt_per_split;                                                                   \
         KT = min(p.kt_per_split, p.d / BK - kt0);      /* k-tiles of this range (>= 1 by construction) */\
     }
-    FF1_TILE_ADDR((int)(blockIdx.x & 7) * per_xcd + slot)
+    FF1_TILE_ADDR(first + slot)
 
 // LDS-DMA instruction number q of the X part (0 .. XQ-1) or of the weights (0 .. WL-1: W1, then Wg) of k-tile kt_, into the stage
 // at slot st_.  The weight tiles carry the non-temporal hint (each is used by one wave of tiles and then never
@@ -450,7 +458,7 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
     u32x4 fa[2][TI], f1[2][NI], fg[2][NI];
     constexpr int NREADS = TI + (GATED ? 2 : 1) * NI;
     // interleaving slots per k-step, with MPS pairs of MFMAs (up, gate) or singles each
-    constexpr int NSLOTS = TI * NI < 16 ? TI * NI : TI * NI % 16 == 0 ? 16 : TI * NI / 2, MPS = TI * NI / NSLOTS;
+    constexpr int NSLOTS = TI * NI < 16 ? TI * NI : TI * NI % 16 == 0 ? 16 : TI * NI % 2 == 0 ? TI * NI / 2 : TI * NI / 3, MPS = TI * NI / NSLOTS;
     static_assert(NREADS <= NSLOTS * 2 && XQ <= NSLOTS && WL <= NSLOTS && TI * NI == NSLOTS * MPS, "a k-step has a slot for everything");
 
 // read number r (0 .. NREADS-1) of fragment set F_ (16 rows = 2048 B apart): the weights first
@@ -619,10 +627,9 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
         const int m0c = m0, n0c = n0, tile_nc = tile_n;
         const bool whole = m0 + BM <= p.M && n0 + TILE_N <= p.F;
         slot += wg_per_xcd;
-        const int logical_n = (int)(blockIdx.x & 7) * per_xcd + slot;
-        const bool more = slot < per_xcd && logical_n < nblk;
+        const bool more = slot < count;
         if (more) {
-            FF1_TILE_ADDR(logical_n)
+            FF1_TILE_ADDR(first + slot)
             FF1_FIRST_LOADS()
         }
         const bool usual = ff1_mfma_epilogue_t<ACT, GATED, TI, NI, PLAIN, EQ2W, EXTRA, DUAL>(pt, accU, accG, lds0 + (uint32_t)(PATCH * 16), m0c, n0c, tile_nc);
@@ -645,6 +652,33 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
 #undef FF1_WAIT_FRAGS
 #undef FF1_KSTEP
 #endif
+}
+
+template <int ACT, bool GATED, int TI, int NI, bool PLAIN, bool EQ2W = false, int EXTRA = 2, bool DUAL = false>
+__global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
+{
+    __shared__ u32x4 lds[Ff1Stages<GATED, TI, NI>::SLOTS];
+    const int nblk = p.mt * p.nt * p.splits, per_xcd = (nblk + 7) / 8, first = (int)(blockIdx.x & 7) * per_xcd;
+    ff1_walk<ACT, GATED, TI, NI, PLAIN, EQ2W, EXTRA, DUAL>(p, lds, first, min(per_xcd, nblk - first), blockIdx.x >> 3);
+}
+
+// Two shapes of tiles in one launch: the neurons of `a` on the first, those of `b`, which follow them, on the second.  The tiles of both
+// together are dealt out evenly over the XCDs, and the second part is walked from the other end, so that the workgroups with fewer tiles
+// of the first have more of it.  The product of 1024 tokens of 5120 x 13824 on 432 tiles of 256 x 128 230 us, on 256 of them and 236 of 256 x 96 218;
+// of 777 tokens on 432 of 224 x 128 206, on 192 and 320 of 224 x 96 194; of 640 tokens of 4096 x 14336 on 450 of 256 x 96 151, on 256 of
+// 160 x 128 and 256 of 160 x 96 128.
+template <int ACT, int EXTRA, int TA, int NA, int TB, int NB>
+__global__ __launch_bounds__(G_THREADS) void ff1_bf16_two_shapes_kernel(Ff1Params a, Ff1Params b)
+{
+    constexpr int SA = Ff1Stages<true, TA, NA>::SLOTS, SB = Ff1Stages<true, TB, NB>::SLOTS;
+    __shared__ u32x4 lds[SA > SB ? SA : SB];
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int tiles_a = a.mt * a.nt, tiles = tiles_a + b.mt * b.nt;
+    const int a0 = (int)((int64_t)xcd * tiles_a / 8), a1 = (int)((int64_t)(xcd + 1) * tiles_a / 8);
+    const int b0 = (int)((int64_t)xcd * tiles / 8) - a0, b1 = (int)((int64_t)(xcd + 1) * tiles / 8) - a1;
+    ff1_walk<ACT, true, TA, NA, false, false, EXTRA, false>(a, lds, a0, a1 - a0, slot);
+    __syncthreads();              // every wave is done with its patches
+    ff1_walk<ACT, true, TB, NB, false, false, EXTRA, false>(b, lds, b0, b1 - b0, (int)(gridDim.x >> 3) - 1 - slot);
 }
 
 // The whole product with its activation on this kernel, tiles of 32 ti tokens x 32 ni neurons (`wide`: an Eq. 2 block, on tiles of
@@ -691,6 +725,27 @@ int launch_ff1_tiles(const Ff1Params &p, int ti, int ni, bool gated, bool wide, 
             return GRIFFIN_OK;                                                                                  \
         }                                                                                                       \
         FF1_SHAPES(FF1_TILES_CASE)                                                                              \
+        return GRIFFIN_EUNSUPPORTED;                                                                            \
+    }
+
+// The product of an Eq. 3 block without biases on tiles of 32 ti tokens x 128 neurons (a) and x 96 neurons (b), in one launch.
+template <int ACT>
+int launch_ff1_two_shapes(const Ff1Params &a, const Ff1Params &b, int ti, int grid, hipStream_t st);
+
+// The heights that are compiled: X(ti, time of a round of 128-neuron tiles, of 96-neuron tiles; 256 x 128 = 1)
+#define FF1_TWO_SHAPES(X) X(8, 1.0, 0.78) X(7, 0.905, 0.71) X(6, 0.8, 0.63) X(5, 0.71, 0.57)
+#define FF1_TWO_CASE(TI_, WIDE_, NARROW_)                                                                       \
+    if (ti == TI_) {                                                                                            \
+        if (a.Zb) hipLaunchKernelGGL((ff1_bf16_two_shapes_kernel<ACT, 1, TI_, 4, TI_, 3>), dim3(grid), dim3(G_THREADS), 0, st, a, b); \
+        else hipLaunchKernelGGL((ff1_bf16_two_shapes_kernel<ACT, 0, TI_, 4, TI_, 3>), dim3(grid), dim3(G_THREADS), 0, st, a, b); \
+        return GRIFFIN_OK;                                                                                      \
+    }
+#define FF1_TWO_OF(ACT_)                                                                                        \
+    template <>                                                                                                 \
+    int launch_ff1_two_shapes<ACT_>(const Ff1Params &a, const Ff1Params &b, int ti, int grid, hipStream_t st)   \
+    {                                                                                                           \
+        constexpr int ACT = ACT_;                                                                               \
+        FF1_TWO_SHAPES(FF1_TWO_CASE)                                                                            \
         return GRIFFIN_EUNSUPPORTED;                                                                            \
     }
 

@@ -630,6 +630,32 @@ FORM_OUT_CASES = [
 ]
 
 
+# Products on two shapes of tiles; tests/test_prompt_routes.py holds them against what the calls launch
+TWO_SHAPES_CASES = [
+    # d, F, tokens, activation, phase (Z leaves in bf16, too); height of the tiles, columns of them 128 wide and 96 wide
+    (768, 8208, 443, synth.ACT_SILU, False, 160, 2, 83),
+    (768, 8507, 415, synth.ACT_GELU_TANH, False, 160, 11, 74),
+    (768, 16586, 501, synth.ACT_RELU, False, 192, 85, 60),
+    (768, 16654, 584, synth.ACT_SILU, False, 224, 85, 61),
+    (768, 16756, 683, synth.ACT_GELU_TANH, False, 256, 85, 62),
+    (832, 16720, 267, synth.ACT_RELU, False, 160, 0, 175),
+    (768, 19233, 391, synth.ACT_GELU_TANH, False, 224, 0, 201),
+    (768, 6446, 1412, synth.ACT_RELU, False, 160, 51, 0),
+    (768, 12800, 258, synth.ACT_SILU, True, 160, 16, 112),
+    (768, 16448, 490, synth.ACT_SILU, True, 192, 85, 58),
+    (768, 16832, 583, synth.ACT_SILU, True, 224, 85, 62),
+    (768, 17088, 683, synth.ACT_SILU, True, 256, 85, 65),
+]
+
+
+@pytest.mark.parametrize("d,F,S,act,phase", [c[:5] for c in TWO_SHAPES_CASES])
+def test_prompt_products_on_two_shapes(d, F, S, act, phase):
+    if phase:
+        test_prompt_phase_is_selection_plus_prompt_output_from_one_z(synth.DT_BF16, d, F, [S], F // 2, True, False)
+    else:
+        test_prefill_select_matches_oracle(synth.DT_BF16, d, F, [S], F // 2, act, True, False)
+
+
 @pytest.mark.parametrize("d,F,S,act,gated,bias", [c[:6] for c in FORM_CASES])
 def test_prefill_select_on_every_form(d, F, S, act, gated, bias):
     test_prefill_select_matches_oracle(synth.DT_BF16, d, F, [S], F // 2, act, gated, bias)

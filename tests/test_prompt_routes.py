@@ -1,5 +1,6 @@
 """Which form of the prompt product a call takes, and what it makes of it (no GPU: tests/launches.py)."""
 import ctypes
+import re
 
 import pytest
 
@@ -69,3 +70,27 @@ def test_the_least_workspace_takes_tiles_of_128_neurons():
     assert [r[0][0] for r in routes(calls)] == ["256x96 Eq. 3", "192x128 Eq. 3", "256x96 Eq. 3 copy", "192x128 Eq. 3 copy"]
     calls = [dict(entry="select", d=1024, n=1000, lens=[40], least=least) for least in (False, True)]
     assert [r[0][::3] for r in routes(calls)] == [("64x64 Eq. 3 copy", 4), ("128x128 Eq. 3", 1)]
+
+
+_TWO = re.compile(r"two_shapes_kernelILi(\d)ELi(\d)ELi(\d)ELi4ELi(\d)ELi3E")
+
+
+def test_products_on_two_shapes_cover_the_block_once():
+    two = cases.TWO_SHAPES_CASES
+    calls = [dict(entry="phase" if ph else "select", d=d, n=F, lens=[S], act=act if not ph else G.ACT_SILU) for d, F, S, act, ph, *_ in two]
+    for c, ls in zip(two, launches.record(calls)):
+        first = [l for l in ls if _TWO.search(l["name"])]
+        assert len(first) == 1 and not any(launches.form(l["name"]) and " raw " not in launches.form(l["name"]) for l in ls), c
+        act, copy, ti, tb = (int(v) for v in _TWO.search(first[0]["name"]).groups())
+        l, (d, F, S, want, ph, height, wide, narrow) = first[0], c
+        assert (32 * ti, ti, copy, act) == (height, tb, int(ph), G.ACT_SILU if ph else want), c
+        assert l["nt"] == wide and l["F"] == min(F, 128 * wide) and -(-(F - l["F"]) // 96) == narrow, c
+        assert l["mt"] == -(-S // height), c
+
+
+def test_two_shapes_need_room_for_their_row_sums_and_a_lean_block():
+    d, F, S = 768, 16756, 683
+    names = lambda **kw: [l["name"] for l in launches.record([dict(dict(entry="select", d=d, n=F, lens=[S]), **kw)])[0]]  # noqa: E731
+    assert any("two_shapes" in n for n in names())
+    for kw in (dict(least=True), dict(bias=True), dict(gated=False), dict(d=704), dict(dtype=G.F32)):
+        assert not any("two_shapes" in n for n in names(**kw)), kw
