@@ -34,6 +34,7 @@ struct ChunkTable {
 // keeps them in LDS; rows past the end of the sequence get weight 0 and a clamped address.
 constexpr int STAT_ROWS_LDS = 256;
 typedef __attribute__((ext_vector_type(4))) float stat_f32x4;
+typedef stat_f32x4 __attribute__((aligned(4))) stat_f32x4_u;      // rows of row partials start anywhere
 #define STAT_LD(p_) (*(p_))
 
 template <int VEC>
@@ -159,59 +160,108 @@ __global__ __launch_bounds__(64) void stat_finalize_kernel(const float *s2part, 
         s_out[(int64_t)seq * F + j] = v;
 }
 
-// Short sequences in one kernel: what bounds them is not Z (1.8 MB for 40 tokens of 11008 neurons) but the two dependent
-// dispatches and the latencies inside them.  A workgroup of sixteen wavefronts takes 64 columns of one sequence from end to end:
-// wave w has the rows w, w + 16, ... (at most eight of them: all its loads are on their way at once), forms their weights
-// itself and leaves its sums in LDS; they are added in wave order and the root is taken at once.  Every workgroup reads the
-// row partials of the whole sequence again, which is why longer ones (128 tokens x 86 partials are 44 KB) go in chunks, and so
-// do calls with more workgroups than the chip holds at once (512).  Whole selections, chunks and second kernel / this one:
-// 40 tokens of 4096 x 11008 64.9 / 60.7 us, 128 tokens 73.7 / 71.4, eight prompts of 40 tokens of 1024 x 4096 49.7 / 47.1, of
-// 4096 x 11008 (1376 workgroups) 119 / 130.
-constexpr int STAT_SHORT_ROWS = 128, STAT_SHORT_WAVES = 16;
+// Sequences that one workgroup takes from end to end, 64 columns each: no partial sums over chunks, and no kernel that adds them.  What bounds
+// short sequences is not Z (1.8 MB for 40 tokens of 11008 neurons) but the dependent dispatches and the latencies inside them.  Of the
+// sixteen wavefronts a load takes 16 VEC rows; a wave has four (16-byte) or eight of its loads on their way while the weights of up to 1024 rows are
+// formed (eight lanes a row, four partials a lane: a partial a lane, 32 bytes of a row an instruction, is slower, 1024 tokens of 1024 x 13824
+// 85.8 us instead of 82.2, 512 of 1024 x 24576 89.1 instead of 83.9), and the waves' sums meet in LDS, in wave order.
+// Every workgroup reads the row partials of its whole sequence again, which is what bounds how long it may be (stat_whole).
+constexpr int STAT_WAVES = 16, STAT_BLOCK = 1024;
 
-__global__ __launch_bounds__(STAT_SHORT_WAVES * 64) void stat_short_kernel(const float *Z, int64_t ldz, const float *rowpart, int nt,
-                                                                           int F, SeqTable seqs, float *s, float *s_out)
+template <int VEC>
+__global__ __launch_bounds__(STAT_WAVES * 64, 8) void stat_whole_kernel(const float *Z, int64_t ldz, const float *rowpart, int nt, int F,
+                                                                     SeqTable seqs, float *s, float *s_out)
 {
-    constexpr int U = STAT_SHORT_ROWS / STAT_SHORT_WAVES;
-    __shared__ float part[STAT_SHORT_WAVES][64];
+    constexpr int U = VEC == 4 ? 4 : 8, ROWS = STAT_WAVES * VEC;             // rows that a load of all waves covers: VEC of them a wave
+    __shared__ float w_s[STAT_BLOCK], part[STAT_WAVES][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, seq = blockIdx.y;
-    const int j = blockIdx.x * 64 + lane, jc = j < F ? j : F - 1;
+    const int c0 = lane % (64 / VEC) * VEC, j = blockIdx.x * 64 + c0;
+    const int mine = wave * VEC + lane / (64 / VEC);          // this lane's first row of a block; the next ones ROWS apart
     const int64_t s0 = seqs.cu[seq];
     const int len = (int)(seqs.cu[seq + 1] - s0);
-    float acc = 0.0f;
-    if (wave < len) {                          // rows past the end repeat the wave's first row with weight 0
-        float z[U], a[U];
+    const float *zp = Z + s0 * ldz + (j < F ? j : 0);
+    float acc[VEC];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int r = wave + STAT_SHORT_WAVES * u;
-            z[u] = Z[(s0 + (r < len ? r : wave)) * ldz + jc];
+    for (int v = 0; v < VEC; ++v)
+        acc[v] = 0.0f;
+    for (int b = 0; b < len; b += STAT_BLOCK) {
+        const int nr = min(STAT_BLOCK, len - b);
+        float z[U][VEC];
+// rows past the end are the last one, with weight 0
+#define STAT_LOAD_ROWS(r_)                                                                       \
+        _Pragma("unroll") for (int u = 0; u < U; ++u)                                            \
+        {                                                                                        \
+            const float *p_ = zp + (int64_t)(b + min((r_) + u * ROWS + mine, nr - 1)) * ldz;     \
+            if (VEC == 4) {                                                                      \
+                const stat_f32x4 t_ = *(const stat_f32x4 *)p_;                                   \
+                z[u][0] = t_.x; z[u][1 % VEC] = t_.y; z[u][2 % VEC] = t_.z; z[u][3 % VEC] = t_.w; \
+            } else {                                                                             \
+                z[u][0] = *p_;                                                                   \
+            }                                                                                    \
         }
+        STAT_LOAD_ROWS(0)
+        __syncthreads();                       // the weights of the block before have been used
+        const int padded = (nr + U * ROWS - 1) / (U * ROWS) * (U * ROWS);
+        for (int r = nr + (int)threadIdx.x; r < padded; r += STAT_WAVES * 64)
+            w_s[r] = 0.0f;
+        for (int r0 = wave * 8; r0 < nr; r0 += STAT_WAVES * 8) {
+            const int r = r0 + (lane >> 3);
+            const float *rp = rowpart + (s0 + b + min(r, nr - 1)) * nt;
+            float a = 0.0f;
+            if (nt < 4) {
+                a = (lane & 7) < nt ? rp[min(lane & 7, nt - 1)] : 0.0f;
+            } else {
+                // four partials a lane, 128 bytes of a row an instruction; the last four come again where the row ends, and count once
+                for (int t0 = (lane & 7) * 4; t0 < nt; t0 += 128) {
+                    stat_f32x4 v[4];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int r = wave + STAT_SHORT_WAVES * u;
-            const float *rp = rowpart + (s0 + (r < len ? r : wave)) * nt;
-            a[u] = 0.0f;
-            for (int t = lane; t < nt; t += 64)
-                a[u] += rp[t];
-        }
+                    for (int i = 0; i < 4; ++i)
+                        v[i] = *(const stat_f32x4_u *)(rp + min(t0 + 32 * i, nt - 4));
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float v = wave_sum(a[u]);
-            const float w = (v > 0.0f && wave + STAT_SHORT_WAVES * u < len) ? 1.0f / v : 0.0f;
-            acc = fmaf(z[u] * z[u], w, acc);
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            a += min(t0 + 32 * i, nt - 4) + e >= t0 + 32 * i ? v[i][e] : 0.0f;
+                }
+            }
+            a += dpp_f32<0xB1>(a);             // over the eight lanes of the row
+            a += dpp_f32<0x4E>(a);
+            a += dpp_f32<0x141>(a);
+            if ((lane & 7) == 0 && r < nr)
+                w_s[r] = a > 0.0f ? 1.0f / a : 0.0f;
         }
+        __syncthreads();
+        for (int r = 0; r < padded; r += U * ROWS) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float w = w_s[r + u * ROWS + mine];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v)
+                    acc[v] = fmaf(z[u][v] * z[u][v], w, acc[v]);
+            }
+            if (r + U * ROWS < padded)
+                STAT_LOAD_ROWS(r + U * ROWS)
+        }
+#undef STAT_LOAD_ROWS
     }
-    part[wave][lane] = acc;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        if (VEC == 4)
+            acc[v] = lane_groups_sum(acc[v]);  // the four rows of a load
+        if (lane < 64 / VEC)
+            part[wave][c0 + v] = acc[v];
+    }
     __syncthreads();
-    if (wave == 0 && j < F) {
+    const int jo = blockIdx.x * 64 + lane;
+    if (wave == 0 && jo < F) {
         float t = 0.0f;
 #pragma unroll
-        for (int w = 0; w < STAT_SHORT_WAVES; ++w)
+        for (int w = 0; w < STAT_WAVES; ++w)
             t += part[w][lane];
         const float v = sqrtf(t);
-        s[(int64_t)seq * F + j] = v;
+        s[(int64_t)seq * F + jo] = v;
         if (s_out)
-            s_out[(int64_t)seq * F + j] = v;
+            s_out[(int64_t)seq * F + jo] = v;
     }
 }
 
@@ -250,6 +300,20 @@ int64_t stat_max_chunks(int64_t total_tokens, int32_t n_seqs, int32_t F)
     return total_tokens / stat_rows_per_chunk(total_tokens, n_seqs, F) + n_seqs;
 }
 
+// Do the workgroups of stat_whole_kernel take the sequences?  A CU then reads, per row, the partials and 64 columns, for as many workgroups
+// as fall to it; beyond some 800 KB that costs more than a second kernel.  Whole selections, chunks and their sum / so (us), by that number of words: one
+// sequence, 512 tokens of 4096 x 11008 96.7 / 93.7 (92e3), 777 of 1024 x 13824 77.3 / 74.8 (134e3), 1024 of it 84.5 / 82.2 (176e3), 1024 of 4096 x 11008
+// 173.4 / 172.3 (183e3), 1500 of it 249 / 252 (268e3), 1024 of 1024 x 24576 131 / 140 (525e3); four of 300 of 1024 x 11008 81.2 / 78.9 (153e3), of 1024 x
+// 14336 104 / 106 (211e3).  More than 1024 workgroups wait for each other's latencies: sixteen of 16 of 1024 x 11008 (2752) 43.1 / 49.4, of 1024 x 4096
+// (1024) 27.4 / 24.6.  Rows that 16-byte loads cannot take (F = 11009) are read at a quarter of the width in chunks: 512 tokens 51.8 / 46.5, 2048
+// 136 / 130 (368e3).  With a kernel for up to 128 tokens that formed its weights a wavefront a row, 128 tokens of 1024 x 13824 took 38.0, 40 29.3:
+// 31.2 and 24.5 so.
+static bool stat_whole(int32_t longest, int32_t n_seqs, int32_t F, int nt, bool vec4)
+{
+    const int64_t wgs = (int64_t)((F + 63) / 64) * n_seqs;
+    return wgs <= 1024 && (wgs + 255) / 256 * longest * (nt + 64) <= (vec4 ? 200000 : 400000);
+}
+
 int launch_stat(const float *Z, int64_t ldz, const float *rowpart, int nt, int64_t M, int32_t F,
                 const SeqTable &seqs, float *s2part, float *s, float *s_out, hipStream_t st)
 {
@@ -257,10 +321,12 @@ int launch_stat(const float *Z, int64_t ldz, const float *rowpart, int nt, int64
     int32_t longest = 0;
     for (int b = 0; b < seqs.n; ++b)
         longest = seqs.cu[b + 1] - seqs.cu[b] > longest ? seqs.cu[b + 1] - seqs.cu[b] : longest;
-    if (longest <= STAT_SHORT_ROWS && (int64_t)((F + 63) / 64) * seqs.n <= 512) {
-        hipLaunchKernelGGL(stat_short_kernel, dim3((F + 63) / 64, seqs.n), dim3(STAT_SHORT_WAVES * 64), 0, st, Z, ldz, rowpart, nt, F,
-                           seqs, s, s_out);
-        return check_launch("stat_short_kernel");
+    const bool vec4 = (F % 4 == 0) && (ldz % 4 == 0) && (((uintptr_t)Z & 15) == 0);
+    if (stat_whole(longest, seqs.n, F, nt, vec4)) {
+        const dim3 grid((F + 63) / 64, seqs.n), block(STAT_WAVES * 64);
+        if (vec4) hipLaunchKernelGGL(stat_whole_kernel<4>, grid, block, 0, st, Z, ldz, rowpart, nt, F, seqs, s, s_out);
+        else hipLaunchKernelGGL(stat_whole_kernel<1>, grid, block, 0, st, Z, ldz, rowpart, nt, F, seqs, s, s_out);
+        return check_launch("stat_whole_kernel");
     }
     const int R = stat_rows_per_chunk(M, seqs.n, F);
     ChunkTable chunks;
@@ -272,7 +338,6 @@ int launch_stat(const float *Z, int64_t ldz, const float *rowpart, int nt, int64
     for (int b = seqs.n; b <= GRIFFIN_MAX_SEQS; ++b)
         chunks.first[b] = n_chunks;
     if (n_chunks > 0) {
-        const bool vec4 = (F % 4 == 0) && (ldz % 4 == 0) && (((uintptr_t)Z & 15) == 0);
         if (vec4) {
             dim3 grid((F / 4 + 255) / 256, n_chunks);
             hipLaunchKernelGGL(col_stat_kernel<4>, grid, dim3(256), 0, st, Z, ldz, rowpart, nt, F, seqs, chunks, s2part);

@@ -630,6 +630,13 @@ FORM_OUT_CASES = [
 ]
 
 
+# a workgroup for 64 columns of a whole sequence: blocks of 1024 rows, loads of 256 (of 128 where rows are not aligned), row partials in steps of 64
+@pytest.mark.parametrize("d,F,lens", [(8, 72, [1]), (8, 72, [255, 0, 256, 257]), (8, 72, [1024]), (8, 72, [1025, 3]), (16, 64, [2049]), (8, 2116, [130]),
+                                      (8, 71, [128, 129, 1]), (8, 71, [1023, 1026]), (8, 4226, [65, 64])])
+def test_statistic_of_whole_sequences(d, F, lens):
+    test_prefill_select_matches_oracle(synth.DT_F32, d, F, lens, max(1, F // 3), synth.ACT_SILU, True, False)
+
+
 # Products on two shapes of tiles; tests/test_prompt_routes.py holds them against what the calls launch
 TWO_SHAPES_CASES = [
     # d, F, tokens, activation, phase (Z leaves in bf16, too); height of the tiles, columns of them 128 wide and 96 wide

@@ -94,3 +94,10 @@ def test_two_shapes_need_room_for_their_row_sums_and_a_lean_block():
     assert any("two_shapes" in n for n in names())
     for kw in (dict(least=True), dict(bias=True), dict(gated=False), dict(d=704), dict(dtype=G.F32)):
         assert not any("two_shapes" in n for n in names(**kw)), kw
+
+
+def test_statistic_in_one_kernel_while_a_cu_reads_little():
+    calls = [(4096, 11008, [512]), (1024, 11008, [1500]), (1024, 24576, [256]), (1024, 24576, [777]), (1024, 4096, [140] * 16), (1024, 4096, [40] * 17),
+             (512, 11009, [1500]), (512, 11009, [3000]), (256, 688, [1])]
+    got = [any("stat_whole" in l["name"] for l in ls) for ls in launches.record([dict(entry="select", d=d, n=F, lens=v) for d, F, v in calls])]
+    assert got == [True, False, True, False, True, False, True, False, True]
