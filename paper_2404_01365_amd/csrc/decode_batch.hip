@@ -17,8 +17,8 @@
 //    barrier per group would tie their load streams to the slowest: 75 us a masked call instead of 71 on 4096 x 14336), add the
 //    tiles in wave order, apply sigma, the gating product and the membership bits, and store Z.  Workgroups start at different
 //    blocks, so that row strides of a power of two do not send them all to the same memory channels at a time.
-//    Measured on the gate and up rows (medians of the kernel trace, each with the ~4 us of a dependent dispatch in it):
-//    5120 x 6912 (142 MB), 16 rows 31 us (34 with five blocks ahead; 38 when rows were streamed through LDS two neurons at a time with two of sixteen
+//    Measured on the gate and up rows (medians of the kernel trace, each with the ~4 us of a dependent dispatch in it, before x came along with the
+//    first group and before the loads past the last one were cut to a line): 5120 x 6912 (142 MB), 16 rows 31 us (34 with five blocks ahead; 38 when rows were streamed through LDS two neurons at a time with two of sixteen
 //    MFMA columns in use; 42 with loads of sixteen half lines instead of eight whole ones); 3072 x 12288, 40 rows 35 us (three
 //    passes of 32 in that form); 4096 x 14336 masked 41 us (44).
 //  * ff_batch_down_kernel: the second line.  Giving every workgroup all d columns would cost one [rows][d] partial per
@@ -32,6 +32,7 @@
 #include "common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace griffin {
 
@@ -130,42 +131,42 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
         __builtin_amdgcn_s_barrier();                                                                \
         asm volatile("" ::: "memory");                                                               \
     }
-    int64_t row_cur[2] = {BT_ROW(0, 0), BT_ROW(0, 1)};
-#pragma unroll
-    for (int s = 0; s < R; ++s)
-        BT_LOAD(s, s, row_cur)
+    int64_t row[2] = {BT_ROW(0, 0), BT_ROW(0, 1)};
 
     // x: fragment (tile t, block s, half h): row t * 16 + r16, elements (q + 4 h) * 8 .. + 7 of the block.  Rows beyond the batch
-    // repeat the last one; their Z is set to zero where it is stored.
+    // repeat the last one; their Z is set to zero where it is stored.  Whole lines of eight rows a load, and halves that change places, as
+    // the weights do it.  The fragments of a block come with its weights of the first group: with all of x in front (295 KB a CU for 40 rows of
+    // 3072) the first MFMA came 6.3 us into the kernel, 4.2 with 16 rows of 4096; so it comes after 2.8 and 2.3.
     u32x4_b xa[T][S][2];
+    // byte offsets of this lane's rows: of the first eight of a tile, and of the last tile's, where rows may be missing
+    const uint32_t xo = (uint32_t)((r16 & 7) * p.d + (q + 4 * (r16 >> 3)) * 8) * 2;
+    uint32_t xl[2];
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-        const int row = t * BT_ROWS + r16;
-        const uint16_t *xr = (const uint16_t *)p.x + (int64_t)min(row, p.rows - 1) * p.d;
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                xa[t][s][h] = *(const u32x4_b *)(xr + BT_K0(s) + (q + 4 * h) * 8);
-            }
+    for (int h = 0; h < 2; ++h)
+        xl[h] = (uint32_t)(min((T - 1) * BT_ROWS + (r16 & 7) + 8 * h, p.rows - 1) * p.d + (q + 4 * (r16 >> 3)) * 8) * 2;
+#define BT_LOAD_X(s_)                                                                                \
+    _Pragma("unroll") for (int t = 0; t < T; ++t)                                                    \
+        _Pragma("unroll") for (int h = 0; h < 2; ++h)                                                \
+        {                                                                                            \
+            const char *b_ = (const char *)p.x + (int64_t)((t < T - 1 ? (t * BT_ROWS + 8 * h) * p.d : 0) + BT_K0(s_)) * 2; \
+            xa[t][s_][h] = *(const u32x4_b *)(b_ + (t < T - 1 ? xo : xl[h]));                        \
+        }
+// the halves of two loads change places: then a register holds sixteen rows (a DPP row holds eight of each)
+#define BT_SWAP(lo_, hi_)                                                                            \
+    _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                    \
+    {                                                                                                \
+        const int a_ = (int)lo_[e], b_ = (int)hi_[e];                                                \
+        lo_[e] = (uint32_t)__builtin_amdgcn_update_dpp(a_, b_, 0x128, 0xF, 0xC, false);   /* lanes 8-15: b of lanes 0-7 */ \
+        hi_[e] = (uint32_t)__builtin_amdgcn_update_dpp(b_, a_, 0x128, 0xF, 0x3, false);   /* lanes 0-7: a of lanes 8-15 */ \
     }
-    if (tail) {
 #pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int s = 0; s < S; ++s)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const bool in = BT_IN(s, h);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        xa[t][s][h][e] = in ? xa[t][s][h][e] : 0u;
-                }
+    for (int s = 0; s < R; ++s) {
+        BT_LOAD(s, s, row)
+        BT_LOAD_X(s)
     }
-    for (int g = 0; g < ngroups; ++g) {
-        const int gn = g + 1 < ngroups ? g + 1 : g;        // past the last group its blocks are loaded again
-        const int64_t row_next[2] = {BT_ROW(gn, 0), BT_ROW(gn, 1)};
-        f32x4_b acc[T][NMAT];
+    f32x4_b acc[T][NMAT];
+    // the blocks of one group; behind the last block the loads of the next group's first ones are on their way
+    auto stream = [&](auto first, const int g) __attribute__((always_inline)) {
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -173,24 +174,29 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
                 acc[t][m] = (f32x4_b){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-            // the halves of the two loads change places: then a register holds sixteen neurons
 #pragma unroll
             for (int m = 0; m < NMAT; ++m)
+                BT_SWAP(wb[s % R][m][0], wb[s % R][m][1])
+            if (first) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int a = (int)wb[s % R][m][0][e], b = (int)wb[s % R][m][1][e];
-                    wb[s % R][m][0][e] = (uint32_t)__builtin_amdgcn_update_dpp(a, b, 0x128, 0xF, 0xC, false);   // lanes 8-15: b of lanes 0-7
-                    wb[s % R][m][1][e] = (uint32_t)__builtin_amdgcn_update_dpp(b, a, 0x128, 0xF, 0x3, false);   // lanes 0-7: a of lanes 8-15
-                }
+                for (int t = 0; t < T; ++t)
+                    BT_SWAP(xa[t][s][0], xa[t][s][1])
+            }
             if (tail) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const bool in = BT_IN(s, h);
 #pragma unroll
-                    for (int m = 0; m < NMAT; ++m)
+                    for (int e = 0; e < 4; ++e) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
+                        for (int m = 0; m < NMAT; ++m)
                             wb[s % R][m][h][e] = in ? wb[s % R][m][h][e] : 0u;
+                        if (first) {
+#pragma unroll
+                            for (int t = 0; t < T; ++t)
+                                xa[t][s][h][e] = in ? xa[t][s][h][e] : 0u;
+                        }
+                    }
                 }
             }
 #pragma unroll
@@ -201,14 +207,23 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
                     for (int t = 0; t < T; ++t)
                         acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_b, wb[s % R][m][h]),
                                                                             __builtin_bit_cast(bf16x8_b, xa[t][s][h]), acc[t][m], 0, 0, 0);
-            if (s + R < S)
-                BT_LOAD(s % R, s + R, row_cur)
-            else
-                BT_LOAD(s % R, s + R - S, row_next)
+            if (s + R < S) {
+                BT_LOAD(s % R, s + R, row)
+                if (first)
+                    BT_LOAD_X(s + R)
+            } else {
+                // past the last group every lane loads the same few bytes: its own blocks once more were a tenth of all that was read
+                if (s + R == S) {
+                    row[0] = g + 1 == ngroups ? 0 : BT_ROW(g + 1, 0);
+                    row[1] = g + 1 == ngroups ? 0 : BT_ROW(g + 1, 1);
+                }
+                BT_LOAD(s % R, s + R - S, row)
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
-        row_cur[0] = row_next[0];
-        row_cur[1] = row_next[1];
+    };
+    stream(std::true_type{}, 0);
+    for (int g = 0;;) {
         // the waves' tiles of the group: lane holds row (of the batch) r16 and neurons 4q .. 4q+3
         const int gi = g % p.NB;
         unsigned char *buf = bt_smem + gi * (W * T * NMAT * 1024) + lane * 16;
@@ -217,14 +232,14 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
 #pragma unroll
             for (int m = 0; m < NMAT; ++m)
                 *(f32x4_b *)(buf + ((wave * T + t) * NMAT + m) * 1024) = acc[t][m];
-        if (gi != p.NB - 1 && g != ngroups - 1)
-            continue;
+        if (gi == p.NB - 1 || g == ngroups - 1) {
         // the waves meet: the tiles of the last NB groups are shared out over them
         BT_BARRIER()
         for (int i = wave; i < (gi + 1) * T; i += W) {
             const int ge = g - gi + i / T, t = i % T;
             buf = bt_smem + (i / T) * (W * T * NMAT * 1024) + lane * 16;
             f32x4_b u = {0.f, 0.f, 0.f, 0.f}, gt = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
             for (int w = 0; w < W; ++w) {
                 u += *(const f32x4_b *)(buf + ((w * T + t) * NMAT) * 1024);
                 if (GATED)
@@ -266,10 +281,16 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
                     }
             }
         }
-        if (g != ngroups - 1)
+        }
+        if (++g == ngroups)
+            break;
+        if (gi == p.NB - 1)
             BT_BARRIER()                 // the tiles may be written again
+        stream(std::false_type{}, g);
     }
 #undef BT_BARRIER
+#undef BT_SWAP
+#undef BT_LOAD_X
 #undef BT_BLK
 #undef BT_K0
 #undef BT_IN
@@ -331,11 +352,12 @@ __global__ __launch_bounds__(BT_WAVES2 * 64) void ff_batch_down_kernel(BatchPara
     const uint32_t za = zs_a + (uint32_t)(q * (T * 512) + bq * 16);
     const uint16_t *w2 = (const uint16_t *)p.W2 + min(c0 + (lane & 7) * 8, p.d - 8);    // columns past d repeat the last eight
     const int lrow = lane >> 3;
-// the four LDS-DMA instructions of step s_: rows 8u .. 8u+7 of its 32 neurons, 128 bytes per row
+// the four LDS-DMA instructions of step s_: rows 8u .. 8u+7 of its 32 neurons, 128 bytes per row (past the last step all take
+// row 0: the last step's once more, a step of the ten that 40 rows of 3072 x 12288 have, is read for nothing)
 #define BD_ISSUE(s_)                                                                                         \
     _Pragma("unroll") for (int u = 0; u < 4; ++u)                                                            \
     {                                                                                                        \
-        const int row_ = min(j_lo + min((s_), S - 1) * 32 + u * 8 + lrow, p.n - 1);                          \
+        const int row_ = (s_) < S ? min(j_lo + (s_) * 32 + u * 8 + lrow, p.n - 1) : 0;                       \
         __builtin_amdgcn_global_load_lds((gbl_cvoid_b *)(w2 + (int64_t)row_ * p.ld),                         \
                                          (lds_void_b *)(ring + ((s_) % BD_DEPTH) * BD_SLOT + u * BD_REGION), 16, 0, BT_NT); \
     }
@@ -346,31 +368,20 @@ __global__ __launch_bounds__(BT_WAVES2 * 64) void ff_batch_down_kernel(BatchPara
         for (int c = 0; c < 4; ++c)
             acc[t][c] = (f32x4_b){0.f, 0.f, 0.f, 0.f};
     // LDS accesses by inline asm here and below: those the compiler knows about would wait for every LDS-DMA in flight.
-    // The range's fragments (32 T units of 16 bytes per eight neurons, zero beyond the range): four loads per thread on
-    // their way at once, and the first pieces of W2 leave right behind the first four.
+    // The range's fragments (32 T units of 16 bytes per eight neurons, zero beyond the range) go straight into the LDS, all of them at
+    // once, and the first pieces of W2 leave right behind them.  (Through registers, four loads a thread at a time, the prologue took 2.5 us
+    // with one tile and 3.8 with three.)
     const u32x4_b *zg = (const u32x4_b *)p.z + (int64_t)(j_lo >> 3) * (32 * T);
     const int units = ((range + 7) >> 3) * (32 * T), units_all = S * 4 * (32 * T);
-    bool first = true;
-    for (int u0 = 0; u0 < units_all; u0 += 4 * BT_WAVES2 * 64) {
-        u32x4_b v[4];
+    for (int u0 = wave * 64; u0 < units; u0 += BT_WAVES2 * 64)
+        if (u0 + lane < units)
+            __builtin_amdgcn_global_load_lds((gbl_cvoid_b *)(zg + u0 + lane), (lds_void_b *)(bt_smem + BD_RING + u0 * 16), 16, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int u = u0 + r * (BT_WAVES2 * 64) + tid;
-            v[r] = u < units ? zg[u] : (u32x4_b){NO_Z, NO_Z, NO_Z, NO_Z};
-        }
-        if (first) {
-#pragma unroll
-            for (int s = 0; s < BD_DEPTH - 1; ++s)
-                BD_ISSUE(s)
-            first = false;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int u = u0 + r * (BT_WAVES2 * 64) + tid;
-            if (u < units_all)
-                asm volatile("ds_write_b128 %0, %1" :: "v"(zs_a + (uint32_t)(u * 16)), "v"(v[r]) : "memory");
-        }
-    }
+    for (int s = 0; s < BD_DEPTH - 1; ++s)
+        BD_ISSUE(s)
+    for (int u = units + tid; u < units_all; u += BT_WAVES2 * 64)
+        asm volatile("ds_write_b128 %0, %1" :: "v"(zs_a + (uint32_t)(u * 16)), "v"((u32x4_b){NO_Z, NO_Z, NO_Z, NO_Z}) : "memory");
+    __builtin_amdgcn_s_waitcnt(bt_vmcnt((BD_DEPTH - 1) * 4));       // the fragments have landed
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -485,8 +496,8 @@ __global__ __launch_bounds__(BT_WAVES2 * 64) void ff_batch_down_kernel(BatchPara
 #undef BD_PACK
 #undef BD_MFMA
     }
-    __builtin_amdgcn_s_waitcnt(bt_vmcnt(0));                   // no LDS-DMA may outlive the loop
     }
+    __builtin_amdgcn_s_waitcnt(bt_vmcnt(0));                   // no LDS-DMA may outlive the loop
 #undef BD_ISSUE
     // lane (column bq, row group q) holds rows 4q .. 4q+3 of every tile of the batch
 #pragma unroll
