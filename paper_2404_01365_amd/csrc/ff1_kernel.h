@@ -303,7 +303,8 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 #define FF1_SWZ(r) (((r) >> 1) & 7)
 
 // Tiles whose accumulators leave the registers for a second set: every kt_per_sum k-tiles the products go to partial sums, which are added
-// in ascending order.  That is what ranges of d (ff1_plan) compute, bit for bit, without slabs and a kernel that adds them.
+// in ascending order.  That is what ranges of d (ff1_plan) compute, without slabs and a kernel that adds them (bit for bit where a tile begins
+// at k-tile 0).
 #define FF1_SUMS_APART(ti_, ni_) ((ti_) * (ni_) <= 16)
 
 // What a tile of a shape has in LDS, in 16-byte slots.  Stages: tiles of up to 128 tokens x 64 neurons, which are for little work, are bound by the
@@ -371,7 +372,15 @@ __device__ __forceinline__ void ff1_walk(const Ff1Params &p, u32x4 *lds, const i
     // (checked at launch).  Raw buffer descriptors (32-bit data format word of gfx9-family raw
     // buffers); every access is in range by construction, the record count is not relied upon.
     constexpr int RSRC_FLAGS = 0x00020000, RSRC_RECORDS = 0x7FFFFFFE;
-    int m0, n0, tile_n, kt0, KT;
+    int m0, n0, tile_n, kt0, KT, rot;
+    // Rows whose stride is a multiple of 8 KB have their k-tile number kt in the same memory channels, all of them.  Where one row of token tiles reads
+    // the weights at the rate of HBM, each column of tiles therefore begins at another k-tile and goes round.  Whole selections with cold weights, all
+    // from k-tile 0 / so (us): 40 tokens of 4096 x 11008 51.5 / 46.0, of 4096 x 14336 64.2 / 52.7, 100 of it 80.6 / 63.3, 256 of 8192 x 8192 103 / 89, 64 of
+    // 4096 x 9800 (160 MB) 50.9 / 46.4; smaller blocks do not fill the channels: 40 of 4096 x 8600 (141 MB) 45.2 / 46.1, 64 of 4096 x 7000 (115 MB)
+    // 39.7 / 41.9, 40 of 8192 x 3000 (98 MB) 35.9 / 39.0; nor do other strides: 40 of 5120 x 13824 60.8 / 62.3.  With more token tiles the X that an
+    // XCD's workgroups share has to come at one time: 260 tokens of 4096 x 11008 83.2 / 85.8, 1024 of 5120 x 13824 with a start an XCD 232 / 249.
+    constexpr int MATRICES = GATED && (!PLAIN || DUAL) && !EQ2W ? 2 : 1;
+    const bool rotate = (p.ldw & 4095) == 0 && p.mt == 1 && (int64_t)p.F * p.ldw * (2 * MATRICES) >= 150000000;
     float *Zt;
     uint32_t xvo[XQ], wvo[WQ], wgvo[WQ];
     __amdgpu_buffer_rsrc_t rX, rW1, rWg;
@@ -409,13 +418,15 @@ __device__ __forceinline__ void ff1_walk(const Ff1Params &p, u32x4 *lds, const i
                                                 RSRC_RECORDS, RSRC_FLAGS);                               \
         kt0 = split_ * p.kt_per_split;                                                                   \
         KT = min(p.kt_per_split, p.d / BK - kt0);      /* k-tiles of this range (>= 1 by construction) */\
+        rot = rotate ? tile_n % KT : 0;                                                                  \
     }
     FF1_TILE_ADDR(first + slot)
 
 // LDS-DMA instruction number q of the X part (0 .. XQ-1) or of the weights (0 .. WL-1: W1, then Wg) of k-tile kt_, into the stage
 // at slot st_.  The weight tiles carry the non-temporal hint (each is used by one wave of tiles and then never
 // again; measured 3 % faster), the X tiles, which every column of tiles re-reads, do not.
-#define FF1_SO(kt_) ((kt0 + min((kt_), KT - 1)) * (BK * 2))
+#define FF1_ROT(k_) ((k_) + rot < KT ? (k_) + rot : (k_) + rot - KT)
+#define FF1_SO(kt_) ((kt0 + FF1_ROT(min((kt_), KT - 1))) * (BK * 2))
 #define FF1_LOAD_X(kt_, st_, q)                                                                          \
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rX, (lds_void_t *)(lds + (st_) + (wave * XQ + (q)) * 64), 16, xvo[q], FF1_SO(kt_), 0, 0);
 #define FF1_LOAD_W(kt_, st_, q)                                                                          \
@@ -639,6 +650,7 @@ __device__ __forceinline__ void ff1_walk(const Ff1Params &p, u32x4 *lds, const i
         stores_known = usual && whole;
     }
 #undef FF1_SO
+#undef FF1_ROT
 #undef FF1_LOAD_X
 #undef FF1_LOAD_W
 #undef FF1_MFMA_GAP

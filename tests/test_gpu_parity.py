@@ -637,6 +637,18 @@ def test_statistic_of_whole_sequences(d, F, lens):
     test_prefill_select_matches_oracle(synth.DT_F32, d, F, lens, max(1, F // 3), synth.ACT_SILU, True, False)
 
 
+# one row of token tiles over 150 MB of rows a multiple of 8 KB apart: each column of tiles begins at another k-tile
+@pytest.mark.parametrize("d,F,S,gated,bias", [(4096, 9160, 7, True, False), (12288, 3056, 60, True, True), (12288, 6112, 30, False, True),
+                                              (12288, 3053, 130, True, False), (8192, 4583, 3, True, False), (12288, 3072, 250, True, False)])
+def test_prompt_products_that_begin_at_other_k_tiles(d, F, S, gated, bias):
+    test_prefill_select_matches_oracle(synth.DT_BF16, d, F, [S], F // 2, synth.ACT_SILU if gated else synth.ACT_RELU, gated, bias)
+
+
+@pytest.mark.parametrize("d,F,S", [(6112, 12288, 20)])
+def test_prompt_outputs_that_begin_at_other_k_tiles(d, F, S):
+    test_prompt_output_of_few_tokens(d, F, S)
+
+
 # Products on two shapes of tiles; tests/test_prompt_routes.py holds them against what the calls launch
 TWO_SHAPES_CASES = [
     # d, F, tokens, activation, phase (Z leaves in bf16, too); height of the tiles, columns of them 128 wide and 96 wide
