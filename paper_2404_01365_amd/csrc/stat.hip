@@ -11,7 +11,7 @@
 // number of chunks in proportion to its length (so that prompts of different lengths give
 // workgroups of the same size), handled by different workgroups; a last small kernel adds a
 // sequence's chunk partials in a fixed order and takes the square root.  All of it is
-// bandwidth-bound: S*F fp32 reads.
+// bandwidth-bound: S*F fp32 reads.  Sequences for which a CU reads little are taken whole, in one kernel (stat_whole).
 #include "common.h"
 
 namespace griffin {
