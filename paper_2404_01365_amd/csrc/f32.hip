@@ -64,25 +64,10 @@ __device__ __forceinline__ f32x4_f fn_load(const void *row, int k, int K)
 // product's C are bf16.  MT: 16-token tiles per workgroup.
 // WAVES: wavefronts of the workgroup, of which each has every WAVES-th slice.
 // CT: its 16-column tiles (two, or one of a plain product).
-// KPT: the first job.rows workgroups are a top-k's, of KPT scores a thread, and the tiles follow (0: no top-k, a grid of two dimensions).
-// All forms are one kernel, with nothing of the tile in a function of its own: the compiler schedules the loop of one that is inlined otherwise
-// (selections of 512 x 1400 blocks in fp32, 4000 tokens 203 us instead of 197; outputs of 520 tokens of a bf16 4096 x 2004 block 136 instead of 133).
-template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT, int WAVES = FN_WAVES, int CT = 2, int KPT = 0>
-__global__ __launch_bounds__(WAVES * 64) void f32_nt_kernel(F32NtParams p, TopkJob job)
+template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT, int WAVES, int CT = 2>
+__device__ __forceinline__ void f32_nt_tile(const F32NtParams &p, int bx, int by, float (*part)[GATED ? 2 : 1][MT * 16][FN_LD])
 {
     constexpr int NMAT = GATED ? 2 : 1, ES = BBF16 ? 2 : 4, S = 2;
-    __shared__ float part[WAVES][NMAT][MT * 16][FN_LD];
-    int bx = blockIdx.x, by = blockIdx.y;
-    if constexpr (KPT > 0) {
-        __shared__ TopkShared topk;
-        if ((bx -= job.rows) < 0) {
-            topk_row<KPT>(topk, job.scores + (int64_t)blockIdx.x * job.n, job.n, job.k, job.idx + (int64_t)blockIdx.x * job.k);
-            return;
-        }
-        const int mt = (p.M + MT * 16 - 1) / (MT * 16);
-        by = bx / mt;
-        bx -= by * mt;
-    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, q = lane >> 4;
     const int m0 = bx * (MT * 16), n0 = by * (CT * 16);
@@ -153,7 +138,7 @@ __global__ __launch_bounds__(WAVES * 64) void f32_nt_kernel(F32NtParams p, TopkJ
             for (int i = 0; i < 4; ++i)
                 part[wave][m][(t / CT) * 16 + q * 4 + i][(t % CT) * 16 + r16] = acc[m][t / CT][t % CT][i];
     __syncthreads();
-    if (!ACT && WAVES != FN_WAVES) {              // a thread has one element
+    if (!ACT) {               // a thread has one element
         for (int e = tid; e < MT * 16 * CT * 16; e += WAVES * 64) {
             const int row = e / (CT * 16), c = e % (CT * 16), col = n0 + c;
             float t = 0.0f;
@@ -177,7 +162,7 @@ __global__ __launch_bounds__(WAVES * 64) void f32_nt_kernel(F32NtParams p, TopkJ
             for (int e = 0; e < 2; ++e) {
                 float t = 0.0f;
 #pragma unroll
-                for (int w = 0; w < FN_WAVES; ++w)
+                for (int w = 0; w < WAVES; ++w)
                     t += part[w][m][row][c0 + e];
                 v[m][e] = t;
             }
@@ -186,23 +171,26 @@ __global__ __launch_bounds__(WAVES * 64) void f32_nt_kernel(F32NtParams p, TopkJ
             const int col = n0 + c0 + e;
             if (col < p.N) {
                 float u = v[0][e] + (p.b ? load_scalar<BBF16>(p.b, col) : 0.0f);
-                if (ACT) {
-                    if (GATED)
-                        u = act_apply(p.act, v[NMAT - 1][e] + (p.bg ? load_scalar<BBF16>(p.bg, col) : 0.0f)) * u;
-                    else
-                        u = act_apply(p.act, u);
-                    sq = fmaf(u, u, sq);
-                }
+                if (GATED)
+                    u = act_apply(p.act, v[NMAT - 1][e] + (p.bg ? load_scalar<BBF16>(p.bg, col) : 0.0f)) * u;
+                else
+                    u = act_apply(p.act, u);
+                sq = fmaf(u, u, sq);
                 if (grow < p.M)
                     store_scalar<BBF16>(p.C, (int64_t)grow * p.ldc + col, u);
             }
         }
-        if (ACT) {
-            sq = row16_sum(sq);
-            if ((tid & 15) == 0 && grow < p.M)
-                p.rowpart[(int64_t)grow * p.nt + by] = sq;
-        }
+        sq = row16_sum(sq);
+        if ((tid & 15) == 0 && grow < p.M)
+            p.rowpart[(int64_t)grow * p.nt + by] = sq;
     }
+}
+
+template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT>
+__global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
+{
+    __shared__ float part[FN_WAVES][GATED ? 2 : 1][MT * 16][FN_LD];
+    f32_nt_tile<ACT, GATED, BBF16, VEC, MT, FN_WAVES>(p, blockIdx.x, blockIdx.y, part);
 }
 
 // Outputs of little work (at most a 32 x 32 tile for every CU): sixteen wavefronts halve the chain of loads, T = 1 has tiles of 16 x 16 (a
@@ -211,6 +199,19 @@ __global__ __launch_bounds__(WAVES * 64) void f32_nt_kernel(F32NtParams p, TopkJ
 // wavefronts and the top-k before / so: 64 tokens of 256 x 688 23.0 / 16.8 (16 x 16 tiles; 21.9 with 32 x 32), 77 of a bf16 512 x 1001 41.7 / 25.6,
 // 200 of 1024 x 4096 113 / 103 (832 tiles of 16 x 16, more bytes a CU: 32 x 32).
 constexpr int FN_WIDE_WAVES = TOPK_THREADS / 64;
+template <bool BBF16, bool VEC, int T, int KPT>
+__global__ __launch_bounds__(TOPK_THREADS) void f32_out_topk_kernel(F32NtParams p, TopkJob t)
+{
+    __shared__ union {
+        float part[FN_WIDE_WAVES][1][T * 16][FN_LD];
+        TopkShared topk;
+    } sh;
+    const int b = (int)blockIdx.x - t.rows, mt = (p.M + T * 16 - 1) / (T * 16);
+    if (b < 0)
+        topk_row<KPT>(sh.topk, t.scores + (int64_t)blockIdx.x * t.n, t.n, t.k, t.idx + (int64_t)blockIdx.x * t.k);
+    else
+        f32_nt_tile<false, false, BBF16, VEC, T, FN_WIDE_WAVES, T>(p, b % mt, b / mt, sh.part);
+}
 
 int f32_ntiles(int32_t n) { return (n + FN_COLS - 1) / FN_COLS; }
 
@@ -228,8 +229,8 @@ int launch_f32_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M
     const dim3 grid((unsigned)((M + (tall ? 63 : 31)) / (tall ? 64 : 32)), p.nt), block(FN_WAVES * 64);
 #define FN_GO(ACT_, GA_, BF_, VEC_)                                                                          \
     {                                                                                                        \
-        if (tall) hipLaunchKernelGGL((f32_nt_kernel<ACT_, GA_, BF_, VEC_, 4>), grid, block, 0, st, p, TopkJob{});       \
-        else hipLaunchKernelGGL((f32_nt_kernel<ACT_, GA_, BF_, VEC_, 2>), grid, block, 0, st, p, TopkJob{});            \
+        if (tall) hipLaunchKernelGGL((f32_nt_kernel<ACT_, GA_, BF_, VEC_, 4>), grid, block, 0, st, p);       \
+        else hipLaunchKernelGGL((f32_nt_kernel<ACT_, GA_, BF_, VEC_, 2>), grid, block, 0, st, p);            \
     }
     if (L.Wg) FN_GO(true, true, false, true)
     else FN_GO(true, false, false, true)
@@ -251,8 +252,8 @@ int launch_f32_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d,
         const TopkJob t = topk ? *topk : TopkJob{nullptr, nullptr, 0, 0, 0};
 #define FN_OUT_GO(BF_, VEC_, KPT_)                                                                                          \
         {                                                                                                                   \
-            if (small <= 256) hipLaunchKernelGGL((f32_nt_kernel<false, false, BF_, VEC_, 1, FN_WIDE_WAVES, 1, KPT_>), dim3((unsigned)(t.rows + small)), dim3(TOPK_THREADS), 0, st, p, t); \
-            else hipLaunchKernelGGL((f32_nt_kernel<false, false, BF_, VEC_, 2, FN_WIDE_WAVES, 2, KPT_>), dim3((unsigned)(t.rows + tiles)), dim3(TOPK_THREADS), 0, st, p, t); \
+            if (small <= 256) hipLaunchKernelGGL((f32_out_topk_kernel<BF_, VEC_, 1, KPT_>), dim3((unsigned)(t.rows + small)), dim3(TOPK_THREADS), 0, st, p, t); \
+            else hipLaunchKernelGGL((f32_out_topk_kernel<BF_, VEC_, 2, KPT_>), dim3((unsigned)(t.rows + tiles)), dim3(TOPK_THREADS), 0, st, p, t); \
         }
 #define FN_OUT(KPT_)                                                                                                        \
         {                                                                                                                   \
@@ -264,7 +265,7 @@ int launch_f32_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d,
         TOPK_RIDE(t.n, FN_OUT)
 #undef FN_OUT
 #undef FN_OUT_GO
-        return check_launch("f32_nt_kernel");
+        return check_launch("f32_out_topk_kernel");
     }
     if (topk) {
         const int rc = launch_topk(topk->scores, topk->rows, topk->n, topk->k, topk->idx, st);
