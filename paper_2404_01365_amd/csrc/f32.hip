@@ -31,24 +31,23 @@ struct F32NtParams {
     int32_t M, N, K, act, nt;
 };
 
-// four elements k .. k+3 of a row; elements past the end of the contraction are zero on both sides
+// Four elements k .. k+3 of a row.  Elements past the end of the contraction are zero on both sides: where rows come an element a load at
+// once, else when they are used (fn_cut).  With a select behind every load it was up to the compiler's order whether the loads of the next slices
+// were waited for before the MFMAs of these, and 1 to 3 % of a call hung on it; the loop itself reads no slice that is not all there.  Select behind
+// the load / so, us: selections of 4000 tokens of 512 x 1400 201 / 172, of 1500 tokens of 2048 x 6000 906 / 820; outputs of 520 tokens of a bf16 4096 x 2004
+// block 136 / 130, of 1500 tokens of 2048 x 6000 429 / 430, of 200 tokens of it 84.9 / 87.3.
 template <bool BF16, bool VEC>
 __device__ __forceinline__ f32x4_f fn_load(const void *row, int k, int K)
 {
-    f32x4_f v = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4_f v;
     if (VEC) {                // K and the strides are multiples of four, rows aligned for four elements
-        const bool in = k < K;
-        const int kc = in ? k : 0;          // the load itself is unconditional: a branch around it would make the next one wait
-        f32x4_f t;
+        const int kc = k < K ? k : 0;       // the load itself is unconditional: a branch around it would make the next one wait
         if (BF16) {
             const uint2 w = *(const uint2 *)((const uint16_t *)row + kc);
-            t = (f32x4_f){bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)};
+            v = (f32x4_f){bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)};
         } else {
-            t = *(const f32x4_f *)((const float *)row + kc);
+            v = *(const f32x4_f *)((const float *)row + kc);
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            v[e] = in ? t[e] : 0.0f;
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -56,6 +55,17 @@ __device__ __forceinline__ f32x4_f fn_load(const void *row, int k, int K)
             const float t = load_scalar<BF16>(row, k + e < K ? k + e : 0);
             v[e] = k + e < K ? t : 0.0f;
         }
+    }
+    return v;
+}
+
+template <bool VEC>
+__device__ __forceinline__ f32x4_f fn_cut(f32x4_f v, int k, int K)
+{
+    if (VEC) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            v[e] = k < K ? v[e] : 0.0f;
     }
     return v;
 }
@@ -110,6 +120,15 @@ __device__ __forceinline__ void f32_nt_tile(const F32NtParams &p, int bx, int by
                 _Pragma("unroll") for (int t = 0; t < CT * MT; ++t)                                  \
                     acc[m][t / CT][t % CT] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_[u][t / CT][c], b_[u][m][t % CT][c], acc[m][t / CT][t % CT], 0, 0, 0);
 
+// ... of which some may lie past the end
+#define FN_CUT(a_, b_, s_)                                                                           \
+    _Pragma("unroll") for (int u = 0; u < S; ++u)                                                    \
+    {                                                                                                \
+        const int k_ = (((s_) + u) * WAVES + wave) * FN_K + q * 4;                                   \
+        _Pragma("unroll") for (int t = 0; t < MT; ++t) a_[u][t] = fn_cut<VEC>(a_[u][t], k_, p.K);    \
+        _Pragma("unroll") for (int t = 0; t < CT * NMAT; ++t) b_[u][t / CT][t % CT] = fn_cut<VEC>(b_[u][t / CT][t % CT], k_, p.K); \
+    }
+
     const int steps = ((p.K + FN_K - 1) / FN_K + WAVES - 1) / WAVES;
     FN_LOAD(a0, b0, 0)
     int s = 0;
@@ -121,12 +140,16 @@ __device__ __forceinline__ void f32_nt_tile(const F32NtParams &p, int bx, int by
     }
     if (s + S < steps) {
         FN_LOAD(a1, b1, s + S)
+        FN_CUT(a0, b0, s)
         FN_MFMA(a0, b0)
+        FN_CUT(a1, b1, s + S)
         FN_MFMA(a1, b1)
     } else {
+        FN_CUT(a0, b0, s)
         FN_MFMA(a0, b0)
     }
 #undef FN_LOAD
+#undef FN_CUT
 #undef FN_MFMA
 
     // lane (column r16, row group q) holds rows 4q .. 4q+3 of every 16 x 16 tile
