@@ -74,10 +74,12 @@ __device__ __forceinline__ f32x4_f fn_cut(f32x4_f v, int k, int K)
 // product's C are bf16.  MT: 16-token tiles per workgroup.
 // WAVES: wavefronts of the workgroup, of which each has every WAVES-th slice.
 // CT: its 16-column tiles (two, or one of a plain product).
-template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT, int WAVES, int CT = 2>
+// SUMS: of a wave's slices, every SUMS-th goes to a sum of its own: eight waves with two add up exactly as sixteen with one.
+template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT, int WAVES, int CT = 2, int SUMS = 1>
 __device__ __forceinline__ void f32_nt_tile(const F32NtParams &p, int bx, int by, float (*part)[GATED ? 2 : 1][MT * 16][FN_LD])
 {
     constexpr int NMAT = GATED ? 2 : 1, ES = BBF16 ? 2 : 4, S = 2;
+    static_assert(S % SUMS == 0, "the slices of a step go to the same sums as those of the one before");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, q = lane >> 4;
     const int m0 = bx * (MT * 16), n0 = by * (CT * 16);
@@ -96,9 +98,9 @@ __device__ __forceinline__ void f32_nt_tile(const F32NtParams &p, int bx, int by
         if (GATED)
             br[NMAT - 1][t] = (const char *)p.Bg + bo;
     }
-    f32x4_f acc[NMAT][MT][CT];
+    f32x4_f acc[SUMS * NMAT][MT][CT];
 #pragma unroll
-    for (int m = 0; m < NMAT; ++m)
+    for (int m = 0; m < SUMS * NMAT; ++m)
 #pragma unroll
         for (int t = 0; t < CT * MT; ++t)
             acc[m][t / CT][t % CT] = (f32x4_f){0.0f, 0.0f, 0.0f, 0.0f};
@@ -118,7 +120,8 @@ __device__ __forceinline__ void f32_nt_tile(const F32NtParams &p, int bx, int by
         _Pragma("unroll") for (int c = 0; c < 4; ++c)                                                \
             _Pragma("unroll") for (int m = 0; m < NMAT; ++m)                                         \
                 _Pragma("unroll") for (int t = 0; t < CT * MT; ++t)                                  \
-                    acc[m][t / CT][t % CT] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_[u][t / CT][c], b_[u][m][t % CT][c], acc[m][t / CT][t % CT], 0, 0, 0);
+                    acc[u % SUMS * NMAT + m][t / CT][t % CT] =                                       \
+                        __builtin_amdgcn_mfma_f32_16x16x4f32(a_[u][t / CT][c], b_[u][m][t % CT][c], acc[u % SUMS * NMAT + m][t / CT][t % CT], 0, 0, 0);
 
 // ... of which some may lie past the end
 #define FN_CUT(a_, b_, s_)                                                                           \
@@ -154,19 +157,19 @@ __device__ __forceinline__ void f32_nt_tile(const F32NtParams &p, int bx, int by
 
     // lane (column r16, row group q) holds rows 4q .. 4q+3 of every 16 x 16 tile
 #pragma unroll
-    for (int m = 0; m < NMAT; ++m)
+    for (int m = 0; m < SUMS * NMAT; ++m)
 #pragma unroll
         for (int t = 0; t < CT * MT; ++t)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                part[wave][m][(t / CT) * 16 + q * 4 + i][(t % CT) * 16 + r16] = acc[m][t / CT][t % CT][i];
+                part[m / NMAT * WAVES + wave][m % NMAT][(t / CT) * 16 + q * 4 + i][(t % CT) * 16 + r16] = acc[m][t / CT][t % CT][i];
     __syncthreads();
     if (!ACT) {               // a thread has one element
         for (int e = tid; e < MT * 16 * CT * 16; e += WAVES * 64) {
             const int row = e / (CT * 16), c = e % (CT * 16), col = n0 + c;
             float t = 0.0f;
 #pragma unroll
-            for (int w = 0; w < WAVES; ++w)
+            for (int w = 0; w < WAVES * SUMS; ++w)
                 t += part[w][0][row][c];
             if (m0 + row < p.M && col < p.N)
                 store_scalar<BBF16>(p.C, (int64_t)(m0 + row) * p.ldc + col, t + (p.b ? load_scalar<BBF16>(p.b, col) : 0.0f));
@@ -209,11 +212,11 @@ __device__ __forceinline__ void f32_nt_tile(const F32NtParams &p, int bx, int by
     }
 }
 
-template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT>
+template <bool ACT, bool GATED, bool BBF16, bool VEC, int MT, int SUMS = 1>
 __global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
 {
-    __shared__ float part[FN_WAVES][GATED ? 2 : 1][MT * 16][FN_LD];
-    f32_nt_tile<ACT, GATED, BBF16, VEC, MT, FN_WAVES>(p, blockIdx.x, blockIdx.y, part);
+    __shared__ float part[FN_WAVES * SUMS][GATED ? 2 : 1][MT * 16][FN_LD];
+    f32_nt_tile<ACT, GATED, BBF16, VEC, MT, FN_WAVES, 2, SUMS>(p, blockIdx.x, blockIdx.y, part);
 }
 
 // Outputs of little work (at most a 32 x 32 tile for every CU): sixteen wavefronts halve the chain of loads, T = 1 has tiles of 16 x 16 (a
@@ -221,6 +224,10 @@ __global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
 // of a prompt phase, which needs one CU a sequence and nothing of the product, goes in the first workgroups.  Whole prompt phases, us, eight
 // wavefronts and the top-k before / so: 64 tokens of 256 x 688 23.0 / 16.8 (16 x 16 tiles; 21.9 with 32 x 32), 77 of a bf16 512 x 1001 41.7 / 25.6,
 // 200 of 1024 x 4096 113 / 103 (832 tiles of 16 x 16, more bytes a CU: 32 x 32).
+// Without a top-k to carry (griffin_ff_prompt_out) eight waves may be faster, with two sums each: the bits are those of the prompt phase.  Outputs
+// alone, us, eight waves with one sum / with two / sixteen waves: 64 tokens of 64 x 128 4.4 / 5.0 / 4.7 (a slice for each of the eight), 500 of 256 x 688 7.5 / 7.8 /
+// 10.0, of 512 x 1400 13.5 / 13.6 / 13.8, of 512 x 2048 19.9 / - / 18.6, 250 of 1024 x 4096 36.1 / - / 33.4; of rows that come an element a load, 400 of
+// 256 x 255 7.3 / 7.5 / 12.1, of 512 x 697 18.6 / 19.3 / 22.8, of 256 x 801 22.3 / - / 22.6, 77 of 1024 x 4099 91 / 111 / 94.
 constexpr int FN_WIDE_WAVES = TOPK_THREADS / 64;
 template <bool BBF16, bool VEC, int T, int KPT>
 __global__ __launch_bounds__(TOPK_THREADS) void f32_out_topk_kernel(F32NtParams p, TopkJob t)
@@ -271,7 +278,8 @@ int launch_f32_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d,
     const dim3 grid((unsigned)((M + (tall ? 63 : 31)) / (tall ? 64 : 32)), p.nt), block(FN_WAVES * 64);
     const bool vec = F % 4 == 0 && ldz % 4 == 0 && ldw % 4 == 0 && ((uintptr_t)Z & 15) == 0 && ((uintptr_t)W2p & (bf16 ? 7 : 15)) == 0;
     const int64_t tiles = (M + 31) / 32 * p.nt, small = (M + 15) / 16 * ((d + 15) / 16);
-    if (tiles <= 256) {
+    const bool little = tiles <= 256, few = F <= FN_WAVES * FN_K, two_sums = little && !topk && !few && small > 256 && F < (vec ? 1700 : 700);
+    if (little && (topk || !few) && !two_sums) {
         const TopkJob t = topk ? *topk : TopkJob{nullptr, nullptr, 0, 0, 0};
 #define FN_OUT_GO(BF_, VEC_, KPT_)                                                                                          \
         {                                                                                                                   \
@@ -294,6 +302,13 @@ int launch_f32_ff2(const float *Z, int64_t ldz, int64_t M, int32_t F, int32_t d,
         const int rc = launch_topk(topk->scores, topk->rows, topk->n, topk->k, topk->idx, st);
         if (rc != GRIFFIN_OK)
             return rc;
+    }
+    if (two_sums) {
+#define FN_TWO(BF_, VEC_) hipLaunchKernelGGL((f32_nt_kernel<false, false, BF_, VEC_, 2, 2>), grid, block, 0, st, p);
+        if (bf16) { if (vec) FN_TWO(true, true) else FN_TWO(true, false) }
+        else      { if (vec) FN_TWO(false, true) else FN_TWO(false, false) }
+#undef FN_TWO
+        return check_launch("f32_nt_kernel");
     }
     if (bf16) { if (vec) FN_GO(false, false, true, true) else FN_GO(false, false, true, false) }
     else      { if (vec) FN_GO(false, false, false, true) else FN_GO(false, false, false, false) }

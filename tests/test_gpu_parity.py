@@ -1048,6 +1048,13 @@ def test_prompt_phase_top_k_beside_the_output(dtype, d, F, lens, gated):
     test_prompt_phase_is_selection_plus_prompt_output_from_one_z(dtype, d, F, lens, F // 3, gated, False)
 
 
+@pytest.mark.parametrize("dtype,d,F,S", [(synth.DT_F32, 64, 128, 1100), (synth.DT_F32, 512, 136, 260), (synth.DT_F32, 520, 1400, 250), (synth.DT_BF16, 512, 1004, 270),
+                                            (synth.DT_F32, 512, 141, 260), (synth.DT_BF16, 104, 687, 650)])
+def test_fp32_output_of_eight_waves_has_the_bits_of_the_prompt_phase(dtype, d, F, S):
+    """The output alone on eight waves, of a sum each (one slice for each of them) or of two; in the prompt phase sixteen waves."""
+    test_prompt_phase_is_selection_plus_prompt_output_from_one_z(dtype, d, F, [S], F // 3, True, False)
+
+
 # ------------------------------------------------------------------ static and sampled selectors, set similarity
 @pytest.mark.parametrize("dtype,d,F,gated", [
     (synth.DT_BF16, 512, 1000, True), (synth.DT_BF16, 8, 5, True), (synth.DT_BF16, 4096, 700, False),

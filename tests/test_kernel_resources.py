@@ -77,7 +77,7 @@ def test_rows_that_go_alone_keep_their_occupancy(pattern, vgprs):
 @pytest.mark.parametrize("flags,tiles,vgprs", [((1, 1, 0, 1), 2, 150), ((1, 1, 0, 1), 4, 248), ((1, 0, 0, 1), 2, 88), ((1, 0, 0, 1), 4, 148),
                                                ((0, 0, 0, 1), 2, 88), ((0, 0, 0, 1), 4, 148), ((0, 0, 1, 1), 2, 88), ((0, 0, 1, 1), 4, 148)])
 def test_fp32_product_keeps_its_registers(flags, tiles, vgprs):
-    hits = [k for n, k in kernels().items() if re.search("f32_nt_kernelI%sLi%dE" % ("".join("Lb%dE" % f for f in flags), tiles), n)]
+    hits = [k for n, k in kernels().items() if re.search("f32_nt_kernelI%sLi%dELi1E" % ("".join("Lb%dE" % f for f in flags), tiles), n)]
     assert len(hits) == 1 and hits[0][".vgpr_count"] <= vgprs and hits[0][".private_segment_fixed_size"] == 0
 
 

@@ -101,3 +101,20 @@ def test_statistic_in_one_kernel_while_a_cu_reads_little():
              (512, 11009, [1500]), (512, 11009, [3000]), (256, 688, [1])]
     got = [any("stat_whole" in l["name"] for l in ls) for ls in launches.record([dict(entry="select", d=d, n=F, lens=v) for d, F, v in calls])]
     assert got == [True, False, True, False, True, False, True, False, True]
+
+
+def test_fp32_outputs_take_sixteen_waves_where_that_is_faster():
+    """Forms of the second product in fp32, with a top-k to carry and without: waves, sums of each, side of the tiles, a top-k apart."""
+    calls = [("out", 256, 688, 250, G.F32), ("out", 256, 688, 500, G.F32), ("phase", 256, 688, 500, G.F32), ("out", 64, 128, 64, G.F32),
+             ("phase", 64, 128, 64, G.F32), ("out", 512, 1400, 500, G.F32), ("out", 512, 2048, 500, G.F32), ("out", 1024, 4099, 77, G.F32),
+             ("out", 512, 1001, 200, G.BF16), ("out", 512, 1004, 250, G.BF16), ("out", 96, 287, 1000, G.F32), ("phase", 96, 287, 1779, G.F32), ("out", 256, 688, 1500, G.F32)]
+    got = []
+    for (entry, d, F, S, _), ls in zip(calls, launches.record([dict(entry=e, d=d, n=F, lens=[S], dtype=dt) for e, d, F, S, dt in calls])):
+        name = ls[-1]["name"]                # f32_out_topk_kernel: sixteen waves; f32_nt_kernel: eight, of one sum or two
+        m = re.search(r"(?:f32_out_topk_kernelILb\dELb\dELi(\d)E|f32_nt_kernelILb0ELb0ELb\dELb\dELi(\d)ELi(\d)E)", name)
+        got.append((entry, F, S, 16 if m[1] else 8, int(m[3] or 1), 16 * int(m[1] or m[2]), any("topk_reg" in l["name"] for l in ls)))
+    assert got == [("out", 688, 250, 16, 1, 16, False), ("out", 688, 500, 8, 2, 32, False), ("phase", 688, 500, 16, 1, 32, False),
+                   ("out", 128, 64, 8, 1, 32, False), ("phase", 128, 64, 16, 1, 16, False), ("out", 1400, 500, 8, 2, 32, False),
+                   ("out", 2048, 500, 16, 1, 32, False), ("out", 4099, 77, 16, 1, 32, False), ("out", 1001, 200, 16, 1, 32, False),
+                   ("out", 1004, 250, 8, 2, 32, False), ("out", 287, 1000, 8, 2, 32, False), ("phase", 287, 1779, 16, 1, 32, False),
+                   ("out", 688, 1500, 8, 1, 32, False)]
