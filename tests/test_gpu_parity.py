@@ -637,6 +637,15 @@ def test_statistic_of_whole_sequences(d, F, lens):
     test_prefill_select_matches_oracle(synth.DT_F32, d, F, lens, max(1, F // 3), synth.ACT_SILU, True, False)
 
 
+# ... of more than one block of 1024 rows, where the chip is full meanwhile
+LONG_WHOLE_CASES = [(8, 10240, [1100]), (8, 10241, [2049]), (8, 512, [1030, 0] + [1100] * 20)]
+
+
+@pytest.mark.parametrize("d,F,lens", LONG_WHOLE_CASES)
+def test_statistic_of_whole_long_sequences(d, F, lens):
+    test_prefill_select_matches_oracle(synth.DT_BF16, d, F, lens, F // 3, synth.ACT_SILU, True, False)
+
+
 # one row of token tiles over 150 MB of rows a multiple of 8 KB apart: each column of tiles begins at another k-tile
 @pytest.mark.parametrize("d,F,S,gated,bias", [(4096, 9160, 7, True, False), (12288, 3056, 60, True, True), (12288, 6112, 30, False, True),
                                               (12288, 3053, 130, True, False), (8192, 4583, 3, True, False), (12288, 3072, 250, True, False)])
