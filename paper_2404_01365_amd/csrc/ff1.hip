@@ -570,7 +570,7 @@ bool ff1_can_write_zb(const griffin_layer &L, int64_t ldx, const float *Z, int64
 int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz,
                float **rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb, float *tail, size_t room)
 {
-    Ff1Params p;
+    Ff1Params p = {};
     p.X = X; p.Wg = L.Wg; p.W1 = L.W1; p.bg = L.bg; p.b1 = L.b1;
     p.Z = Z; p.rowpart = *rowpart;
     p.Zb = (Zb && ff1_can_write_zb(L, ldx, Z, ldz)) ? Zb : nullptr;
@@ -717,7 +717,7 @@ void gemm_nt_split_plan(int64_t M, int32_t N, int32_t K, int *splits, int *kt_pe
 int launch_gemm_nt_partials(const void *A, int64_t lda, const void *B, int64_t ldb, int64_t M, int32_t N, int32_t K,
                             int splits, int kt_per_split, float *C, int64_t ldc, hipStream_t st)
 {
-    Ff1Params p;
+    Ff1Params p = {};
     p.X = A; p.Wg = nullptr; p.W1 = B; p.bg = nullptr; p.b1 = nullptr;
     p.Z = C; p.rowpart = nullptr;
     p.Zb = nullptr; p.ldzb = 0;

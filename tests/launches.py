@@ -44,7 +44,7 @@ int hipFuncSetAttribute(const void *f, int a, int v) { return 0; }
 class Ff1Params(ctypes.Structure):          # as in csrc/ff1_kernel.h
     _fields_ = ([(p, ctypes.c_void_p) for p in ("X", "Wg", "W1", "bg", "b1", "Z", "rowpart", "Zb")] +
                 [(v, ctypes.c_int64) for v in ("ldx", "ldw", "ldz", "ldzb")] +
-                [(v, ctypes.c_int32) for v in ("M", "F", "d", "nt", "mt", "splits", "kt_per_split", "kt_per_sum", "z_stream")])
+                [(v, ctypes.c_int32) for v in ("M", "F", "d", "nt", "mt", "splits", "kt_per_split", "kt_per_sum", "z_stream", "nt_row")])
 
 
 class _Note(ctypes.Structure):

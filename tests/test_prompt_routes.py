@@ -130,3 +130,12 @@ def test_fp32_outputs_take_sixteen_waves_where_that_is_faster():
                    ("out", 2048, 500, 16, 1, 32, False), ("out", 4099, 77, 16, 1, 32, False), ("out", 1001, 200, 16, 1, 32, False),
                    ("out", 1004, 250, 8, 2, 32, False), ("out", 287, 1000, 8, 2, 32, False), ("phase", 287, 1779, 16, 1, 32, False),
                    ("out", 688, 1500, 8, 1, 32, False)]
+
+
+def test_every_field_of_a_launch_is_set():
+    """The row partials' stride of products that write none (raw ranges, outputs of a prompt) and of those that do."""
+    calls = [dict(entry="select", d=2560, n=17424, lens=[47]), dict(entry="out", d=512, n=4096, lens=[40]),
+             dict(entry="select", d=512, n=1000, lens=[300])]
+    got = [[l for l in ls if launches.form(l["name"])][0] for ls in launches.record(calls)]
+    assert [" raw " in launches.form(l["name"]) for l in got] == [True, True, False]
+    assert [l["nt_row"] for l in got] == [0, 0, got[2]["nt"]]
