@@ -567,6 +567,23 @@ bool ff1_can_write_zb(const griffin_layer &L, int64_t ldx, const float *Z, int64
     return L.dtype == GRIFFIN_BF16 && !ktail && vec && bias8 && ldz <= FF1_LDZ_MAX;
 }
 
+// Rows whose stride is a multiple of 8 KB have their k-tile number kt in the same memory channels, all of them.  Where one row of token tiles reads
+// the weights at the rate of HBM, each column of tiles therefore begins at another k-tile and goes round.  What counts is the bytes that are
+// read, not the stride: rows may be padded or interleaved.  Whole selections with cold weights, all from k-tile 0 / so (us).  Eq. 3: 40 tokens of
+// 4096 x 11008 (180 MB) 52 / 46 or 47.6 / 46.2, after where the matrices lie, of 4096 x 14336 64 / 51, 100 of it 81 / 66, 40 of 4096 x 9100 46.5 / 44.1; smaller
+// blocks as often lose: 40 of 4096 x 8900 (146 MB) 46.2 / 47.3, 64 of it 49.0 / 46.7, 40 of 8192 x 4400 42.8 / 43.6, of 8192 x 3000 (98 MB) 36.6 / 39.3; nor
+// do other strides gain: 40 of 5120 x 13824 60.8 / 62.3.  Rows with room between them gain from 139 MB on (40 and 64 tokens of 4096 x 8500 at a stride of 24 KB 46.2 / 47.2
+// and 52.5 / 48.2, 100 of 5120 x 6912 at 16 KB 51.7 / 48.2), below that as often lose as gain (sixteen blocks of 51 to 131 MB, 8 to 250 tokens: 0.96 to 1.02 a block, 0.998 in
+// all; 40 of 4096 x 5504, 90 MB, at 24 KB 38.1 / 39.2, 100 of 4096 x 7168, 117 MB, 44.5 / 46.4).
+// Eq. 2: 40 and 100 tokens of 8192 x 16384 (268 MB) 84 / 63 and 94 / 74, 200 of 4096 x 20000 (164 MB) 80.6 / 78.7, but 40 of it 55.1 / 56.6.  Ranges of d: 2 tokens of
+// 16384 x 2300 (151 MB) 42.8 / 39.3, 100 of 12288 x 3100 51.9 / 50.4.  Outputs (one matrix): 100 tokens of 6144 x 12288 (151 MB) 48.1 / 45.1, 40 of 5120 x 16384 43.8 / 40.7,
+// 128 of 7168 x 20480 81 / 75.  With more token tiles the X that an XCD's workgroups share has to come at one time: 260 tokens of
+// 4096 x 11008 83.2 / 85.8, 1024 of 5120 x 13824 with a start an XCD 232 / 249.
+static int32_t ff1_rotates(const Ff1Params &p, int matrices)
+{
+    return (p.ldw & 4095) == 0 && p.mt == 1 && (int64_t)p.F * p.d * (2 * matrices) >= (p.ldw == p.d ? 150000000 : 139000000);
+}
+
 int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, float *Z, int64_t ldz,
                float **rowpart, int32_t *nt_out, hipStream_t st, uint16_t *Zb, int64_t ldzb, float *tail, size_t room)
 {
@@ -595,6 +612,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
             p.splits = pl.splits; p.kt_per_split = pl.per;
             const int ti = ff1_plain_tile(M).ti;
             p.mt = (int32_t)((M + 32 * ti - 1) / (32 * ti));
+            p.rotate = ff1_rotates(p, 2);
             launch_plain<true>(p, ti, ff1_grid(p.mt * p.nt * pl.splits, M <= 64 ? 2 : 1), st);
             rc = check_launch("ff1_bf16_mfma_kernel");
         } else {
@@ -620,6 +638,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
     if (two.ti && room >= ff1_two_bytes(two, M)) {
         const int64_t split = std::min((int64_t)L.n, two.wide * 128);
         p.mt = (int32_t)((M + 32 * two.ti - 1) / (32 * two.ti));
+        p.rotate = ff1_rotates(p, 2);
         p.rowpart = *rowpart = tail;
         p.nt_row = *nt_out = (int32_t)(two.wide + two.narrow);
         Ff1Params b = p;
@@ -654,6 +673,7 @@ int launch_ff1(const griffin_layer &L, const void *X, int64_t ldx, int64_t M, fl
         }
         p.mt = (int32_t)((M + 32 * t.ti - 1) / (32 * t.ti));
     }
+    p.rotate = ff1_rotates(p, gated ? 2 : 1);
     *nt_out = p.nt_row = p.nt;
     if (M == 0)
         return GRIFFIN_OK;
@@ -728,6 +748,7 @@ int launch_gemm_nt_partials(const void *A, int64_t lda, const void *B, int64_t l
     p.nt = (N + 2 * G_BN - 1) / (2 * G_BN);        // 256-column tiles: both sets of accumulators hold columns of B
     const int ti = ff1_plain_tile(M).ti;
     p.mt = (int32_t)((M + 32 * ti - 1) / (32 * ti));
+    p.rotate = ff1_rotates(p, 1);
     launch_plain<false>(p, ti, ff1_grid(p.mt * p.nt * splits, M <= 64 ? 2 : 1), st);
     return check_launch("ff1_bf16_mfma_kernel");
 }

@@ -28,6 +28,7 @@ struct Ff1Params {
     int32_t splits, kt_per_split;    // ranges of the contraction (1 for the activations) and 64-wide k-tiles per range
     int32_t kt_per_sum;              // k-tiles that are summed apart and then added (FF1_SUMS_APART shapes)
     int32_t z_stream;                // Z leaves with the non-temporal hint (see launch_ff1)
+    int32_t rotate;                  // each column of tiles begins at another k-tile (ff1_rotates)
     int32_t nt_row;                  // row partials of a token (nt, or those of both parts of a product on two shapes of tiles)
 };
 
@@ -373,14 +374,6 @@ __device__ __forceinline__ void ff1_walk(const Ff1Params &p, u32x4 *lds, const i
     // buffers); every access is in range by construction, the record count is not relied upon.
     constexpr int RSRC_FLAGS = 0x00020000, RSRC_RECORDS = 0x7FFFFFFE;
     int m0, n0, tile_n, kt0, KT, rot;
-    // Rows whose stride is a multiple of 8 KB have their k-tile number kt in the same memory channels, all of them.  Where one row of token tiles reads
-    // the weights at the rate of HBM, each column of tiles therefore begins at another k-tile and goes round.  Whole selections with cold weights, all
-    // from k-tile 0 / so (us): 40 tokens of 4096 x 11008 51.5 / 46.0, of 4096 x 14336 64.2 / 52.7, 100 of it 80.6 / 63.3, 256 of 8192 x 8192 103 / 89, 64 of
-    // 4096 x 9800 (160 MB) 50.9 / 46.4; smaller blocks do not fill the channels: 40 of 4096 x 8600 (141 MB) 45.2 / 46.1, 64 of 4096 x 7000 (115 MB)
-    // 39.7 / 41.9, 40 of 8192 x 3000 (98 MB) 35.9 / 39.0; nor do other strides: 40 of 5120 x 13824 60.8 / 62.3.  With more token tiles the X that an
-    // XCD's workgroups share has to come at one time: 260 tokens of 4096 x 11008 83.2 / 85.8, 1024 of 5120 x 13824 with a start an XCD 232 / 249.
-    constexpr int MATRICES = GATED && (!PLAIN || DUAL) && !EQ2W ? 2 : 1;
-    const bool rotate = (p.ldw & 4095) == 0 && p.mt == 1 && (int64_t)p.F * p.ldw * (2 * MATRICES) >= 150000000;
     float *Zt;
     uint32_t xvo[XQ], wvo[WQ], wgvo[WQ];
     __amdgpu_buffer_rsrc_t rX, rW1, rWg;
@@ -418,7 +411,7 @@ __device__ __forceinline__ void ff1_walk(const Ff1Params &p, u32x4 *lds, const i
                                                 RSRC_RECORDS, RSRC_FLAGS);                               \
         kt0 = split_ * p.kt_per_split;                                                                   \
         KT = min(p.kt_per_split, p.d / BK - kt0);      /* k-tiles of this range (>= 1 by construction) */\
-        rot = rotate ? tile_n % KT : 0;                                                                  \
+        rot = p.rotate ? tile_n % KT : 0;                                                                 \
     }
     FF1_TILE_ADDR(first + slot)
 

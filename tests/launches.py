@@ -16,7 +16,7 @@ _SHIM = r"""
 #include <stddef.h>
 #include <string.h>
 typedef struct { unsigned x, y, z; } dim3_t;
-typedef struct { char name[400]; unsigned grid[3]; unsigned char params[136]; } note_t;
+typedef struct { char name[400]; unsigned grid[3]; unsigned char params[144]; } note_t;
 static note_t notes[64];
 static int count;
 int shim_take(void *out) { int n = count; memcpy(out, notes, sizeof(note_t) * n); count = 0; return n; }
@@ -44,11 +44,11 @@ int hipFuncSetAttribute(const void *f, int a, int v) { return 0; }
 class Ff1Params(ctypes.Structure):          # as in csrc/ff1_kernel.h
     _fields_ = ([(p, ctypes.c_void_p) for p in ("X", "Wg", "W1", "bg", "b1", "Z", "rowpart", "Zb")] +
                 [(v, ctypes.c_int64) for v in ("ldx", "ldw", "ldz", "ldzb")] +
-                [(v, ctypes.c_int32) for v in ("M", "F", "d", "nt", "mt", "splits", "kt_per_split", "kt_per_sum", "z_stream", "nt_row")])
+                [(v, ctypes.c_int32) for v in ("M", "F", "d", "nt", "mt", "splits", "kt_per_split", "kt_per_sum", "z_stream", "rotate", "nt_row")])
 
 
 class _Note(ctypes.Structure):
-    _fields_ = [("name", ctypes.c_char * 400), ("grid", ctypes.c_uint32 * 3), ("params", ctypes.c_ubyte * 136)]
+    _fields_ = [("name", ctypes.c_char * 400), ("grid", ctypes.c_uint32 * 3), ("params", ctypes.c_ubyte * 144)]
 
 
 _FAKE = 0x7F0000001000
@@ -61,7 +61,7 @@ def _child():
     out = []
     for c in json.load(sys.stdin):
         L = G.griffin_layer()
-        L.d, L.n, L.dtype, L.act, L.W1, L.W2, L.ld = c["d"], c["n"], c.get("dtype", G.BF16), c.get("act", G.ACT_SILU), _FAKE, _FAKE, c["d"]
+        L.d, L.n, L.dtype, L.act, L.W1, L.W2, L.ld = c["d"], c["n"], c.get("dtype", G.BF16), c.get("act", G.ACT_SILU), _FAKE, _FAKE, c.get("ld") or c["d"]
         L.Wg = _FAKE if c.get("gated", True) else None
         L.b1 = _FAKE if c.get("bias") else None
         L.bg = _FAKE if c.get("bias") and c.get("gated", True) else None
@@ -70,7 +70,7 @@ def _child():
             cu.append(cu[-1] + v)
         cu = (ctypes.c_int32 * len(cu))(*cu)
         S, M, k = len(cu) - 1, cu[len(cu) - 1], max(1, c["n"] // 2)
-        ldw = (c["n"] + 7) // 8 * 8
+        ldw = c.get("ldw") or (c["n"] + 7) // 8 * 8
 
         def call(ws):
             if c["entry"] == "select":       # ldz: rows of a caller's Z that far apart
@@ -97,7 +97,7 @@ def _child():
 
 
 def record(calls):
-    """calls: dicts of entry ("select", "phase" or "out"), d, n, lens, gated, bias, act, dtype, least, ldz -> the launches of each"""
+    """calls: dicts of entry ("select", "phase" or "out"), d, n, lens, gated, bias, act, dtype, least, ldz, ld (of the block), ldw (of W2p) -> the launches of each"""
     with tempfile.TemporaryDirectory() as tmp:
         src, so = os.path.join(tmp, "shim.c"), os.path.join(tmp, "shim.so")
         with open(src, "w") as f:

@@ -139,3 +139,16 @@ def test_every_field_of_a_launch_is_set():
     got = [[l for l in ls if launches.form(l["name"])][0] for ls in launches.record(calls)]
     assert [" raw " in launches.form(l["name"]) for l in got] == [True, True, False]
     assert [l["nt_row"] for l in got] == [0, 0, got[2]["nt"]]
+
+
+def test_columns_of_tiles_begin_at_other_k_tiles_by_the_bytes_that_are_read():
+    """Not by the rows' stride: interleaved and padded rows read no more than d of it."""
+    calls = [(dict(entry="select", d=4096, n=9800, lens=[64]), 1), (dict(entry="select", d=4096, n=8600, lens=[40]), 0),
+             (dict(entry="select", d=4096, n=5504, lens=[40], ld=3 * 4096), 0), (dict(entry="select", d=4096, n=7168, lens=[100], ld=3 * 4096), 0),
+             (dict(entry="select", d=4096, n=8750, lens=[64], ld=3 * 4096), 1), (dict(entry="select", d=4096, n=7168, lens=[100], ld=8192), 0),
+             (dict(entry="select", d=5120, n=6912, lens=[100], ld=8192), 1), (dict(entry="select", d=5120, n=13824, lens=[40]), 0),
+             (dict(entry="select", d=4096, n=20000, lens=[100], gated=False), 1), (dict(entry="select", d=4096, n=13000, lens=[40], gated=False, ld=8192), 0),
+             (dict(entry="select", d=4096, n=11008, lens=[260]), 0), (dict(entry="out", d=6144, n=12288, lens=[40]), 1),
+             (dict(entry="out", d=4096, n=12288, lens=[40], ldw=4 * 12288), 0)]
+    first = [[l for l in ls if launches.form(l["name"])][0] for ls in launches.record([c for c, _ in calls])]
+    assert [(c, l["rotate"]) for (c, _), l in zip(calls, first)] == calls
