@@ -1,5 +1,5 @@
 """What a call of the library launches, without a GPU: the call is made in a process whose runtime's launch function only notes the
-kernel, its grid and (of the prompt product) its parameters."""
+kernel, its grid and (of the prompt product) its parameters, of a launch on two shapes those of both."""
 import ctypes
 import json
 import os
@@ -16,12 +16,17 @@ _SHIM = r"""
 #include <stddef.h>
 #include <string.h>
 typedef struct { unsigned x, y, z; } dim3_t;
-typedef struct { char name[400]; unsigned grid[3]; unsigned char params[144]; } note_t;
+typedef struct { char name[400]; unsigned grid[3]; unsigned char params[2][144]; } note_t;
 static note_t notes[64];
 static int count;
 int shim_take(void *out) { int n = count; memcpy(out, notes, sizeof(note_t) * n); count = 0; return n; }
-int __hipPushCallConfiguration(void) { return 0; }
-int __hipPopCallConfiguration(void) { return 0; }
+static dim3_t grid_of, block_of;
+int __hipPushCallConfiguration(dim3_t grid, dim3_t block, size_t lds, void *stream) { grid_of = grid; block_of = block; return 0; }
+int __hipPopCallConfiguration(dim3_t *grid, dim3_t *block, size_t *lds, void **stream)
+{
+    *grid = grid_of; *block = block_of; *lds = 0; *stream = 0;
+    return 0;
+}
 int hipLaunchKernel(const void *f, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream)
 {
     Dl_info at;
@@ -31,7 +36,9 @@ int hipLaunchKernel(const void *f, dim3_t grid, dim3_t block, void **args, size_
         strncpy(n->name, at.dli_sname, sizeof n->name - 1);
     n->grid[0] = grid.x; n->grid[1] = grid.y; n->grid[2] = grid.z;
     if (strstr(n->name, "Ff1Params"))
-        memcpy(n->params, args[0], sizeof n->params);
+        memcpy(n->params[0], args[0], sizeof n->params[0]);
+    if (strstr(n->name, "two_shapes"))
+        memcpy(n->params[1], args[1], sizeof n->params[1]);
     return 0;
 }
 int hipGetLastError(void) { return 0; }
@@ -48,7 +55,7 @@ class Ff1Params(ctypes.Structure):          # as in csrc/ff1_kernel.h
 
 
 class _Note(ctypes.Structure):
-    _fields_ = [("name", ctypes.c_char * 400), ("grid", ctypes.c_uint32 * 3), ("params", ctypes.c_ubyte * 144)]
+    _fields_ = [("name", ctypes.c_char * 400), ("grid", ctypes.c_uint32 * 3), ("params", ctypes.c_ubyte * 144 * 2)]
 
 
 _FAKE = 0x7F0000001000
@@ -90,8 +97,8 @@ def _child():
         assert call(ws) == G.OK, c
         found = []
         for i in range(shim.shim_take(notes)):
-            p = Ff1Params.from_buffer_copy(bytes(notes[i].params))
-            found.append(dict(name=notes[i].name.decode(), grid=list(notes[i].grid), **{f: getattr(p, f) or 0 for f, _ in Ff1Params._fields_}))
+            p, p2 = ({f: getattr(q, f) or 0 for f, _ in Ff1Params._fields_} for q in (Ff1Params.from_buffer_copy(bytes(b)) for b in notes[i].params))
+            found.append(dict(name=notes[i].name.decode(), grid=list(notes[i].grid), second=p2, **p))
         out.append(found)
     json.dump(out, sys.stdout)
 
@@ -126,6 +133,15 @@ def form(name):
     if not gated:
         return "%dx%d Eq. 2 narrow" % (32 * ti, 32 * ni)
     return "%dx%d Eq. 3%s" % (32 * ti, 32 * ni, {0: "", 1: " copy", 2: " biases"}[extra])
+
+
+_TWO = re.compile(r"ff1_bf16_two_shapes_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)E")
+
+
+def two_shapes(name):
+    """activation, bf16 copy, (tokens, neurons) of the tiles of the first and the second shape (None: another kernel)"""
+    m = _TWO.search(name)
+    return m and (int(m[1]), m[2] == "1", (32 * int(m[3]), 32 * int(m[4])), (32 * int(m[5]), 32 * int(m[6])))
 
 
 def route(launch):

@@ -673,6 +673,11 @@ TWO_SHAPES_CASES = [
     (768, 16448, 490, synth.ACT_SILU, True, 192, 85, 58),
     (768, 16832, 583, synth.ACT_SILU, True, 224, 85, 62),
     (768, 17088, 683, synth.ACT_SILU, True, 256, 85, 65),
+    # a workgroup walks several tiles of both, over more than one panel of eight token tiles; the last ones of both parts are ragged
+    (768, 9773, 1570, synth.ACT_GELU_TANH, False, 192, 51, 34),
+    (768, 6147, 2914, synth.ACT_SILU, False, 224, 31, 23),
+    (768, 6632, 2305, synth.ACT_SILU, True, 192, 31, 28),
+    (768, 9768, 2053, synth.ACT_SILU, True, 256, 51, 34),
 ]
 
 

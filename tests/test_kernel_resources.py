@@ -92,8 +92,11 @@ def test_rows_that_go_four_at_a_time_leave_room_for_three_workgroups(bf16, gated
 def test_forms_of_the_prompt_product_keep_their_registers():
     """One wave a SIMD: nothing in scratch but for the largest tile of an Eq. 2 block.  Raw products of 64 tokens go two workgroups a CU."""
     import launches
-    seen = 0
+    seen = two = 0
     for n, k in kernels().items():
+        if launches.two_shapes(n):
+            two += 1
+            assert k[".private_segment_fixed_size"] == 0 and k[".group_segment_fixed_size"] <= 160 * 1024, n
         form = launches.form(n)
         if form is None:
             continue
@@ -103,3 +106,13 @@ def test_forms_of_the_prompt_product_keep_their_registers():
         if form in ("64x128 raw Eq. 3", "64x256 raw one matrix"):
             assert k[".vgpr_count"] <= 256 and k[".group_segment_fixed_size"] <= 80 * 1024
     assert seen == 121                   # 37 of each activation and ten raw products
+    assert two == 24                     # four heights, with a copy and without, of each activation
+
+
+def test_selection_kernels_stay_out_of_scratch():
+    """... but for two words of a top-k of 32 scores a thread, on its own and beside other work; and workgroups of sixteen waves, two of them a CU."""
+    found = {n: k for n, k in kernels().items() if re.search("topk_reg_kernel|topk_kernel|stat_whole_kernel", n)}
+    assert len(found) == 8 + 4 + 4 * 8 + 2
+    for n, k in found.items():
+        assert k[".private_segment_fixed_size"] <= (8 if "Li32E" in n else 0), n
+        assert k[".group_segment_fixed_size"] <= 80 * 1024 and k[".vgpr_count"] <= (64 if "stat_whole" in n else 128), n

@@ -72,20 +72,39 @@ def test_the_least_workspace_takes_tiles_of_128_neurons():
     assert [r[0][::3] for r in routes(calls)] == [("64x64 Eq. 3 copy", 4), ("128x128 Eq. 3", 1)]
 
 
-_TWO = re.compile(r"two_shapes_kernelILi(\d)ELi(\d)ELi(\d)ELi4ELi(\d)ELi3E")
+def dealt(tiles_a, tiles_b, workgroups):
+    """The tiles of both shapes that each workgroup of ff1_bf16_two_shapes_kernel takes, by its own rule."""
+    for wg in range(workgroups):
+        x, slot, per = wg % 8, wg // 8, workgroups // 8
+        a0, a1 = x * tiles_a // 8, (x + 1) * tiles_a // 8
+        b0, b1 = x * (tiles_a + tiles_b) // 8 - a0, (x + 1) * (tiles_a + tiles_b) // 8 - a1
+        yield list(range(a0 + slot, a1, per)), list(range(b0 + per - 1 - slot, b1, per))
 
 
 def test_products_on_two_shapes_cover_the_block_once():
     two = cases.TWO_SHAPES_CASES
     calls = [dict(entry="phase" if ph else "select", d=d, n=F, lens=[S], act=act if not ph else G.ACT_SILU) for d, F, S, act, ph, *_ in two]
+    walked = 0
     for c, ls in zip(two, launches.record(calls)):
-        first = [l for l in ls if _TWO.search(l["name"])]
+        first = [l for l in ls if launches.two_shapes(l["name"])]
         assert len(first) == 1 and not any(launches.form(l["name"]) and " raw " not in launches.form(l["name"]) for l in ls), c
-        act, copy, ti, tb = (int(v) for v in _TWO.search(first[0]["name"]).groups())
-        l, (d, F, S, want, ph, height, wide, narrow) = first[0], c
-        assert (32 * ti, ti, copy, act) == (height, tb, int(ph), G.ACT_SILU if ph else want), c
-        assert l["nt"] == wide and l["F"] == min(F, 128 * wide) and -(-(F - l["F"]) // 96) == narrow, c
-        assert l["mt"] == -(-S // height), c
+        act, copy, shape_a, shape_b = launches.two_shapes(first[0]["name"])
+        l, b, (d, F, S, want, ph, height, wide, narrow) = first[0], first[0]["second"], c
+        assert (shape_a, shape_b, copy, act) == ((height, 128), (height, 96), ph, G.ACT_SILU if ph else want), c
+        assert l["nt"] == wide and l["F"] == min(F, 128 * wide) and l["mt"] == -(-S // height), c
+        # the second part: the neurons that follow, their rows of the weights, columns of Z and of its copy, and row sums
+        assert b["F"] == F - l["F"] and b["nt"] == narrow == -(-b["F"] // 96), c
+        at = {"W1": 2 * l["ldw"] * l["F"], "Wg": 2 * l["ldw"] * l["F"], "Z": 4 * l["F"], "rowpart": 4 * wide, "Zb": 2 * l["F"] if copy else 0}
+        assert {f: b[f] - l[f] for f in at} == at, c
+        assert all(b[f] == l[f] for f in ("X", "ldx", "ldw", "ldz", "ldzb", "M", "d", "mt", "splits", "kt_per_split", "kt_per_sum", "z_stream", "rotate", "nt_row"))
+        assert l["nt_row"] == wide + narrow and l["splits"] == 1 and l["kt_per_split"] == d // 64, c
+        # every tile of both is dealt once
+        tiles_a, tiles_b = l["mt"] * wide, l["mt"] * narrow
+        assert l["grid"][0] % 8 == 0 and l["grid"][1:] == [1, 1]
+        shares = list(dealt(tiles_a, tiles_b, l["grid"][0]))
+        assert sorted(t for a, _ in shares for t in a) == list(range(tiles_a)) and sorted(t for _, b_ in shares for t in b_) == list(range(tiles_b)), c
+        walked += max(len(a) for a, _ in shares) > 1 and max(len(b_) for _, b_ in shares) > 1 and l["mt"] > 8
+    assert walked >= 3             # cases where a workgroup walks several tiles of both, over more than one panel
 
 
 def test_two_shapes_need_room_for_their_row_sums_and_a_lean_block():
