@@ -676,8 +676,8 @@ TWO_SHAPES_CASES = [
     # a workgroup walks several tiles of both, over more than one panel of eight token tiles; the last ones of both parts are ragged
     (768, 9773, 1570, synth.ACT_GELU_TANH, False, 192, 51, 34),
     (768, 6147, 2914, synth.ACT_SILU, False, 224, 31, 23),
-    (768, 6632, 2305, synth.ACT_SILU, True, 192, 31, 28),
-    (768, 9768, 2053, synth.ACT_SILU, True, 256, 51, 34),
+    (768, 13120, 2053, synth.ACT_SILU, True, 192, 69, 45),
+    (768, 12032, 2242, synth.ACT_SILU, True, 256, 56, 51),
 ]
 
 
