@@ -311,10 +311,11 @@ int64_t stat_max_chunks(int64_t total_tokens, int32_t n_seqs, int32_t F)
 // 136 / 130 (368e3).  With a kernel for up to 128 tokens that formed its weights a wavefront a row, 128 tokens of 1024 x 13824 took 38.0, 40 29.3:
 // 31.2 and 24.5 so.
 // Where they are too few to fill the chip while the longest sequence lasts (of `full` CUs, as if all sequences were as long), what counts is that one
-// workgroup has all its rows, a load of 256 (128) behind the other, and chunks bring more CUs.  The lines, rows: 1000 of 1400 columns in fp32 45 / 47, 1700 60 / 66;
+// workgroup has all its rows, a load of 256 (128) behind the other, and chunks bring more CUs.  1200 rows of 1400 columns in fp32 50 / 54, 1700 60 / 66;
 // 800 of 4096 30.0 / 28.0, 1700 39.7 / 42.2; 1100 of 7000 41.7 / 40.9, 1400 44.3 / 45.7; 700 of 1400 and three prompts of 40 24.3 / 22.0, 1400 28.6 / 32.9.  Rows an
 // element a load: 500 of 2623 24.9 / 22.6, 800 30.7 / 31.1, 2500 49.4 / 60.5; 1100 of 7001 53.0 / 49.9, 2500 of 11009 134 / 128.  Where rows are eight
-// 4 KB pieces, the column blocks of the chunks fall to an XCD each and chunks are faster sooner: 450 rows of 8192 28.1 / 26.8, 550 28.3 / 30.4, 900 31.0 / 35.9.
+// 4 KB pieces, the column blocks of the chunks fall to an XCD each and chunks are faster sooner: 480 rows of 7172 to 8192 lose 3 to 14 % of the call in chunks, 600 5 to
+// 7 % less to 5 % more, 900 gain 5 to 14 % (8192: 31.0 / 35.9).
 static bool stat_whole(int32_t longest, int64_t total, int32_t n_seqs, int32_t F, int nt, bool vec4)
 {
     const int64_t columns = (F + 63) / 64, wgs = columns * n_seqs;
@@ -322,7 +323,7 @@ static bool stat_whole(int32_t longest, int64_t total, int32_t n_seqs, int32_t F
         return false;
     const int64_t full = columns * total / (longest > 0 ? longest : 1);
     if (vec4 && (F + 1023) / 1024 == 8 && full < 320)
-        return longest <= 450;
+        return longest <= 600;
     return full >= 160 || longest <= (vec4 ? std::min((int64_t)1150, 800 + 5 * full) : full < 70 ? 640 + 3 * full : 1000 + 30 * (full - 70));
 }
 

@@ -127,7 +127,7 @@ def test_statistic_in_chunks_where_one_kernel_would_leave_the_chip_idle():
     calls = [(64, 1000, [700], G.F32, True), (64, 1000, [1000], G.F32, False), (1024, 2623, [600], G.BF16, True), (1024, 2623, [2341], G.BF16, False),
              (184, 486, [2022], G.F32, False), (96, 287, [1779], G.F32, False), (64, 4096, [1000], G.BF16, True), (64, 4096, [1400], G.BF16, False),
              (64, 4096, [1400, 1400], G.BF16, False), (64, 4096, [1000] * 4, G.BF16, True), (64, 1400, [1400, 40, 40, 40], G.BF16, False),
-             (64, 8192, [450], G.BF16, True), (64, 8192, [700], G.BF16, False), (64, 8193, [2000], G.BF16, True), (64, 11008, [1200], G.BF16, True),
+             (64, 8192, [600], G.BF16, True), (64, 8192, [700], G.BF16, False), (64, 8193, [2000], G.BF16, True), (64, 11008, [1200], G.BF16, True),
              (64, 1400, [0, 1000], G.BF16, False), (64, 1400, [0, 0], G.BF16, True)]
     calls += [(d, F, lens, G.BF16, True) for d, F, lens in cases.LONG_WHOLE_CASES]
     got = [any("stat_whole" in l["name"] for l in ls) for ls in launches.record([dict(entry="select", d=d, n=F, lens=v, dtype=t) for d, F, v, t, _ in calls])]
