@@ -17,10 +17,11 @@
 //    barrier per group would tie their load streams to the slowest: 75 us a masked call instead of 71 on 4096 x 14336), add the
 //    tiles in wave order, apply sigma, the gating product and the membership bits, and store Z.  Workgroups start at different
 //    blocks, so that row strides of a power of two do not send them all to the same memory channels at a time.
-//    Measured on the gate and up rows (medians of the kernel trace, each with the ~4 us of a dependent dispatch in it, before x came along with the
-//    first group and before the loads past the last one were cut to a line): 5120 x 6912 (142 MB), 16 rows 31 us (34 with five blocks ahead; 38 when rows were streamed through LDS two neurons at a time with two of sixteen
-//    MFMA columns in use; 42 with loads of sixteen half lines instead of eight whole ones); 3072 x 12288, 40 rows 35 us (three
-//    passes of 32 in that form); 4096 x 14336 masked 41 us (44).
+//    Measured on the gate and up rows (medians of the kernel trace, each with the ~4 us of a dependent dispatch in it): 5120 x 6912 (142 MB),
+//    16 rows 27.8 us, 3072 x 12288, 40 rows 32, 4096 x 14336 masked 40 to 41; 30.6, 34.6 and 42.8 before x came along with the first group
+//    and the loads past the last one were cut to a line.  Before that, and each against the form then: 16 rows of 5120 x 6912 31 (34 with five blocks
+//    ahead; 38 when rows were streamed through LDS two neurons at a time with two of sixteen MFMA columns in use; 42 with loads of sixteen
+//    half lines instead of eight whole ones).
 //  * ff_batch_down_kernel: the second line.  Giving every workgroup all d columns would cost one [rows][d] partial per
 //    workgroup, so the work is cut in two directions: a workgroup owns 512 columns and one of NR ranges of neurons, and
 //    writes one [rows][512] partial into the partial-row buffer that the single-row path uses (NR rows per batch row).
@@ -233,54 +234,54 @@ __global__ __launch_bounds__(BT_WAVES * 64) void ff_batch_gu_kernel(BatchParams 
             for (int m = 0; m < NMAT; ++m)
                 *(f32x4_b *)(buf + ((wave * T + t) * NMAT + m) * 1024) = acc[t][m];
         if (gi == p.NB - 1 || g == ngroups - 1) {
-        // the waves meet: the tiles of the last NB groups are shared out over them
-        BT_BARRIER()
-        for (int i = wave; i < (gi + 1) * T; i += W) {
-            const int ge = g - gi + i / T, t = i % T;
-            buf = bt_smem + (i / T) * (W * T * NMAT * 1024) + lane * 16;
-            f32x4_b u = {0.f, 0.f, 0.f, 0.f}, gt = {0.f, 0.f, 0.f, 0.f};
+            // the waves meet: the tiles of the last NB groups are shared out over them
+            BT_BARRIER()
+            for (int i = wave; i < (gi + 1) * T; i += W) {
+                const int ge = g - gi + i / T, t = i % T;
+                buf = bt_smem + (i / T) * (W * T * NMAT * 1024) + lane * 16;
+                f32x4_b u = {0.f, 0.f, 0.f, 0.f}, gt = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-            for (int w = 0; w < W; ++w) {
-                u += *(const f32x4_b *)(buf + ((w * T + t) * NMAT) * 1024);
-                if (GATED)
-                    gt += *(const f32x4_b *)(buf + ((w * T + t) * NMAT + NMAT - 1) * 1024);
-            }
-            const int j0 = BT_FIRST(ge) + q * 4;
-            const int cnt = BT_COUNT(ge) - q * 4;           // neurons of this lane, an even number
-            if (cnt > 0) {
-                float zv[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int j = min(j0 + i, p.n - 1);
-                    float uu = u[i];
-                    if (p.b1) uu += bf16_bits_to_f32(((const uint16_t *)p.b1)[j]);
-                    float z;
-                    if (GATED) {
-                        float gg = gt[i];
-                        if (p.bg) gg += bf16_bits_to_f32(((const uint16_t *)p.bg)[j]);
-                        z = act_apply(p.act, gg) * uu;
-                    } else {
-                        z = act_apply(p.act, uu);
-                    }
-                    // beyond the block or the batch, or not in this row's own expert set: no part in the sum (-0, which no other z is)
-                    const bool out = j0 + i >= p.n || t * BT_ROWS + r16 >= p.rows || (p.mask && !((p.mask[(int64_t)t * p.n + j] >> r16) & 1u));
-                    zv[i] = out ? -0.0f : z + 0.0f;
+                for (int w = 0; w < W; ++w) {
+                    u += *(const f32x4_b *)(buf + ((w * T + t) * NMAT) * 1024);
+                    if (GATED)
+                        gt += *(const f32x4_b *)(buf + ((w * T + t) * NMAT + NMAT - 1) * 1024);
                 }
+                const int j0 = BT_FIRST(ge) + q * 4;
+                const int cnt = BT_COUNT(ge) - q * 4;           // neurons of this lane, an even number
+                if (cnt > 0) {
+                    float zv[4];
 #pragma unroll
-                for (int i = 0; i < 4; i += 2)
-                    if (i < cnt) {
-                        const int j = j0 + i;
-                        char *zo = (char *)p.z + ((int64_t)(j >> 3) * T + t) * 512;
-                        if (p.exact) {
-                            *(float2 *)(zo + ((j >> 2) & 1) * 256 + r16 * 16 + (j & 3) * 4) = make_float2(zv[i], zv[i + 1]);
+                    for (int i = 0; i < 4; ++i) {
+                        const int j = min(j0 + i, p.n - 1);
+                        float uu = u[i];
+                        if (p.b1) uu += bf16_bits_to_f32(((const uint16_t *)p.b1)[j]);
+                        float z;
+                        if (GATED) {
+                            float gg = gt[i];
+                            if (p.bg) gg += bf16_bits_to_f32(((const uint16_t *)p.bg)[j]);
+                            z = act_apply(p.act, gg) * uu;
                         } else {
-                            const uint32_t hi = f32x2_to_bf16x2(zv[i], zv[i + 1]);
-                            *(uint32_t *)(zo + r16 * 16 + (j & 7) * 2) = hi;
-                            *(uint32_t *)(zo + 256 + r16 * 16 + (j & 7) * 2) = f32x2_to_bf16x2(zv[i] - bf16_lo(hi), zv[i + 1] - bf16_hi(hi));
+                            z = act_apply(p.act, uu);
                         }
+                        // beyond the block or the batch, or not in this row's own expert set: no part in the sum (-0, which no other z is)
+                        const bool out = j0 + i >= p.n || t * BT_ROWS + r16 >= p.rows || (p.mask && !((p.mask[(int64_t)t * p.n + j] >> r16) & 1u));
+                        zv[i] = out ? -0.0f : z + 0.0f;
                     }
+#pragma unroll
+                    for (int i = 0; i < 4; i += 2)
+                        if (i < cnt) {
+                            const int j = j0 + i;
+                            char *zo = (char *)p.z + ((int64_t)(j >> 3) * T + t) * 512;
+                            if (p.exact) {
+                                *(float2 *)(zo + ((j >> 2) & 1) * 256 + r16 * 16 + (j & 3) * 4) = make_float2(zv[i], zv[i + 1]);
+                            } else {
+                                const uint32_t hi = f32x2_to_bf16x2(zv[i], zv[i + 1]);
+                                *(uint32_t *)(zo + r16 * 16 + (j & 7) * 2) = hi;
+                                *(uint32_t *)(zo + 256 + r16 * 16 + (j & 7) * 2) = f32x2_to_bf16x2(zv[i] - bf16_lo(hi), zv[i + 1] - bf16_hi(hi));
+                            }
+                        }
+                }
             }
-        }
         }
         if (++g == ngroups)
             break;

@@ -225,9 +225,9 @@ __global__ __launch_bounds__(FN_WAVES * 64) void f32_nt_kernel(F32NtParams p)
 // wavefronts and the top-k before / so: 64 tokens of 256 x 688 23.0 / 16.8 (16 x 16 tiles; 21.9 with 32 x 32), 77 of a bf16 512 x 1001 41.7 / 25.6,
 // 200 of 1024 x 4096 113 / 103 (832 tiles of 16 x 16, more bytes a CU: 32 x 32).
 // Without a top-k to carry (griffin_ff_prompt_out) eight waves may be faster, with two sums each: the bits are those of the prompt phase.  Outputs
-// alone, us, eight waves with one sum / with two / sixteen waves: 64 tokens of 64 x 128 4.4 / 5.0 / 4.7 (a slice for each of the eight), 500 of 256 x 688 7.5 / 7.8 /
-// 10.0, of 512 x 1400 13.5 / 13.6 / 13.8, of 512 x 2048 19.9 / - / 18.6, 250 of 1024 x 4096 36.1 / - / 33.4; of rows that come an element a load, 400 of
-// 256 x 255 7.3 / 7.5 / 12.1, of 512 x 697 18.6 / 19.3 / 22.8, of 256 x 801 22.3 / - / 22.6, 77 of 1024 x 4099 91 / 111 / 94.
+// alone, us, eight waves with one sum / with two / sixteen waves: 64 tokens of 64 x 128 4.4 / 5.0 / 4.7 (a slice for each of the eight), 500 of 256 x 688 7.4 / 6.6 /
+// 9.9, of 512 x 2048 19.9 / - / 18.6, 250 of 1024 x 4096 36.1 / - / 33.4; of rows that come an element a load, 400 of
+// 256 x 255 7.3 / 7.5 / 12.1, of 512 x 697 18.8 / 20.5 / 22.9, of 256 x 801 22.3 / - / 22.6, 77 of 1024 x 4099 91 / 111 / 94.
 constexpr int FN_WIDE_WAVES = TOPK_THREADS / 64;
 template <bool BBF16, bool VEC, int T, int KPT>
 __global__ __launch_bounds__(TOPK_THREADS) void f32_out_topk_kernel(F32NtParams p, TopkJob t)

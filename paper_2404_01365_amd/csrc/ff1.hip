@@ -337,7 +337,9 @@ static Ff1Tile ff1_tile(int64_t M, int32_t n, bool gated, bool any_width, bool s
 // Where the line lies: whole selections and prompt phases, one shape / two (us), by the ratio that the model gives.  0.83 to 0.9: 788 tokens of
 // 6144 x 11392 270 / 230, 774 of 4096 x 17088 251 / 218; 0.9 to 0.95: 1026 of 5120 x 13664 302 / 277, 864 of 2048 x 9872 100 / 96; 0.95 to
 // 0.97: 1285 of 4096 x 17088 347 / 341, 3748 of 1536 x 7776 207 / 199; 0.97 to 0.98: 491 of 3072 x 18832 138.2 / 137.8, 3979 of 4096 x 17088 935 / 901;
-// from 0.99 on as often slower as faster (723 of 2560 x 7392 70.8 / 75.3).  Going over to the second shape costs a tile's first loads, which nothing
+// from 0.99 on as often slower as faster (723 of 2560 x 7392 70.8 / 75.3).  Over 51 random selections and 41 prompt phases that this sends on two shapes
+// 0.96 and 0.99 (geometric means; 0.89 to 1.05).  Tiles of 160 tokens are as often slower as faster from 0.933 on already (41 calls, 0.95 to 1.07, mean 1.00; 1404
+// tokens of 1536 x 6592 on nine of them 87.3 / 91.5, 419 of 4096 x 10416 0.956).  Going over to the second shape costs a tile's first loads, which nothing
 // hides, so short k loops gain nothing: d = 512 31.7 / 31.6 at 0.95, 128 55.2 / 54.7 at 0.94; 768 144 / 142 at 0.97.
 constexpr int FF1_TWO_MIN_D = 768;
 constexpr double FF1_TWO_LINE = 0.97;
@@ -481,7 +483,7 @@ static Ff1Plan ff1_plan(const griffin_layer &L, int64_t M)
     return pl;
 }
 
-// Does the product go on two shapes of tiles?
+// Does the product go on two shapes of tiles?  (Kernels with biases, and for Eq. 2 blocks, are not compiled; what they would gain is not measured.)
 static Ff1Two ff1_takes_two(const griffin_layer &L, int64_t M, const Ff1Plan &pl)
 {
     const Ff1Two none = {0, 0, 0, 0.0};

@@ -669,9 +669,10 @@ __global__ __launch_bounds__(G_THREADS) void ff1_bf16_mfma_kernel(Ff1Params p)
 
 // Two shapes of tiles in one launch: the neurons of `a` on the first, those of `b`, which follow them, on the second.  The tiles of both
 // together are dealt out evenly over the XCDs, and the second part is walked from the other end, so that the workgroups with fewer tiles
-// of the first have more of it.  The product of 1024 tokens of 5120 x 13824 on 432 tiles of 256 x 128 230 us, on 256 of them and 236 of 256 x 96 218;
-// of 777 tokens on 432 of 224 x 128 206, on 192 and 320 of 224 x 96 194; of 640 tokens of 4096 x 14336 on 450 of 256 x 96 151, on 256 of
-// 160 x 128 and 256 of 160 x 96 128.
+// of the first have more of it.  Kernel medians, both builds in turn in one session (us): 1024 tokens of 5120 x 13824 on 432 tiles of 256 x 128 232 to
+// 233, on 256 of them and 236 of 256 x 96 222 to 224 (with the copy of Z 249 to 251 and 246 to 247); 777 tokens on 432 of 224 x 128 202 to 203, on 192
+// and 320 of 224 x 96 200 to 205; 640 tokens of 4096 x 14336 on 450 of 256 x 96 146, on 256 of 160 x 128 and 256 of 160 x 96 127 to 131.  Whole selections, in turn
+// in one process: 255 / 239, 225 / 214, 169 / 146.
 template <int ACT, int EXTRA, int TA, int NA, int TB, int NB>
 __global__ __launch_bounds__(G_THREADS) void ff1_bf16_two_shapes_kernel(Ff1Params a, Ff1Params b)
 {
