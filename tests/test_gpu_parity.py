@@ -630,7 +630,8 @@ FORM_OUT_CASES = [
 ]
 
 
-# a workgroup for 64 columns of a whole sequence: blocks of 1024 rows, loads of 256 (of 128 where rows are not aligned), row partials in steps of 64
+# a workgroup for 64 columns of a whole sequence: loads of 256 rows (of 128 where they are not aligned), row partials in steps of 64; from some 650 to 810 rows on
+# so few columns go in chunks
 @pytest.mark.parametrize("d,F,lens", [(8, 72, [1]), (8, 72, [255, 0, 256, 257]), (8, 72, [1024]), (8, 72, [1025, 3]), (16, 64, [2049]), (8, 2116, [130]),
                                       (8, 71, [128, 129, 1]), (8, 71, [1023, 1026]), (8, 4226, [65, 64])])
 def test_statistic_of_whole_sequences(d, F, lens):
@@ -638,7 +639,7 @@ def test_statistic_of_whole_sequences(d, F, lens):
 
 
 # ... of more than one block of 1024 rows, where the chip is full meanwhile
-LONG_WHOLE_CASES = [(8, 10240, [1100]), (8, 10241, [2049]), (8, 512, [1030, 0] + [1100] * 20)]
+LONG_WHOLE_CASES = [(8, 10240, [1024]), (8, 10240, [1100]), (8, 10241, [1025]), (8, 10241, [2049]), (8, 512, [1030, 0] + [1100] * 20)]
 
 
 @pytest.mark.parametrize("d,F,lens", LONG_WHOLE_CASES)
