@@ -537,7 +537,7 @@ def run_single(args, cfg, torch, np, G, synth, hip, brief):
                                           "GBps_weights_once": (3 * k * d * w + 2 * Bsh * d * w) / (b_us * 1e-6) / 1e9},
         }
 
-    # the box's own copy bandwidth, for scale: a plain device-to-device copy of 1 GiB (read + write
+    # the card's own copy bandwidth, for scale: a plain device-to-device copy of 1 GiB (read + write
     # counted), larger than the 256 MB Infinity Cache
     cp_src = torch.empty((1 << 30,), dtype=torch.uint8, device="cuda")
     cp_dst = torch.empty_like(cp_src)
